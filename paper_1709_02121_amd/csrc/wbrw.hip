@@ -32,7 +32,7 @@ struct Layout {
     size_t zero_begin = 0, zero_end = 0;   // region cleared at init
     // offsets
     size_t ens[2][8] = {}, gens[2][8] = {};
-    size_t ip = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
+    size_t ip = 0, dev = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
     size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, evc = 0, tileA = 0, Nsrt = 0, srtS = 0, tileB = 0, tileR = 0,
            tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, ev_idx = 0, gev_idx = 0,
            tcA = 0, tcAg = 0, supA = 0, supAg = 0, spart = 0, emA = 0, emAg = 0, tcB = 0, tcBg = 0, supB = 0, supBg = 0, tsB = 0, tsBg = 0, stg = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
@@ -229,6 +229,7 @@ Layout make_layout(const wbrw_config *c)
     L.ev_idx = take(cur, C * 4);
     if (tan) L.gev_idx = take(cur, G * 4);
     L.ip = take(cur, BB * sizeof(InstParam));
+    L.dev = take(cur, sizeof(Dev));
     for (int m = 0; m < c->n_components; ++m)
         if (c->comp[m].kind == WBRW_KERNEL_TABLE) {
             L.tab[m] = take(cur, ((size_t)c->comp[m].table_n + 1) * 8);
@@ -413,6 +414,47 @@ int persistent_blocks(K kernel, int cus, int nt = kThreads)
 constexpr int kStreamShapes[3][2] = {{kThreads, kPPT}, {128, 16}, {512, 4}};
 constexpr int kBinSlots[3] = {4096, 2048, 8192};
 
+// The particles' family kernel of this handle.  One static Gaussian
+// component with the majorant sampler (every tangent form has that) takes the
+// instantiation without the component loop.
+using FamilyKernel = void (*)(Dev, int);
+template <int DIM>
+FamilyKernel family_kernel(const wbrw_handle *h)
+{
+    const bool sp2 = h->strategy == WBRW_SP2;
+    if constexpr (DIM == 1) {
+        if (h->tangent) return sp2 ? k_family<1, true, true, true> : k_family<1, false, true, true>;
+        if (h->M == 1 && h->d.kind[0] == WBRW_KERNEL_GAUSSIAN && h->d.sampler[0] == 0 && !h->d.tdep)
+            return sp2 ? k_family<1, true, false, true> : k_family<1, false, false, true>;
+    }
+    return sp2 ? k_family<DIM, true, false, false> : k_family<DIM, false, false, false>;
+}
+
+// Event parents per family tile: a tile's records should fill at most three
+// quarters of its pool of `pool` records, and the further jumps of a round
+// two thirds of its queue.  A jump leaves rb = 2 per pair (sp1: a pair of
+// component m with probability c_m <|sin|> = 2/pi c_m) records; a parent
+// jumps again, and each of its offspring too, with about g/2 = gamma0 dt / 2.
+int family_tile(const wbrw_handle *h, bool ghost, int pool, int queue)
+{
+    double need = 0.0, more = 0.0;
+    for (const InstParam &P : h->ip) {
+        double rb = 0.0;
+        for (int m = 0; m < h->M; ++m) {
+            const double sp1 = 4.0 / 3.14159265358979 * P.c[m];
+            rb += (h->strategy == WBRW_SP2 && !ghost) ? 2.0 : sp1;
+            if (h->tangent == 2 && !ghost) rb += sp1;
+        }
+        const double g = P.gamma0 * h->d.dt, again = 0.5 * g * (1.0 + rb);
+        need = std::max(need, rb * (1.0 + 1.3 * again));
+        more = std::max(more, again);
+    }
+    double n = kThreads;
+    if (need > 0.0) n = std::min(n, 0.75 * pool / need);
+    if (more > 0.0) n = std::min(n, 0.67 * queue / more);
+    return std::max(kTileB, (int)n / kTileB * kTileB);
+}
+
 template <int DIM>
 void launch_stream(const wbrw_handle *h, hipStream_t s, int ghost)
 {
@@ -590,14 +632,7 @@ void enqueue_step_dim(wbrw_t h)
     hipLaunchKernelGGL(k_events, dim3(h->grid[G_EVENTS] + 1), dim3(kThreads), 0, s, d, 0, h->grid[G_STREAM]);
     stage_end(h);
     stage_begin(h, WBRW_STAGE_FAMILY);
-    if (h->strategy == WBRW_SP2 && tan)
-        hipLaunchKernelGGL((k_family<DIM, true, true>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 0);
-    else if (h->strategy == WBRW_SP2)
-        hipLaunchKernelGGL((k_family<DIM, true, false>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 0);
-    else if (tan)
-        hipLaunchKernelGGL((k_family<DIM, false, true>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 0);
-    else
-        hipLaunchKernelGGL((k_family<DIM, false, false>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 0);
+    hipLaunchKernelGGL(family_kernel<DIM>(h), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 0);
     stage_end(h);
     stage_begin(h, WBRW_STAGE_PLACE);
     const dim3 pg(h->grid[G_EVENTS] + 1);
@@ -616,8 +651,8 @@ void enqueue_step_dim(wbrw_t h)
         stage_begin(h, WBRW_STAGE_GHOST);
         launch_stream<DIM>(h, s, 1);
         hipLaunchKernelGGL(k_events, dim3(h->grid[G_EVENTS] + 1), dim3(kThreads), 0, s, d, 1, h->grid[G_STREAM]);
-        hipLaunchKernelGGL((k_family<DIM, false, true>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 1);
-        hipLaunchKernelGGL((k_place_records<DIM, false, true>), pg, dim3(kThreads), 0, s, d, 1, 1, fg);
+        hipLaunchKernelGGL((k_family<1, false, true, true>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 1);
+        hipLaunchKernelGGL((k_place_records<1, false, true>), pg, dim3(kThreads), 0, s, d, 1, 1, fg);
         stage_end(h);
     }
 }
@@ -717,14 +752,7 @@ void set_grids_dim(wbrw_t h)
     h->stream_shape = 0;
     h->bin_slots = kBinSlots[0];
     h->grid[G_STREAM] = std::min(h->occ_stream[0] * cus, kMaxGrid);
-    if (h->strategy == WBRW_SP2 && h->tangent)
-        h->grid[G_FAMILY] = persistent_blocks(k_family<DIM, true, true>, cus);
-    else if (h->strategy == WBRW_SP2)
-        h->grid[G_FAMILY] = persistent_blocks(k_family<DIM, true, false>, cus);
-    else if (h->tangent)
-        h->grid[G_FAMILY] = persistent_blocks(k_family<DIM, false, true>, cus);
-    else
-        h->grid[G_FAMILY] = persistent_blocks(k_family<DIM, false, false>, cus);
+    h->grid[G_FAMILY] = persistent_blocks(family_kernel<DIM>(h), cus);
     h->occ_family = std::max(1, h->grid[G_FAMILY] / std::max(1, cus));
     h->grid[G_BIN] = std::min(h->occ_bin[0] * cus, kMaxGrid);
     h->grid[G_SCAN] = persistent_blocks(k_scan, cus);
@@ -955,6 +983,10 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     }
 
     if (h->dim == 1) set_grids_dim<1>(h); else set_grids_dim<2>(h);
+    d.ftile = h->dim == 1 ? family_tile(h, false, Families<1, false, false>::kRec, Families<1, false, false>::kQueue)
+                          : family_tile(h, false, Families<2, false, false>::kRec, Families<2, false, false>::kQueue);
+    d.gftile = family_tile(h, true, Families<1, false, true>::kRec, Families<1, false, true>::kQueue);
+    d.self = at<Dev>(w, L.dev);
 
     hipStream_t s = h->stream;
     auto fail = [&](int rc) { delete h; return rc; };
@@ -966,7 +998,8 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     // constants and initial counts / plans
     std::vector<int64_t> N0(cfg->N0, cfg->N0 + h->B), plan;
     plan_host(plan, N0.data(), h->B, kTileA);
-    if (hipMemcpyAsync((void *)d.ip, h->ip.data(), sizeof(InstParam) * h->B, hipMemcpyHostToDevice, s) != hipSuccess ||
+    if (hipMemcpyAsync((void *)d.self, &d, sizeof(Dev), hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipMemcpyAsync((void *)d.ip, h->ip.data(), sizeof(InstParam) * h->B, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(d.N, N0.data(), 8 * h->B, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(d.tileA, plan.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, s) != hipSuccess)
         return fail(WBRW_EHIP);

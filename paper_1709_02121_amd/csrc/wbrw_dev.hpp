@@ -16,7 +16,7 @@ constexpr int kMaxM = 4;
 constexpr int kThreads = 256;           // threads per block in every kernel
 constexpr int kPPT = 8;                 // particles (or cells) per thread in streaming passes
 constexpr int kTileA = kThreads * kPPT; // particles per streaming tile
-constexpr int kTileB = kThreads;        // event-parents per family tile (the smallest; see fam_tile)
+constexpr int kTileB = 32;              // fewest event parents per family tile (see Dev::ftile)
 constexpr int kTileS = kThreads * kPPT; // cells per scan tile
 constexpr int kSupGroup = 64;           // tiles per group sum of per-tile counts
 constexpr int kSupStride = 16;          // u64 slots between group sums (one per 128 B line)
@@ -28,21 +28,13 @@ constexpr int kXiN = 4096;              // xi(r) grid intervals (Alg. 4 sampler)
 constexpr int kXiQ = 8192;              // quadrature nodes for xi(r)
 constexpr uint32_t kRejectMax = 256u;   // rejection proposals per kick
 constexpr int kMaxGrid = 8192;          // blocks of a persistent launch (per-block partials)
-// 4D family kernels: records of the general walks beyond the block's LDS pool
-// go to a per-block overflow area in HBM (kGPool records for each of the
-// first kGPoolBlocks blocks), so that they need not be walked a second time
-// when they are written.  Per record: eight doubles (x0, k0, x1, k1, w and
-// three tangents), the id, slot and rank, and the sign.
+// 4D family kernels: the payloads of a tile's records beyond the block's LDS
+// pool go to a per-block overflow area in HBM (kGPool records for each of the
+// first kGPoolBlocks blocks).  Per record: eight doubles (x0, k0, x1, k1, w
+// and three tangents), the id and the sign.
 constexpr int kGPool = 1024;
 constexpr int kGPoolBlocks = 1024;
-constexpr size_t kGPoolBytes = (size_t)kGPool * (8 * 8 + 8 + 4 + 1);
-
-// Event parents per family tile of the particle pass.  A tile's slow family
-// walks run concurrently, so larger tiles shorten the walk-bound critical
-// path; the 1D plain and sp2 kernels have the LDS for two parents per thread,
-// the 4D and tangent ones (larger records, four stash rows) one.  Ghost passes
-// use the tangent kernel, hence kTileB.
-constexpr int fam_tile(int dim, bool tangent) { return (dim == 1 && !tangent) ? 2 * kThreads : kTileB; }
+constexpr size_t kGPoolBytes = (size_t)kGPool * (8 * 8 + 8 + 1);
 
 enum : uint32_t { kErrCapacity = 1u, kErrDepth = 2u, kErrRange = 4u };
 
@@ -105,6 +97,7 @@ struct Ctl {
 };
 
 struct Dev {
+    const Dev *self;            // a copy of this structure in device memory
     // sizes and constants
     int32_t B, dim, M, strategy, tangent;
     int32_t tdep;               // some Gaussian height varies in time
@@ -122,6 +115,9 @@ struct Dev {
     double dt, vfac;
     double x_lo, x_hi, k_lo, k_hi, dx, dk;
     int32_t kind[kMaxM], axis[kMaxM], sampler[kMaxM];
+    int32_t ftile, gftile;      // event parents per family tile (particles, ghosts): as many
+                                // as kThreads, fewer where their records (see Families)
+                                // would not fit the tile's pool or queue
     const double *xi_tab;       // [B][M][kXiN + 1] xi(r) tables of the Alg. 4 sampler
     Table tab[kMaxM];
     // buffers

@@ -27,6 +27,13 @@ enum : uint32_t {
 
 struct W4 { uint32_t a, b, c, d; };
 
+// a ^ b ^ c in one instruction (gfx950's three-input bit operation; the
+// compiler leaves most of these chains as two exclusive-ors)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ W4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                             uint32_t k0, uint32_t k1)
 {
@@ -34,8 +41,8 @@ __device__ __forceinline__ W4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)c0 * 0xD2511F53ull;
         const uint64_t p1 = (uint64_t)c2 * 0xCD9E8D57ull;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -94,14 +101,14 @@ __device__ __forceinline__ double ln_series(double y)
     return fe * 0x1.62e42fee00000p-1 + (fe * 0x1.a39ef35793c76p-33 + lnm);
 }
 
-// r = a - n pi/2 and the quadrant n mod 4
+// r = a - n pi/2 and the quadrant n mod 4 (n - 4 floor(n/4) is exact)
 __device__ __forceinline__ double quarter_turns(double a, int& quad)
 {
     const double n = rint(a * 0x1.45f306dc9c883p-1);   // a * (2/pi)
     double r = a - n * 0x1.921fb54400000p+0;
     r = r - n * 0x1.0b4611a600000p-34;
     r = r - n * 0x1.3198a2e037073p-69;
-    quad = (int)((long long)n & 3);
+    quad = (int)(n - 4.0 * floor(n * 0.25));
     return r;
 }
 
@@ -136,24 +143,24 @@ __device__ __forceinline__ double taylor_cos(double r)
     return 1.0 + r2 * acc;
 }
 
+// Both series are evaluated and one is picked: a wavefront holds all four
+// quadrants, so branches on the quadrant would run each series twice.
 __device__ __forceinline__ double sin_det(double a)
 {
     int q;
     const double r = quarter_turns(a, q);
-    if (q == 0) return taylor_sin(r);
-    if (q == 1) return taylor_cos(r);
-    if (q == 2) return -taylor_sin(r);
-    return -taylor_cos(r);
+    const double sn = taylor_sin(r), cs = taylor_cos(r);
+    const double v = (q & 1) ? cs : sn;
+    return (q & 2) ? -v : v;
 }
 
 __device__ __forceinline__ double cos_det(double a)
 {
     int q;
     const double r = quarter_turns(a, q);
-    if (q == 0) return taylor_cos(r);
-    if (q == 1) return -taylor_sin(r);
-    if (q == 2) return -taylor_cos(r);
-    return taylor_sin(r);
+    const double sn = taylor_sin(r), cs = taylor_cos(r);
+    const double v = (q & 1) ? sn : cs;
+    return ((q + 1) & 2) ? -v : v;
 }
 
 constexpr double kTwoPi = 0x1.921fb54442d18p+2;

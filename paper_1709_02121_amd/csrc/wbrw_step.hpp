@@ -30,8 +30,10 @@ namespace wbrw {
 // ---------------------------------------------------------------------------
 // Kernel phase and kick sampling (Sec. 4.2, Remark 3 / Eq. majorant_approach)
 // ---------------------------------------------------------------------------
+template <int DIM>
 __device__ __forceinline__ double phase_offset(const Dev &d, int m, const double *xe, double c)
 {
+    if (DIM == 1) return xe[0] - c;
     const int a = d.axis[m];
     if (a == 0) return xe[0] - c;
     if (a == 1) return xe[1] - c;
@@ -46,10 +48,11 @@ __device__ __forceinline__ double phase_offset(const Dev &d, int m, const double
 // in [guide[i], guide[i + 1]], nearly always one or two bins wide, where a
 // binary search over the whole table took 12 dependent loads.  The bin found
 // is the same.
+template <bool ONE>
 __device__ __forceinline__ double kick_sample(const Dev &d, const InstParam &P, int m, double u1,
                                               double u2)
 {
-    if (d.kind[m] == 0) {
+    if (ONE || d.kind[m] == 0) {
         const double R = sqrt(-2.0 * ln_series(1.0 - u1));
         const double z = R * cos_det(kTwoPi * u2);
         return z * P.sq[m];
@@ -144,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void k_events(Dev d, int ghost, int sgrid
             for (int b = tid; b < B; b += kThreads)
                 if (s_ev[b]) atomicAdd((unsigned long long *)&evc[b], (unsigned long long)s_ev[b]);
         __syncthreads();
-        const int64_t ftile = ghost ? kTileB : fam_tile(d.dim, d.tangent != 0);
+        const int64_t ftile = ghost ? d.gftile : d.ftile;
         block_prefix(d.tileB + (int64_t)ghost * (B + 1), B, [&](int b) {
             const int64_t e = (int64_t)__hip_atomic_load((unsigned long long *)&evc[b], __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_AGENT);
@@ -238,98 +241,22 @@ struct Tally {
     int32_t maxdepth;
 };
 
-// The records of a family found by fast_family (at most R: nearly always
-// one pair in 1D; in 4D, where each of the three components may add a pair,
-// up to two; with derivative pairs at most one of each), kept in LDS until
-// the ordered scan has placed them.  All of them are born at the family's
-// one jump, so that jump's position and time are kept once per slot and the
-// end-of-step positions are formed when the records are written.
-template <int DIM, bool SP2, bool TAN>
-struct Stash {
-    static constexpr int R = (!SP2 && (TAN || DIM == 2)) ? 4 : 2;
-    static constexpr int F = fam_tile(DIM, TAN);   // event parents per tile
-    double xe0[F], te[F];
-    double xe1[DIM == 2 ? F : 1];
-    double k0[R][F];
-    double k1[DIM == 2 ? R : 1][DIM == 2 ? F : 1];
-    double w[SP2 ? R : 1][SP2 ? F : 1];
-    double D[TAN ? 3 * R : 1][TAN ? F : 1];
-    uint64_t id[R][F];
-    int8_t sg[R][F];
-};
-
-// The families of a tile that are not of the lockstep kind, expanded level
-// by level: every node (a family root, or a kept offspring, which is a
-// record) of one level is expanded by one lane, which walks its jumps in time
-// order and appends its kept offspring with their parent, rank among the
-// parent's offspring and depth; offspring that jump again within the step
-// form the next level.  Subtree sizes and depth-first positions then give
-// every record its place in the canonical order.  The tallies are kept per
-// node, so that a family whose nodes do not all fit can be dropped and
-// walked again depth first.
-template <int DIM, bool SP2, bool TAN>
-struct Tree {
-    static constexpr int kNodes = 256;
-    double x0[kNodes], k0[kNodes];   // position at birth (t0), wave vector
-    double x1[DIM == 2 ? kNodes : 1], k1[DIM == 2 ? kNodes : 1];
-    double t0[kNodes];
-    double w[SP2 ? kNodes : 1];
-    double D[TAN ? 3 : 1][TAN ? kNodes : 1];
-    uint64_t id[kNodes];
-    int64_t killed[kNodes];          // k-truncation tally of the node's jumps
-    uint32_t size[kNodes];           // records in the subtree (a root: its family's)
-    uint16_t par[kNodes];            // parent node (roots: none)
-    uint16_t rank[kNodes];           // among the parent's kept offspring
-    uint16_t slot[kNodes];           // tile slot of the family
-    uint16_t nch[kNodes];            // kept offspring
-    uint16_t cst[kNodes];            // first of its offspring in `child`
-    uint16_t child[kNodes];          // offspring grouped by parent, in rank order
-    uint16_t front[2][kNodes];       // the levels being expanded / collected
-    uint16_t events[kNodes], pairs[kNodes];
-    int16_t pos[kNodes];             // depth-first position within the family
-    int8_t sg[kNodes];
-    uint8_t depth[kNodes], capped[kNodes];
-    uint32_t n, nf[2], maxd;
-};
-
-// 4D kernels: the records of the families that took the general walk, in
-// order of creation across the tile, each tagged with its family's slot and
-// its rank within the family; past kPool they go on in the block's overflow
-// area in HBM.  A family whose records do not all fit there either is walked
-// again when the records are written.  (In 4D about a fifth of
-// the families of a tile are not of the lockstep kind, with some ten records
-// each: too many nodes for a Tree in an LDS budget that keeps three blocks
-// per CU.)  384 records fill the LDS that three blocks per CU leave; a record
-// kept in LDS is cheaper than one stored to HBM, since a later load of the
-// walk waits on the same counter as every store before it.
-constexpr int kPool = 384;
-template <int DIM, bool SP2, bool TAN>
-struct Pool {
-    double x0[kPool], k0[kPool];
-    double x1[DIM == 2 ? kPool : 1], k1[DIM == 2 ? kPool : 1];
-    double w[SP2 ? kPool : 1];
-    double D[TAN ? 3 : 1][TAN ? kPool : 1];
-    uint64_t id[kPool];
-    uint16_t slot[kPool], rank[kPool];
-    int8_t sg[kPool];
-    uint32_t n;
-};
-
 // Pair decision and kick of component m at jump e of particle `id`
 // (Alg. 1 rules 3-5 with the majorant sampler of Remark 3, or Alg. 4):
 // returns false if no pair is created.
 
-template <bool SP2>
+// ONE: a single static Gaussian component with the majorant sampler.
+template <int DIM, bool SP2, bool ONE>
 __device__ __forceinline__ bool draw_pair(const Dev &d, const InstParam &P, uint64_t id, uint32_t step,
                                           uint32_t e, int m, const double *xe, double te, double ua0,
-                                          double w, PairDraw &J, const W4 *kick_draw = nullptr)
+                                          double w, PairDraw &J)
 {
     const uint32_t seed = d.seed, key = P.key;
     double cm = P.c[m], sgv = P.sgnV[m];
     bool alg4 = false;
-    if (d.sampler[m] == 1) {
+    if (!ONE && d.sampler[m] == 1) {
         // Alg. 1 sp1 box with Pr = xi(x)/gamma0, kick by Alg. 4
-        const double r = phase_offset(d, m, xe, P.center[m]);
+        const double r = phase_offset<DIM>(d, m, xe, P.center[m]);
         double ua = ua0;
         if (m > 0) {
             const W4 ra = draw(id, step, kTagStep, e, (uint32_t)(8 + m), seed, key);
@@ -345,12 +272,12 @@ __device__ __forceinline__ bool draw_pair(const Dev &d, const InstParam &P, uint
         sgv = 1.0;
         alg4 = true;
     } else {
-        const W4 rq = kick_draw ? *kick_draw : draw(id, step, kTagStep, e, (uint32_t)(1 + m), seed, key);
-        J.q = kick_sample(d, P, m, unit53(rq.a, rq.b), unit53(rq.c, rq.d));
-        J.arg = (2.0 * J.q) * phase_offset(d, m, xe, P.center[m]);
+        const W4 rq = draw(id, step, kTagStep, e, (uint32_t)(1 + m), seed, key);
+        J.q = kick_sample<ONE>(d, P, m, unit53(rq.a, rq.b), unit53(rq.c, rq.d));
+        J.arg = (2.0 * J.q) * phase_offset<DIM>(d, m, xe, P.center[m]);
         J.sn = sin_det(J.arg);
     }
-    if (d.tdep && d.kind[m] == 0 && !alg4) {   // Remark 1: kernel at the absolute jump time
+    if (!ONE && d.tdep && d.kind[m] == 0 && !alg4) {   // Remark 1: kernel at the absolute jump time
         const double tabs = (double)step * d.dt + te;
         const double f = P.ma[m] + P.mb[m] * cos_det(P.mw[m] * tabs + P.mp[m]);
         const double He = P.H[m] * f;
@@ -375,6 +302,7 @@ __device__ __forceinline__ bool draw_pair(const Dev &d, const InstParam &P, uint
 // Offspring `side` (0: "+", 1: "-") of the pair J of component m at jump e;
 // rc is the child-id draw of (parent, e, m).  Sets k, sign, weight, id and
 // tangent of ch.
+template <int DIM>
 __device__ __forceinline__ void child_id_k(const Dev &d, const Node &par, uint64_t cls, int m, int side,
                                            const PairDraw &J, const W4 &rc, Node &ch)
 {
@@ -383,7 +311,7 @@ __device__ __forceinline__ void child_id_k(const Dev &d, const Node &par, uint64
     const double kick = J.sigma * J.q;
     ch.k[0] = par.k[0];
     ch.k[1] = par.k[1];
-    const int ax = d.axis[m];
+    const int ax = DIM == 1 ? 0 : d.axis[m];
     if (ax == 0) {
         ch.k[0] = side == 0 ? par.k[0] + kick : par.k[0] - kick;
     } else if (ax == 1) {
@@ -394,12 +322,12 @@ __device__ __forceinline__ void child_id_k(const Dev &d, const Node &par, uint64
     }
 }
 
-template <bool SP2, bool TAN>
+template <int DIM, bool SP2, bool TAN>
 __device__ __forceinline__ void make_child(const Dev &d, const InstParam &P, const Node &par, int m, int side,
                                            const PairDraw &J, const W4 &rc, Node &ch)
 {
     const uint64_t cls = ((par.id >> 62) & 1ull) ? 3ull : 2ull;   // ghost lineages keep bit 62
-    child_id_k(d, par, cls, m, side, J, rc, ch);
+    child_id_k<DIM>(d, par, cls, m, side, J, rc, ch);
     ch.sg = side == 0 ? par.sg : -par.sg;
     ch.w = side == 0 ? J.amp : -J.amp;
     if constexpr (TAN && SP2) {
@@ -450,13 +378,12 @@ __device__ __forceinline__ void make_child(const Dev &d, const InstParam &P, con
 // measure with a tangent bounded by 2|q|, where the score -2q cot(2 q r) has
 // infinite variance.  Returns false if no pair is created.
 __device__ __forceinline__ bool draw_deriv(const Dev &d, const InstParam &P, uint64_t id, uint32_t step,
-                                           uint32_t e, int m, const double *xe, PairDraw &J,
-                                           const W4 *kick_draw = nullptr)
+                                           uint32_t e, int m, const double *xe, PairDraw &J)
 {
-    const W4 rq = kick_draw ? *kick_draw : draw(id, step, kTagStep, e, (uint32_t)(1 + m), d.seed, P.key);
+    const W4 rq = draw(id, step, kTagStep, e, (uint32_t)(1 + m), d.seed, P.key);
     const W4 ru = draw(id, step, kTagDeriv, e, (uint32_t)m, d.seed, P.key);
-    J.q = kick_sample(d, P, m, unit53(rq.a, rq.b), unit53(rq.c, rq.d));
-    J.arg = (2.0 * J.q) * phase_offset(d, m, xe, P.center[m]);
+    J.q = kick_sample<true>(d, P, m, unit53(rq.a, rq.b), unit53(rq.c, rq.d));
+    J.arg = (2.0 * J.q) * phase_offset<1>(d, m, xe, P.center[m]);
     const double cs = cos_det(J.arg);
     if (!(unit53(ru.a, ru.b) < P.c[m] * fabs(cs))) return false;
     J.sn = cs;
@@ -469,7 +396,7 @@ __device__ __forceinline__ bool draw_deriv(const Dev &d, const InstParam &P, uin
 __device__ __forceinline__ void make_deriv_child(const Dev &d, const Node &par, int m, int side,
                                                  const PairDraw &J, const W4 &rc, Node &ch)
 {
-    child_id_k(d, par, 3ull, m, side, J, rc, ch);
+    child_id_k<1>(d, par, 3ull, m, side, J, rc, ch);
     ch.sg = 0;
     ch.w = 0.0;
     const double dx0 = (2.0 * J.q) * (double)par.sg;
@@ -489,174 +416,21 @@ __device__ __forceinline__ int64_t killed_amount(const Node &ch)
     return ch.sg;
 }
 
-// Child ch of the family in `slot`, kept in stash row r (the family's jump
-// is kept in the slot's xe0, xe1, te).
-template <int DIM, bool SP2, bool TAN>
-__device__ __forceinline__ void stash_record(Stash<DIM, SP2, TAN> *sh, int r, int slot, const Node &ch)
-{
-    sh->k0[r][slot] = ch.k[0];
-    if (DIM == 2) sh->k1[r][slot] = ch.k[1];
-    if (SP2) sh->w[r][slot] = ch.w; else sh->sg[r][slot] = (int8_t)ch.sg;
-    sh->id[r][slot] = ch.id;
-    if (TAN) {
-        sh->D[3 * r][slot] = ch.D[0];
-        sh->D[3 * r + 1][slot] = ch.D[1];
-        sh->D[3 * r + 2][slot] = ch.D[2];
-    }
-}
-
 // The block's overflow area of the pool (see kGPool): field f of record g
 // is at f * kGPool + g of the doubles.
 struct GPoolView {
     double *f;
     uint64_t *id;
-    uint32_t *sr;    // slot | rank << 16
     int8_t *sg;
 };
 __device__ __forceinline__ GPoolView gpool_view(const Dev &d)
 {
     char *b = d.gpool + (size_t)blockIdx.x * kGPoolBytes;
-    return {(double *)b, (uint64_t *)(b + (size_t)8 * 8 * kGPool), (uint32_t *)(b + (size_t)9 * 8 * kGPool),
-            (int8_t *)(b + (size_t)(9 * 8 + 4) * kGPool)};
+    return {(double *)b, (uint64_t *)(b + (size_t)8 * 8 * kGPool), (int8_t *)(b + (size_t)9 * 8 * kGPool)};
 }
 __device__ __forceinline__ uint32_t gpool_cap(const Dev &d)
 {
     return (int)blockIdx.x < d.gpool_blocks ? (uint32_t)kGPool : 0u;
-}
-
-template <int DIM, bool SP2, bool TAN>
-__device__ __forceinline__ bool pool_record(const Dev &d, Pool<DIM, SP2, TAN> *pl, int rank, int slot,
-                                            const double *xe, double te, const Node &ch)
-{
-    const uint32_t r = atomicAdd(&pl->n, 1u);
-    const double x0 = xe[0] + (d.vfac * ch.k[0]) * (d.dt - te);
-    const double x1 = DIM == 2 ? xe[1] + (d.vfac * ch.k[1]) * (d.dt - te) : 0.0;
-    if (r < (uint32_t)kPool) {
-        pl->x0[r] = x0;
-        pl->k0[r] = ch.k[0];
-        if (DIM == 2) {
-            pl->x1[r] = x1;
-            pl->k1[r] = ch.k[1];
-        }
-        if (SP2) pl->w[r] = ch.w; else pl->sg[r] = (int8_t)ch.sg;
-        pl->id[r] = ch.id;
-        if (TAN) {
-            pl->D[0][r] = ch.D[0];
-            pl->D[1][r] = ch.D[1];
-            pl->D[2][r] = ch.D[2];
-        }
-        pl->slot[r] = (uint16_t)slot;
-        pl->rank[r] = (uint16_t)rank;
-        return true;
-    }
-    const uint32_t g = r - (uint32_t)kPool;
-    if (g >= gpool_cap(d)) return false;
-    const GPoolView v = gpool_view(d);
-    v.f[g] = x0;
-    v.f[kGPool + g] = ch.k[0];
-    if (DIM == 2) {
-        v.f[2 * kGPool + g] = x1;
-        v.f[3 * kGPool + g] = ch.k[1];
-    }
-    if (SP2) v.f[4 * kGPool + g] = ch.w; else v.sg[g] = (int8_t)ch.sg;
-    if (TAN) {
-        v.f[5 * kGPool + g] = ch.D[0];
-        v.f[6 * kGPool + g] = ch.D[1];
-        v.f[7 * kGPool + g] = ch.D[2];
-    }
-    v.id[g] = ch.id;
-    v.sr[g] = (uint32_t)slot | ((uint32_t)rank << 16);
-    return true;
-}
-
-// A pair created at time te, as fast_family keeps it: both children into
-// the stash (clearing `fast` if it is full) unless the k-box removes them,
-// and `fast` cleared if either child jumps again within the step.
-template <int DIM, bool SP2, bool TAN>
-__device__ __forceinline__ void leaf_pair(const Dev &d, const InstParam &P, uint32_t step, const Node (&ch)[2],
-                                          double te, Stash<DIM, SP2, TAN> *sh, int slot,
-                                          uint32_t &cnt, Tally &tl, bool &fast)
-{
-    // both offspring's first clock draws, together
-    const W4 l0 = draw(ch[0].id, step, kTagStep, 0u, 0u, d.seed, P.key);
-    const W4 l1 = draw(ch[1].id, step, kTagStep, 0u, 0u, d.seed, P.key);
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-        if (!in_kbox<DIM>(d, ch[side].k)) {
-            tl.killed += killed_amount<SP2>(ch[side]);
-            continue;
-        }
-        if (cnt < (uint32_t)Stash<DIM, SP2, TAN>::R)
-            stash_record<DIM, SP2, TAN>(sh, (int)cnt, slot, ch[side]);
-        else fast = false;
-        cnt++;
-        if (tl.maxdepth < 1) tl.maxdepth = 1;
-        const double u0 = side == 0 ? unit53(l0.a, l0.b) : unit53(l1.a, l1.b);
-        if (!surely_no_jump(u0, te, d.dt, P.gamma0) && te + (-ln_series(1.0 - u0) / P.gamma0) <= d.dt)
-            fast = false;
-    }
-}
-
-// The common family in lockstep: the parent jumps once in the step, and
-// every kept child is a leaf (its first clock draw falls past the end of
-// the step).  Produces the same records, in the same order, and the same
-// tallies as walk_family would, with no per-lane state machine.  Returns
-// false if the family is not of this kind (a second jump of the parent, a
-// child that jumps again, or more than kStash records); cnt and tl are then
-// to be discarded.
-template <int DIM, bool SP2, bool TAN>
-__device__ __forceinline__ bool fast_family(const Dev &d, const InstParam &P, uint32_t step,
-                                            const Node &root, Stash<DIM, SP2, TAN> *sh, int slot,
-                                            uint32_t &cnt, Tally &tl)
-{
-    const uint32_t seed = d.seed, key = P.key;
-    cnt = 0;
-    // The draws that do not depend on each other are taken together, so
-    // their Philox chains interleave: the first and second clock draws, and
-    // the kick and child-id draws of component 0.
-    const W4 r = draw(root.id, step, kTagStep, 0u, 0u, seed, key);
-    const W4 r1 = draw(root.id, step, kTagStep, 1u, 0u, seed, key);
-    const W4 rq0 = draw(root.id, step, kTagStep, 0u, 1u, seed, key);
-    const W4 rc0 = draw(root.id, step, kTagChild, 0u, 0u, seed, key);
-    const double te = root.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
-    if (!(te <= d.dt)) return true;
-    tl.events++;
-    const double ua0 = unit53(r.c, r.d);
-    double xe[2];
-    xe[0] = root.x[0] + (d.vfac * root.k[0]) * (te - root.t0);
-    xe[1] = DIM == 2 ? root.x[1] + (d.vfac * root.k[1]) * (te - root.t0) : 0.0;
-    sh->xe0[slot] = xe[0];
-    if (DIM == 2) sh->xe1[slot] = xe[1];
-    sh->te[slot] = te;
-    bool fast = true;
-    for (int m = 0; m < d.M; ++m) {
-        PairDraw J;
-        if (!draw_pair<SP2>(d, P, root.id, step, 0u, m, xe, te, ua0, root.w, J, m == 0 ? &rq0 : nullptr))
-            continue;
-        tl.pairs++;
-        const W4 rc = m == 0 ? rc0 : draw(root.id, step, kTagChild, 0u, (uint32_t)m, seed, key);
-        Node ch[2];
-        make_child<SP2, TAN>(d, P, root, m, 0, J, rc, ch[0]);
-        make_child<SP2, TAN>(d, P, root, m, 1, J, rc, ch[1]);
-        leaf_pair<DIM, SP2, TAN>(d, P, step, ch, te, sh, slot, cnt, tl, fast);
-    }
-    if constexpr (TAN) {
-        if (d.tangent == 2 && root.sg != 0) {
-            for (int m = 0; m < d.M; ++m) {    // derivative pairs, after the jump's real pairs
-                PairDraw J;
-                if (!draw_deriv(d, P, root.id, step, 0u, m, xe, J, m == 0 ? &rq0 : nullptr)) continue;
-                const W4 rc = draw(root.id, step, kTagDeriv, 0u, (uint32_t)(8 + m), seed, key);
-                Node ch[2];
-                make_deriv_child(d, root, m, 0, J, rc, ch[0]);
-                make_deriv_child(d, root, m, 1, J, rc, ch[1]);
-                leaf_pair<DIM, SP2, TAN>(d, P, step, ch, te, sh, slot, cnt, tl, fast);
-            }
-        }
-    }
-    const double u1 = unit53(r1.a, r1.b);
-    if (!surely_no_jump(u1, te, d.dt, P.gamma0) && te + (-ln_series(1.0 - u1) / P.gamma0) <= d.dt)
-        fast = false;
-    return fast;
 }
 
 // Pair slots of a jump in walk_family: components 0..M-1, then (tangent
@@ -669,7 +443,7 @@ __device__ __forceinline__ int slot_end(const Dev &d, const Node &cur, int M)
     else return M;
 }
 
-template <bool SP2, bool TAN>
+template <int DIM, bool SP2, bool TAN, bool ONE>
 __device__ __forceinline__ bool slot_draw(const Dev &d, const InstParam &P, const Node &cur, uint32_t step,
                                           int slot, int M, PairDraw &J, W4 &rc)
 {
@@ -680,12 +454,12 @@ __device__ __forceinline__ bool slot_draw(const Dev &d, const InstParam &P, cons
             return true;
         }
     }
-    if (!draw_pair<SP2>(d, P, cur.id, step, cur.e, slot, cur.xe, cur.te, cur.ua0, cur.w, J)) return false;
+    if (!draw_pair<DIM, SP2, ONE>(d, P, cur.id, step, cur.e, slot, cur.xe, cur.te, cur.ua0, cur.w, J)) return false;
     rc = draw(cur.id, step, kTagChild, cur.e, (uint32_t)slot, d.seed, P.key);
     return true;
 }
 
-template <bool SP2, bool TAN>
+template <int DIM, bool SP2, bool TAN>
 __device__ __forceinline__ void slot_child(const Dev &d, const InstParam &P, const Node &cur, int slot, int M,
                                            int side, const PairDraw &J, const W4 &rc, Node &ch)
 {
@@ -695,24 +469,25 @@ __device__ __forceinline__ void slot_child(const Dev &d, const InstParam &P, con
             return;
         }
     }
-    make_child<SP2, TAN>(d, P, cur, slot, side, J, rc, ch);
+    make_child<DIM, SP2, TAN>(d, P, cur, slot, side, J, rc, ch);
 }
 
-// General depth-first walk of one family (any number of jumps and levels):
-// in the 4D and tangent kernels for every family that is not of the lockstep
-// kind, in the others for those whose nodes do not fit the tile's Tree.  Counting mode (EMIT false)
-// tallies, counts the records and puts them into the tile's pool if one is
-// given (clearing `pooled` if one did not fit); emitting mode writes every
-// record from first_rec on.
-template <int DIM, bool SP2, bool TAN, bool EMIT>
-__device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step, Node cur,
-                                const Ens &out, int64_t base, int64_t first_rec, int64_t cap,
-                                int64_t dstride, Tally &tl, uint32_t &err,
-                                Pool<DIM, SP2, TAN> *pl, int slot, bool &pooled)
+// General depth-first walk of one family (any number of jumps and levels),
+// by one lane: the path of the tiles whose families the pool below cannot
+// hold.  Counting (emit false) tallies and counts the records; emitting
+// writes every record from first_rec on.  Its stack makes it large, so it is
+// a function of its own: the common path keeps its registers.
+template <int DIM, bool SP2, bool TAN>
+__device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step, const Node *root, bool emit,
+                                             Ens out, int64_t base, int64_t first_rec, int64_t cap, int64_t dstride,
+                                             Tally *tl, uint32_t *err)
 {
+    const Dev &d = *dp;
+    const InstParam &P = d.ip[b];
     Node stack[kMaxDepth];
     PairDraw stackJ[kMaxDepth];
     W4 stackR[kMaxDepth];
+    Node cur = *root;
     int sp = 0;
     uint32_t nrec = 0;
     const uint32_t seed = d.seed, key = P.key;
@@ -725,7 +500,7 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
         if (!cur.in_ev) {
             bool done = false;
             if (cur.e >= kEventCap) {
-                if (!EMIT) tl.cap++;
+                if (!emit) tl->cap++;
                 done = true;
             } else {
                 const W4 r = draw(cur.id, step, kTagStep, cur.e, 0u, seed, key);
@@ -735,7 +510,7 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
                 if (!(te <= d.dt)) {
                     done = true;
                 } else {
-                    if (!EMIT) tl.events++;
+                    if (!emit) tl->events++;
                     cur.te = te;
                     cur.ua0 = unit53(r.c, r.d);
                     cur.xe[0] = cur.x[0] + (d.vfac * cur.k[0]) * (te - cur.t0);
@@ -762,11 +537,11 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
         PairDraw J;
         W4 rc;
         if (cur.side == 0) {
-            if (!slot_draw<SP2, TAN>(d, P, cur, step, m, M, J, rc)) {
+            if (!slot_draw<DIM, SP2, TAN, false>(d, P, cur, step, m, M, J, rc)) {
                 cur.m += 1;
                 continue;
             }
-            if (!EMIT && (!TAN || m < M)) tl.pairs++;
+            if (!emit && (!TAN || m < M)) tl->pairs++;
         } else {
             J = stackJ[sp];        // saved when this frame descended into its "+" offspring
             rc = stackR[sp];
@@ -774,12 +549,12 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
         bool descend = false;
         Node ch;
         for (int side = cur.side; side < 2 && !descend; ++side) {
-            slot_child<SP2, TAN>(d, P, cur, m, M, side, J, rc, ch);
+            slot_child<DIM, SP2, TAN>(d, P, cur, m, M, side, J, rc, ch);
             if (!in_kbox<DIM>(d, ch.k)) {          // k-truncation (Sec. 2)
-                if (!EMIT) tl.killed += killed_amount<SP2>(ch);
+                if (!emit) tl->killed += killed_amount<SP2>(ch);
                 continue;
             }
-            if (EMIT) {
+            if (emit) {
                 const int64_t li = first_rec + nrec;
                 if (li < cap) {
                     const int64_t o = base + li;
@@ -797,14 +572,12 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
                         out.D[2 * dstride + o] = ch.D[2];
                     }
                 } else {
-                    err |= kErrCapacity;
+                    *err |= kErrCapacity;
                 }
-            } else if (pooled) {
-                pooled = pool_record<DIM, SP2, TAN>(d, pl, (int)nrec, slot, cur.xe, cur.te, ch);
             }
             nrec++;
             ch.depth = cur.depth + 1;
-            if (!EMIT && ch.depth > tl.maxdepth) tl.maxdepth = ch.depth;
+            if (!emit && ch.depth > tl->maxdepth) tl->maxdepth = ch.depth;
             // The child's first clock draw, exactly as its own walk would take
             // it: most children do not jump before the end of the step, and
             // then there is nothing to walk and the parent stays off the stack.
@@ -814,7 +587,7 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
                 !(cur.te + (-ln_series(1.0 - u0) / P.gamma0) <= d.dt))
                 continue;
             if (sp >= kMaxDepth) {
-                err |= kErrDepth;
+                *err |= kErrDepth;
                 continue;
             }
             // descend into the child; the parent resumes with its "-"
@@ -848,144 +621,253 @@ __device__ uint32_t walk_family(const Dev &d, const InstParam &P, uint32_t step,
     return nrec;
 }
 
-// Expands node n of the tile's Tree (see Tree): walks its jumps from its
-// birth time to the end of the step and appends every kept offspring, and
-// the offspring that jump again to the next level.  The draws and the
-// arithmetic are walk_family's, so the records are the same.  A family
-// whose nodes overflow the Tree is marked in `in_tree` and left to
-// walk_family.
+// ---------------------------------------------------------------------------
+// The families of a tile, jump by jump.  A unit of work is one jump of one
+// particle: its pair decisions, its offspring with their first clock draws,
+// and the jumping particle's next clock draw.  Round 0 takes the parents'
+// first jumps, one per lane; every further jump found (the particle's next
+// one, or an offspring's first) goes to a queue in LDS and is taken in the
+// next round, the queue's jumps side by side in the first lanes.  A tile's
+// critical path is then its longest chain of jumps (2 to 4 for the barriers)
+// at about a thousand instructions each, and a rare second jump costs one
+// lane of a full round instead of a walk of its own.
+//
+// Every kept offspring is a record of the tile's pool.  Its place in the
+// canonical depth-first order is its path: one byte per level (jump index
+// + 1, pair slot, side), left-aligned in 64 bits, so that an unsigned
+// comparison orders a family's records (a node before its offspring).  The
+// records of a family are linked, and a record's rank is the number of its
+// family's smaller paths.  A particle that jumps again is referred to by its
+// record (a parent by a pool entry with path 0, which is no output).
+//
+// Payloads past kLds go to the block's overflow area in HBM (4D), the paths
+// and links stay in LDS.  A tile whose records, queue, levels (8) or jump
+// indexes (15) do not fit is done again by walk_family; Dev::ftile, the
+// parents per tile, is chosen so that this is rare.
+// ---------------------------------------------------------------------------
 template <int DIM, bool SP2, bool TAN>
-__device__ void expand_node(const Dev &d, const InstParam &P, uint32_t step, Tree<DIM, SP2, TAN> *tr, int n,
-                            int next, uint8_t *in_tree)
+struct Families {
+    static constexpr int kLds = DIM == 2 ? 384 : 512;           // records whose payload is in LDS
+    static constexpr int kRec = kLds + (DIM == 2 ? kGPool : 0); // records in all
+    static constexpr int kQueue = DIM == 2 ? 192 : 128;         // further jumps of a round
+    static constexpr int kLevels = 8;
+    // records
+    uint64_t key[kRec], id[kLds];
+    double x0[kLds], k0[kLds];
+    double x1[DIM == 2 ? kLds : 1], k1[DIM == 2 ? kLds : 1];
+    double w[SP2 ? kLds : 1];
+    double D[TAN ? 3 : 1][TAN ? kLds : 1];
+    uint16_t slot[kRec], next[kRec];
+    int8_t sg[kLds];
+    // jumps of the next round
+    double qx0[kQueue], qx1[DIM == 2 ? kQueue : 1], qt0[kQueue], qte[kQueue], qua[kQueue];
+    uint16_t qrec[kQueue], qe[kQueue];
+    // per family
+    uint32_t cnt[kThreads], first[kThreads];
+    uint32_t head[kThreads];
+    uint32_t n, nq[2], overflow;
+    uint32_t events, pairs, maxdepth;
+    long long killed;
+};
+
+constexpr uint32_t kNone = 0xFFFFu;
+
+// Puts node `ch` with path `key` into the pool (end-of-step position from
+// the jump at xe, te; a parent's entry has path 0 and is not linked) and
+// returns its index, or kNone if the pool is full.
+template <int DIM, bool SP2, bool TAN>
+__device__ __forceinline__ uint32_t add_record(const Dev &d, Families<DIM, SP2, TAN> &F, uint64_t key, int slot,
+                                               const double *xe, double te, const Node &ch)
 {
-    const uint32_t seed = d.seed, key = P.key;
-    const int M = d.M;
-    const int fam = tr->slot[n];
-    Node cur;
-    cur.x[0] = tr->x0[n];
-    cur.k[0] = tr->k0[n];
-    cur.x[1] = DIM == 2 ? tr->x1[n] : 0.0;
-    cur.k[1] = DIM == 2 ? tr->k1[n] : 0.0;
-    cur.t0 = tr->t0[n];
-    cur.w = SP2 ? tr->w[n] : 0.0;
+    using FT = Families<DIM, SP2, TAN>;
+    const uint32_t r = atomicAdd(&F.n, 1u);
+    if (r >= (uint32_t)FT::kRec || (DIM == 2 && r >= (uint32_t)FT::kLds && r - (uint32_t)FT::kLds >= gpool_cap(d))) {
+        F.overflow = 1u;
+        return kNone;
+    }
+    const double x0 = xe[0] + (d.vfac * ch.k[0]) * (d.dt - te);
+    const double x1 = DIM == 2 ? xe[1] + (d.vfac * ch.k[1]) * (d.dt - te) : 0.0;
+    F.key[r] = key;
+    F.slot[r] = (uint16_t)slot;
+    if (key) {
+        F.next[r] = (uint16_t)atomicExch(&F.head[slot], r);
+        atomicAdd(&F.cnt[slot], 1u);
+    }
+    if (DIM == 1 || r < (uint32_t)FT::kLds) {
+        F.x0[r] = x0;
+        F.k0[r] = ch.k[0];
+        if (DIM == 2) {
+            F.x1[r] = x1;
+            F.k1[r] = ch.k[1];
+        }
+        if (SP2) F.w[r] = ch.w; else F.sg[r] = (int8_t)ch.sg;
+        F.id[r] = ch.id;
+        if (TAN) {
+            F.D[0][r] = ch.D[0];
+            F.D[1][r] = ch.D[1];
+            F.D[2][r] = ch.D[2];
+        }
+        return r;
+    }
+    const uint32_t g = r - (uint32_t)FT::kLds;
+    const GPoolView v = gpool_view(d);
+    v.f[g] = x0;
+    v.f[kGPool + g] = ch.k[0];
+    if (DIM == 2) {
+        v.f[2 * kGPool + g] = x1;
+        v.f[3 * kGPool + g] = ch.k[1];
+    }
+    if (SP2) v.f[4 * kGPool + g] = ch.w; else v.sg[g] = (int8_t)ch.sg;
     if (TAN) {
-        cur.D[0] = tr->D[0][n];
-        cur.D[1] = tr->D[1][n];
-        cur.D[2] = tr->D[2][n];
-    } else {
-        cur.D[0] = cur.D[1] = cur.D[2] = 0.0;
+        v.f[5 * kGPool + g] = ch.D[0];
+        v.f[6 * kGPool + g] = ch.D[1];
+        v.f[7 * kGPool + g] = ch.D[2];
     }
-    cur.id = tr->id[n];
-    cur.sg = SP2 ? 0 : (int32_t)tr->sg[n];
-    cur.depth = tr->depth[n];
-    uint32_t nkept = 0, nev = 0, npairs = 0;
-    int64_t killed = 0;
-    uint8_t capped = 0;
-    double t = cur.t0;
-    for (uint32_t e = 0;; ++e) {
-        if (e >= kEventCap) {
-            capped = 1;
-            break;
-        }
-        const W4 r = draw(cur.id, step, kTagStep, e, 0u, seed, key);
-        const double u = unit53(r.a, r.b);
-        const double te = surely_no_jump(u, t, d.dt, P.gamma0) ? d.dt + 1.0 : t + (-ln_series(1.0 - u) / P.gamma0);
-        if (!(te <= d.dt)) break;
-        nev++;
-        cur.e = e;
-        cur.te = te;
-        cur.ua0 = unit53(r.c, r.d);
-        cur.xe[0] = cur.x[0] + (d.vfac * cur.k[0]) * (te - cur.t0);
-        cur.xe[1] = DIM == 2 ? cur.x[1] + (d.vfac * cur.k[1]) * (te - cur.t0) : 0.0;
-        const int mend = slot_end<TAN>(d, cur, M);
-        for (int m = 0; m < mend; ++m) {
-            PairDraw J;
-            W4 rc;
-            if (!slot_draw<SP2, TAN>(d, P, cur, step, m, M, J, rc)) continue;
-            if (!TAN || m < M) npairs++;
-            for (int side = 0; side < 2; ++side) {
-                Node ch;
-                slot_child<SP2, TAN>(d, P, cur, m, M, side, J, rc, ch);
-                if (!in_kbox<DIM>(d, ch.k)) {          // k-truncation (Sec. 2)
-                    killed += killed_amount<SP2>(ch);
-                    continue;
-                }
-                const uint32_t c = atomicAdd(&tr->n, 1u);
-                if (c >= (uint32_t)Tree<DIM, SP2, TAN>::kNodes) {
-                    in_tree[fam] = 0;
-                    continue;
-                }
-                tr->x0[c] = cur.xe[0];
-                tr->k0[c] = ch.k[0];
-                if (DIM == 2) {
-                    tr->x1[c] = cur.xe[1];
-                    tr->k1[c] = ch.k[1];
-                }
-                tr->t0[c] = te;
-                if (SP2) tr->w[c] = ch.w; else tr->sg[c] = (int8_t)ch.sg;
-                if (TAN) {
-                    tr->D[0][c] = ch.D[0];
-                    tr->D[1][c] = ch.D[1];
-                    tr->D[2][c] = ch.D[2];
-                }
-                tr->id[c] = ch.id;
-                tr->par[c] = (uint16_t)n;
-                tr->rank[c] = (uint16_t)nkept;
-                tr->slot[c] = (uint16_t)fam;
-                tr->depth[c] = (uint8_t)(cur.depth + 1);
-                atomicMax(&tr->maxd, (uint32_t)(cur.depth + 1));
-                tr->nch[c] = 0;
-                tr->size[c] = 0;
-                tr->events[c] = 0;
-                tr->pairs[c] = 0;
-                tr->killed[c] = 0;
-                tr->capped[c] = 0;
-                nkept++;
-                // the offspring's first clock draw, as its own walk takes it
-                const W4 r0 = draw(ch.id, step, kTagStep, 0u, 0u, seed, key);
-                const double u0 = unit53(r0.a, r0.b);
-                if (!surely_no_jump(u0, te, d.dt, P.gamma0) && te + (-ln_series(1.0 - u0) / P.gamma0) <= d.dt) {
-                    tr->front[next][atomicAdd(&tr->nf[next], 1u)] = (uint16_t)c;
-                }
-            }
-        }
-        t = te;
-    }
-    tr->nch[n] = (uint16_t)nkept;
-    tr->events[n] = (uint16_t)nev;
-    tr->pairs[n] = (uint16_t)npairs;
-    tr->killed[n] = killed;
-    tr->capped[n] = capped;
+    v.id[g] = ch.id;
+    return r;
 }
 
+// Record r's node (its end-of-step position in x): for the particles that
+// jump again, and for the output.
 template <int DIM, bool SP2, bool TAN>
-__global__ __launch_bounds__(kThreads, 3) void k_family(Dev d, int ghost)
+__device__ __forceinline__ void load_record(const Dev &d, const Families<DIM, SP2, TAN> &F, uint32_t r, Node &n)
 {
-    // A tile holds FS event parents, slot = tid + h * kThreads for h < SPT.
-    constexpr int FS = Stash<DIM, SP2, TAN>::F;
-    constexpr int SPT = FS / kThreads;
-    constexpr int NN = Tree<DIM, SP2, TAN>::kNodes;
-    // level-by-level expansion for the 1D kernels (with tangents the table
-    // needs 78 KB of LDS, two blocks per CU, which their registers allow
-    // anyway); the 4D ones (about half the families of a tile are slow) keep
-    // the pool and one depth-first walk per lane
-    constexpr bool kTree = DIM == 1;
-    __shared__ int64_t s_t;
+    using FT = Families<DIM, SP2, TAN>;
+    n.x[1] = n.k[1] = n.w = n.D[0] = n.D[1] = n.D[2] = 0.0;
+    n.sg = 0;
+    if (DIM == 1 || r < (uint32_t)FT::kLds) {
+        n.x[0] = F.x0[r];
+        n.k[0] = F.k0[r];
+        if (DIM == 2) {
+            n.x[1] = F.x1[r];
+            n.k[1] = F.k1[r];
+        }
+        if (SP2) n.w = F.w[r]; else n.sg = F.sg[r];
+        n.id = F.id[r];
+        if (TAN) {
+            n.D[0] = F.D[0][r];
+            n.D[1] = F.D[1][r];
+            n.D[2] = F.D[2][r];
+        }
+        return;
+    }
+    const uint32_t g = r - (uint32_t)FT::kLds;
+    const GPoolView v = gpool_view(d);
+    n.x[0] = v.f[g];
+    n.k[0] = v.f[kGPool + g];
+    if (DIM == 2) {
+        n.x[1] = v.f[2 * kGPool + g];
+        n.k[1] = v.f[3 * kGPool + g];
+    }
+    if (SP2) n.w = v.f[4 * kGPool + g]; else n.sg = v.sg[g];
+    if (TAN) {
+        n.D[0] = v.f[5 * kGPool + g];
+        n.D[1] = v.f[6 * kGPool + g];
+        n.D[2] = v.f[7 * kGPool + g];
+    }
+    n.id = v.id[g];
+}
+
+// A further jump, at te, of the particle in record rec born at (x, t0).
+template <int DIM, bool SP2, bool TAN>
+__device__ __forceinline__ void add_jump(Families<DIM, SP2, TAN> &F, int round, const double *x, double t0, double te,
+                                         double ua, uint32_t rec, uint32_t e)
+{
+    using FT = Families<DIM, SP2, TAN>;
+    const uint32_t q = atomicAdd(&F.nq[round & 1], 1u);
+    if (q >= (uint32_t)FT::kQueue || rec == kNone) {
+        F.overflow = 1u;
+        return;
+    }
+    F.qx0[q] = x[0];
+    if (DIM == 2) F.qx1[q] = x[1];
+    F.qt0[q] = t0;
+    F.qte[q] = te;
+    F.qua[q] = ua;
+    F.qrec[q] = (uint16_t)rec;
+    F.qe[q] = (uint16_t)e;
+}
+
+// One jump: particle cur (x, k at its birth time t0) jumps at te, its e-th
+// jump of the step, in family `slot`, with path `key` of `lev` levels.  rec:
+// its record, or kNone for a parent's first jump.
+template <int DIM, bool SP2, bool TAN, bool ONE>
+__device__ __forceinline__ void take_jump(const Dev &d, const InstParam &P, uint32_t step, int round, Node &cur,
+                                          uint64_t key, int lev, int slot, uint32_t rec,
+                                          Families<DIM, SP2, TAN> &F)
+{
+    using FT = Families<DIM, SP2, TAN>;
+    const uint32_t seed = d.seed, pk = P.key;
+    const int M = ONE ? 1 : d.M;
+    const double te = cur.te, g0 = P.gamma0;
+    if (lev >= FT::kLevels || cur.e >= 15u) {
+        F.overflow = 1u;
+        return;
+    }
+    const int sh = 56 - 8 * lev;
+    cur.xe[0] = cur.x[0] + (d.vfac * cur.k[0]) * (te - cur.t0);
+    cur.xe[1] = DIM == 2 ? cur.x[1] + (d.vfac * cur.k[1]) * (te - cur.t0) : 0.0;
+    atomicAdd(&F.events, 1u);
+    const W4 rn = draw(cur.id, step, kTagStep, cur.e + 1u, 0u, seed, pk);
+    const int mend = slot_end<TAN>(d, cur, M);
+    for (int m = 0; m < mend; ++m) {
+        PairDraw J;
+        W4 rc;
+        if (!slot_draw<DIM, SP2, TAN, ONE>(d, P, cur, step, m, M, J, rc)) continue;
+        if (!TAN || m < M) atomicAdd(&F.pairs, 1u);
+        const uint64_t base = key | ((uint64_t)(((cur.e + 1u) << 4) | ((uint32_t)m << 1)) << sh);
+        // both offspring, then the first clock draws of those that may jump
+        // again before the end of the step (a few percent): the logarithm
+        // is shared by the two
+        Node ch;
+        uint32_t rr[2], pend = 0u;
+        double uu[2], ua[2];
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            slot_child<DIM, SP2, TAN>(d, P, cur, m, M, side, J, rc, ch);
+            const W4 l = draw(ch.id, step, kTagStep, 0u, 0u, seed, pk);
+            uu[side] = unit53(l.a, l.b);
+            ua[side] = unit53(l.c, l.d);
+            rr[side] = kNone;
+            if (in_kbox<DIM>(d, ch.k)) {
+                rr[side] = add_record<DIM, SP2, TAN>(d, F, base | ((uint64_t)side << sh), slot, cur.xe, te, ch);
+                if (!surely_no_jump(uu[side], te, d.dt, g0)) pend |= 1u << side;
+            } else {                                       // k-truncation (Sec. 2)
+                atomicAdd((unsigned long long *)&F.killed, (unsigned long long)killed_amount<SP2>(ch));
+            }
+        }
+        while (pend) {
+            const bool s0 = pend & 1u;
+            const double tc = te + (-ln_series(1.0 - (s0 ? uu[0] : uu[1])) / g0);
+            if (tc <= d.dt)
+                add_jump<DIM, SP2, TAN>(F, round, cur.xe, te, tc, s0 ? ua[0] : ua[1], s0 ? rr[0] : rr[1], 0u);
+            pend &= s0 ? 2u : 0u;
+        }
+    }
+    const double un = unit53(rn.a, rn.b);
+    if (!surely_no_jump(un, te, d.dt, g0)) {
+        const double tn = te + (-ln_series(1.0 - un) / g0);
+        if (tn <= d.dt) {
+            if (rec == kNone) rec = add_record<DIM, SP2, TAN>(d, F, 0ull, slot, cur.xe, te, cur);
+            add_jump<DIM, SP2, TAN>(F, round, cur.x, cur.t0, tn, unit53(rn.c, rn.d), rec, cur.e + 1u);
+        }
+    }
+}
+
+template <int DIM, bool SP2, bool TAN, bool ONE>
+__global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_family(Dev d, int ghost)
+{
+    using FT = Families<DIM, SP2, TAN>;
+    __shared__ int32_t s_t;
     __shared__ uint32_t s_wsum[4];
     __shared__ int64_t s_excl;
     __shared__ int64_t s_tal[5];
-    __shared__ uint32_t s_nslow;
-    __shared__ uint16_t s_slow[FS];          // slots whose family needs the general walk
-    __shared__ uint32_t s_cnt[FS];           // record count of every slot
-    __shared__ int64_t s_first[FS];          // output offset of every slot's first record
-    __shared__ uint8_t s_tree[FS];           // the slot's family is in the Tree (or the pool)
-    __shared__ uint8_t s_fast[FS];           // the slot's records are in the stash
-    __shared__ Stash<DIM, SP2, TAN> s_stash;
-    __shared__ typename std::conditional<kTree, Tree<DIM, SP2, TAN>, Pool<DIM, SP2, TAN>>::type s_walk;
+    __shared__ FT F;
 
     Ctl *ctl = d.ctl;
     const uint32_t step = ctl->step;
     const int B = d.B;
+    const int FS = ghost ? d.gftile : d.ftile;     // event parents per tile
     const int64_t *plan = d.tileB + (int64_t)ghost * (B + 1);
     const int64_t ntiles = plan[B];
     const uint32_t set = ghost ? ctl->gcur : ctl->cur;
@@ -1002,31 +884,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_family(Dev d, int ghost)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     uint32_t err = 0;
 
-    // the event parent at index i of the particle set, at the start of the
-    // step, and that of tile position `slot`
-    auto load_root_at = [&](int64_t i) {
-        Node root;
-        root.x[0] = E.x0[i];
-        root.x[1] = DIM == 2 ? E.x1[i] : 0.0;
-        root.k[0] = E.k0[i];
-        root.k[1] = DIM == 2 ? E.k1[i] : 0.0;
-        root.t0 = 0.0;
-        root.id = E.id[i];
-        root.w = SP2 ? E.w[i] : 0.0;
-        root.sg = SP2 ? 0 : (int32_t)E.sg[i];
-        if (TAN) {
-            root.D[0] = E.D[i];
-            root.D[1] = E.D[dstride + i];
-            root.D[2] = E.D[2 * dstride + i];
-        } else {
-            root.D[0] = root.D[1] = root.D[2] = 0.0;
-        }
-        return root;
-    };
-    auto load_root = [&](int64_t base, int64_t j0, int slot) {
-        return load_root_at(base + (int64_t)evi[base + j0 + slot]);
-    };
-
     // Tallies stay in LDS while the block works on one instance; they go to
     // the instance's counters when the block moves on to another one, and the
     // last instance's share is left in the block's slot of fpart for the
@@ -1037,14 +894,16 @@ __global__ __launch_bounds__(kThreads, 3) void k_family(Dev d, int ghost)
     if (tid < 5) s_tal[tid] = 0;
     for (;;) {
         if (tid == 0) {
-            s_t = next_tile_static_first(&ctl->ticket[pass], ntiles, first);
-            s_nslow = 0;
-            if constexpr (!kTree) s_walk.n = 0;
+            s_t = (int32_t)next_tile_static_first(&ctl->ticket[pass], ntiles, first);
+            F.n = F.nq[0] = F.nq[1] = F.overflow = F.events = F.pairs = F.maxdepth = 0u;
+            F.killed = 0;
         }
+        F.cnt[tid] = 0u;
+        F.head[tid] = kNone;
         __syncthreads();
-        const int64_t t = s_t;
+        const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
         if (t >= ntiles) break;
-        const int b = segment_of(plan, B, t);
+        const int b = __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
         if (b != cb) {
             if (tid == 0 && cb >= 0) {
                 int64_t *T = d.tally + (int64_t)cb * kTalCount;
@@ -1057,225 +916,95 @@ __global__ __launch_bounds__(kThreads, 3) void k_family(Dev d, int ghost)
             }
             cb = b;
         }
-        const int64_t tl_i = t - plan[b];
         const InstParam &P = d.ip[b];
         const int64_t base = ghost ? P.gbase : P.base;
         const int64_t cap = ghost ? P.gcap : P.cap;
         const int64_t nev = d.evc[(int64_t)ghost * B + b];
-        const int64_t j0 = tl_i * FS;
+        const int64_t j0 = (t - plan[b]) * FS;
+        const bool live = tid < FS && j0 + tid < nev;
 
-        // 1. every family in lockstep on the common path; a slow family's
-        //    partial tallies are dropped (its general walk counts them)
+        // 1. the parents' first jumps, then round by round those found
+        int64_t pi = base;
+        auto load_root = [&]() {
+            Node root;
+            root.x[0] = E.x0[pi];
+            root.x[1] = DIM == 2 ? E.x1[pi] : 0.0;
+            root.k[0] = E.k0[pi];
+            root.k[1] = DIM == 2 ? E.k1[pi] : 0.0;
+            root.t0 = 0.0;
+            root.id = E.id[pi];
+            root.w = SP2 ? E.w[pi] : 0.0;
+            root.sg = SP2 ? 0 : (int32_t)E.sg[pi];
+            root.D[0] = TAN ? E.D[pi] : 0.0;
+            root.D[1] = TAN ? E.D[dstride + pi] : 0.0;
+            root.D[2] = TAN ? E.D[2 * dstride + pi] : 0.0;
+            return root;
+        };
+        {
+            Node cur;
+            uint64_t key = 0ull;
+            uint32_t rec = kNone;
+            int slot = tid, lev = 0;
+            bool act = false;
+            if (live) {
+                pi = base + (int64_t)evi[base + j0 + tid];
+                cur = load_root();
+                const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
+                cur.te = cur.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
+                cur.ua0 = unit53(r.c, r.d);
+                cur.e = 0u;
+                act = cur.te <= d.dt;
+            }
+            for (int round = 0;; ++round) {
+                if (act) take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, F);
+                __syncthreads();
+                const uint32_t nq = F.nq[round & 1];
+                if (nq == 0u || F.overflow) break;
+                act = tid < (int)nq;
+                if (act) {
+                    rec = F.qrec[tid];
+                    load_record<DIM, SP2, TAN>(d, F, rec, cur);
+                    cur.x[0] = F.qx0[tid];
+                    cur.x[1] = DIM == 2 ? F.qx1[tid] : 0.0;
+                    cur.t0 = F.qt0[tid];
+                    cur.te = F.qte[tid];
+                    cur.ua0 = F.qua[tid];
+                    cur.e = F.qe[tid];
+                    key = F.key[rec];
+                    slot = F.slot[rec];
+                    lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
+                }
+                if (tid == 0) F.nq[(round + 1) & 1] = 0u;
+                __syncthreads();
+            }
+        }
+        const bool overflow = F.overflow != 0u;
         Tally tal{0, 0, 0, 0, 0};
-#pragma unroll
-        for (int h = 0; h < SPT; ++h) {
-            const int slot = tid + h * kThreads;
-            uint32_t cnt = 0;
-            bool fast = false;
-            if (j0 + slot < nev) {
-                const int64_t pi = base + (int64_t)evi[base + j0 + slot];
-                const Node root = load_root_at(pi);
-                // the parent's position at the end of the step (k_stream left
-                // it at the start)
-                const double xend0 = root.x[0] + (d.vfac * root.k[0]) * d.dt;
-                const double xend1 = DIM == 2 ? root.x[1] + (d.vfac * root.k[1]) * d.dt : 0.0;
-                Tally th{0, 0, 0, 0, 0};
-                fast = fast_family<DIM, SP2, TAN>(d, P, step, root, &s_stash, slot, cnt, th);
-                if (fast) {
-                    tal.events += th.events;
-                    tal.pairs += th.pairs;
-                    tal.killed += th.killed;
-                    tal.cap += th.cap;
-                    tal.maxdepth = max(tal.maxdepth, th.maxdepth);
-                    // nothing in this launch reads a lockstep family's parent
-                    // again: it moves now, with no second gather
-                    E.x0[pi] = xend0;
-                    if (DIM == 2) E.x1[pi] = xend1;
-                } else {
-                    s_slow[atomicAdd(&s_nslow, 1u)] = (uint16_t)slot;
-                }
+        if (overflow) {   // (uniform) every family of the tile by the general walk
+            F.cnt[tid] = 0u;
+            if (live) {
+                const Node root = load_root();
+                F.cnt[tid] = walk_family<DIM, SP2, TAN>(d.self, b, step, &root, false, S, base, 0, cap, dstride, &tal, &err);
             }
-            s_cnt[slot] = fast ? cnt : 0u;
-            s_fast[slot] = fast ? 1 : 0;
+            __syncthreads();
         }
+
+        // 2. ordered exclusive scan of the record counts over the tile
+        const uint32_t c = F.cnt[tid];
+        uint32_t incl = c;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += v;
+        }
+        if (lane == 63) s_wsum[wv] = incl;
         __syncthreads();
-        // 2. the other families: level by level in the Tree, or walked depth
-        //    first, one family per lane, with their records pooled
-        const int nslow = (int)s_nslow;
-        const int kme = lane * 4 + wv;
-        int nn = 0;                          // Tree nodes
-        if constexpr (kTree) {
-            auto &tree = s_walk;
-            // root k of the slow list is node k; nodes are spread over the
-            // block's threads with consecutive ones in different wavefronts
-            for (int k = tid; k < nslow; k += kThreads) {
-                const int slot = s_slow[k];
-                s_tree[slot] = k < NN ? 1 : 0;
-                if (k >= NN) continue;
-                const Node root = load_root(base, j0, slot);
-                tree.x0[k] = root.x[0];
-                tree.k0[k] = root.k[0];
-                if (DIM == 2) {
-                    tree.x1[k] = root.x[1];
-                    tree.k1[k] = root.k[1];
-                }
-                tree.t0[k] = 0.0;
-                if (SP2) tree.w[k] = root.w; else tree.sg[k] = (int8_t)root.sg;
-                if (TAN) {
-                    tree.D[0][k] = root.D[0];
-                    tree.D[1][k] = root.D[1];
-                    tree.D[2][k] = root.D[2];
-                }
-                tree.id[k] = root.id;
-                tree.slot[k] = (uint16_t)slot;
-                tree.depth[k] = 0;
-                tree.size[k] = 0;
-                tree.nch[k] = 0;
-                tree.events[k] = 0;
-                tree.pairs[k] = 0;
-                tree.killed[k] = 0;
-                tree.capped[k] = 0;
-                tree.front[0][k] = (uint16_t)k;
-            }
-            if (tid == 0) {
-                const uint32_t nr = (uint32_t)min(nslow, NN);
-                tree.n = nr;
-                tree.nf[0] = nr;
-                tree.nf[1] = 0;
-                tree.maxd = 0;
-            }
-            __syncthreads();
-            for (int lv = 0;; lv ^= 1) {
-                const uint32_t nf = tree.nf[lv];
-                if (nf == 0) break;
-                for (uint32_t k = kme; k < nf; k += kThreads) {
-                    const int n = tree.front[lv][k];
-                    if (s_tree[tree.slot[n]]) expand_node<DIM, SP2, TAN>(d, P, step, &tree, n, lv ^ 1, s_tree);
-                }
-                __syncthreads();
-                if (tid == 0) tree.nf[lv] = 0;
-                __syncthreads();
-            }
-            nn = (int)min(tree.n, (uint32_t)NN);
-            const int maxd = (int)tree.maxd;
-            // subtree sizes, deepest level first (a root gets its family's count)
-            for (int dd = maxd; dd >= 1; --dd) {
-                for (int k = tid; k < nn; k += kThreads)
-                    if (tree.depth[k] == dd) {
-                        const uint32_t sz = tree.size[k] + 1u;
-                        tree.size[k] = sz;
-                        atomicAdd(&tree.size[tree.par[k]], sz);
-                    }
-                __syncthreads();
-            }
-            // offspring grouped by parent (exclusive scan of the offspring counts
-            // in node order), then depth-first positions, top level first
-            {
-                constexpr int NPT = NN / kThreads;    // nodes tid * NPT + q, q < NPT
-                uint32_t c[NPT], csum = 0;
-    #pragma unroll
-                for (int q = 0; q < NPT; ++q) {
-                    const int k = tid * NPT + q;
-                    c[q] = k < nn ? (uint32_t)tree.nch[k] : 0u;
-                    csum += c[q];
-                }
-                uint32_t incl = csum;
-    #pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t v = __shfl_up(incl, o, 64);
-                    if (lane >= o) incl += v;
-                }
-                if (lane == 63) s_wsum[wv] = incl;
-                __syncthreads();
-                uint32_t run = incl - csum;
-                for (int q = 0; q < wv; ++q) run += s_wsum[q];
-    #pragma unroll
-                for (int q = 0; q < NPT; ++q) {
-                    const int k = tid * NPT + q;
-                    if (k < nn) {
-                        tree.cst[k] = (uint16_t)run;
-                        if (tree.depth[k] == 0) tree.pos[k] = -1;
-                    }
-                    run += c[q];
-                }
-                __syncthreads();
-            }
-            for (int k = tid; k < nn; k += kThreads)
-                if (tree.depth[k] > 0) tree.child[tree.cst[tree.par[k]] + tree.rank[k]] = (uint16_t)k;
-            __syncthreads();
-            for (int dd = 0; dd < maxd; ++dd) {
-                for (int k = tid; k < nn; k += kThreads)
-                    if (tree.depth[k] == dd) {
-                        int run = tree.pos[k] + 1;
-                        const int c0 = tree.cst[k], nc = tree.nch[k];
-                        for (int j = 0; j < nc; ++j) {
-                            const int c = tree.child[c0 + j];
-                            tree.pos[c] = (int16_t)run;
-                            run += (int)tree.size[c];
-                        }
-                    }
-                __syncthreads();
-            }
-            // record counts, tallies (from the Tree, or by a counting walk for the
-            // families that did not fit)
-            for (int k = tid; k < nn; k += kThreads) {
-                if (!s_tree[tree.slot[k]]) continue;
-                tal.events += tree.events[k];
-                tal.pairs += tree.pairs[k];
-                tal.killed += tree.killed[k];
-                tal.cap += tree.capped[k];
-                tal.maxdepth = max(tal.maxdepth, (int32_t)tree.depth[k]);
-            }
-            for (int k = kme; k < nslow; k += kThreads) {
-                const int slot = s_slow[k];
-                if (s_tree[slot]) {
-                    s_cnt[slot] = tree.size[k];
-                    continue;
-                }
-                const Node root = load_root(base, j0, slot);
-                bool unused = false;
-                s_cnt[slot] = walk_family<DIM, SP2, TAN, false>(d, P, step, root, E, base, 0, cap, dstride, tal, err,
-                                                                nullptr, slot, unused);
-            }
-            __syncthreads();
-
-        } else {
-            auto &s_pool = s_walk;
-            for (int k = kme; k < nslow; k += kThreads) {
-                const int slot = s_slow[k];
-                const Node root = load_root(base, j0, slot);
-                bool pooled = true;
-                s_cnt[slot] = walk_family<DIM, SP2, TAN, false>(d, P, step, root, E, base, 0, cap, dstride, tal,
-                                                                err, &s_pool, slot, pooled);
-                s_tree[slot] = pooled ? 1 : 0;
-            }
-            __syncthreads();
+        uint32_t excl = incl - c, agg = 0;
+        for (int q = 0; q < 4; ++q) {
+            if (q < wv) excl += s_wsum[q];
+            agg += s_wsum[q];
         }
-
-        // 3. ordered exclusive scan of the record counts over the tile, in
-        //    slot order (h, then tid)
-        uint32_t excl[SPT];
-        uint32_t agg = 0;
-#pragma unroll
-        for (int h = 0; h < SPT; ++h) {
-            const uint32_t c = s_cnt[tid + h * kThreads];
-            uint32_t incl = c;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t v = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += v;
-            }
-            if (lane == 63) s_wsum[wv] = incl;
-            __syncthreads();
-            uint32_t woff = 0, part = 0;
-            for (int q = 0; q < 4; ++q) {
-                if (q < wv) woff += s_wsum[q];
-                part += s_wsum[q];
-            }
-            excl[h] = agg + woff + incl - c;
-            agg += part;
-            __syncthreads();
-        }
+        F.first[tid] = excl;
         if (tid == 0) {
             // the tile's records take a contiguous stretch of the staging
             // area; no tile waits for another
@@ -1288,164 +1017,70 @@ __global__ __launch_bounds__(kThreads, 3) void k_family(Dev d, int ghost)
                 atomicAdd((unsigned long long *)&tsup[(t / kSupGroup) * kSupStride], (unsigned long long)agg);
         }
         __syncthreads();
-#pragma unroll
-        for (int h = 0; h < SPT; ++h) s_first[tid + h * kThreads] = s_excl + (int64_t)excl[h];
 
-        // 4. records into the staging area: from the stash and the Tree (or
-        //    the pool), or by a second full walk for a family that did not fit
-#pragma unroll
-        for (int h = 0; h < SPT; ++h) {
-            const int slot = tid + h * kThreads;
-            if (!s_fast[slot]) continue;
-            const uint32_t cnt = s_cnt[slot];
-            const int64_t my_first = s_excl + (int64_t)excl[h];
-            const double xe0 = s_stash.xe0[slot], xe1 = DIM == 2 ? s_stash.xe1[slot] : 0.0;
-            const double rest = d.dt - s_stash.te[slot];
-            for (uint32_t r = 0; r < cnt; ++r) {
-                const int64_t li = my_first + r;
+        // 3. records into the staging area, each at its rank in its family
+        const int64_t sfirst = s_excl;
+        if (!overflow) {
+            const uint32_t nrec = F.n;
+            uint32_t deep = 0;
+            for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
+                const uint64_t key = F.key[r];
+                if (key == 0ull) continue;
+                const int slot = F.slot[r];
+                uint32_t rank = 0;
+                for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
+                deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
+                const int64_t li = sfirst + (int64_t)(F.first[slot] + rank);
                 if (li >= cap) { err |= kErrCapacity; continue; }
                 const int64_t o = base + li;
-                const double k0 = s_stash.k0[r][slot];
-                S.x0[o] = xe0 + (d.vfac * k0) * rest;
-                S.k0[o] = k0;
+                Node n;
+                load_record<DIM, SP2, TAN>(d, F, r, n);
+                S.x0[o] = n.x[0];
+                S.k0[o] = n.k[0];
                 if (DIM == 2) {
-                    const double k1 = s_stash.k1[r][slot];
-                    S.x1[o] = xe1 + (d.vfac * k1) * rest;
-                    S.k1[o] = k1;
+                    S.x1[o] = n.x[1];
+                    S.k1[o] = n.k[1];
                 }
-                if (SP2) S.w[o] = s_stash.w[r][slot]; else S.sg[o] = s_stash.sg[r][slot];
-                S.id[o] = s_stash.id[r][slot];
+                if (SP2) S.w[o] = n.w; else S.sg[o] = (int8_t)n.sg;
+                S.id[o] = n.id;
                 if (TAN) {
-                    S.D[o] = s_stash.D[3 * r][slot];
-                    S.D[dstride + o] = s_stash.D[3 * r + 1][slot];
-                    S.D[2 * dstride + o] = s_stash.D[3 * r + 2][slot];
+                    S.D[o] = n.D[0];
+                    S.D[dstride + o] = n.D[1];
+                    S.D[2 * dstride + o] = n.D[2];
                 }
             }
-        }
-        __syncthreads();
-        if constexpr (kTree) {
-            auto &tree = s_walk;
-            for (int k = tid; k < nn; k += kThreads) {
-                if (tree.depth[k] == 0 || !s_tree[tree.slot[k]]) continue;
-                const int64_t li = s_first[tree.slot[k]] + tree.pos[k];
-                if (li >= cap) { err |= kErrCapacity; continue; }
-                const int64_t o = base + li;
-                const double t0 = tree.t0[k];
-                S.x0[o] = tree.x0[k] + (d.vfac * tree.k0[k]) * (d.dt - t0);
-                S.k0[o] = tree.k0[k];
-                if (DIM == 2) {
-                    S.x1[o] = tree.x1[k] + (d.vfac * tree.k1[k]) * (d.dt - t0);
-                    S.k1[o] = tree.k1[k];
-                }
-                if (SP2) S.w[o] = tree.w[k]; else S.sg[o] = tree.sg[k];
-                S.id[o] = tree.id[k];
-                if (TAN) {
-                    S.D[o] = tree.D[0][k];
-                    S.D[dstride + o] = tree.D[1][k];
-                    S.D[2 * dstride + o] = tree.D[2][k];
-                }
-            }
-            for (int k = kme; k < nslow; k += kThreads) {
-                const int slot = s_slow[k];
-                if (s_tree[slot]) continue;
-                const Node root = load_root(base, j0, slot);
-                Tally none{0, 0, 0, 0, 0};
-                bool unused = false;
-                walk_family<DIM, SP2, TAN, true>(d, P, step, root, S, base, s_first[slot], cap, dstride, none, err,
-                                                 nullptr, slot, unused);
-            }
+            atomicMax(&F.maxdepth, deep);
         } else {
-            auto &s_pool = s_walk;
-            const int npool = (int)min(s_pool.n, (uint32_t)kPool);
-            for (int r = tid; r < npool; r += kThreads) {
-                const int slot = s_pool.slot[r];
-                if (!s_tree[slot]) continue;
-                const int64_t li = s_first[slot] + s_pool.rank[r];
-                if (li >= cap) { err |= kErrCapacity; continue; }
-                const int64_t o = base + li;
-                S.x0[o] = s_pool.x0[r];
-                S.k0[o] = s_pool.k0[r];
-                if (DIM == 2) {
-                    S.x1[o] = s_pool.x1[r];
-                    S.k1[o] = s_pool.k1[r];
-                }
-                if (SP2) S.w[o] = s_pool.w[r]; else S.sg[o] = s_pool.sg[r];
-                S.id[o] = s_pool.id[r];
-                if (TAN) {
-                    S.D[o] = s_pool.D[0][r];
-                    S.D[dstride + o] = s_pool.D[1][r];
-                    S.D[2 * dstride + o] = s_pool.D[2][r];
-                }
-            }
-            // the overflow area (written by this block's threads before the
-            // last barrier)
-            const int ngp = (int)min(s_pool.n - min(s_pool.n, (uint32_t)kPool), gpool_cap(d));
-            if (ngp) {
-                const GPoolView v = gpool_view(d);
-                for (int g = tid; g < ngp; g += kThreads) {
-                    const uint32_t sr = v.sr[g];
-                    const int slot = (int)(sr & 0xFFFFu);
-                    if (!s_tree[slot]) continue;
-                    const int64_t li = s_first[slot] + (int64_t)(sr >> 16);
-                    if (li >= cap) { err |= kErrCapacity; continue; }
-                    const int64_t o = base + li;
-                    S.x0[o] = v.f[g];
-                    S.k0[o] = v.f[kGPool + g];
-                    if (DIM == 2) {
-                        S.x1[o] = v.f[2 * kGPool + g];
-                        S.k1[o] = v.f[3 * kGPool + g];
-                    }
-                    if (SP2) S.w[o] = v.f[4 * kGPool + g]; else S.sg[o] = v.sg[g];
-                    S.id[o] = v.id[g];
-                    if (TAN) {
-                        S.D[o] = v.f[5 * kGPool + g];
-                        S.D[dstride + o] = v.f[6 * kGPool + g];
-                        S.D[2 * dstride + o] = v.f[7 * kGPool + g];
-                    }
-                }
-            }
-            for (int k = kme; k < nslow; k += kThreads) {
-                const int slot = s_slow[k];
-                if (s_tree[slot]) continue;
-                const Node root = load_root(base, j0, slot);
+            if (live) {
+                const Node root = load_root();
                 Tally none{0, 0, 0, 0, 0};
-                bool unused = false;
-                walk_family<DIM, SP2, TAN, true>(d, P, step, root, S, base, s_first[slot], cap, dstride, none, err,
-                                                 &s_pool, slot, unused);
+                walk_family<DIM, SP2, TAN>(d.self, b, step, &root, true, S, base, sfirst + (int64_t)excl, cap, dstride,
+                                           &none, &err);
             }
+            atomicAdd((unsigned long long *)&s_tal[0], (unsigned long long)tal.events);
+            atomicAdd((unsigned long long *)&s_tal[1], (unsigned long long)tal.pairs);
+            atomicAdd((unsigned long long *)&s_tal[2], (unsigned long long)tal.killed);
+            atomicAdd((unsigned long long *)&s_tal[3], (unsigned long long)tal.cap);
+            atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tal.maxdepth);
         }
-
-        // per-instance tallies, summed over the wavefront first
-        int64_t tv[4] = {tal.events, tal.pairs, tal.killed, tal.cap};
-        int64_t tm = tal.maxdepth;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) tv[q] += __shfl_xor(tv[q], o, 64);
-            tm = max(tm, __shfl_xor(tm, o, 64));
-        }
-        if (lane == 0) {
-            for (int q = 0; q < 4; ++q)
-                if (tv[q]) atomicAdd((unsigned long long *)&s_tal[q], (unsigned long long)tv[q]);
-            if (tm) atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tm);
+        // the parents move to the end of the step (k_stream left them at its
+        // start)
+        if (live) {
+            E.x0[pi] = E.x0[pi] + (d.vfac * E.k0[pi]) * d.dt;
+            if (DIM == 2) E.x1[pi] = E.x1[pi] + (d.vfac * E.k1[pi]) * d.dt;
         }
         __syncthreads();
-        // every walk of this tile is done: the other parents move to the end
-        // of the step
-#pragma unroll
-        for (int h = 0; h < SPT; ++h) {
-            const int slot = tid + h * kThreads;
-            if (j0 + slot < nev && !s_fast[slot]) {
-                const int64_t pi = base + (int64_t)evi[base + j0 + slot];
-                E.x0[pi] = E.x0[pi] + (d.vfac * E.k0[pi]) * d.dt;
-                if (DIM == 2) E.x1[pi] = E.x1[pi] + (d.vfac * E.k1[pi]) * d.dt;
-            }
+        if (tid == 0 && !overflow) {
+            s_tal[0] += F.events;
+            s_tal[1] += F.pairs;
+            s_tal[2] += F.killed;
+            s_tal[4] = max(s_tal[4], (int64_t)F.maxdepth);
         }
     }
     if (tid == 0) {
-        int64_t *F = d.fpart + (int64_t)blockIdx.x * 8;
-        F[0] = cb;
-        for (int q = 0; q < 5; ++q) F[1 + q] = s_tal[q];
+        int64_t *T = d.fpart + (int64_t)blockIdx.x * 8;
+        T[0] = cb;
+        for (int q = 0; q < 5; ++q) T[1 + q] = s_tal[q];
     }
     if (err) atomicOr(&ctl->err, err);
 }
