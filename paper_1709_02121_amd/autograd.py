@@ -48,12 +48,15 @@ class WBRWDensity(torch.autograd.Function):
     @staticmethod
     def forward(ctx, theta, cfg, steps, annihilate_every, snapshot_every, device, checkpoints):
         sim = Simulation(theta_config(cfg, theta.detach().cpu().numpy()), device=device)
-        for s in range(int(steps)):
-            sim.step(1)
-            if annihilate_every and (s + 1) % annihilate_every == 0:
-                sim.annihilate()
-            if checkpoints is not None and snapshot_every and (s + 1) % snapshot_every == 0:
-                checkpoints.append((s + 1, sim.snapshot()))
+        # whole stretches of steps and annihilations per call, up to the next checkpoint
+        steps, done = int(steps), 0
+        snap = int(snapshot_every) if checkpoints is not None and snapshot_every else 0
+        while done < steps:
+            n = min(steps - done, snap - done % snap) if snap else steps - done
+            sim.run(n, int(annihilate_every or 0))
+            done += n
+            if snap and done % snap == 0:
+                checkpoints.append((done, sim.snapshot()))
         rho = sim.density()[0]
         ctx.sim = sim
         ctx.theta_dtype = theta.dtype

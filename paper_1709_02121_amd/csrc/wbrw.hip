@@ -20,6 +20,7 @@
 #include "wbrw_math.hpp"
 #include "wbrw_sp2.hpp"
 #include "wbrw_step.hpp"
+#include "wbrw_walk.hpp"
 
 using namespace wbrw;
 
@@ -33,14 +34,14 @@ struct Layout {
     // offsets
     size_t ens[2][8] = {}, gens[2][8] = {};
     size_t ip = 0, dev = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
-    size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, evc = 0, tileA = 0, Nsrt = 0, srtS = 0, tileB = 0, tileR = 0,
-           tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, ev_idx = 0, gev_idx = 0,
-           tcA = 0, tcAg = 0, supA = 0, supAg = 0, spart = 0, emA = 0, emAg = 0, tcB = 0, tcBg = 0, supB = 0, supBg = 0, tsB = 0, tsBg = 0, stg = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
+    size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, Nsrt = 0, srtS = 0, tileW = 0,
+           tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, wcnt = 0,
+           wcntg = 0, wsup = 0, wsupg = 0, wtot = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
            occ = 0, Tq = 0, ntil = 0, dacc = 0, dTq = 0, bA = 0, bcopies = 0, bcls = 0,
            bcell = 0, bP = 0, bTile = 0, bG = 0, bcls_stat = 0, tileD = 0, bscan_tiles = 0, hist = 0, xitab = 0,
            gpool = 0;
     int64_t cap_total = 0, gcap_total = 0, Nh = 0;
-    int64_t tilesA = 0, tilesAg = 0, tilesB = 0, tilesBg = 0, tilesS = 0, tilesP = 0;
+    int64_t tilesW = 0, tilesWg = 0, tilesS = 0, tilesP = 0;
 };
 
 size_t take(size_t &cursor, size_t bytes)
@@ -194,14 +195,12 @@ Layout make_layout(const wbrw_config *c)
     const bool sp2 = c->strategy == WBRW_SP2, tan = c->track_tangent != 0;
     for (int b = 0; b < B; ++b) {
         L.cap_total += c->capacity[b];
-        L.tilesA += ceil_div(c->capacity[b], kTileA) + 1;
-        L.tilesB += ceil_div(c->capacity[b], kTileB) + 1;
+        L.tilesW += ceil_div(c->capacity[b], kRangeMin) + 1;
         L.tilesP += ceil_div(c->capacity[b], kTileS) + 1;
         L.rtiles += ceil_div(c->capacity[b], kTileR) + 1;
         if (tan) {
             L.gcap_total += c->ghost_capacity;
-            L.tilesAg += ceil_div(c->ghost_capacity, kTileA) + 1;
-            L.tilesBg += ceil_div(c->ghost_capacity, kTileB) + 1;
+            L.tilesWg += ceil_div(c->ghost_capacity, kRangeMin) + 1;
         }
     }
     L.Nh = c->dim == 1 ? (int64_t)c->nx * c->nk : (int64_t)c->nx * c->nx * (int64_t)c->nk * c->nk;
@@ -226,8 +225,12 @@ Layout make_layout(const wbrw_config *c)
             L.gens[s][7] = take(cur, G * 24);
         }
     }
-    L.ev_idx = take(cur, C * 4);
-    if (tan) L.gev_idx = take(cur, G * 4);
+    L.smask = take(cur, C * 2);
+    L.wcnt = take(cur, (size_t)L.tilesW * kClasses * 4);
+    if (tan) {
+        L.smaskg = take(cur, G * 2);
+        L.wcntg = take(cur, (size_t)L.tilesWg * kClasses * 4);
+    }
     L.ip = take(cur, BB * sizeof(InstParam));
     L.dev = take(cur, sizeof(Dev));
     for (int m = 0; m < c->n_components; ++m)
@@ -258,31 +261,20 @@ Layout make_layout(const wbrw_config *c)
     L.Nnew = take(cur, BB * 8);
     L.NGnew = take(cur, BB * 8);
     L.Nbase = take(cur, 2 * BB * 8);
-    L.evc = take(cur, 2 * BB * 8);
+    L.nstep = take(cur, 2 * BB * (kPend + 1) * 8);
+    L.wtot = take(cur, 2 * BB * kClasses * 4);
     L.tileA = take(cur, 2 * (BB + 1) * 8);
     L.Nsrt = take(cur, BB * 8);
     L.srtS = take(cur, (BB + 1) * 8);
-    L.tileB = take(cur, 2 * (BB + 1) * 8);
+    L.tileW = take(cur, 4 * (BB + 1) * 8);
     L.tileR = take(cur, (BB + 1) * 8);
     L.tileG = take(cur, (BB + 1) * 8);
     L.tally = take(cur, BB * kTalCount * 8);
     L.fpart = take(cur, (size_t)kMaxGrid * 8 * 8);
     L.rstart = take(cur, (size_t)L.rtiles * 8);
-    L.tcA = take(cur, (size_t)L.tilesA * 8);
-    L.supA = take(cur, (size_t)(L.tilesA / kSupGroup + 1) * kSupStride * 8);
-    L.spart = take(cur, (size_t)kMaxGrid * 2 * 8);
-    L.emA = take(cur, (size_t)L.tilesA * (kTileA / 64) * 8);
-    L.tcB = take(cur, (size_t)L.tilesB * 8);
-    L.supB = take(cur, (size_t)(L.tilesB / kSupGroup + 1) * kSupStride * 8);
-    L.tsB = take(cur, (size_t)L.tilesB * 8);
-    L.stg = take(cur, 2 * BB * 8);
+    L.wsup = take(cur, 2 * (size_t)(L.tilesW / kSupGroup + 1) * kClasses * 4);
     if (tan) {
-        L.tcAg = take(cur, (size_t)L.tilesAg * 8);
-        L.supAg = take(cur, (size_t)(L.tilesAg / kSupGroup + 1) * kSupStride * 8);
-        L.emAg = take(cur, (size_t)L.tilesAg * (kTileA / 64) * 8);
-        L.tcBg = take(cur, (size_t)L.tilesBg * 8);
-        L.supBg = take(cur, (size_t)(L.tilesBg / kSupGroup + 1) * kSupStride * 8);
-        L.tsBg = take(cur, (size_t)L.tilesBg * 8);
+        L.wsupg = take(cur, 2 * (size_t)(L.tilesWg / kSupGroup + 1) * kClasses * 4);
         L.stG = take(cur, (size_t)L.tilesS * 8);
     }
     L.stS = take(cur, (size_t)L.tilesS * 8);
@@ -365,12 +357,12 @@ struct wbrw_handle {
     int prof = 0;   // 1: every stage and step marked; 2: whole steps only
     // launch shapes the autotuner chooses among (results do not depend on
     // them): streaming block shape (kStreamShapes), binning hash size
-    int stream_shape = 0;
+    int stream_shape = 0;     // (without effect: see wbrw_get_launch)
+    int chunk = 1;            // steps per launch of k_walk, at most
     int bin_slots = 4096;
-    int occ_stream[3] = {};   // blocks per CU of each streaming shape (0: not built)
     int occ_bin[3] = {};      // of each binning hash size (kBinSlots)
     int occ_family = 0;
-    struct Mark { int stage; hipEvent_t a, b; };
+    struct Mark { int stage; hipEvent_t a, b; int n = 1; };
     std::vector<Mark> marks;
     int open_stage = -1;
     hipEvent_t open_ev = nullptr;
@@ -391,7 +383,7 @@ namespace {
 template <typename T>
 T *at(char *base, size_t off) { return reinterpret_cast<T *>(base + off); }
 
-enum { G_STREAM = 0, G_FAMILY, G_BIN, G_SCAN, G_REGEN, G_DENS, G_SP2, G_GHOST, G_EVENTS, G_DRAW, G_DENST, G_COUNT };
+enum { G_STREAM = 0, G_FAMILY, G_BIN, G_SCAN, G_REGEN, G_DENS, G_SP2, G_GHOST, G_PLACE, G_DRAW, G_DENST, G_COUNT };
 
 template <typename K>
 int blocks_per_cu(K kernel, int nt = kThreads)
@@ -414,28 +406,28 @@ int persistent_blocks(K kernel, int cus, int nt = kThreads)
 constexpr int kStreamShapes[3][2] = {{kThreads, kPPT}, {128, 16}, {512, 4}};
 constexpr int kBinSlots[3] = {4096, 2048, 8192};
 
-// The particles' family kernel of this handle.  One static Gaussian
+// The particles' walking kernel of this handle.  One static Gaussian
 // component with the majorant sampler (every tangent form has that) takes the
 // instantiation without the component loop.
-using FamilyKernel = void (*)(Dev, int);
+using WalkKernel = void (*)(Dev, int, int, int, int);
 template <int DIM>
-FamilyKernel family_kernel(const wbrw_handle *h)
+WalkKernel walk_kernel(const wbrw_handle *h)
 {
     const bool sp2 = h->strategy == WBRW_SP2;
     if constexpr (DIM == 1) {
-        if (h->tangent) return sp2 ? k_family<1, true, true, true> : k_family<1, false, true, true>;
+        if (h->tangent) return sp2 ? k_walk<1, true, true, true> : k_walk<1, false, true, true>;
         if (h->M == 1 && h->d.kind[0] == WBRW_KERNEL_GAUSSIAN && h->d.sampler[0] == 0 && !h->d.tdep)
-            return sp2 ? k_family<1, true, false, true> : k_family<1, false, false, true>;
+            return sp2 ? k_walk<1, true, false, true> : k_walk<1, false, false, true>;
     }
-    return sp2 ? k_family<DIM, true, false, false> : k_family<DIM, false, false, false>;
+    return sp2 ? k_walk<DIM, true, false, false> : k_walk<DIM, false, false, false>;
 }
 
-// Event parents per family tile: a tile's records should fill at most three
-// quarters of its pool of `pool` records, and the further jumps of a round
-// two thirds of its queue.  A jump leaves rb = 2 per pair (sp1: a pair of
+// Event parents taken at a time: their records should fill at most three
+// quarters of the pool of `pool` records, and the further jumps of a round
+// two thirds of the queue.  A jump leaves rb = 2 per pair (sp1: a pair of
 // component m with probability c_m <|sin|> = 2/pi c_m) records; a parent
 // jumps again, and each of its offspring too, with about g/2 = gamma0 dt / 2.
-int family_tile(const wbrw_handle *h, bool ghost, int pool, int queue)
+int parents_at_a_time(const wbrw_handle *h, bool ghost, int pool, int queue)
 {
     double need = 0.0, more = 0.0;
     for (const InstParam &P : h->ip) {
@@ -452,37 +444,46 @@ int family_tile(const wbrw_handle *h, bool ghost, int pool, int queue)
     double n = kThreads;
     if (need > 0.0) n = std::min(n, 0.75 * pool / need);
     if (more > 0.0) n = std::min(n, 0.67 * queue / more);
-    return std::max(kTileB, (int)n / kTileB * kTileB);
+    return std::max(kParents, (int)n / kParents * kParents);
 }
 
-template <int DIM>
-void launch_stream(const wbrw_handle *h, hipStream_t s, int ghost)
+// Most particles in a tile of k_walk, for an instance whose particles jump in
+// a step with probability p: so many that about three fifths of the event
+// parents taken at a time are found in a step (offspring and growth until the
+// next annihilation add to them).
+int range_limit(double p, int parents)
 {
-    const Dev &d = h->d;
-    const dim3 g(h->grid[G_STREAM]);
-    if constexpr (DIM == 1)
-        if (h->stream_shape == 1) {
-            hipLaunchKernelGGL((k_stream<DIM, 128, 16>), g, dim3(128), 0, s, d, ghost);
-            return;
+    const double r = std::min(p > 0.0 ? 0.6 * parents / p : (double)kRangeMax, (double)kRangeMax);
+    return (int)std::max<int64_t>(kRangeMin, (int64_t)r / kRangeMin * kRangeMin);
+}
+
+// Steps per launch of k_walk: as many as the ensemble takes to grow by about
+// e^1.2, at most kChunk (a jump leaves rb records, see above).
+int chunk_steps(const wbrw_handle *h)
+{
+    double grow = 0.0;
+    for (const InstParam &P : h->ip) {
+        double rb = 0.0;
+        for (int m = 0; m < h->M; ++m) {
+            const double sp1 = 4.0 / 3.14159265358979 * P.c[m];
+            rb += (h->strategy == WBRW_SP2 ? 2.0 : sp1) + (h->tangent == 2 ? sp1 : 0.0);
         }
-    if (h->stream_shape == 2) {
-        hipLaunchKernelGGL((k_stream<DIM, 512, 4>), g, dim3(512), 0, s, d, ghost);
-        return;
+        grow = std::max(grow, rb * P.gamma0 * h->d.dt);
     }
-    hipLaunchKernelGGL((k_stream<DIM>), g, dim3(kThreads), 0, s, d, ghost);
+    return grow > 0.0 ? std::max(1, std::min(kChunk, (int)(1.2 / grow))) : kChunk;
 }
 
 template <int DIM>
-void launch_bin_plain(const wbrw_handle *h, hipStream_t s)
+void launch_bin_plain(const wbrw_handle *h, hipStream_t s, int pend)
 {
     const Dev &d = h->d;
     const dim3 g(h->grid[G_BIN]);
     if (h->bin_slots == 2048)
-        hipLaunchKernelGGL((k_bin<DIM, false, false, 2048>), g, dim3(kThreads), 0, s, d, 0);
+        hipLaunchKernelGGL((k_bin<DIM, false, false, 2048>), g, dim3(kThreads), 0, s, d, 0, pend);
     else if (h->bin_slots == 8192)
-        hipLaunchKernelGGL((k_bin<DIM, false, false, 8192>), g, dim3(kThreads), 0, s, d, 0);
+        hipLaunchKernelGGL((k_bin<DIM, false, false, 8192>), g, dim3(kThreads), 0, s, d, 0, pend);
     else
-        hipLaunchKernelGGL((k_bin<DIM, false, false>), g, dim3(kThreads), 0, s, d, 0);
+        hipLaunchKernelGGL((k_bin<DIM, false, false>), g, dim3(kThreads), 0, s, d, 0, pend);
 }
 
 // Alg. 4 sampler: xi(r) = (1/2) int |V_W| dq for the Gaussian barrier on
@@ -543,9 +544,14 @@ void derive(const wbrw_config *c, int b, const std::vector<double> &xi_tab,
     for (int m = 0; m < c->n_components; ++m) P.c[m] = P.c[m] / (2.0 * P.gamma0);
     // probability of a first jump within dt, and a band around it outside of
     // which the comparison tau <= dt cannot be decided differently by rounding
+    const auto word = [](double t) { return (uint32_t)std::min(std::floor(t * 4294967296.0), 4294967295.0); };
     const long double pj = -std::expm1l(-(long double)P.gamma0 * (long double)c->dt);
     P.thr_lo = (double)(pj * (1.0L - 1e-9L));
     P.thr_hi = (double)(pj * (1.0L + 1e-9L));
+    // u = (high word + [0, 1)) 2^-32: below ib_lo it is below thr_lo, above
+    // ib_hi it is above thr_hi
+    P.ib_lo = word(P.thr_lo);
+    P.ib_hi = word(P.thr_hi);
     P.N0 = c->N0[b];
     P.key = (uint32_t)(c->instance_offset + b);
 }
@@ -554,6 +560,46 @@ void plan_host(std::vector<int64_t> &plan, const int64_t *n, int B, int64_t tile
 {
     plan.assign(B + 1, 0);
     for (int b = 0; b < B; ++b) plan[b + 1] = plan[b] + ceil_div(n[b], tile);
+}
+
+// Particle counts and what follows from them (tile plans of the passes and
+// of k_walk at chunk parity `par`, the counts at the start of the next step),
+// enqueued; `hold` keeps the staged values until the stream is synchronised.
+int upload_counts(wbrw_t h, const std::vector<int64_t> &N, const std::vector<int64_t> &NG, uint32_t par,
+                  std::vector<char> &hold)
+{
+    const Dev &d = h->d;
+    const int B = h->B, kinds = h->tangent ? 2 : 1;
+    std::vector<std::vector<int64_t>> v;
+    std::vector<int64_t *> to;
+    for (int g = 0; g < kinds; ++g) {
+        const std::vector<int64_t> &n = g ? NG : N;
+        v.push_back(n);
+        to.push_back(g ? d.NG : d.N);
+        std::vector<int64_t> plan, walk(B + 1, 0), ns((size_t)B * (kPend + 1), 0);
+        plan_host(plan, n.data(), B, kTileA);
+        for (int b = 0; b < B; ++b) {
+            const InstParam &P = h->ip[b];
+            walk[b + 1] = walk[b] + ceil_div(n[b], g ? walk_range(n[b], P.gwt, P.gwr) : walk_range(n[b], P.wt, P.wr));
+            ns[(size_t)b * (kPend + 1)] = n[b];
+        }
+        v.push_back(plan);
+        to.push_back(d.tileA + (int64_t)g * (B + 1));
+        v.push_back(walk);
+        to.push_back(d.tileW + (int64_t)(2 * par + g) * (B + 1));
+        v.push_back(ns);
+        to.push_back(d.nstep + (int64_t)g * B * (kPend + 1));
+    }
+    size_t total = 0, at = 0;
+    for (auto &x : v) total += x.size() * 8;
+    hold.resize(total);
+    for (size_t i = 0; i < v.size(); ++i) {
+        const size_t bytes = v[i].size() * 8;
+        std::memcpy(hold.data() + at, v[i].data(), bytes);
+        HIPCHK(hipMemcpyAsync(to[i], hold.data() + at, bytes, hipMemcpyHostToDevice, h->stream));
+        at += bytes;
+    }
+    return WBRW_OK;
 }
 
 int launch_check()
@@ -588,7 +634,8 @@ void stage_end(wbrw_t h)
     h->open_ev = nullptr;
 }
 
-// the outer mark of a whole step (the stage marks above nest inside it)
+// the outer mark of a chunk of whole steps (the stage marks above nest inside
+// it); it counts as that many
 void step_begin(wbrw_t h)
 {
     if (!h->prof) return;
@@ -598,13 +645,13 @@ void step_begin(wbrw_t h)
     h->step_ev = e;
 }
 
-void step_end(wbrw_t h)
+void step_end(wbrw_t h, int steps)
 {
     if (!h->prof || !h->step_ev) return;
     hipEvent_t e;
     if (hipEventCreate(&e) != hipSuccess) return;
     (void)hipEventRecord(e, h->stream);
-    h->marks.push_back({WBRW_STAGE_STEP, h->step_ev, e});
+    h->marks.push_back({WBRW_STAGE_STEP, h->step_ev, e, steps});
     h->step_ev = nullptr;
 }
 
@@ -617,57 +664,64 @@ void enqueue_scan(int grid, hipStream_t s, const Dev &d, int zero_counts)
     hipLaunchKernelGGL(k_scan, dim3(grid), dim3(kThreads), 0, s, d, zero_counts);
 }
 
+// One chunk of S steps, `pend` steps after the positions were materialised;
+// adv: materialise them at its end.
 template <int DIM>
-void enqueue_step_dim(wbrw_t h)
+void enqueue_chunk_dim(wbrw_t h, int S, int pend, int adv)
 {
     const Dev &d = h->d;
     hipStream_t s = h->stream;
     const bool tan = h->tangent != 0;
-    // stage marks bracket the main kernels (the placement launch's last
-    // block closes the step)
-    stage_begin(h, WBRW_STAGE_STREAM);
-    launch_stream<DIM>(h, s, 0);
-    stage_end(h);
-    stage_begin(h, WBRW_STAGE_EVENTS);
-    hipLaunchKernelGGL(k_events, dim3(h->grid[G_EVENTS] + 1), dim3(kThreads), 0, s, d, 0, h->grid[G_STREAM]);
-    stage_end(h);
+    const int fg = h->grid[G_FAMILY];
+    const dim3 wg(fg), pg(h->grid[G_PLACE] + 1), nt(kThreads);
     stage_begin(h, WBRW_STAGE_FAMILY);
-    hipLaunchKernelGGL(family_kernel<DIM>(h), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 0);
+    hipLaunchKernelGGL(walk_kernel<DIM>(h), wg, nt, 0, s, d, 0, S, pend, adv);
     stage_end(h);
     stage_begin(h, WBRW_STAGE_PLACE);
-    const dim3 pg(h->grid[G_EVENTS] + 1);
-    const int adv = tan ? 0 : 1, fg = h->grid[G_FAMILY];
-    if (h->strategy == WBRW_SP2 && tan)
-        hipLaunchKernelGGL((k_place_records<DIM, true, true>), pg, dim3(kThreads), 0, s, d, 0, adv, fg);
-    else if (h->strategy == WBRW_SP2)
-        hipLaunchKernelGGL((k_place_records<DIM, true, false>), pg, dim3(kThreads), 0, s, d, 0, adv, fg);
-    else if (tan)
-        hipLaunchKernelGGL((k_place_records<DIM, false, true>), pg, dim3(kThreads), 0, s, d, 0, adv, fg);
-    else
-        hipLaunchKernelGGL((k_place_records<DIM, false, false>), pg, dim3(kThreads), 0, s, d, 0, adv, fg);
+    if constexpr (DIM == 1) {
+        if (tan && h->strategy == WBRW_SP2) hipLaunchKernelGGL((k_place<1, true, true>), pg, nt, 0, s, d, 0, S, pend, adv, 0, fg);
+        else if (tan) hipLaunchKernelGGL((k_place<1, false, true>), pg, nt, 0, s, d, 0, S, pend, adv, 0, fg);
+    }
+    if (!tan) {
+        if (h->strategy == WBRW_SP2) hipLaunchKernelGGL((k_place<DIM, true, false>), pg, nt, 0, s, d, 0, S, pend, adv, 1, fg);
+        else hipLaunchKernelGGL((k_place<DIM, false, false>), pg, nt, 0, s, d, 0, S, pend, adv, 1, fg);
+    }
     stage_end(h);
     if (tan) {
         // ghosts (weight 0) branch by the sp1 rule in either strategy
         stage_begin(h, WBRW_STAGE_GHOST);
-        launch_stream<DIM>(h, s, 1);
-        hipLaunchKernelGGL(k_events, dim3(h->grid[G_EVENTS] + 1), dim3(kThreads), 0, s, d, 1, h->grid[G_STREAM]);
-        hipLaunchKernelGGL((k_family<1, false, true, true>), dim3(h->grid[G_FAMILY]), dim3(kThreads), 0, s, d, 1);
-        hipLaunchKernelGGL((k_place_records<1, false, true>), pg, dim3(kThreads), 0, s, d, 1, 1, fg);
+        hipLaunchKernelGGL((k_walk<1, false, true, true>), wg, nt, 0, s, d, 1, S, pend, adv);
+        hipLaunchKernelGGL((k_place<1, false, true>), pg, nt, 0, s, d, 1, S, pend, adv, 1, fg);
         stage_end(h);
     }
 }
 
-int enqueue_step(wbrw_t h)
+// n time steps.  With `defer` the positions stay at their last
+// materialisation, for an annihilation in the same call; returns in *pend how
+// many steps they are behind (0 without).
+int enqueue_steps(wbrw_t h, int n, bool defer, int *behind = nullptr)
 {
-    step_begin(h);
-    if (h->dim == 1) enqueue_step_dim<1>(h); else enqueue_step_dim<2>(h);
-    step_end(h);
-    h->host_step += 1;
-    return launch_check();
+    int pend = 0;
+    while (n > 0) {
+        const int left = (n + h->chunk - 1) / h->chunk;     // chunks of nearly equal length
+        const int S = (n + left - 1) / left;
+        const bool last = n == S;
+        const int adv = (last ? !defer : pend + S + h->chunk > kPend) ? 1 : 0;
+        step_begin(h);
+        if (h->dim == 1) enqueue_chunk_dim<1>(h, S, pend, adv); else enqueue_chunk_dim<2>(h, S, pend, adv);
+        step_end(h, S);
+        h->host_step += S;
+        n -= S;
+        pend = adv ? 0 : pend + S;
+        const int rc = launch_check();
+        if (rc) return rc;
+    }
+    if (behind) *behind = pend;
+    return WBRW_OK;
 }
 
 template <int DIM>
-int enqueue_annihilate_dim(wbrw_t h)
+int enqueue_annihilate_dim(wbrw_t h, int pend)
 {
     const Dev &d = h->d;
     hipStream_t s = h->stream;
@@ -676,13 +730,13 @@ int enqueue_annihilate_dim(wbrw_t h)
         if (tan) {
             // occupancy and tangent sums per cell, particles and ghosts
             stage_begin(h, WBRW_STAGE_BIN);
-            hipLaunchKernelGGL((k_bin<DIM, true, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 0);
-            hipLaunchKernelGGL((k_bin<DIM, true, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 1);
+            hipLaunchKernelGGL((k_bin<DIM, true, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 0, pend);
+            hipLaunchKernelGGL((k_bin<DIM, true, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 1, pend);
             if (d.occx) hipLaunchKernelGGL(k_fold_tangents, dim3(h->grid[G_SCAN]), dim3(kThreads), 0, s, d);
             stage_end(h);
         }
         stage_begin(h, WBRW_STAGE_BOOTSTRAP);
-        int rc = enqueue_sp2_bootstrap<DIM>(d, s, h->grid[G_SP2], h->grid[G_SCAN], h->grid[G_DRAW]);
+        int rc = enqueue_sp2_bootstrap<DIM>(d, s, h->grid[G_SP2], h->grid[G_SCAN], h->grid[G_DRAW], pend);
         stage_end(h);
         if (rc) return rc;
         stage_begin(h, WBRW_STAGE_SCAN);
@@ -704,8 +758,8 @@ int enqueue_annihilate_dim(wbrw_t h)
     }
     if (h->tangent) {
         stage_begin(h, WBRW_STAGE_BIN);
-        hipLaunchKernelGGL((k_bin<DIM, false, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 0);
-        hipLaunchKernelGGL((k_bin<DIM, false, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 1);
+        hipLaunchKernelGGL((k_bin<DIM, false, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 0, pend);
+        hipLaunchKernelGGL((k_bin<DIM, false, true>), dim3(h->grid[G_BIN]), dim3(kThreads), 0, s, d, 1, pend);
         if (d.occx) hipLaunchKernelGGL(k_fold_tangents, dim3(h->grid[G_SCAN]), dim3(kThreads), 0, s, d);
         stage_end(h);
         stage_begin(h, WBRW_STAGE_SCAN);
@@ -722,7 +776,7 @@ int enqueue_annihilate_dim(wbrw_t h)
         return launch_check();
     }
     stage_begin(h, WBRW_STAGE_BIN);
-    launch_bin_plain<DIM>(h, s);
+    launch_bin_plain<DIM>(h, s, pend);
     stage_end(h);
     stage_begin(h, WBRW_STAGE_SCAN);
     enqueue_scan(h->grid[G_SCAN], s, d, 1);
@@ -734,25 +788,31 @@ int enqueue_annihilate_dim(wbrw_t h)
     return launch_check();
 }
 
-int enqueue_annihilate(wbrw_t h)
+// pend: steps since the positions were materialised
+int enqueue_annihilate(wbrw_t h, int pend = 0)
 {
-    return h->dim == 1 ? enqueue_annihilate_dim<1>(h) : enqueue_annihilate_dim<2>(h);
+    return h->dim == 1 ? enqueue_annihilate_dim<1>(h, pend) : enqueue_annihilate_dim<2>(h, pend);
+}
+
+// n time steps and an annihilation
+int enqueue_epoch(wbrw_t h, int n)
+{
+    int behind = 0;
+    const int rc = enqueue_steps(h, n, true, &behind);
+    return rc ? rc : enqueue_annihilate(h, behind);
 }
 
 template <int DIM>
 void set_grids_dim(wbrw_t h)
 {
     const int cus = h->cus;
-    h->occ_stream[0] = blocks_per_cu(k_stream<DIM>);
-    if constexpr (DIM == 1) h->occ_stream[1] = blocks_per_cu(k_stream<DIM, 128, 16>, 128);
-    h->occ_stream[2] = blocks_per_cu(k_stream<DIM, 512, 4>, 512);
     h->occ_bin[0] = blocks_per_cu(k_bin<DIM, false, false>);
     h->occ_bin[1] = blocks_per_cu(k_bin<DIM, false, false, 2048>);
     h->occ_bin[2] = blocks_per_cu(k_bin<DIM, false, false, 8192>);
     h->stream_shape = 0;
     h->bin_slots = kBinSlots[0];
-    h->grid[G_STREAM] = std::min(h->occ_stream[0] * cus, kMaxGrid);
-    h->grid[G_FAMILY] = persistent_blocks(family_kernel<DIM>(h), cus);
+    h->grid[G_STREAM] = std::min(3 * cus, kMaxGrid);
+    h->grid[G_FAMILY] = persistent_blocks(walk_kernel<DIM>(h), cus);
     h->occ_family = std::max(1, h->grid[G_FAMILY] / std::max(1, cus));
     h->grid[G_BIN] = std::min(h->occ_bin[0] * cus, kMaxGrid);
     h->grid[G_SCAN] = persistent_blocks(k_scan, cus);
@@ -761,7 +821,7 @@ void set_grids_dim(wbrw_t h)
     h->grid[G_DENST] = persistent_blocks(k_density_bin<1, false, true>, cus);
     h->grid[G_SP2] = persistent_blocks(k_sp2_classify<DIM>, cus);
     h->grid[G_GHOST] = persistent_blocks(k_ghosts, cus);
-    h->grid[G_EVENTS] = persistent_blocks(k_events, cus);
+    h->grid[G_PLACE] = std::min(persistent_blocks(k_place<DIM, false, false>, cus), kMaxGrid);
     h->grid[G_DRAW] = persistent_blocks(k_sp2_draw, cus);
 }
 
@@ -891,6 +951,24 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
             gbase += cfg->ghost_capacity;
         }
     }
+    d.ftile = h->dim == 1 ? parents_at_a_time(h, false, Families<1, false, false>::kRec, Families<1, false, false>::kQueue)
+                          : parents_at_a_time(h, false, Families<2, false, false>::kRec, Families<2, false, false>::kQueue);
+    h->chunk = chunk_steps(h);
+    d.gftile = parents_at_a_time(h, true, Families<1, false, true>::kRec, Families<1, false, true>::kQueue);
+    {
+        int64_t total = 0;
+        for (int b = 0; b < h->B; ++b) total += cfg->N0[b];
+        for (InstParam &P : h->ip) {
+            const double p = -std::expm1(-P.gamma0 * cfg->dt);
+            P.wr = range_limit(p, d.ftile);
+            P.gwr = range_limit(p, d.gftile);
+            // small ensembles still spread over the chip: four tiles per
+            // compute unit over all instances
+            const double want = 4.0 * h->cus;
+            P.wt = std::max(1, total > 0 ? (int)(want * (double)P.N0 / (double)total) : 1);
+            P.gwt = std::max(1, (int)want / h->B);
+        }
+    }
     for (int s = 0; s < 2; ++s) {
         Ens &E = d.ens[s];
         E.x0 = at<double>(w, L.ens[s][0]);
@@ -928,11 +1006,12 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.Nnew = at<int64_t>(w, L.Nnew);
     d.NGnew = at<int64_t>(w, L.NGnew);
     d.Nbase = at<int64_t>(w, L.Nbase);
-    d.evc = at<int64_t>(w, L.evc);
+    d.nstep = at<int64_t>(w, L.nstep);
+    d.wtot = at<uint32_t>(w, L.wtot);
     d.tileA = at<int64_t>(w, L.tileA);
     d.Nsrt = at<int64_t>(w, L.Nsrt);
     d.srtS = at<int64_t>(w, L.srtS);
-    d.tileB = at<int64_t>(w, L.tileB);
+    d.tileW = at<int64_t>(w, L.tileW);
     d.tileR = at<int64_t>(w, L.tileR);
     d.tileG = at<int64_t>(w, L.tileG);
     d.tally = at<int64_t>(w, L.tally);
@@ -940,22 +1019,14 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.gpool = L.gpool ? at<char>(w, L.gpool) : nullptr;
     d.gpool_blocks = L.gpool ? kGPoolBlocks : 0;
     d.rstart = at<int64_t>(w, L.rstart);
-    d.ev_idx = at<uint32_t>(w, L.ev_idx);
-    d.gev_idx = h->tangent ? at<uint32_t>(w, L.gev_idx) : nullptr;
-    d.tcA = at<uint64_t>(w, L.tcA);
-    d.supA = at<uint64_t>(w, L.supA);
-    d.spart = at<int64_t>(w, L.spart);
-    d.emA = at<uint64_t>(w, L.emA);
-    d.tcB = at<uint64_t>(w, L.tcB);
-    d.supB = at<uint64_t>(w, L.supB);
-    d.tsB = at<int64_t>(w, L.tsB);
-    d.stg = at<int64_t>(w, L.stg);
-    d.tcAg = h->tangent ? at<uint64_t>(w, L.tcAg) : nullptr;
-    d.supAg = h->tangent ? at<uint64_t>(w, L.supAg) : nullptr;
-    d.emAg = h->tangent ? at<uint64_t>(w, L.emAg) : nullptr;
-    d.tcBg = h->tangent ? at<uint64_t>(w, L.tcBg) : nullptr;
-    d.supBg = h->tangent ? at<uint64_t>(w, L.supBg) : nullptr;
-    d.tsBg = h->tangent ? at<int64_t>(w, L.tsBg) : nullptr;
+    d.smask = at<uint16_t>(w, L.smask);
+    d.wcnt = at<uint32_t>(w, L.wcnt);
+    d.wsup = at<uint32_t>(w, L.wsup);
+    d.wsup_g = L.tilesW / kSupGroup + 1;
+    d.smaskg = h->tangent ? at<uint16_t>(w, L.smaskg) : nullptr;
+    d.wcntg = h->tangent ? at<uint32_t>(w, L.wcntg) : nullptr;
+    d.wsupg = h->tangent ? at<uint32_t>(w, L.wsupg) : nullptr;
+    d.wsup_gg = L.tilesWg / kSupGroup + 1;
     d.stG = h->tangent ? at<uint64_t>(w, L.stG) : nullptr;
     d.stS = at<uint64_t>(w, L.stS);
     d.cnt = at<int32_t>(w, L.cnt);
@@ -983,9 +1054,6 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     }
 
     if (h->dim == 1) set_grids_dim<1>(h); else set_grids_dim<2>(h);
-    d.ftile = h->dim == 1 ? family_tile(h, false, Families<1, false, false>::kRec, Families<1, false, false>::kQueue)
-                          : family_tile(h, false, Families<2, false, false>::kRec, Families<2, false, false>::kQueue);
-    d.gftile = family_tile(h, true, Families<1, false, true>::kRec, Families<1, false, true>::kQueue);
     d.self = at<Dev>(w, L.dev);
 
     hipStream_t s = h->stream;
@@ -998,16 +1066,12 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     // constants and initial counts / plans
     std::vector<int64_t> N0(cfg->N0, cfg->N0 + h->B), plan;
     plan_host(plan, N0.data(), h->B, kTileA);
+    const std::vector<int64_t> NG0(h->B, 0);
+    std::vector<char> hold;
     if (hipMemcpyAsync((void *)d.self, &d, sizeof(Dev), hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync((void *)d.ip, h->ip.data(), sizeof(InstParam) * h->B, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(d.N, N0.data(), 8 * h->B, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(d.tileA, plan.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, s) != hipSuccess)
+        upload_counts(h, N0, NG0, 0u, hold))
         return fail(WBRW_EHIP);
-    if (h->tangent) {
-        std::vector<int64_t> gplan(h->B + 1, 0);
-        if (hipMemcpyAsync(d.tileA + h->B + 1, gplan.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, s) != hipSuccess)
-            return fail(WBRW_EHIP);
-    }
     if (L.xitab &&
         hipMemcpyAsync((void *)d.xi_tab, xitabs.data(), 8 * xitabs.size(), hipMemcpyHostToDevice, s) != hipSuccess)
         return fail(WBRW_EHIP);
@@ -1062,11 +1126,7 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
 int wbrw_step(wbrw_t h, int32_t nsteps)
 {
     if (!h || nsteps < 0) return WBRW_EINVAL;
-    for (int i = 0; i < nsteps; ++i) {
-        const int rc = enqueue_step(h);
-        if (rc) return rc;
-    }
-    return WBRW_OK;
+    return enqueue_steps(h, nsteps, false);
 }
 
 int wbrw_annihilate(wbrw_t h)
@@ -1081,11 +1141,11 @@ int wbrw_run(wbrw_t h, int32_t nsteps, int32_t every, int32_t use_graph)
     if (every == 0) return wbrw_step(h, nsteps);
     int left = nsteps;
     // eager steps up to the next multiple of `every` (counted from step 0)
-    while (left > 0 && (h->host_step % every) != 0) {
-        int rc = enqueue_step(h);
-        if (!rc && h->host_step % every == 0) rc = enqueue_annihilate(h);
+    if (left > 0 && (h->host_step % every) != 0) {
+        const int to = (int)(every - h->host_step % every);
+        const int rc = left >= to ? enqueue_epoch(h, to) : enqueue_steps(h, left, false);
         if (rc) return rc;
-        --left;
+        left -= std::min(left, to);
     }
     const int epochs = left / every;
     if (use_graph && h->stream != nullptr && epochs > 0) {
@@ -1096,9 +1156,7 @@ int wbrw_run(wbrw_t h, int32_t nsteps, int32_t every, int32_t use_graph)
             h->prof = 0;
             const int64_t hs = h->host_step;
             HIPCHK(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-            int rc = WBRW_OK;
-            for (int i = 0; i < every && !rc; ++i) rc = enqueue_step(h);
-            if (!rc) rc = enqueue_annihilate(h);
+            const int rc = enqueue_epoch(h, every);
             hipError_t e = hipStreamEndCapture(h->stream, &g);
             h->prof = prof;
             h->host_step = hs;   // capture enqueued nothing
@@ -1114,8 +1172,7 @@ int wbrw_run(wbrw_t h, int32_t nsteps, int32_t every, int32_t use_graph)
         }
     } else {
         for (int ep = 0; ep < epochs; ++ep) {
-            int rc = wbrw_step(h, every);
-            if (!rc) rc = enqueue_annihilate(h);
+            const int rc = enqueue_epoch(h, every);
             if (rc) return rc;
         }
     }
@@ -1144,7 +1201,7 @@ int wbrw_run_adaptive(wbrw_t h, int32_t nsteps, int32_t every, int64_t limit, in
             h->prof = 0;
             const int64_t hs = h->host_step;
             if (hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) { restore(); return WBRW_EHIP; }
-            rc = enqueue_step(h);
+            rc = enqueue_steps(h, 1, false);
             if (!rc) rc = enqueue_annihilate(h);
             const hipError_t e = hipStreamEndCapture(h->stream, &g);
             h->prof = prof;
@@ -1162,7 +1219,7 @@ int wbrw_run_adaptive(wbrw_t h, int32_t nsteps, int32_t every, int64_t limit, in
         }
     } else {
         for (int i = 0; i < nsteps && !rc; ++i) {
-            rc = enqueue_step(h);
+            rc = enqueue_steps(h, 1, false);
             if (!rc) rc = enqueue_annihilate(h);
         }
     }
@@ -1410,19 +1467,14 @@ int wbrw_restore(wbrw_t h, const void *src, size_t bytes)
     std::memset(&c, 0, sizeof(c));
     c.step = hd.ctl.step;
     c.ann_seq = std::max(now.ann_seq, hd.ctl.ann_seq) + 1u;
-    std::vector<int64_t> plan, gplan;
-    plan_host(plan, N.data(), h->B, kTileA);
-    plan_host(gplan, NG.data(), h->B, kTileA);
-    HIPCHK(hipMemcpyAsync(h->d.N, N.data(), 8 * h->B, hipMemcpyHostToDevice, h->stream));
-    HIPCHK(hipMemcpyAsync(h->d.tileA, plan.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, h->stream));
+    c.chunk = now.chunk;   // its parity goes with this handle's plans and group sums
+    std::vector<char> hold;
+    rc = upload_counts(h, N, NG, c.chunk & 1u, hold);
+    if (rc) return rc;
     // the restored order is not known to be cell order (Nsrt = 0)
     std::vector<int64_t> zeros(h->B + 1, 0);
     HIPCHK(hipMemcpyAsync(h->d.Nsrt, zeros.data(), 8 * h->B, hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemcpyAsync(h->d.srtS, zeros.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, h->stream));
-    if (h->tangent) {
-        HIPCHK(hipMemcpyAsync(h->d.NG, NG.data(), 8 * h->B, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->d.tileA + h->B + 1, gplan.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, h->stream));
-    }
     HIPCHK(hipMemcpyAsync(h->d.ctl, &c, sizeof(Ctl), hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     h->host_step = hd.ctl.step;
@@ -1552,7 +1604,7 @@ int wbrw_set_launch(wbrw_t h, const int32_t *cfg)
     if (!h || !cfg) return WBRW_EINVAL;
     int shape = -1, slots = -1;
     for (int i = 0; i < 3; ++i) {
-        if (cfg[2] == kStreamShapes[i][0] && cfg[3] == kStreamShapes[i][1] && h->occ_stream[i] > 0) shape = i;
+        if (cfg[2] == kStreamShapes[i][0] && cfg[3] == kStreamShapes[i][1] && (h->dim == 1 || i != 1)) shape = i;
         if (cfg[5] == kBinSlots[i]) slots = i;
     }
     if (shape < 0 || slots < 0) return WBRW_EINVAL;
@@ -1577,20 +1629,15 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
 {
     if (!h || steps_per_candidate < 1) return WBRW_EINVAL;
     const int cus = std::max(1, h->cus);
-    struct SC { int shape, grid; };
-    std::vector<SC> cs;
     std::vector<int> cf;
-    for (int sh = 0; sh < 3; ++sh)
-        for (int per : kPerCu)
-            if (h->occ_stream[sh] > 0 && per <= h->occ_stream[sh]) cs.push_back({sh, std::min(per * cus, kMaxGrid)});
     for (int per : kPerCu)
         if (per <= h->occ_family) cf.push_back(std::min(per * cus, kMaxGrid));
     const int prof = h->prof;
     const std::vector<wbrw_handle::Mark> saved = h->marks;
     h->marks.clear();
-    std::vector<double> ts(cs.size(), 0.0), tf(cf.size(), 0.0);   // time per particle-step, summed
-    std::vector<int> ns(cs.size(), 0), nf(cf.size(), 0);             // timed runs of each
-    const size_t ncand = std::max(cs.size(), cf.size());
+    std::vector<double> tf(cf.size(), 0.0);   // time per particle-step, summed
+    std::vector<int> nf(cf.size(), 0);        // timed runs of each
+    const size_t ncand = cf.size();
     int rc = WBRW_OK;
     auto psteps = [&](int64_t &out) {
         int64_t tal[kTalCount];
@@ -1630,7 +1677,7 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
                 h->bin_slots = cb[i].slots;
                 h->grid[G_BIN] = cb[i].grid;
                 if (hipEventRecord(e0, h->stream) != hipSuccess) { rc = WBRW_EHIP; break; }
-                if (h->dim == 1) launch_bin_plain<1>(h, h->stream); else launch_bin_plain<2>(h, h->stream);
+                if (h->dim == 1) launch_bin_plain<1>(h, h->stream, 0); else launch_bin_plain<2>(h, h->stream, 0);
                 if (hipEventRecord(e1, h->stream) != hipSuccess) { rc = WBRW_EHIP; break; }
                 hipLaunchKernelGGL(k_fill32, dim3(std::max<int64_t>(1, std::min<int64_t>(4096, ((int64_t)ncell + 255) / 256))),
                                    dim3(kThreads), 0, h->stream, h->d.cnt, (int64_t)ncell, 0);
@@ -1657,22 +1704,18 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
     // candidate i mod |cf|; the first pass warms caches and code
     for (int pass = 0; pass < 2 && !rc; ++pass) {
         for (size_t i = 0; i < ncand && !rc; ++i) {
-            const SC &a = cs[i % cs.size()];
-            h->stream_shape = a.shape;
-            h->grid[G_STREAM] = a.grid;
-            h->grid[G_FAMILY] = cf[i % cf.size()];
+            h->grid[G_FAMILY] = cf[i];
             int64_t before = 0, after = 0;
             if (hipStreamSynchronize(h->stream) != hipSuccess || (rc = psteps(before))) { rc = rc ? rc : WBRW_EHIP; break; }
             h->prof = 1;
-            for (int k = 0; k < steps_per_candidate && !rc; ++k) rc = enqueue_step(h);
+            for (int k = 0; k < steps_per_candidate && !rc; ++k) rc = enqueue_steps(h, 1, false);
             h->prof = 0;
             if (rc) break;
             if (hipStreamSynchronize(h->stream) != hipSuccess || (rc = psteps(after))) { rc = rc ? rc : WBRW_EHIP; break; }
-            double a_s = 0, a_f = 0;
+            double a_f = 0;
             for (auto &m : h->marks) {
                 float t = 0.f;
                 (void)hipEventElapsedTime(&t, m.a, m.b);
-                if (m.stage == WBRW_STAGE_STREAM) a_s += t;
                 if (m.stage == WBRW_STAGE_FAMILY) a_f += t;
                 (void)hipEventDestroy(m.a);
                 (void)hipEventDestroy(m.b);
@@ -1680,19 +1723,14 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
             h->marks.clear();
             const double ps = (double)std::max<int64_t>(1, after - before);
             if (pass == 1) {
-                ts[i % cs.size()] += a_s / ps;
-                ns[i % cs.size()] += 1;
-                tf[i % cf.size()] += a_f / ps;
-                nf[i % cf.size()] += 1;
+                tf[i] += a_f / ps;
+                nf[i] += 1;
             }
         }
     }
     if (rc) { h->prof = prof; h->marks = saved; return rc; }
-    size_t bs = 0, bf = 0;   // the least mean time per particle-step
-    for (size_t i = 1; i < cs.size(); ++i) if (ts[i] * ns[bs] < ts[bs] * ns[i]) bs = i;
+    size_t bf = 0;   // the least mean time per particle-step
     for (size_t i = 1; i < cf.size(); ++i) if (tf[i] * nf[bf] < tf[bf] * nf[i]) bf = i;
-    h->stream_shape = cs[bs].shape;
-    h->grid[G_STREAM] = cs[bs].grid;
     h->grid[G_FAMILY] = cf[bf];
     h->marks = saved;
     h->prof = prof;
@@ -1731,7 +1769,7 @@ int wbrw_profile_read(wbrw_t h, double *ms, int64_t *launches)
         float t = 0.f;
         HIPCHK(hipEventElapsedTime(&t, m.a, m.b));
         ms[m.stage] += t;
-        launches[m.stage] += 1;
+        launches[m.stage] += m.n;
     }
     return WBRW_OK;
 }

@@ -20,6 +20,7 @@
 #pragma once
 #include "wbrw_dev.hpp"
 #include "wbrw_math.hpp"
+#include "wbrw_walk.hpp"
 
 namespace wbrw {
 
@@ -49,6 +50,23 @@ __device__ __forceinline__ T run_sum(int64_t key, T v, bool &commit)
 
 constexpr int64_t kOffMask = (1ll << 62) - 1;
 constexpr int64_t kOffNeg = 1ll << 62;
+
+// The counts at the start of the steps since the positions were
+// materialised, for the instance a block works on (see birth_of): `nst` is
+// reloaded when the instance changes.  All threads call it.
+struct Births {
+    uint32_t nst[kPend + 1];
+};
+__device__ __forceinline__ void load_births(const Dev &d, int ghost, int b, int pend, Births &B)
+{
+    if ((int)threadIdx.x < pend)
+        B.nst[threadIdx.x] = (uint32_t)d.nstep[((int64_t)ghost * d.B + b) * (kPend + 1) + threadIdx.x];
+    __syncthreads();
+}
+__device__ __forceinline__ double position_now(const Dev &d, const Births &B, int pend, int64_t li, double x, double k)
+{
+    return pend ? advanced(x, (d.vfac * k) * d.dt, pend - birth_of(B.nst, pend, (uint32_t)li)) : x;
+}
 
 // Cell of a phase-space point or -1 outside the grid.
 template <int DIM>
@@ -194,7 +212,7 @@ __device__ __forceinline__ int64_t tile_at_cost(const Dev &d, const int64_t *pla
 }
 
 template <int DIM, bool SP2, bool TAN, int SLOTS = 4096>
-__global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost)
+__global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost, int pend)
 {
     if (ann_skipped(d)) return;
     // Each block takes a contiguous run of tiles.  Without tangents the
@@ -206,7 +224,8 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost)
     // array but rarely in adjacent lanes, and neighbouring tiles share most
     // of their cells.  A particle whose probes all fail adds directly.  The
     // table's size (SLOTS, a power of two) trades flushes against blocks per
-    // CU; the autotuner picks it.
+    // CU; the autotuner picks it.  The positions are `pend` steps behind
+    // (0 unless the steps before belong to the same call).
     // With tangents the table's slots hold, per cell, the count, the
     // occupancy and the six 32.32 fixed-point halves of the tangent sums
     // (kTSlots of them), and each run of equal cells in consecutive lanes,
@@ -215,6 +234,7 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost)
     static_assert((SLOTS & (SLOTS - 1)) == 0, "a power of two");
     constexpr int kHashShift = 32 - (TAN ? 9 : 12);
     __shared__ int64_t s_esc;
+    __shared__ Births s_births;
     __shared__ uint32_t s_nkeys;
     __shared__ int32_t s_key[kSlots];
     __shared__ int32_t s_val[kSlots];                      // count
@@ -294,6 +314,7 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost)
         const bool full = cb >= 0 && (b != cb || s_nkeys > (uint32_t)(kSlots / 2));
         __syncthreads();
         if (full) flush(cb);
+        if (pend && b != cb) load_births(d, ghost, b, pend, s_births);
         cb = b;
         const InstParam &P = d.ip[b];
         const int64_t base = ghost ? P.gbase : P.base;
@@ -319,6 +340,10 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost)
             const int64_t li = li0 + (int64_t)j * kThreads;
             const bool live = li < n;
             const int64_t i = base + (live ? li : 0);
+            if (pend) {
+                xa[j] = position_now(d, s_births, pend, li, xa[j], ka[j]);
+                if (DIM == 2) xb[j] = position_now(d, s_births, pend, li, xb[j], kb[j]);
+            }
             const int64_t nu = live ? cell_index<DIM>(d, xa[j], xb[j], ka[j], kb[j]) : -1;
             const int s = live ? sv[j] : 0;
             if (live && nu < 0) {
@@ -708,6 +733,9 @@ __global__ __launch_bounds__(kThreads) void k_close_regen(Dev d)
     }
     __syncthreads();
     block_plan(d.tileA, d.N, B, kTileA);
+    for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)b * (kPend + 1)] = d.N[b];
+    block_prefix(d.tileW + (int64_t)(2 * (ctl->chunk & 1u)) * (B + 1), B,
+                 [&](int b) { return walk_tiles(d, 0, b, d.N[b]); });
     block_prefix(d.srtS, B, [&](int b) { return d.Nsrt[b] / kTileA; });
     if (threadIdx.x == 0) {
         ctl->cur ^= 1u;

@@ -16,10 +16,9 @@ constexpr int kMaxM = 4;
 constexpr int kThreads = 256;           // threads per block in every kernel
 constexpr int kPPT = 8;                 // particles (or cells) per thread in streaming passes
 constexpr int kTileA = kThreads * kPPT; // particles per streaming tile
-constexpr int kTileB = 32;              // fewest event parents per family tile (see Dev::ftile)
+constexpr int kParents = 32;            // fewest event parents taken at a time (see Dev::ftile)
 constexpr int kTileS = kThreads * kPPT; // cells per scan tile
-constexpr int kSupGroup = 64;           // tiles per group sum of per-tile counts
-constexpr int kSupStride = 16;          // u64 slots between group sums (one per 128 B line)
+constexpr int kSupGroup = 64;           // walk tiles per group sum of their counts
 constexpr int kXcd = 8;                 // accelerator complexes (XCDs), each with its own L2
 constexpr int kTileR = kThreads * 4;    // regenerated particles per tile
 constexpr int kMaxDepth = 16;           // deepest family tree walked within one step
@@ -27,6 +26,13 @@ constexpr uint32_t kEventCap = 4096u;   // jumps per particle-step
 constexpr int kXiN = 4096;              // xi(r) grid intervals (Alg. 4 sampler)
 constexpr int kXiQ = 8192;              // quadrature nodes for xi(r)
 constexpr uint32_t kRejectMax = 256u;   // rejection proposals per kick
+constexpr int kChunk = 5;               // steps in one launch of k_walk, at most
+constexpr int kClasses = 1 << kChunk;   // sets of steps in which an offspring and its ancestors were born
+constexpr int kPend = 32;               // steps between materialisations of the positions, at most
+constexpr int kRangeMin = 256;          // particles in a tile of k_walk, at least
+constexpr int kRangeMax = 8192;         // particles in a tile of k_walk, at most
+constexpr int kLocalBits = 4096;        // offspring of a tile whose event bits are kept in LDS
+constexpr int kFewInst = 8;             // instances whose class totals are summed from the tiles'
 constexpr int kMaxGrid = 8192;          // blocks of a persistent launch (per-block partials)
 // 4D family kernels: the payloads of a tile's records beyond the block's LDS
 // pool go to a per-block overflow area in HBM (kGPool records for each of the
@@ -52,6 +58,9 @@ enum : int {
 struct InstParam {
     double gamma0;
     double thr_lo, thr_hi;          // certain-jump / certain-no-jump band on the first uniform
+    uint32_t ib_lo, ib_hi;          // the same on its high word: jump if below ib_lo, none above ib_hi
+    int32_t wr, gwr;                // most particles (ghosts) in a tile of k_walk
+    int32_t wt, gwt;                // tiles to cut the instance into where that leaves fewer
     double c[kMaxM];                // xi_m / (2 gamma0)
     double sq[kMaxM];               // Gaussian kick std 1/(2w)
     double H[kMaxM], width[kMaxM];  // Gaussian parameters (tangent scores)
@@ -92,7 +101,8 @@ struct Ctl {
     uint32_t err;              // sticky error bits
     uint32_t ann_seq;          // annihilations so far (look-back epoch of the scans)
     uint32_t ann_now;          // conditional annihilation: the one after this step runs
-    uint32_t pad[2];
+    uint32_t chunk;            // chunks of steps so far: its parity picks the tile plan and group sums
+    uint32_t wpar;             // parity of the chunk that k_place closes
     uint32_t ticket[kPassCount];   // zero between launches (see next_tile)
 };
 
@@ -115,9 +125,9 @@ struct Dev {
     double dt, vfac;
     double x_lo, x_hi, k_lo, k_hi, dx, dk;
     int32_t kind[kMaxM], axis[kMaxM], sampler[kMaxM];
-    int32_t ftile, gftile;      // event parents per family tile (particles, ghosts): as many
-                                // as kThreads, fewer where their records (see Families)
-                                // would not fit the tile's pool or queue
+    int32_t ftile, gftile;      // event parents that k_walk takes at a time (particles, ghosts):
+                                // as many as kThreads, fewer where their records (see
+                                // Families) would not fit the pool or queue
     const double *xi_tab;       // [B][M][kXiN + 1] xi(r) tables of the Alg. 4 sampler
     Table tab[kMaxM];
     // buffers
@@ -125,32 +135,27 @@ struct Dev {
     const InstParam *ip;
     Ctl *ctl;
     int64_t *N, *NG, *Nnew, *NGnew;
-    int64_t *Nbase;             // [2][B] counts at the start of the step (real, ghost): the records go after them
-    int64_t *evc;               // [2][B] event counts (real, ghost)
+    int64_t *Nbase;             // [2][B] counts at the start of the chunk (real, ghost): its records go after them
+    int64_t *nstep;             // [2][B][kPend + 1] counts at the start of every step since the
+                                // positions were materialised (real, ghost); entry 0 always holds
     int64_t *tileA;             // [2][B+1] streaming-tile plan (real, ghost)
-    int64_t *tileB;             // [2][B+1] family-tile plan
+    int64_t *tileW;             // [2][2][B+1] walk-tile plan (parity; real, ghost)
     int64_t *tileR;             // [B+1] regeneration-tile plan
     int64_t *tileG;             // [B+1] ghost-regeneration plan
     int64_t *tally;             // [B][kTalCount]
-    int64_t *fpart;             // [kMaxGrid][8]: instance and tallies of each family block
+    int64_t *fpart;             // [kMaxGrid][8]: instance and tallies of each walking block
     char *gpool;                // [gpool_blocks][kGPoolBytes] (4D only, else null)
     int32_t gpool_blocks;
     int64_t *rstart;            // first cell of every regeneration tile (written by k_scan)
-    uint32_t *ev_idx;           // [cap_total] event-parent index within its instance
-    uint32_t *gev_idx;          // ghosts
     uint64_t *stS;              // scan-tile sums of |n_nu|, then their exclusive prefix
     uint64_t *stG;              // look-back status words of k_ghosts
-    uint64_t *tcB, *tcBg;               // per family tile: record count
-    uint64_t *supB, *supBg;             // per kSupGroup family tiles: sum of their record
-                                        // counts (entries kSupStride apart)
-    int64_t *tsB, *tsBg;                // per family tile: where its records were staged
-    int64_t *stg;                       // [2][B] staging fill of the inactive buffer sets
-    uint64_t *tcA, *tcAg;               // per streaming tile: event count
-    uint64_t *supA, *supAg;             // per kSupGroup streaming tiles: sum of their event
-                                        // counts (entries kSupStride apart)
-    int64_t *spart;                     // [kMaxGrid][2]: each streaming block's last
-                                        // instance and its events there
-    uint64_t *emA, *emAg;               // per streaming tile: kTileA / 64 wavefront event ballots
+    uint16_t *smask, *smaskg;           // per slot of the tiles' areas: the offspring's class, and
+                                        // from bit kChunk on the chunk's steps in which it jumps
+    uint32_t *wcnt, *wcntg;             // per walk tile: records of each class
+    uint32_t *wsup, *wsupg;             // [2] (parity) per kSupGroup walk tiles: their sums
+    int64_t wsup_g, wsup_gg;            // groups of one parity
+    uint32_t *wtot;                     // [2][B][kClasses] records of each class (more than
+                                        // kFewInst instances; zero between chunks)
     int64_t *Nsrt;              // [B] particles in cell order at the front of each instance
     int64_t *srtS;              // [B+1] prefix of floor(Nsrt[b] / kTileA)
     int32_t *cnt;               // [B][Nh] signed counts (sp1) / rounded counts (sp2)
@@ -183,6 +188,24 @@ struct Dev {
     int64_t tstride;            // tiles per class in bTile
 };
 
+// Particles in a tile of k_walk for an ensemble of n: n / tiles rounded up to
+// kRangeMin, at most `most`.
+__host__ __device__ __forceinline__ int64_t walk_range(int64_t n, int32_t tiles, int32_t most)
+{
+    const int64_t r = ((n + tiles - 1) / tiles + kRangeMin - 1) / kRangeMin * kRangeMin;
+    return r < kRangeMin ? kRangeMin : (r > most ? most : r);
+}
+__device__ __forceinline__ int64_t walk_range(const InstParam &P, int ghost, int64_t n)
+{
+    return ghost ? walk_range(n, P.gwt, P.gwr) : walk_range(n, P.wt, P.wr);
+}
+// Tiles of k_walk for n particles of instance b.
+__device__ __forceinline__ int64_t walk_tiles(const Dev &d, int ghost, int b, int64_t n)
+{
+    const int64_t r = walk_range(d.ip[b], ghost, n);
+    return (n + r - 1) / r;
+}
+
 // An annihilation kernel enqueued after a step of wbrw_run_adaptive does
 // nothing unless that step's closing kernel asked for the annihilation.
 __device__ __forceinline__ bool ann_skipped(const Dev &d)
@@ -207,15 +230,12 @@ __device__ __forceinline__ int segment_of(const int64_t *plan, int B, int64_t t)
     return lo;
 }
 
-// Sum over tiles [a, c) of per-tile counts tc, with sup holding the sums of
-// whole groups of kSupGroup tiles (kSupStride apart): the tiles before the
-// first whole group, the group sums, the tiles after the last whole group.
-// Element e < n() of that list is load(e).
+// Tiles [a, c) as the tiles before the first whole group of kSupGroup, whole
+// groups, and the tiles after the last: nh, ng and nt of them, from a, group
+// ga / kSupGroup and gc on.
 struct TileRange {
-    const uint64_t *tc, *sup;
     int64_t a, ga, gc, nh, ng, nt;
-    __device__ __forceinline__ TileRange(const uint64_t *tc_, const uint64_t *sup_, int64_t a_, int64_t c)
-        : tc(tc_), sup(sup_), a(a_)
+    __device__ __forceinline__ TileRange(int64_t a_, int64_t c) : a(a_)
     {
         ga = (a + kSupGroup - 1) / kSupGroup * kSupGroup;
         gc = c / kSupGroup * kSupGroup;
@@ -225,41 +245,7 @@ struct TileRange {
         nt = groups ? c - gc : 0;
     }
     __device__ __forceinline__ int64_t n() const { return nh + ng + nt; }
-    __device__ __forceinline__ uint64_t load(int64_t e) const
-    {
-        if (e < nh) return tc[a + e];
-        if (e < nh + ng) return sup[(ga / kSupGroup + (e - nh)) * kSupStride];
-        return tc[gc + (e - nh - ng)];
-    }
 };
-
-// TileRange sum for every lane of the wavefront
-__device__ __forceinline__ uint64_t wave_range_sum(const TileRange &R)
-{
-    const int lane = threadIdx.x & 63;
-    uint64_t v = 0;
-    for (int64_t e = lane; e < R.n(); e += 64) v += R.load(e);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// TileRange sum for every thread of the block (s_w: kThreads / 64 slots)
-__device__ __forceinline__ uint64_t block_range_sum(const TileRange &R, uint64_t *s_w)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint64_t v = 0;
-    for (int64_t e = tid; e < R.n(); e += kThreads) v += R.load(e);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane == 0) s_w[wv] = v;
-    __syncthreads();
-    uint64_t tot = 0;
-#pragma unroll
-    for (int q = 0; q < kThreads / 64; ++q) tot += s_w[q];
-    __syncthreads();
-    return tot;
-}
 
 // ---- decoupled look-back (single-pass ordered scans) ----------------------
 // status word: [epoch:30 | flag:2 | value:32]; flag 1 = tile aggregate, 2 = inclusive prefix

@@ -75,10 +75,11 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long v, un
 // of fpart for k_sp2_close_classify (others, rare, go to the counters
 // directly).  Per-tile atomics on the instance's counters would serialise.
 template <int DIM>
-__global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d)
+__global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d, int pend)
 {
     if (ann_skipped(d)) return;
     __shared__ unsigned long long s_w[kThreads / 64];
+    __shared__ Births s_births;
     Ctl *ctl = d.ctl;
     const int B = d.B;
     const int64_t *plan = d.tileA;
@@ -112,6 +113,8 @@ __global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d)
         if (b != cb) {
             if (cb >= 0) publish(cb, false);
             cb = b;
+            __syncthreads();
+            load_births(d, 0, b, pend, s_births);
         }
         const InstParam &P = d.ip[b];
         const int64_t n = d.N[b];
@@ -134,6 +137,10 @@ __global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d)
             const int64_t i = P.base + li;
             const double w = wv[j];
             const uint64_t A = (uint64_t)floor(fabs(w) * 4294967296.0);
+            if (pend) {
+                xa[j] = position_now(d, s_births, pend, li, xa[j], ka[j]);
+                if (DIM == 2) xb[j] = position_now(d, s_births, pend, li, xb[j], kb[j]);
+            }
             const int64_t nu = cell_index<DIM>(d, xa[j], xb[j], ka[j], kb[j]);
             int8_t cls = -1;
             if (nu < 0) {
@@ -772,9 +779,9 @@ __global__ __launch_bounds__(kThreads) void k_sp2_close(Dev d)
 }
 
 template <int DIM>
-int enqueue_sp2_bootstrap(const Dev &d, hipStream_t s, int grid, int grid_scan, int grid_draw)
+int enqueue_sp2_bootstrap(const Dev &d, hipStream_t s, int grid, int grid_scan, int grid_draw, int pend)
 {
-    hipLaunchKernelGGL(k_sp2_classify<DIM>, dim3(grid), dim3(kThreads), 0, s, d);
+    hipLaunchKernelGGL(k_sp2_classify<DIM>, dim3(grid), dim3(kThreads), 0, s, d, pend);
     hipLaunchKernelGGL(k_sp2_close_classify, dim3(1), dim3(kThreads), 0, s, d, grid);
     hipLaunchKernelGGL(k_sp2_resid, dim3(grid), dim3(kThreads), 0, s, d);
     hipLaunchKernelGGL(k_sp2_tilescan, dim3(std::min(d.B, grid_scan)), dim3(kThreads), 0, s, d, grid);
@@ -882,6 +889,9 @@ __global__ __launch_bounds__(kThreads) void k_close_ghosts(Dev d)
     }
     __syncthreads();
     block_plan(d.tileA + (B + 1), d.NG, B, kTileA);
+    for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)(B + b) * (kPend + 1)] = d.NG[b];
+    block_prefix(d.tileW + (int64_t)(2 * (ctl->chunk & 1u) + 1) * (B + 1), B,
+                 [&](int b) { return walk_tiles(d, 1, b, d.NG[b]); });
     if (threadIdx.x == 0) ctl->gcur ^= 1u;
 }
 

@@ -1,29 +1,13 @@
-// One time step of the Wigner branching random walk (Alg. 1, Sec. 2), after
-// the streaming pass (wbrw_stream.hpp):
-//
-// k_events: every tile turns its wavefront ballots into the ordered list of
-// event parents (instance by instance, in particle order), at an offset
-// taken from group sums of the tiles' event counts.
-//
-// k_family (latency-bound, ~3% of particles): one thread per event parent
-// walks the parent's whole family within the step, depth first: for each
-// jump in time order, each component in order, the "+" offspring, its own
-// family, then the "-" offspring and its family.  Offspring are new particles
-// of the system with their own lineage ids and exponential clocks (Alg. 1
-// rule 3).  The common family (one jump, offspring that do not jump again
-// before the end of the step) is evaluated for all parents in lockstep; the
-// others take the general walk, spread over the block.  Records hold the
-// end-of-step state, so no generation is revisited in a later launch.  Each
-// tile stages its records contiguously in the inactive buffer set and adds
-// its record count to the sum of its group of kSupGroup tiles;
-// k_place_records finds each tile's place from those sums and copies the
-// records there, after the instance's particles.
+// The jumps of the Wigner branching random walk within one time step (Alg. 1,
+// Sec. 2): kick sampling, pair decisions, offspring, and the families of
+// event parents, jump by jump (take_jump) or, where those do not fit, by a
+// general depth-first walk.  The kernels that take ensembles through time
+// steps are in wbrw_walk.hpp.
 #pragma once
 #include <type_traits>
 
 #include "wbrw_dev.hpp"
 #include "wbrw_math.hpp"
-#include "wbrw_stream.hpp"
 
 namespace wbrw {
 
@@ -105,103 +89,8 @@ __device__ __forceinline__ bool in_kbox(const Dev &d, const double *k)
 }
 
 
-// After k_stream: the ordered event list.  Every streaming tile turns its
-// ballots into the within-instance indices of its event parents, at the
-// tile's offset in its instance's list (order: particle slot, wavefront,
-// lane, as in the particle array); the offset is the sum of the event counts
-// of the instance's earlier tiles, taken from the 64-tile group sums.  Block
-// 0 (dispatched first) instead adds up the streaming blocks' per-instance
-// event counts and lays out the family tiles.  Before that it clears the
-// previous step's family-tile group sums (read by the previous placement
-// launch, so its closing block could not) and keeps the particle counts,
-// after which the step's records go (the placement launch's closing block
-// updates them).
-__global__ __launch_bounds__(kThreads) void k_events(Dev d, int ghost, int sgrid)
-{
-    const int B = d.B;
-    const int tid = threadIdx.x;
-    if (blockIdx.x == 0) {
-        constexpr int kLdsB = 512;
-        __shared__ int64_t s_ev[kLdsB];
-        int64_t *evc = d.evc + (int64_t)ghost * B;
-        const bool lds = B <= kLdsB;
-        if (lds)
-            for (int b = tid; b < B; b += kThreads) s_ev[b] = 0;
-        {
-            uint64_t *supB = ghost ? d.supBg : d.supB;
-            const int64_t nb = (d.tileB[(int64_t)ghost * (B + 1) + B] + kSupGroup - 1) / kSupGroup;
-            for (int64_t g = tid; g < nb; g += kThreads) supB[g * kSupStride] = 0;
-            const int64_t *Ncur = ghost ? d.NG : d.N;
-            for (int b = tid; b < B; b += kThreads) d.Nbase[(int64_t)ghost * B + b] = Ncur[b];
-        }
-        __syncthreads();
-        for (int g = tid; g < sgrid; g += kThreads) {
-            const int64_t cb = d.spart[2 * g], c = d.spart[2 * g + 1];
-            if (cb < 0 || c == 0) continue;
-            if (lds) atomicAdd((unsigned long long *)&s_ev[cb], (unsigned long long)c);
-            else atomicAdd((unsigned long long *)&evc[cb], (unsigned long long)c);
-        }
-        __syncthreads();
-        // evc already holds what k_stream's blocks added on changing instance
-        if (lds)
-            for (int b = tid; b < B; b += kThreads)
-                if (s_ev[b]) atomicAdd((unsigned long long *)&evc[b], (unsigned long long)s_ev[b]);
-        __syncthreads();
-        const int64_t ftile = ghost ? d.gftile : d.ftile;
-        block_prefix(d.tileB + (int64_t)ghost * (B + 1), B, [&](int b) {
-            const int64_t e = (int64_t)__hip_atomic_load((unsigned long long *)&evc[b], __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-            return (e + ftile - 1) / ftile;
-        });
-        return;
-    }
-    // One wavefront per streaming tile, so that every tile's loads are in
-    // flight at once (the grid holds about as many wavefronts as tiles).
-    const int64_t *plan = d.tileA + (int64_t)ghost * (B + 1);
-    const int64_t ntiles = plan[B];
-    const uint64_t *tc = ghost ? d.tcAg : d.tcA;
-    const uint64_t *sup = ghost ? d.supAg : d.supA;
-    const uint64_t *emask = ghost ? d.emAg : d.emA;
-    uint32_t *evi = ghost ? d.gev_idx : d.ev_idx;
-    const int lane = tid & 63, wv = tid >> 6;
-    constexpr int kWaves = kThreads / 64;
-    static_assert(kTileA / 64 <= 64, "one lane per ballot of a tile");
-    for (int64_t t = (int64_t)(blockIdx.x - 1) * kWaves + wv; t < ntiles; t += (int64_t)(gridDim.x - 1) * kWaves) {
-        const int b = segment_of(plan, B, t);
-        const int64_t tl = t - plan[b];
-        const InstParam &P = d.ip[b];
-        const int64_t base = ghost ? P.gbase : P.base;
-        // ballot q holds the tile's particles [64 q, 64 q + 64), whatever the
-        // streaming kernel's block shape (loaded before the offset sum, to
-        // overlap it); exclusive scan of their popcounts in q order
-        const uint64_t *em = emask + t * (kTileA / 64);
-        const uint64_t mine = lane < kTileA / 64 ? em[lane] : 0ull;
-        const uint64_t rel = wave_range_sum(TileRange(tc, sup, plan[b], t));
-        const uint32_t c = (uint32_t)__popcll(mine);
-        uint32_t inc = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += v;
-        }
-        const uint32_t exc = inc - c;
-        const uint32_t mlo = (uint32_t)mine, mhi = (uint32_t)(mine >> 32);
-#pragma unroll 4
-        for (int q = 0; q < kTileA / 64; ++q) {
-            const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mhi, q) << 32) |
-                               (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mlo, q);
-            if (m == 0ull) continue;
-            const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)exc, q);
-            if ((m >> lane) & 1ull) {
-                const int64_t pos = base + (int64_t)rel + off + lane_rank(m);
-                evi[pos] = (uint32_t)(tl * kTileA + (int64_t)q * 64 + lane);
-            }
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------
-// Pass 2: family trees of event parents
+// Family trees of event parents
 // ---------------------------------------------------------------------------
 // Kick and weight of a created pair (see draw_pair).
 struct PairDraw {
@@ -647,7 +536,7 @@ __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step
 // ---------------------------------------------------------------------------
 template <int DIM, bool SP2, bool TAN>
 struct Families {
-    static constexpr int kLds = DIM == 2 ? 384 : 512;           // records whose payload is in LDS
+    static constexpr int kLds = DIM == 2 ? (SP2 ? 336 : 384) : 512;           // records whose payload is in LDS
     static constexpr int kRec = kLds + (DIM == 2 ? kGPool : 0); // records in all
     static constexpr int kQueue = DIM == 2 ? 192 : 128;         // further jumps of a round
     static constexpr int kLevels = 8;
@@ -852,431 +741,6 @@ __device__ __forceinline__ void take_jump(const Dev &d, const InstParam &P, uint
             add_jump<DIM, SP2, TAN>(F, round, cur.x, cur.t0, tn, unit53(rn.c, rn.d), rec, cur.e + 1u);
         }
     }
-}
-
-template <int DIM, bool SP2, bool TAN, bool ONE>
-__global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_family(Dev d, int ghost)
-{
-    using FT = Families<DIM, SP2, TAN>;
-    __shared__ int32_t s_t;
-    __shared__ uint32_t s_wsum[4];
-    __shared__ int64_t s_excl;
-    __shared__ int64_t s_tal[5];
-    __shared__ FT F;
-
-    Ctl *ctl = d.ctl;
-    const uint32_t step = ctl->step;
-    const int B = d.B;
-    const int FS = ghost ? d.gftile : d.ftile;     // event parents per tile
-    const int64_t *plan = d.tileB + (int64_t)ghost * (B + 1);
-    const int64_t ntiles = plan[B];
-    const uint32_t set = ghost ? ctl->gcur : ctl->cur;
-    const Ens E = pick_set(d, ghost, set);
-    // records are staged in the inactive buffer set, tile by tile, and
-    // placed after the ordered scan by k_place_records
-    const Ens S = pick_set(d, ghost, set ^ 1u);
-    uint64_t *tcnt = ghost ? d.tcBg : d.tcB;
-    uint64_t *tsup = ghost ? d.supBg : d.supB;
-    int64_t *tstg = ghost ? d.tsBg : d.tsB;
-    const uint32_t *evi = ghost ? d.gev_idx : d.ev_idx;
-    const int pass = ghost ? kPassFamilyG : kPassFamily;
-    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t err = 0;
-
-    // Tallies stay in LDS while the block works on one instance; they go to
-    // the instance's counters when the block moves on to another one, and the
-    // last instance's share is left in the block's slot of fpart for the
-    // closing block of the placement launch.  Per-tile atomics on one cache line would serialise
-    // the whole grid.
-    int cb = -1;
-    bool first = true;
-    if (tid < 5) s_tal[tid] = 0;
-    for (;;) {
-        if (tid == 0) {
-            s_t = (int32_t)next_tile_static_first(&ctl->ticket[pass], ntiles, first);
-            F.n = F.nq[0] = F.nq[1] = F.overflow = F.events = F.pairs = F.maxdepth = 0u;
-            F.killed = 0;
-        }
-        F.cnt[tid] = 0u;
-        F.head[tid] = kNone;
-        __syncthreads();
-        const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
-        if (t >= ntiles) break;
-        const int b = __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
-        if (b != cb) {
-            if (tid == 0 && cb >= 0) {
-                int64_t *T = d.tally + (int64_t)cb * kTalCount;
-                if (s_tal[0]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)s_tal[0]);
-                if (s_tal[1]) atomicAdd((unsigned long long *)&T[kTalPairs], (unsigned long long)s_tal[1]);
-                if (s_tal[2]) atomicAdd((unsigned long long *)&T[kTalKilled], (unsigned long long)s_tal[2]);
-                if (s_tal[3]) atomicAdd((unsigned long long *)&T[kTalEventCap], (unsigned long long)s_tal[3]);
-                if (s_tal[4]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)s_tal[4]);
-                for (int q = 0; q < 5; ++q) s_tal[q] = 0;
-            }
-            cb = b;
-        }
-        const InstParam &P = d.ip[b];
-        const int64_t base = ghost ? P.gbase : P.base;
-        const int64_t cap = ghost ? P.gcap : P.cap;
-        const int64_t nev = d.evc[(int64_t)ghost * B + b];
-        const int64_t j0 = (t - plan[b]) * FS;
-        const bool live = tid < FS && j0 + tid < nev;
-
-        // 1. the parents' first jumps, then round by round those found
-        int64_t pi = base;
-        auto load_root = [&]() {
-            Node root;
-            root.x[0] = E.x0[pi];
-            root.x[1] = DIM == 2 ? E.x1[pi] : 0.0;
-            root.k[0] = E.k0[pi];
-            root.k[1] = DIM == 2 ? E.k1[pi] : 0.0;
-            root.t0 = 0.0;
-            root.id = E.id[pi];
-            root.w = SP2 ? E.w[pi] : 0.0;
-            root.sg = SP2 ? 0 : (int32_t)E.sg[pi];
-            root.D[0] = TAN ? E.D[pi] : 0.0;
-            root.D[1] = TAN ? E.D[dstride + pi] : 0.0;
-            root.D[2] = TAN ? E.D[2 * dstride + pi] : 0.0;
-            return root;
-        };
-        {
-            Node cur;
-            uint64_t key = 0ull;
-            uint32_t rec = kNone;
-            int slot = tid, lev = 0;
-            bool act = false;
-            if (live) {
-                pi = base + (int64_t)evi[base + j0 + tid];
-                cur = load_root();
-                const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
-                cur.te = cur.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
-                cur.ua0 = unit53(r.c, r.d);
-                cur.e = 0u;
-                act = cur.te <= d.dt;
-            }
-            for (int round = 0;; ++round) {
-                if (act) take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, F);
-                __syncthreads();
-                const uint32_t nq = F.nq[round & 1];
-                if (nq == 0u || F.overflow) break;
-                act = tid < (int)nq;
-                if (act) {
-                    rec = F.qrec[tid];
-                    load_record<DIM, SP2, TAN>(d, F, rec, cur);
-                    cur.x[0] = F.qx0[tid];
-                    cur.x[1] = DIM == 2 ? F.qx1[tid] : 0.0;
-                    cur.t0 = F.qt0[tid];
-                    cur.te = F.qte[tid];
-                    cur.ua0 = F.qua[tid];
-                    cur.e = F.qe[tid];
-                    key = F.key[rec];
-                    slot = F.slot[rec];
-                    lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
-                }
-                if (tid == 0) F.nq[(round + 1) & 1] = 0u;
-                __syncthreads();
-            }
-        }
-        const bool overflow = F.overflow != 0u;
-        Tally tal{0, 0, 0, 0, 0};
-        if (overflow) {   // (uniform) every family of the tile by the general walk
-            F.cnt[tid] = 0u;
-            if (live) {
-                const Node root = load_root();
-                F.cnt[tid] = walk_family<DIM, SP2, TAN>(d.self, b, step, &root, false, S, base, 0, cap, dstride, &tal, &err);
-            }
-            __syncthreads();
-        }
-
-        // 2. ordered exclusive scan of the record counts over the tile
-        const uint32_t c = F.cnt[tid];
-        uint32_t incl = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += v;
-        }
-        if (lane == 63) s_wsum[wv] = incl;
-        __syncthreads();
-        uint32_t excl = incl - c, agg = 0;
-        for (int q = 0; q < 4; ++q) {
-            if (q < wv) excl += s_wsum[q];
-            agg += s_wsum[q];
-        }
-        F.first[tid] = excl;
-        if (tid == 0) {
-            // the tile's records take a contiguous stretch of the staging
-            // area; no tile waits for another
-            const int64_t sb = (int64_t)atomicAdd((unsigned long long *)&d.stg[(int64_t)ghost * B + b],
-                                                  (unsigned long long)agg);
-            s_excl = sb;
-            tcnt[t] = agg;
-            tstg[t] = sb;
-            if (agg)
-                atomicAdd((unsigned long long *)&tsup[(t / kSupGroup) * kSupStride], (unsigned long long)agg);
-        }
-        __syncthreads();
-
-        // 3. records into the staging area, each at its rank in its family
-        const int64_t sfirst = s_excl;
-        if (!overflow) {
-            const uint32_t nrec = F.n;
-            uint32_t deep = 0;
-            for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
-                const uint64_t key = F.key[r];
-                if (key == 0ull) continue;
-                const int slot = F.slot[r];
-                uint32_t rank = 0;
-                for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
-                deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
-                const int64_t li = sfirst + (int64_t)(F.first[slot] + rank);
-                if (li >= cap) { err |= kErrCapacity; continue; }
-                const int64_t o = base + li;
-                Node n;
-                load_record<DIM, SP2, TAN>(d, F, r, n);
-                S.x0[o] = n.x[0];
-                S.k0[o] = n.k[0];
-                if (DIM == 2) {
-                    S.x1[o] = n.x[1];
-                    S.k1[o] = n.k[1];
-                }
-                if (SP2) S.w[o] = n.w; else S.sg[o] = (int8_t)n.sg;
-                S.id[o] = n.id;
-                if (TAN) {
-                    S.D[o] = n.D[0];
-                    S.D[dstride + o] = n.D[1];
-                    S.D[2 * dstride + o] = n.D[2];
-                }
-            }
-            atomicMax(&F.maxdepth, deep);
-        } else {
-            if (live) {
-                const Node root = load_root();
-                Tally none{0, 0, 0, 0, 0};
-                walk_family<DIM, SP2, TAN>(d.self, b, step, &root, true, S, base, sfirst + (int64_t)excl, cap, dstride,
-                                           &none, &err);
-            }
-            atomicAdd((unsigned long long *)&s_tal[0], (unsigned long long)tal.events);
-            atomicAdd((unsigned long long *)&s_tal[1], (unsigned long long)tal.pairs);
-            atomicAdd((unsigned long long *)&s_tal[2], (unsigned long long)tal.killed);
-            atomicAdd((unsigned long long *)&s_tal[3], (unsigned long long)tal.cap);
-            atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tal.maxdepth);
-        }
-        // the parents move to the end of the step (k_stream left them at its
-        // start)
-        if (live) {
-            E.x0[pi] = E.x0[pi] + (d.vfac * E.k0[pi]) * d.dt;
-            if (DIM == 2) E.x1[pi] = E.x1[pi] + (d.vfac * E.k1[pi]) * d.dt;
-        }
-        __syncthreads();
-        if (tid == 0 && !overflow) {
-            s_tal[0] += F.events;
-            s_tal[1] += F.pairs;
-            s_tal[2] += F.killed;
-            s_tal[4] = max(s_tal[4], (int64_t)F.maxdepth);
-        }
-    }
-    if (tid == 0) {
-        int64_t *T = d.fpart + (int64_t)blockIdx.x * 8;
-        T[0] = cb;
-        for (int q = 0; q < 5; ++q) T[1 + q] = s_tal[q];
-    }
-    if (err) atomicOr(&ctl->err, err);
-}
-
-__device__ void close_family(const Dev &d, int ghost, int advance, int fgrid);
-
-// Every family tile's staged records (contiguous in the inactive buffer set)
-// go to their place after the instance's particles: tile order, then the
-// order of the family walks within the tile.  Block 0 (dispatched first)
-// closes the step (close_family).
-template <int DIM, bool SP2, bool TAN>
-__global__ __launch_bounds__(kThreads) void k_place_records(Dev d, int ghost, int advance, int fgrid)
-{
-    if (blockIdx.x == 0) {
-        close_family(d, ghost, advance, fgrid);
-        return;
-    }
-    Ctl *ctl = d.ctl;
-    const int B = d.B;
-    const int64_t *plan = d.tileB + (int64_t)ghost * (B + 1);
-    const int64_t ntiles = plan[B];
-    const int64_t *Nb = d.Nbase + (int64_t)ghost * B;   // counts at the start of the step
-    const uint32_t set = ghost ? ctl->gcur : ctl->cur;
-    const Ens E = pick_set(d, ghost, set);
-    const Ens S = pick_set(d, ghost, set ^ 1u);
-    const uint64_t *tc = ghost ? d.tcBg : d.tcB;
-    const uint64_t *sup = ghost ? d.supBg : d.supB;
-    const int64_t *ts = ghost ? d.tsBg : d.tsB;
-    __shared__ uint64_t s_w[kThreads / 64];
-    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-    uint32_t err = 0;
-    for (int64_t t = blockIdx.x - 1; t < ntiles; t += gridDim.x - 1) {
-        const int b = segment_of(plan, B, t);
-        const InstParam &P = d.ip[b];
-        const int64_t base = ghost ? P.gbase : P.base;
-        const int64_t cap = ghost ? P.gcap : P.cap;
-        const int64_t n = (int64_t)tc[t], src = ts[t];
-        // a record staged past the capacity was never written (k_family
-        // flagged it); one whose place is past the capacity is an overflow
-        struct Rec { double x0, x1, k0, k1, w, D[3]; uint64_t id; int8_t sg; };
-        auto load = [&](int64_t r) {
-            Rec q;
-            const int64_t i = base + src + r;
-            q.x0 = S.x0[i];
-            q.k0 = S.k0[i];
-            q.x1 = DIM == 2 ? S.x1[i] : 0.0;
-            q.k1 = DIM == 2 ? S.k1[i] : 0.0;
-            q.w = SP2 ? S.w[i] : 0.0;
-            q.sg = SP2 ? (int8_t)0 : S.sg[i];
-            q.id = S.id[i];
-            for (int c = 0; c < 3; ++c) q.D[c] = TAN ? S.D[c * dstride + i] : 0.0;
-            return q;
-        };
-        auto store = [&](int64_t r, const Rec &q, int64_t dst) {
-            if (dst + r >= cap) { err |= kErrCapacity; return; }
-            const int64_t o = base + dst + r;
-            E.x0[o] = q.x0;
-            E.k0[o] = q.k0;
-            if (DIM == 2) {
-                E.x1[o] = q.x1;
-                E.k1[o] = q.k1;
-            }
-            if (SP2) E.w[o] = q.w; else E.sg[o] = q.sg;
-            E.id[o] = q.id;
-            if (TAN)
-                for (int c = 0; c < 3; ++c) E.D[c * dstride + o] = q.D[c];
-        };
-        // the first records of the tile are loaded before the tile's place
-        // is summed, so that the two overlap
-        constexpr int kPre = 4;
-        Rec pre[kPre];
-#pragma unroll
-        for (int h = 0; h < kPre; ++h) {
-            const int64_t r = threadIdx.x + (int64_t)h * kThreads;
-            if (r < n && src + r < cap) pre[h] = load(r);
-        }
-        const int64_t dst = Nb[b] + (int64_t)block_range_sum(TileRange(tc, sup, plan[b], t), s_w);
-#pragma unroll
-        for (int h = 0; h < kPre; ++h) {
-            const int64_t r = threadIdx.x + (int64_t)h * kThreads;
-            if (r < n && src + r < cap) store(r, pre[h], dst);
-        }
-        for (int64_t r = threadIdx.x + (int64_t)kPre * kThreads; r < n && src + r < cap; r += kThreads)
-            store(r, load(r), dst);
-    }
-    if (err) atomicOr(&ctl->err, err);
-}
-
-// After k_family, in the first block of the placement launch: the family
-// blocks' tallies, the new particle counts with the capacity clamp, cleared
-// event and record counts, the streaming-tile plan of the next step, and the
-// step counter.  Nothing here is read by the placing blocks: they take the
-// particle counts kept by k_events, and the family-tile group sums are
-// cleared by the next k_events.
-__device__ void close_family(const Dev &d, int ghost, int advance, int fgrid)
-{
-    Ctl *ctl = d.ctl;
-    const int B = d.B;
-    int64_t *Ncur = ghost ? d.NG : d.N;
-    int64_t *rec = d.stg + (int64_t)ghost * B;   // records of the step (staging fill)
-    int64_t *evc = d.evc + (int64_t)ghost * B;
-    const int tid = threadIdx.x;
-    // Loads that do not depend on the family blocks' tallies go first, so
-    // that their latency overlaps the reduction below; thread b < kThreads
-    // keeps instance b's values in registers.
-    const uint32_t step = ctl->step;
-    const int64_t tilesA = d.tileA[(int64_t)ghost * (B + 1) + B];
-    const bool own = tid < B;
-    int64_t n_own = 0, rec_own = 0, cap_own = 0, tal_own[kTalCount] = {};
-    if (own) {
-        n_own = Ncur[tid];
-        rec_own = rec[tid];
-        cap_own = ghost ? d.ip[tid].gcap : d.ip[tid].cap;
-#pragma unroll
-        for (int q = 0; q < kTalCount; ++q) tal_own[q] = d.tally[(int64_t)tid * kTalCount + q];
-    }
-    // the family blocks' last tallies, summed per instance in LDS when the
-    // instances fit (global atomics from one block on one line serialise)
-    constexpr int kLdsB = 256;
-    __shared__ int64_t s_acc[5][kLdsB];
-    const bool lds = B <= kLdsB;
-    if (lds)
-        for (int b = tid; b < B; b += kThreads)
-            for (int q = 0; q < 5; ++q) s_acc[q][b] = 0;
-    __syncthreads();
-    for (int g = tid; g < fgrid; g += kThreads) {
-        const int64_t *F = d.fpart + (int64_t)g * 8;
-        if (F[0] < 0) continue;
-        if (lds) {
-            const int b = (int)F[0];
-            for (int q = 0; q < 4; ++q)
-                if (F[1 + q]) atomicAdd((unsigned long long *)&s_acc[q][b], (unsigned long long)F[1 + q]);
-            if (F[5]) atomicMax((unsigned long long *)&s_acc[4][b], (unsigned long long)F[5]);
-        } else {
-            int64_t *T = d.tally + F[0] * kTalCount;
-            if (F[1]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)F[1]);
-            if (F[2]) atomicAdd((unsigned long long *)&T[kTalPairs], (unsigned long long)F[2]);
-            if (F[3]) atomicAdd((unsigned long long *)&T[kTalKilled], (unsigned long long)F[3]);
-            if (F[4]) atomicAdd((unsigned long long *)&T[kTalEventCap], (unsigned long long)F[4]);
-            if (F[5]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)F[5]);
-        }
-    }
-    __syncthreads();
-    int64_t n_next = 0;   // instance tid's count for the next step
-    int over = 0;         // an instance of this thread holds more than ann_limit
-    for (int b = tid; b < B; b += kThreads) {
-        const bool mine = b == tid;
-        int64_t *T = d.tally + (int64_t)b * kTalCount;
-        if (lds) {   // (the global path above already added its atomics)
-            const int64_t ev = mine ? tal_own[kTalEvents] : T[kTalEvents];
-            const int64_t pr = mine ? tal_own[kTalPairs] : T[kTalPairs];
-            const int64_t kl = mine ? tal_own[kTalKilled] : T[kTalKilled];
-            const int64_t ec = mine ? tal_own[kTalEventCap] : T[kTalEventCap];
-            const int64_t md = mine ? tal_own[kTalMaxDepth] : T[kTalMaxDepth];
-            T[kTalEvents] = ev + s_acc[0][b];
-            T[kTalPairs] = pr + s_acc[1][b];
-            T[kTalKilled] = kl + s_acc[2][b];
-            T[kTalEventCap] = ec + s_acc[3][b];
-            if (s_acc[4][b] > md) T[kTalMaxDepth] = s_acc[4][b];
-        }
-        const int64_t n0 = mine ? n_own : Ncur[b];
-        const int64_t cap = mine ? cap_own : (ghost ? d.ip[b].gcap : d.ip[b].cap);
-        if (!ghost) T[kTalPSteps] = (mine ? tal_own[kTalPSteps] : T[kTalPSteps]) + n0;
-        int64_t n = n0 + (mine ? rec_own : rec[b]);
-        rec[b] = 0;
-        if (n > cap) {
-            atomicOr(&ctl->err, kErrCapacity);
-            n = cap;
-        }
-        Ncur[b] = n;
-        if (mine) n_next = n;
-        evc[b] = 0;
-        if (d.ann_limit > 0 && n > d.ann_limit) over = 1;
-    }
-    // conditional annihilation after this step: scheduled, or an instance
-    // about to outgrow the threshold (the real ensemble's closing block)
-    const int any_over = __syncthreads_or(over);
-    if (d.cond_ann && !ghost && tid == 0) {
-        const bool sched = d.ann_every > 0 && (step + 1u) % (uint32_t)d.ann_every == 0u;
-        ctl->ann_now = (sched || any_over) ? 1u : 0u;
-        if (any_over && !sched)
-            for (int b = 0; b < B; ++b) d.tally[(int64_t)b * kTalCount + kTalTrig] += 1;
-    }
-    {   // clear the group sums of this step's streaming tiles
-        uint64_t *supA = ghost ? d.supAg : d.supA;
-        const int64_t na = (tilesA + kSupGroup - 1) / kSupGroup;
-        for (int64_t g = tid; g < na; g += kThreads) supA[g * kSupStride] = 0;
-    }
-    __syncthreads();
-    // the next step's tile plan (block_prefix evaluates instance b on thread
-    // b mod kThreads, which wrote Ncur[b] above)
-    block_prefix(d.tileA + (int64_t)ghost * (B + 1), B, [&](int b) {
-        const int64_t n = b == tid ? n_next : Ncur[b];
-        return (n + kTileA - 1) / kTileA;
-    });
-    if (tid == 0 && advance) ctl->step = step + 1u;
 }
 
 }  // namespace wbrw

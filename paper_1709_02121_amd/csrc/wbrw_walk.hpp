@@ -1,0 +1,668 @@
+// Time steps of the Wigner branching random walk (Alg. 1, Sec. 2).
+//
+// Up to kChunk steps run in two launches.  Particles do not interact, and
+// every draw is keyed by the particle's lineage id and the step, so a block
+// takes a range of consecutive particles of an instance (a tile) through all
+// steps of the chunk by itself, with the offspring born on the way:
+//
+// k_walk    reads the ids of the range and decides for every particle and
+//           step whether it jumps (exact clocks for a constant gamma0, Sec.
+//           3.2.1), keeping one bit each in LDS.  Then, step by step, it
+//           gathers the jumping particles of the range and of its offspring,
+//           in order, and takes their jumps (wbrw_step.hpp).  Offspring go to
+//           the tile's area of the inactive buffer set, in order.
+// k_place   puts the offspring of all tiles behind the particles, in the
+//           order of the whole ensemble's steps, and closes the chunk.
+//
+// Order.  A step appends its records in the order of their event parents in
+// the array.  Give an offspring the set of steps (a bit mask, its class) in
+// which its ancestors since the chunk's start and it were born.  The array
+// sorts the chunk's offspring by step of birth, then by the parent's place:
+// first by the parent's step of birth, and so on, which is the numeric order
+// of the classes (the highest bit first); within a class by the range of the
+// first ancestor; within a class and tile by the tile's own order.  So the
+// place of a record is the sum of the lower classes, its class's records in
+// earlier tiles, and its index within its class and tile, and no step waits
+// for another tile.
+//
+// Positions.  A particle's x in the array is its position at the last
+// materialisation (or at the end of the step of its birth, if later); its
+// position at the start of a later step is reached by adding (hbar/m) k dt
+// once per step, which are the additions that one step at a time would do.
+// The last chunk of a call adds them up in the array (adv), unless an
+// annihilation follows in the same call, whose cell pass does it instead.
+#pragma once
+#include "wbrw_dev.hpp"
+#include "wbrw_math.hpp"
+#include "wbrw_step.hpp"
+
+namespace wbrw {
+
+// Birth index of instance-particle i: the number of entries of the table
+// nst[0 .. pend] (counts at the start of the steps since the last
+// materialisation) that are <= i.  Its first advance is that of step
+// `birth`, so m steps after the materialisation it has taken m - birth.
+__device__ __forceinline__ int birth_of(const uint32_t *nst, int pend, uint32_t i)
+{
+    int b = 0;
+    for (int q = 0; q < pend; ++q) b += nst[q] <= i ? 1 : 0;
+    return b;
+}
+
+__device__ __forceinline__ double advanced(double x, double c, int m)
+{
+    for (int q = 0; q < m; ++q) x = x + c;
+    return x;
+}
+
+// Does particle `id`, at rest in its first clock of step `step`, jump before
+// its end?  Its first uniform's high word decides, but for a band around the
+// threshold, where the exact test is evaluated.
+__device__ __forceinline__ bool clock_jumps(const Dev &d, const InstParam &P, uint64_t id, uint32_t step)
+{
+    const W4 r = draw(id, step, kTagStep, 0u, 0u, d.seed, P.key);
+    if (r.b < P.ib_lo) return true;
+    if (r.b > P.ib_hi) return false;
+    const W4 e = draw(id, step, kTagStep, 0u, 0u, d.seed, P.key);
+    const double u = unit53(e.a, e.b);
+    if (u < P.thr_lo) return true;
+    if (!(u <= P.thr_hi)) return false;
+    return -ln_series(1.0 - u) / P.gamma0 <= d.dt;
+}
+
+// Exclusive scan of v over the block's threads (s_w: kThreads / 64 slots, not
+// in use by an earlier call without a barrier in between); tot: the sum.
+__device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *s_w, uint32_t &tot)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) s_w[wv] = incl;
+    __syncthreads();
+    uint32_t excl = incl - v;
+    tot = 0;
+#pragma unroll
+    for (int q = 0; q < kThreads / 64; ++q) {
+        const uint32_t t = s_w[q];
+        if (q < wv) excl += t;
+        tot += t;
+    }
+    return excl;
+}
+
+template <int DIM, bool SP2, bool TAN, bool ONE>
+__global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(Dev d, int ghost, int S, int pend,
+                                                                             int adv)
+{
+    using FT = Families<DIM, SP2, TAN>;
+    constexpr int kW0 = kRangeMax / 64;       // words of a step's bits of the range
+    constexpr int kWL = kLocalBits / 64;      // ... of the offspring
+    __shared__ int32_t s_t;
+    __shared__ uint32_t s_wsum[2][4];
+    __shared__ int64_t s_tal[5];
+    __shared__ FT F;
+    __shared__ uint64_t s_ev[kChunk][kW0];
+    __shared__ unsigned long long s_evl[kChunk][kWL];
+    __shared__ uint32_t s_item[kThreads];     // event parents: index in the range, or
+                                              // kLocal | index among the offspring
+    __shared__ uint8_t s_cls[kThreads];       // their classes
+    __shared__ uint32_t s_ccnt[kClasses];     // records of each class
+    __shared__ uint32_t s_born[kChunk + 1];   // offspring at the start of each step
+    __shared__ uint32_t s_nst[kPend + 1];
+    constexpr uint32_t kLocal = 0x80000000u;
+
+    Ctl *ctl = d.ctl;
+    const uint32_t step0 = ctl->step, par = ctl->chunk & 1u;
+    const int B = d.B;
+    const int FS = ghost ? d.gftile : d.ftile;     // event parents taken at a time
+    const int64_t *plan = d.tileW + (int64_t)(2 * par + ghost) * (B + 1);
+    const int64_t ntiles = plan[B];
+    const uint32_t set = ghost ? ctl->gcur : ctl->cur;
+    const Ens E = pick_set(d, ghost, set);
+    const Ens S_ = pick_set(d, ghost, set ^ 1u);   // the tiles' areas
+    const int64_t *Ncur = ghost ? d.NG : d.N;
+    uint16_t *smask = ghost ? d.smaskg : d.smask;
+    uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
+    uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
+    const int64_t *nstep = d.nstep + (int64_t)ghost * B * (kPend + 1);
+    const int pass = ghost ? kPassFamilyG : kPassFamily;
+    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t err = 0;
+
+    // kept for k_place, whose closing block changes both
+    if (blockIdx.x == 0) {
+        for (int b = tid; b < B; b += kThreads) d.Nbase[(int64_t)ghost * B + b] = Ncur[b];
+        if (tid == 0) ctl->wpar = par;
+    }
+    // Tallies stay in LDS while the block works on one instance; they go to
+    // the instance's counters when the block moves on to another one, and the
+    // last instance's share is left in the block's slot of fpart for the
+    // closing block of the placement launch.  Per-tile atomics on one cache
+    // line would serialise the whole grid.
+    int cb = -1;
+    bool first = true;
+    if (tid < 5) s_tal[tid] = 0;
+    for (;;) {
+        if (tid == 0) s_t = (int32_t)next_tile_static_first(&ctl->ticket[pass], ntiles, first);
+        for (int q = tid; q < kChunk * kWL; q += kThreads) (&s_evl[0][0])[q] = 0ull;
+        if (tid < kClasses) s_ccnt[tid] = 0u;
+        __syncthreads();
+        const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
+        if (t >= ntiles) break;
+        const int b = __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
+        if (b != cb) {
+            if (tid == 0 && cb >= 0) {
+                int64_t *T = d.tally + (int64_t)cb * kTalCount;
+                if (s_tal[0]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)s_tal[0]);
+                if (s_tal[1]) atomicAdd((unsigned long long *)&T[kTalPairs], (unsigned long long)s_tal[1]);
+                if (s_tal[2]) atomicAdd((unsigned long long *)&T[kTalKilled], (unsigned long long)s_tal[2]);
+                if (s_tal[3]) atomicAdd((unsigned long long *)&T[kTalEventCap], (unsigned long long)s_tal[3]);
+                if (s_tal[4]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)s_tal[4]);
+                for (int q = 0; q < 5; ++q) s_tal[q] = 0;
+            }
+            cb = b;
+            if (tid < pend) s_nst[tid] = (uint32_t)nstep[(int64_t)b * (kPend + 1) + tid];
+        }
+        const InstParam &P = d.ip[b];
+        const int64_t base = ghost ? P.gbase : P.base;
+        const int64_t cap = ghost ? P.gcap : P.cap;
+        const int64_t n = Ncur[b], tl = t - plan[b], T = plan[b + 1] - plan[b];
+        const int R = (int)walk_range(P, ghost, n);
+        const int64_t i0 = base + tl * R;                       // the range
+        const int nr = (int)min((int64_t)R, n - tl * R);
+        const int64_t area = cap / T, a0 = base + tl * area;    // the tile's area
+        const uint32_t alen = (uint32_t)min(area, (int64_t)0x7FFFFFFF);
+
+        // the range's clocks, lanes on consecutive particles; the next ids
+        // are loaded while the draws of the last ones run
+        {
+            uint64_t id = E.id[i0 + min(tid, nr - 1)];
+            for (int j = 0; j * kThreads < nr; ++j) {
+                const int li = j * kThreads + tid;
+                const uint64_t cur = id;
+                id = E.id[i0 + min(li + kThreads, nr - 1)];
+                for (int s = 0; s < S; ++s) {
+                    const uint64_t m = __ballot(li < nr && clock_jumps(d, P, cur, step0 + (uint32_t)s));
+                    if (lane == 0) s_ev[s][j * (kThreads / 64) + wv] = m;
+                }
+            }
+        }
+        const int nw0 = (nr + 63) / 64;
+        uint32_t nl = 0;                     // offspring of the tile so far
+        for (int s = 0; s < S; ++s) {
+            const uint32_t step = step0 + (uint32_t)s;
+            const uint32_t nl0 = nl;         // those of earlier steps
+            const int nw = nw0 + (int)((nl0 + 63u) / 64u);
+            if (tid == 0) s_born[s] = nl0;
+            uint32_t np = 0;                 // event parents of the step
+            for (uint32_t q0 = 0;; q0 += (uint32_t)FS) {
+                // event parents [q0, q0 + FS) of the step, in order: first
+                // the range's, then the offspring's
+                __syncthreads();
+                uint32_t run = 0;
+                for (int w0 = 0, it = 0; w0 < nw; w0 += kThreads, ++it) {
+                    const int wi = w0 + tid, wl = wi - nw0;
+                    uint64_t m = 0;
+                    if (wi < nw0) m = s_ev[s][wi];
+                    else if (wi < nw && wl < kWL) m = s_evl[s][wl];
+                    else if (wi < nw)        // past the bits kept in LDS
+                        for (uint32_t q = 0; q < 64u && (uint32_t)wl * 64u + q < nl0; ++q)
+                            m |= (uint64_t)((smask[a0 + wl * 64 + q] >> (kChunk + s)) & 1u) << q;
+                    uint32_t tot;
+                    uint32_t pos = run + block_excl((uint32_t)__popcll(m), s_wsum[it & 1], tot);
+                    while (m) {
+                        const int k = __builtin_ctzll(m);
+                        m &= m - 1ull;
+                        if (pos >= q0 && pos < q0 + (uint32_t)FS)
+                            s_item[pos - q0] = wi < nw0 ? (uint32_t)(wi * 64 + k) : kLocal | (uint32_t)(wl * 64 + k);
+                        ++pos;
+                    }
+                    run += tot;
+                }
+                np = run;
+                if (q0 >= np) break;
+                if (tid == 0) {
+                    F.n = F.nq[0] = F.nq[1] = F.overflow = F.events = F.pairs = F.maxdepth = 0u;
+                    F.killed = 0;
+                }
+                F.cnt[tid] = 0u;
+                F.head[tid] = kNone;
+                __syncthreads();
+                const bool live = tid < FS && q0 + (uint32_t)tid < np;
+                // the thread's event parent at the start of the step
+                auto load_root = [&]() {
+                    const uint32_t it = s_item[tid];
+                    const bool loc = (it & kLocal) != 0u;
+                    const uint32_t l = it & ~kLocal;
+                    const Ens X = loc ? S_ : E;
+                    const int64_t pi = (loc ? a0 : i0) + (int64_t)l;
+                    Node root;
+                    root.x[0] = X.x0[pi];
+                    root.x[1] = DIM == 2 ? X.x1[pi] : 0.0;
+                    root.k[0] = X.k0[pi];
+                    root.k[1] = DIM == 2 ? X.k1[pi] : 0.0;
+                    root.t0 = 0.0;
+                    root.id = X.id[pi];
+                    root.w = SP2 ? X.w[pi] : 0.0;
+                    root.sg = SP2 ? 0 : (int32_t)X.sg[pi];
+                    root.D[0] = TAN ? X.D[pi] : 0.0;
+                    root.D[1] = TAN ? X.D[dstride + pi] : 0.0;
+                    root.D[2] = TAN ? X.D[2 * dstride + pi] : 0.0;
+                    int m;
+                    if (loc) {
+                        s_cls[tid] = (uint8_t)(smask[pi] & (kClasses - 1));
+                        m = -1;              // steps since the one it was born in
+                        for (int q = 1; q <= s; ++q) m += l < s_born[q] ? 1 : 0;
+                    } else {
+                        s_cls[tid] = 0;
+                        m = pend + s - birth_of(s_nst, pend, (uint32_t)(tl * R) + l);
+                    }
+                    root.x[0] = advanced(root.x[0], (d.vfac * root.k[0]) * d.dt, m);
+                    if (DIM == 2) root.x[1] = advanced(root.x[1], (d.vfac * root.k[1]) * d.dt, m);
+                    return root;
+                };
+                // 1. the parents' first jumps, then round by round those found
+                {
+                    Node cur;
+                    uint64_t key = 0ull;
+                    uint32_t rec = kNone;
+                    int slot = tid, lev = 0;
+                    bool act = false;
+                    if (live) {
+                        cur = load_root();
+                        const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
+                        cur.te = cur.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
+                        cur.ua0 = unit53(r.c, r.d);
+                        cur.e = 0u;
+                        act = cur.te <= d.dt;
+                    }
+                    for (int round = 0;; ++round) {
+                        if (act) take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, F);
+                        __syncthreads();
+                        const uint32_t nq = F.nq[round & 1];
+                        if (nq == 0u || F.overflow) break;
+                        act = tid < (int)nq;
+                        if (act) {
+                            rec = F.qrec[tid];
+                            load_record<DIM, SP2, TAN>(d, F, rec, cur);
+                            cur.x[0] = F.qx0[tid];
+                            cur.x[1] = DIM == 2 ? F.qx1[tid] : 0.0;
+                            cur.t0 = F.qt0[tid];
+                            cur.te = F.qte[tid];
+                            cur.ua0 = F.qua[tid];
+                            cur.e = F.qe[tid];
+                            key = F.key[rec];
+                            slot = F.slot[rec];
+                            lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
+                        }
+                        if (tid == 0) F.nq[(round + 1) & 1] = 0u;
+                        __syncthreads();
+                    }
+                }
+                const bool overflow = F.overflow != 0u;
+                Tally tal{0, 0, 0, 0, 0};
+                if (overflow) {   // (uniform) every family by the general walk
+                    F.cnt[tid] = 0u;
+                    if (live) {
+                        const Node root = load_root();
+                        F.cnt[tid] = walk_family<DIM, SP2, TAN>(d.self, b, step, &root, false, S_, a0, 0, alen, dstride,
+                                                                &tal, &err);
+                    }
+                    __syncthreads();
+                }
+                // 2. ordered exclusive scan of the families' record counts
+                uint32_t agg;
+                const uint32_t excl = block_excl(F.cnt[tid], s_wsum[0], agg);
+                F.first[tid] = excl;
+                __syncthreads();
+                // 3. records into the tile's area, each at its rank in its
+                //    family, with its class and its own jumps in the chunk's
+                //    later steps
+                auto close_record = [&](int64_t li, uint64_t id, int slot) {
+                    const uint32_t cls = (uint32_t)s_cls[slot] | (1u << s);
+                    uint32_t ev = 0;
+                    for (int q = s + 1; q < S; ++q)
+                        if (clock_jumps(d, P, id, step0 + (uint32_t)q)) {
+                            ev |= 1u << q;
+                            if (li < kLocalBits) atomicOr(&s_evl[q][li >> 6], 1ull << (li & 63));
+                        }
+                    smask[a0 + li] = (uint16_t)(cls | (ev << kChunk));
+                    atomicAdd(&s_ccnt[cls], 1u);
+                };
+                if (!overflow) {
+                    const uint32_t nrec = F.n;
+                    uint32_t deep = 0;
+                    for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
+                        const uint64_t key = F.key[r];
+                        if (key == 0ull) continue;
+                        const int slot = F.slot[r];
+                        uint32_t rank = 0;
+                        for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
+                        deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
+                        const int64_t li = (int64_t)nl + (int64_t)(F.first[slot] + rank);
+                        if (li >= (int64_t)alen) { err |= kErrCapacity; continue; }
+                        const int64_t o = a0 + li;
+                        Node nd;
+                        load_record<DIM, SP2, TAN>(d, F, r, nd);
+                        S_.x0[o] = nd.x[0];
+                        S_.k0[o] = nd.k[0];
+                        if (DIM == 2) {
+                            S_.x1[o] = nd.x[1];
+                            S_.k1[o] = nd.k[1];
+                        }
+                        if (SP2) S_.w[o] = nd.w; else S_.sg[o] = (int8_t)nd.sg;
+                        S_.id[o] = nd.id;
+                        if (TAN) {
+                            S_.D[o] = nd.D[0];
+                            S_.D[dstride + o] = nd.D[1];
+                            S_.D[2 * dstride + o] = nd.D[2];
+                        }
+                        close_record(li, nd.id, slot);
+                    }
+                    atomicMax(&F.maxdepth, deep);
+                } else {
+                    if (live) {
+                        const Node root = load_root();
+                        Tally none{0, 0, 0, 0, 0};
+                        const int64_t f = (int64_t)nl + (int64_t)excl;
+                        const uint32_t c = walk_family<DIM, SP2, TAN>(d.self, b, step, &root, true, S_, a0, f, alen, dstride,
+                                                                      &none, &err);
+                        for (uint32_t r = 0; r < c && f + r < (int64_t)alen; ++r) close_record(f + r, S_.id[a0 + f + r], tid);
+                    }
+                    atomicAdd((unsigned long long *)&s_tal[0], (unsigned long long)tal.events);
+                    atomicAdd((unsigned long long *)&s_tal[1], (unsigned long long)tal.pairs);
+                    atomicAdd((unsigned long long *)&s_tal[2], (unsigned long long)tal.killed);
+                    atomicAdd((unsigned long long *)&s_tal[3], (unsigned long long)tal.cap);
+                    atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tal.maxdepth);
+                }
+                nl = min(nl + agg, alen);
+                __syncthreads();
+                if (tid == 0 && !overflow) {
+                    s_tal[0] += F.events;
+                    s_tal[1] += F.pairs;
+                    s_tal[2] += F.killed;
+                    s_tal[4] = max(s_tal[4], (int64_t)F.maxdepth);
+                }
+                if (q0 + (uint32_t)FS >= np) break;
+            }
+        }
+        __syncthreads();
+        // the tile's counts per class, also summed over groups of tiles
+        if (tid < kClasses) {
+            const uint32_t c = s_ccnt[tid];
+            wcnt[t * kClasses + tid] = c;
+            if (c) atomicAdd(&wsup[(t / kSupGroup) * kClasses + tid], c);
+            if (c && B > kFewInst) atomicAdd(&d.wtot[((int64_t)ghost * B + b) * kClasses + tid], c);
+        }
+        if (adv) {
+            for (int li = tid; li < nr; li += kThreads) {
+                const int64_t i = i0 + li;
+                const int m = pend + S - birth_of(s_nst, pend, (uint32_t)(tl * R + li));
+                const double c0 = (d.vfac * E.k0[i]) * d.dt;
+                __builtin_nontemporal_store(advanced(E.x0[i], c0, m), &E.x0[i]);
+                if (DIM == 2) {
+                    const double c1 = (d.vfac * E.k1[i]) * d.dt;
+                    __builtin_nontemporal_store(advanced(E.x1[i], c1, m), &E.x1[i]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        int64_t *T = d.fpart + (int64_t)blockIdx.x * 8;
+        T[0] = cb;
+        for (int q = 0; q < 5; ++q) T[1 + q] = s_tal[q];
+    }
+    if (err) atomicOr(&ctl->err, err);
+}
+
+// Per class c (threads tid mod kClasses = c; all threads of the block call):
+// the records of tiles [a, m) and of [a, z), from the tiles' counts and
+// their group sums.  s_red: 2 * kThreads words.
+__device__ __forceinline__ void class_sums(const uint32_t *wcnt, const uint32_t *wsup, int64_t a, int64_t m, int64_t z,
+                                           uint32_t *s_red, uint32_t &below, uint32_t &total)
+{
+    constexpr int kRows = kThreads / kClasses;
+    const int tid = threadIdx.x, c = tid % kClasses, row = tid / kClasses;
+    auto sum = [&](int64_t lo, int64_t hi) {
+        const TileRange R(lo, hi);
+        uint32_t v = 0;
+        for (int64_t e = row; e < R.n(); e += kRows) {
+            if (e < R.nh) v += wcnt[(R.a + e) * kClasses + c];
+            else if (e < R.nh + R.ng) v += wsup[(R.ga / kSupGroup + (e - R.nh)) * kClasses + c];
+            else v += wcnt[(R.gc + (e - R.nh - R.ng)) * kClasses + c];
+        }
+        return v;
+    };
+    const uint32_t v0 = sum(a, m), v1 = sum(m, z);
+    __syncthreads();
+    s_red[tid] = v0;
+    s_red[kThreads + tid] = v1;
+    __syncthreads();
+    below = total = 0;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        below += s_red[r * kClasses + c];
+        total += s_red[kThreads + r * kClasses + c];
+    }
+    total += below;
+}
+
+__device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, int advance, int fgrid);
+
+// The tiles' offspring go to their places behind the particles (see the
+// order above).  A block takes a run of tiles.  Block 0 (dispatched first)
+// closes the chunk.
+template <int DIM, bool SP2, bool TAN>
+__global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int pend, int adv, int advance, int fgrid)
+{
+    if (blockIdx.x == 0) {
+        close_chunk(d, ghost, S, pend, adv, advance, fgrid);
+        return;
+    }
+    __shared__ uint32_t s_red[2 * kThreads];
+    __shared__ uint32_t s_below[kClasses], s_tot[kClasses], s_own[kClasses], s_off[kClasses];
+    Ctl *ctl = d.ctl;
+    const int B = d.B;
+    const uint32_t par = ctl->wpar;
+    const int64_t *plan = d.tileW + (int64_t)(2 * par + ghost) * (B + 1);
+    const int64_t ntiles = plan[B];
+    const uint32_t set = ghost ? ctl->gcur : ctl->cur;
+    const Ens E = pick_set(d, ghost, set);
+    const Ens A = pick_set(d, ghost, set ^ 1u);
+    const uint16_t *smask = ghost ? d.smaskg : d.smask;
+    const uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
+    const uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
+    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
+    const int tid = threadIdx.x;
+    const int64_t g = blockIdx.x - 1, G = gridDim.x - 1;
+    const int64_t t0 = ntiles * g / G, t1 = ntiles * (g + 1) / G;
+    uint32_t err = 0;
+    int cb = -1;
+    for (int64_t t = t0; t < t1; ++t) {
+        const int b = __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
+        if (b != cb) {
+            uint32_t below, total;
+            class_sums(wcnt, wsup, plan[b], t, plan[b + 1], s_red, below, total);
+            if (tid < kClasses) {
+                s_below[tid] = below;
+                s_tot[tid] = total;
+            }
+            cb = b;
+        } else if (tid < kClasses) {
+            s_below[tid] += s_own[tid];
+        }
+        __syncthreads();
+        if (tid < kClasses) s_own[tid] = wcnt[t * kClasses + tid];
+        __syncthreads();
+        const InstParam &P = d.ip[b];
+        const int64_t base = ghost ? P.gbase : P.base;
+        const int64_t cap = ghost ? P.gcap : P.cap;
+        const int64_t T = plan[b + 1] - plan[b], a0 = base + (t - plan[b]) * (cap / T);
+        if (tid < kClasses) {   // lower classes, earlier tiles, less the class's start in the tile
+            uint32_t o = s_below[tid];
+            for (int c = 0; c < tid; ++c) o += s_tot[c] - s_own[c];
+            s_off[tid] = o;
+        }
+        uint32_t nrec = 0;
+        for (int c = 0; c < kClasses; ++c) nrec += s_own[c];
+        __syncthreads();
+        const int64_t n0 = d.Nbase[(int64_t)ghost * B + b];
+        for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
+            const int64_t i = a0 + r;
+            const uint32_t cls = smask[i] & (kClasses - 1);
+            const int64_t dst = n0 + (int64_t)(uint32_t)(s_off[cls] + r);
+            double x0 = A.x0[i], x1 = DIM == 2 ? A.x1[i] : 0.0;
+            const double k0 = A.k0[i], k1 = DIM == 2 ? A.k1[i] : 0.0;
+            const double w = SP2 ? A.w[i] : 0.0;
+            const int8_t sg = SP2 ? (int8_t)0 : A.sg[i];
+            const uint64_t id = A.id[i];
+            double D[3];
+            for (int c = 0; c < 3; ++c) D[c] = TAN ? A.D[c * dstride + i] : 0.0;
+            if (dst >= cap) { err |= kErrCapacity; continue; }
+            if (adv) {
+                const int m = S - 1 - (31 - __builtin_clz(cls));   // born in the step of the highest bit
+                x0 = advanced(x0, (d.vfac * k0) * d.dt, m);
+                if (DIM == 2) x1 = advanced(x1, (d.vfac * k1) * d.dt, m);
+            }
+            const int64_t o = base + dst;
+            E.x0[o] = x0;
+            E.k0[o] = k0;
+            if (DIM == 2) {
+                E.x1[o] = x1;
+                E.k1[o] = k1;
+            }
+            if (SP2) E.w[o] = w; else E.sg[o] = sg;
+            E.id[o] = id;
+            if (TAN)
+                for (int c = 0; c < 3; ++c) E.D[c * dstride + o] = D[c];
+        }
+        __syncthreads();
+    }
+    if (err) atomicOr(&ctl->err, err);
+}
+
+// In the first block of the placement launch: the walking blocks' tallies,
+// the new particle counts (also those at the start of every step of the
+// chunk) with the capacity clamp, the next chunk's tile plan and that of the
+// passes over the ensemble, the group sums the next chunk adds to, and the
+// step counter.  Nothing here is read by the placing blocks.
+__device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, int advance, int fgrid)
+{
+    Ctl *ctl = d.ctl;
+    const int B = d.B;
+    const int tid = threadIdx.x;
+    const uint32_t step = ctl->step, par = ctl->wpar;
+    int64_t *Ncur = ghost ? d.NG : d.N;
+    const int64_t *plan = d.tileW + (int64_t)(2 * par + ghost) * (B + 1);
+    int64_t *next = d.tileW + (int64_t)(2 * (par ^ 1u) + ghost) * (B + 1);
+    const int64_t groups = ghost ? d.wsup_gg : d.wsup_g;
+    const uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
+    uint32_t *sup = ghost ? d.wsupg : d.wsup;
+    {   // clear the other parity's group sums (the tiles of the chunk before)
+        const int64_t used = (next[B] + kSupGroup - 1) / kSupGroup * kClasses;
+        uint32_t *o = sup + (int64_t)(par ^ 1u) * groups * kClasses;
+        for (int64_t q = tid; q < used; q += kThreads) o[q] = 0u;
+    }
+    const uint32_t *wsup = sup + (int64_t)par * groups * kClasses;
+    // the walking blocks' last tallies, summed per instance in LDS when the
+    // instances fit (global atomics from one block on one line serialise)
+    constexpr int kLdsB = 256;
+    __shared__ int64_t s_acc[5][kLdsB];
+    __shared__ uint32_t s_red[2 * kThreads];
+    __shared__ uint32_t s_tot[kClasses];
+    const bool lds = B <= kLdsB;
+    if (lds)
+        for (int b = tid; b < B; b += kThreads)
+            for (int q = 0; q < 5; ++q) s_acc[q][b] = 0;
+    __syncthreads();
+    for (int g = tid; g < fgrid; g += kThreads) {
+        const int64_t *F = d.fpart + (int64_t)g * 8;
+        if (F[0] < 0) continue;
+        if (lds) {
+            const int b = (int)F[0];
+            for (int q = 0; q < 4; ++q)
+                if (F[1 + q]) atomicAdd((unsigned long long *)&s_acc[q][b], (unsigned long long)F[1 + q]);
+            if (F[5]) atomicMax((unsigned long long *)&s_acc[4][b], (unsigned long long)F[5]);
+        } else {
+            int64_t *T = d.tally + F[0] * kTalCount;
+            if (F[1]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)F[1]);
+            if (F[2]) atomicAdd((unsigned long long *)&T[kTalPairs], (unsigned long long)F[2]);
+            if (F[3]) atomicAdd((unsigned long long *)&T[kTalKilled], (unsigned long long)F[3]);
+            if (F[4]) atomicAdd((unsigned long long *)&T[kTalEventCap], (unsigned long long)F[4]);
+            if (F[5]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)F[5]);
+        }
+    }
+    __syncthreads();
+    int over = 0;         // an instance of this thread holds more than ann_limit
+    // counts from the class totals: by all threads from the tiles' counts
+    // where there are few instances, else kept per instance by k_walk (whose
+    // tiles of one instance are then few: their additions to its line of
+    // totals do not queue up)
+    auto finish = [&](int b, auto total) {   // total(c): the instance's records of class c
+        int64_t *T = d.tally + (int64_t)b * kTalCount;
+        if (lds) {
+            T[kTalEvents] += s_acc[0][b];
+            T[kTalPairs] += s_acc[1][b];
+            T[kTalKilled] += s_acc[2][b];
+            T[kTalEventCap] += s_acc[3][b];
+            if (s_acc[4][b] > T[kTalMaxDepth]) T[kTalMaxDepth] = s_acc[4][b];
+        }
+        const int64_t cap = ghost ? d.ip[b].gcap : d.ip[b].cap;
+        int64_t n = Ncur[b], ps = 0;
+        int64_t *ns = d.nstep + ((int64_t)ghost * B + b) * (kPend + 1);
+        for (int s = 0; s < S; ++s) {
+            ps += n;
+            for (int c = 1 << s; c < (2 << s); ++c) n += (int64_t)total(c);
+            if (n > cap) {
+                atomicOr(&ctl->err, kErrCapacity);
+                n = cap;
+            }
+            if (!adv) ns[pend + s + 1] = n;
+        }
+        if (adv) ns[0] = n;
+        if (!ghost) T[kTalPSteps] += ps;
+        Ncur[b] = n;
+        if (d.ann_limit > 0 && n > d.ann_limit) over = 1;
+    };
+    if (B <= kFewInst) {
+        for (int b = 0; b < B; ++b) {
+            uint32_t below, tot;
+            class_sums(wcnt, wsup, plan[b], plan[b], plan[b + 1], s_red, below, tot);
+            if (tid < kClasses) s_tot[tid] = tot;
+            __syncthreads();
+            if (tid == 0) finish(b, [&](int c) { return s_tot[c]; });
+            __syncthreads();
+        }
+    } else {
+        for (int b = tid; b < B; b += kThreads) {
+            uint32_t *W = d.wtot + ((int64_t)ghost * B + b) * kClasses;
+            finish(b, [&](int c) { return W[c]; });
+            for (int c = 0; c < kClasses; ++c) W[c] = 0u;
+        }
+    }
+    // conditional annihilation after this step (chunks of one step):
+    // scheduled, or an instance about to outgrow the threshold (the real
+    // ensemble's closing block)
+    const int any_over = __syncthreads_or(over);
+    if (d.cond_ann && !ghost && tid == 0) {
+        const bool sched = d.ann_every > 0 && (step + (uint32_t)S) % (uint32_t)d.ann_every == 0u;
+        ctl->ann_now = (sched || any_over) ? 1u : 0u;
+        if (any_over && !sched)
+            for (int b = 0; b < B; ++b) d.tally[(int64_t)b * kTalCount + kTalTrig] += 1;
+    }
+    // the tile plans
+    block_plan(d.tileA + (int64_t)ghost * (B + 1), Ncur, B, kTileA);
+    block_prefix(next, B, [&](int b) { return walk_tiles(d, ghost, b, Ncur[b]); });
+    if (tid == 0 && advance) {
+        ctl->step = step + (uint32_t)S;
+        ctl->chunk += 1u;
+    }
+}
+
+}  // namespace wbrw
