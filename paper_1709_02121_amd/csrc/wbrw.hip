@@ -448,12 +448,11 @@ int parents_at_a_time(const wbrw_handle *h, bool ghost, int pool, int queue)
 }
 
 // Most particles in a tile of k_walk, for an instance whose particles jump in
-// a step with probability p: so many that about three fifths of the event
-// parents taken at a time are found in a step (offspring and growth until the
-// next annihilation add to them).
+// a step with probability p: so many that three quarters of the event parents
+// taken at a time are found in a step (the offspring's add to them).
 int range_limit(double p, int parents)
 {
-    const double r = std::min(p > 0.0 ? 0.6 * parents / p : (double)kRangeMax, (double)kRangeMax);
+    const double r = std::min(p > 0.0 ? 0.75 * parents / p : (double)kRangeMax, (double)kRangeMax);
     return (int)std::max<int64_t>(kRangeMin, (int64_t)r / kRangeMin * kRangeMin);
 }
 

@@ -29,7 +29,7 @@ constexpr uint32_t kRejectMax = 256u;   // rejection proposals per kick
 constexpr int kChunk = 5;               // steps in one launch of k_walk, at most
 constexpr int kClasses = 1 << kChunk;   // sets of steps in which an offspring and its ancestors were born
 constexpr int kPend = 32;               // steps between materialisations of the positions, at most
-constexpr int kRangeMin = 256;          // particles in a tile of k_walk, at least
+constexpr int kRangeMin = 64;           // particles in a tile of k_walk, at least; a multiple of 64
 constexpr int kRangeMax = 8192;         // particles in a tile of k_walk, at most
 constexpr int kLocalBits = 4096;        // offspring of a tile whose event bits are kept in LDS
 constexpr int kFewInst = 8;             // instances whose class totals are summed from the tiles'
@@ -103,6 +103,8 @@ struct Ctl {
     uint32_t ann_now;          // conditional annihilation: the one after this step runs
     uint32_t chunk;            // chunks of steps so far: its parity picks the tile plan and group sums
     uint32_t wpar;             // parity of the chunk that k_place closes
+    uint32_t fill[24];         // the counters below start a line of their own: their
+                               // atomics do not hold up the reads of the words above
     uint32_t ticket[kPassCount];   // zero between launches (see next_tile)
 };
 
@@ -188,11 +190,14 @@ struct Dev {
     int64_t tstride;            // tiles per class in bTile
 };
 
-// Particles in a tile of k_walk for an ensemble of n: n / tiles rounded up to
-// kRangeMin, at most `most`.
+// Particles in a tile of k_walk for an ensemble of n: an equal share of a
+// whole multiple of `tiles` tiles (so that the blocks that run at once all
+// take the same number of tiles), rounded up to kRangeMin, at most `most`.
 __host__ __device__ __forceinline__ int64_t walk_range(int64_t n, int32_t tiles, int32_t most)
 {
-    const int64_t r = ((n + tiles - 1) / tiles + kRangeMin - 1) / kRangeMin * kRangeMin;
+    const int64_t waves = (n + (int64_t)tiles * most - 1) / ((int64_t)tiles * most);
+    const int64_t t = (waves < 1 ? 1 : waves) * tiles;
+    const int64_t r = ((n + t - 1) / t + kRangeMin - 1) / kRangeMin * kRangeMin;
     return r < kRangeMin ? kRangeMin : (r > most ? most : r);
 }
 __device__ __forceinline__ int64_t walk_range(const InstParam &P, int ghost, int64_t n)
@@ -341,21 +346,21 @@ __device__ __forceinline__ int64_t next_tile(uint32_t *ctr, int64_t ntiles)
 // The same dispenser with every block's first tile given statically (block
 // b takes tile b): when the tiles are about as many as the blocks, every
 // block starts at once instead of queueing behind one atomic on one line
-// (some 11 ns each).  The counter then hands out tiles gridDim.x, ...: each
-// of those tickets is drawn once and every block draws one ticket past the
-// end, so the block that draws ticket max(0, ntiles - gridDim.x) +
-// gridDim.x - 1 clears the counter.  `first` is the caller's flag, true on
-// its first call.
+// (some 11 ns each).  With no more tiles than blocks no ticket is drawn at
+// all; otherwise the counter hands out tiles gridDim.x, ...: each of those
+// tickets is drawn once and every block draws one ticket past the end, so the
+// block that draws ticket ntiles - 1 clears the counter.  `first` is the
+// caller's flag, true on its first call.
 __device__ __forceinline__ int64_t next_tile_static_first(uint32_t *ctr, int64_t ntiles, bool &first)
 {
     const int64_t G = (int64_t)gridDim.x;
     if (first) {
         first = false;
-        if ((int64_t)blockIdx.x < ntiles) return (int64_t)blockIdx.x;
+        return (int64_t)blockIdx.x;
     }
-    const int64_t D = ntiles > G ? ntiles - G : 0;
+    if (ntiles <= G) return ntiles;
     const uint32_t u = atomicAdd(ctr, 1u);
-    if ((int64_t)u == D + G - 1) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((int64_t)u == ntiles - 1) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return G + (int64_t)u;
 }
 

@@ -38,6 +38,13 @@
 
 namespace wbrw {
 
+// Instance b's parameters (b uniform over the wavefront), which no kernel
+// writes: read by scalar loads, also after stores to global memory.
+__device__ __forceinline__ const InstParam &inst_param(const Dev &d, int b)
+{
+    return *(const InstParam *)(const __attribute__((address_space(4))) InstParam *)(d.ip + b);
+}
+
 // Birth index of instance-particle i: the number of entries of the table
 // nst[0 .. pend] (counts at the start of the steps since the last
 // materialisation) that are <= i.  Its first advance is that of step
@@ -55,19 +62,88 @@ __device__ __forceinline__ double advanced(double x, double c, int m)
     return x;
 }
 
-// Does particle `id`, at rest in its first clock of step `step`, jump before
-// its end?  Its first uniform's high word decides, but for a band around the
-// threshold, where the exact test is evaluated.
-__device__ __forceinline__ bool clock_jumps(const Dev &d, const InstParam &P, uint64_t id, uint32_t step)
+// The high word of the first uniform of particle `id` in step `step` (word 1
+// of its clock draw, counter (id, step, 0)): the rounds of Philox4x32-10 as
+// far as this word needs them, 15 products.  The first round's products of
+// the id and the second round's product that follows from them do not depend
+// on the step (Clock), those of the step not on the particle.
+struct Clock {
+    uint32_t id_hi, h1, l1, h2, l2;
+};
+__device__ __forceinline__ Clock clock_of(const Dev &d, uint64_t id, uint32_t key)
 {
-    const W4 r = draw(id, step, kTagStep, 0u, 0u, d.seed, P.key);
-    if (r.b < P.ib_lo) return true;
-    if (r.b > P.ib_hi) return false;
-    const W4 e = draw(id, step, kTagStep, 0u, 0u, d.seed, P.key);
+    const uint64_t p0 = (uint64_t)(uint32_t)id * 0xD2511F53ull;
+    const uint32_t c2 = (uint32_t)(p0 >> 32) ^ key;
+    const uint64_t p1 = (uint64_t)c2 * 0xCD9E8D57ull;
+    return {(uint32_t)(id >> 32), c2, (uint32_t)p0, (uint32_t)(p1 >> 32), (uint32_t)p1};
+}
+__device__ __forceinline__ uint32_t clock_word(const Dev &d, const Clock &c, uint32_t step, uint32_t key)
+{
+    uint32_t k0 = d.seed, k1 = key;
+    const uint64_t ps = (uint64_t)step * 0xCD9E8D57ull;
+    // round 1: c0 ^= ..., c1 = low word of the step's product, c2 = h1, c3 = l1
+    uint32_t c0 = c.id_hi ^ ((uint32_t)(ps >> 32) ^ k0);
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+    // round 2
+    uint64_t p0 = (uint64_t)c0 * 0xD2511F53ull;
+    c0 = c.h2 ^ ((uint32_t)ps ^ k0);
+    uint32_t c1 = c.l2, c2 = xor3((uint32_t)(p0 >> 32), c.l1, k1), c3 = (uint32_t)p0;
+#pragma unroll
+    for (int r = 3; r <= 8; ++r) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        p0 = (uint64_t)c0 * 0xD2511F53ull;
+        const uint64_t p1 = (uint64_t)c2 * 0xCD9E8D57ull;
+        c0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        c1 = (uint32_t)p1;
+        c2 = xor3((uint32_t)(p0 >> 32), c3, k1);
+        c3 = (uint32_t)p0;
+    }
+    k1 += 0xBB67AE85u;
+    c2 = xor3(__umulhi(c0, 0xD2511F53u), c3, k1);   // round 9
+    return c2 * 0xCD9E8D57u;                        // round 10
+}
+
+// Does the particle jump before the end of the step?  The whole test, where
+// the high word of its first uniform does not decide.
+__device__ __noinline__ bool clock_exact(uint64_t id, uint32_t step, uint32_t seed, uint32_t key, double thr_lo,
+                                         double thr_hi, double g0, double dt)
+{
+    const W4 e = draw(id, step, kTagStep, 0u, 0u, seed, key);
     const double u = unit53(e.a, e.b);
-    if (u < P.thr_lo) return true;
-    if (!(u <= P.thr_hi)) return false;
-    return -ln_series(1.0 - u) / P.gamma0 <= d.dt;
+    if (u < thr_lo) return true;
+    if (!(u <= thr_hi)) return false;
+    return -ln_series(1.0 - u) / g0 <= dt;
+}
+__device__ __forceinline__ bool clock_jumps(const Dev &d, const InstParam &P, const Clock &c, uint64_t id, uint32_t step)
+{
+    const uint32_t w = clock_word(d, c, step, P.key);
+    bool j = w < P.ib_lo;
+    if (!j && w <= P.ib_hi) j = clock_exact(id, step, d.seed, P.key, P.thr_lo, P.thr_hi, P.gamma0, d.dt);
+    return j;
+}
+
+// Synchronises the block where only LDS is shared: stores to global memory
+// may still be under way.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Inclusive scan of v over the wavefront, by data-parallel moves within rows
+// of 16 lanes and broadcasts of the rows' last lanes (all 64 lanes call).
+__device__ __forceinline__ uint32_t wave_incl(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return v;
 }
 
 // Exclusive scan of v over the block's threads (s_w: kThreads / 64 slots, not
@@ -75,14 +151,9 @@ __device__ __forceinline__ bool clock_jumps(const Dev &d, const InstParam &P, ui
 __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *s_w, uint32_t &tot)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += y;
-    }
+    const uint32_t incl = wave_incl(v);
     if (lane == 63) s_w[wv] = incl;
-    __syncthreads();
+    lds_barrier();
     uint32_t excl = incl - v;
     tot = 0;
 #pragma unroll
@@ -151,7 +222,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
         if (tid == 0) s_t = (int32_t)next_tile_static_first(&ctl->ticket[pass], ntiles, first);
         for (int q = tid; q < kChunk * kWL; q += kThreads) (&s_evl[0][0])[q] = 0ull;
         if (tid < kClasses) s_ccnt[tid] = 0u;
-        __syncthreads();
+        lds_barrier();
         const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
         if (t >= ntiles) break;
         const int b = __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
@@ -168,7 +239,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
             cb = b;
             if (tid < pend) s_nst[tid] = (uint32_t)nstep[(int64_t)b * (kPend + 1) + tid];
         }
-        const InstParam &P = d.ip[b];
+        const InstParam &P = inst_param(d, b);
         const int64_t base = ghost ? P.gbase : P.base;
         const int64_t cap = ghost ? P.gcap : P.cap;
         const int64_t n = Ncur[b], tl = t - plan[b], T = plan[b + 1] - plan[b];
@@ -185,10 +256,17 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
             for (int j = 0; j * kThreads < nr; ++j) {
                 const int li = j * kThreads + tid;
                 const uint64_t cur = id;
+                const Clock c = clock_of(d, cur, P.key);
+                const uint64_t in = __ballot(li < nr);
                 id = E.id[i0 + min(li + kThreads, nr - 1)];
                 for (int s = 0; s < S; ++s) {
-                    const uint64_t m = __ballot(li < nr && clock_jumps(d, P, cur, step0 + (uint32_t)s));
-                    if (lane == 0) s_ev[s][j * (kThreads / 64) + wv] = m;
+                    const uint32_t w = clock_word(d, c, step0 + (uint32_t)s, P.key);
+                    uint64_t m = __ballot(w < P.ib_lo);
+                    const uint64_t band = __ballot(w <= P.ib_hi) ^ m;   // not decided by this word
+                    if (band)
+                        m |= band & __ballot(clock_exact(cur, step0 + (uint32_t)s, d.seed, P.key, P.thr_lo, P.thr_hi,
+                                                         P.gamma0, d.dt));
+                    if (lane == 0) s_ev[s][j * (kThreads / 64) + wv] = m & in;
                 }
             }
         }
@@ -203,7 +281,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
             for (uint32_t q0 = 0;; q0 += (uint32_t)FS) {
                 // event parents [q0, q0 + FS) of the step, in order: first
                 // the range's, then the offspring's
-                __syncthreads();
+                if (nl0 > (uint32_t)kLocalBits) __syncthreads(); else lds_barrier();
                 uint32_t run = 0;
                 for (int w0 = 0, it = 0; w0 < nw; w0 += kThreads, ++it) {
                     const int wi = w0 + tid, wl = wi - nw0;
@@ -283,7 +361,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                     }
                     for (int round = 0;; ++round) {
                         if (act) take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, F);
-                        __syncthreads();
+                        if (DIM == 2) __syncthreads(); else lds_barrier();   // 4D records may be in HBM
                         const uint32_t nq = F.nq[round & 1];
                         if (nq == 0u || F.overflow) break;
                         act = tid < (int)nq;
@@ -301,7 +379,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                             lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
                         }
                         if (tid == 0) F.nq[(round + 1) & 1] = 0u;
-                        __syncthreads();
+                        lds_barrier();
                     }
                 }
                 const bool overflow = F.overflow != 0u;
@@ -319,15 +397,16 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                 uint32_t agg;
                 const uint32_t excl = block_excl(F.cnt[tid], s_wsum[0], agg);
                 F.first[tid] = excl;
-                __syncthreads();
+                lds_barrier();
                 // 3. records into the tile's area, each at its rank in its
                 //    family, with its class and its own jumps in the chunk's
                 //    later steps
                 auto close_record = [&](int64_t li, uint64_t id, int slot) {
                     const uint32_t cls = (uint32_t)s_cls[slot] | (1u << s);
                     uint32_t ev = 0;
+                    const Clock c = clock_of(d, id, P.key);
                     for (int q = s + 1; q < S; ++q)
-                        if (clock_jumps(d, P, id, step0 + (uint32_t)q)) {
+                        if (clock_jumps(d, P, c, id, step0 + (uint32_t)q)) {
                             ev |= 1u << q;
                             if (li < kLocalBits) atomicOr(&s_evl[q][li >> 6], 1ull << (li & 63));
                         }
@@ -381,7 +460,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                     atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tal.maxdepth);
                 }
                 nl = min(nl + agg, alen);
-                __syncthreads();
+                lds_barrier();
                 if (tid == 0 && !overflow) {
                     s_tal[0] += F.events;
                     s_tal[1] += F.pairs;
@@ -391,7 +470,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                 if (q0 + (uint32_t)FS >= np) break;
             }
         }
-        __syncthreads();
+        lds_barrier();
         // the tile's counts per class, also summed over groups of tiles
         if (tid < kClasses) {
             const uint32_t c = s_ccnt[tid];
@@ -411,7 +490,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
     }
     if (tid == 0) {
         int64_t *T = d.fpart + (int64_t)blockIdx.x * 8;
