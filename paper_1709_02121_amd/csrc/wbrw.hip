@@ -34,7 +34,7 @@ struct Layout {
     // offsets
     size_t ens[2][8] = {}, gens[2][8] = {};
     size_t ip = 0, dev = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
-    size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, Nsrt = 0, srtS = 0, tileW = 0,
+    size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, Nsrt = 0, srtS = 0, tileW = 0, wrange = 0,
            tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, wcnt = 0,
            wcntg = 0, wsup = 0, wsupg = 0, wtot = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
            occ = 0, Tq = 0, ntil = 0, dacc = 0, dTq = 0, bA = 0, bcopies = 0, bcls = 0,
@@ -267,6 +267,7 @@ Layout make_layout(const wbrw_config *c)
     L.Nsrt = take(cur, BB * 8);
     L.srtS = take(cur, (BB + 1) * 8);
     L.tileW = take(cur, 4 * (BB + 1) * 8);
+    L.wrange = take(cur, 8 * BB * 8);
     L.tileR = take(cur, (BB + 1) * 8);
     L.tileG = take(cur, (BB + 1) * 8);
     L.tally = take(cur, BB * kTalCount * 8);
@@ -409,7 +410,7 @@ constexpr int kBinSlots[3] = {4096, 2048, 8192};
 // The particles' walking kernel of this handle.  One static Gaussian
 // component with the majorant sampler (every tangent form has that) takes the
 // instantiation without the component loop.
-using WalkKernel = void (*)(Dev, int, int, int, int);
+using WalkKernel = void (*)(const Dev *, int, int, int, int);
 template <int DIM>
 WalkKernel walk_kernel(const wbrw_handle *h)
 {
@@ -575,17 +576,22 @@ int upload_counts(wbrw_t h, const std::vector<int64_t> &N, const std::vector<int
         const std::vector<int64_t> &n = g ? NG : N;
         v.push_back(n);
         to.push_back(g ? d.NG : d.N);
-        std::vector<int64_t> plan, walk(B + 1, 0), ns((size_t)B * (kPend + 1), 0);
+        std::vector<int64_t> plan, walk(B + 1, 0), range(2 * (size_t)B), ns((size_t)B * (kPend + 1), 0);
         plan_host(plan, n.data(), B, kTileA);
         for (int b = 0; b < B; ++b) {
             const InstParam &P = h->ip[b];
-            walk[b + 1] = walk[b] + ceil_div(n[b], g ? walk_range(n[b], P.gwt, P.gwr) : walk_range(n[b], P.wt, P.wr));
+            const int64_t r = g ? walk_range(n[b], P.gwt, P.gwr) : walk_range(n[b], P.wt, P.wr), t = ceil_div(n[b], r);
+            walk[b + 1] = walk[b] + t;
+            range[2 * b] = r;
+            range[2 * b + 1] = (g ? P.gcap : P.cap) / std::max<int64_t>(t, 1);
             ns[(size_t)b * (kPend + 1)] = n[b];
         }
         v.push_back(plan);
         to.push_back(d.tileA + (int64_t)g * (B + 1));
         v.push_back(walk);
         to.push_back(d.tileW + (int64_t)(2 * par + g) * (B + 1));
+        v.push_back(range);
+        to.push_back(d.wrange + (int64_t)(2 * par + g) * 2 * B);
         v.push_back(ns);
         to.push_back(d.nstep + (int64_t)g * B * (kPend + 1));
     }
@@ -674,7 +680,7 @@ void enqueue_chunk_dim(wbrw_t h, int S, int pend, int adv)
     const int fg = h->grid[G_FAMILY];
     const dim3 wg(fg), pg(h->grid[G_PLACE] + 1), nt(kThreads);
     stage_begin(h, WBRW_STAGE_FAMILY);
-    hipLaunchKernelGGL(walk_kernel<DIM>(h), wg, nt, 0, s, d, 0, S, pend, adv);
+    hipLaunchKernelGGL(walk_kernel<DIM>(h), wg, nt, 0, s, d.self, 0, S, pend, adv);
     stage_end(h);
     stage_begin(h, WBRW_STAGE_PLACE);
     if constexpr (DIM == 1) {
@@ -689,7 +695,7 @@ void enqueue_chunk_dim(wbrw_t h, int S, int pend, int adv)
     if (tan) {
         // ghosts (weight 0) branch by the sp1 rule in either strategy
         stage_begin(h, WBRW_STAGE_GHOST);
-        hipLaunchKernelGGL((k_walk<1, false, true, true>), wg, nt, 0, s, d, 1, S, pend, adv);
+        hipLaunchKernelGGL((k_walk<1, false, true, true>), wg, nt, 0, s, d.self, 1, S, pend, adv);
         hipLaunchKernelGGL((k_place<1, false, true>), pg, nt, 0, s, d, 1, S, pend, adv, 1, fg);
         stage_end(h);
     }
@@ -1011,6 +1017,7 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.Nsrt = at<int64_t>(w, L.Nsrt);
     d.srtS = at<int64_t>(w, L.srtS);
     d.tileW = at<int64_t>(w, L.tileW);
+    d.wrange = at<int64_t>(w, L.wrange);
     d.tileR = at<int64_t>(w, L.tileR);
     d.tileG = at<int64_t>(w, L.tileG);
     d.tally = at<int64_t>(w, L.tally);

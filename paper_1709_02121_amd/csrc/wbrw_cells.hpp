@@ -734,8 +734,7 @@ __global__ __launch_bounds__(kThreads) void k_close_regen(Dev d)
     __syncthreads();
     block_plan(d.tileA, d.N, B, kTileA);
     for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)b * (kPend + 1)] = d.N[b];
-    block_prefix(d.tileW + (int64_t)(2 * (ctl->chunk & 1u)) * (B + 1), B,
-                 [&](int b) { return walk_tiles(d, 0, b, d.N[b]); });
+    plan_walk(d, ctl->chunk & 1u, 0, d.N);
     block_prefix(d.srtS, B, [&](int b) { return d.Nsrt[b] / kTileA; });
     if (threadIdx.x == 0) {
         ctl->cur ^= 1u;

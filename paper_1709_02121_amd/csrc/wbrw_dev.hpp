@@ -142,6 +142,8 @@ struct Dev {
                                 // positions were materialised (real, ghost); entry 0 always holds
     int64_t *tileA;             // [2][B+1] streaming-tile plan (real, ghost)
     int64_t *tileW;             // [2][2][B+1] walk-tile plan (parity; real, ghost)
+    int64_t *wrange;            // [2][2][B][2] its particles per tile, and the slots of a tile's
+                                // area in the inactive set
     int64_t *tileR;             // [B+1] regeneration-tile plan
     int64_t *tileG;             // [B+1] ghost-regeneration plan
     int64_t *tally;             // [B][kTalCount]
@@ -200,17 +202,6 @@ __host__ __device__ __forceinline__ int64_t walk_range(int64_t n, int32_t tiles,
     const int64_t r = ((n + t - 1) / t + kRangeMin - 1) / kRangeMin * kRangeMin;
     return r < kRangeMin ? kRangeMin : (r > most ? most : r);
 }
-__device__ __forceinline__ int64_t walk_range(const InstParam &P, int ghost, int64_t n)
-{
-    return ghost ? walk_range(n, P.gwt, P.gwr) : walk_range(n, P.wt, P.wr);
-}
-// Tiles of k_walk for n particles of instance b.
-__device__ __forceinline__ int64_t walk_tiles(const Dev &d, int ghost, int b, int64_t n)
-{
-    const int64_t r = walk_range(d.ip[b], ghost, n);
-    return (n + r - 1) / r;
-}
-
 // An annihilation kernel enqueued after a step of wbrw_run_adaptive does
 // nothing unless that step's closing kernel asked for the annihilation.
 __device__ __forceinline__ bool ann_skipped(const Dev &d)
@@ -486,6 +477,20 @@ __device__ __forceinline__ void block_prefix(int64_t *plan, int B, F value)
 __device__ __forceinline__ void block_plan(int64_t *plan, const int64_t *cnt, int B, int64_t tile)
 {
     block_prefix(plan, B, [&](int b) { return (cnt[b] + tile - 1) / tile; });
+}
+
+// The tile plan of k_walk at chunk parity `par` for counts n[b]; one block.
+__device__ __forceinline__ void plan_walk(const Dev &d, uint32_t par, int ghost, const int64_t *n)
+{
+    const int64_t at = 2 * par + (uint32_t)ghost;
+    block_prefix(d.tileW + at * (d.B + 1), d.B, [&](int b) {
+        const InstParam &P = d.ip[b];
+        const int64_t r = ghost ? walk_range(n[b], P.gwt, P.gwr) : walk_range(n[b], P.wt, P.wr);
+        const int64_t t = (n[b] + r - 1) / r;
+        d.wrange[2 * (at * d.B + b)] = r;
+        d.wrange[2 * (at * d.B + b) + 1] = (ghost ? P.gcap : P.cap) / (t > 0 ? t : 1);
+        return t;
+    });
 }
 
 // Cost of binning a streaming tile: kBinSortedCost inside the cell-ordered

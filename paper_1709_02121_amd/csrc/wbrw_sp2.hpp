@@ -890,8 +890,7 @@ __global__ __launch_bounds__(kThreads) void k_close_ghosts(Dev d)
     __syncthreads();
     block_plan(d.tileA + (B + 1), d.NG, B, kTileA);
     for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)(B + b) * (kPend + 1)] = d.NG[b];
-    block_prefix(d.tileW + (int64_t)(2 * (ctl->chunk & 1u) + 1) * (B + 1), B,
-                 [&](int b) { return walk_tiles(d, 1, b, d.NG[b]); });
+    plan_walk(d, ctl->chunk & 1u, 1, d.NG);
     if (threadIdx.x == 0) ctl->gcur ^= 1u;
 }
 

@@ -38,11 +38,23 @@
 
 namespace wbrw {
 
+// The launch constants, read again from memory by scalar loads.  k_walk holds
+// more of them than there are scalar registers; values read where a scope
+// begins do not stay live across the loops around it.  (Kept in registers
+// from the kernel's start, some 200 of them lived in lanes of vector
+// registers.)  The copy in device memory is written once, at wbrw_init.
+__device__ __forceinline__ const Dev &fresh(const Dev *self)
+{
+    uint64_t p = (uint64_t)self;
+    asm volatile("" : "+s"(p));
+    return *(const Dev *)(const __attribute__((address_space(4))) Dev *)p;
+}
+
 // Instance b's parameters (b uniform over the wavefront), which no kernel
 // writes: read by scalar loads, also after stores to global memory.
 __device__ __forceinline__ const InstParam &inst_param(const Dev &d, int b)
 {
-    return *(const InstParam *)(const __attribute__((address_space(4))) InstParam *)(d.ip + b);
+    return *(const InstParam *)(const __attribute__((address_space(4))) InstParam *)(uintptr_t)(d.ip + b);
 }
 
 // Birth index of instance-particle i: the number of entries of the table
@@ -166,8 +178,8 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *s_w, uint32
 }
 
 template <int DIM, bool SP2, bool TAN, bool ONE>
-__global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(Dev d, int ghost, int S, int pend,
-                                                                             int adv)
+__global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(const Dev *self, int ghost, int S,
+                                                                             int pend, int adv)
 {
     using FT = Families<DIM, SP2, TAN>;
     constexpr int kW0 = kRangeMax / 64;       // words of a step's bits of the range
@@ -186,29 +198,24 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
     __shared__ uint32_t s_nst[kPend + 1];
     constexpr uint32_t kLocal = 0x80000000u;
 
-    Ctl *ctl = d.ctl;
-    const uint32_t step0 = ctl->step, par = ctl->chunk & 1u;
-    const int B = d.B;
-    const int FS = ghost ? d.gftile : d.ftile;     // event parents taken at a time
-    const int64_t *plan = d.tileW + (int64_t)(2 * par + ghost) * (B + 1);
-    const int64_t ntiles = plan[B];
-    const uint32_t set = ghost ? ctl->gcur : ctl->cur;
-    const Ens E = pick_set(d, ghost, set);
-    const Ens S_ = pick_set(d, ghost, set ^ 1u);   // the tiles' areas
-    const int64_t *Ncur = ghost ? d.NG : d.N;
-    uint16_t *smask = ghost ? d.smaskg : d.smask;
-    uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
-    uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
-    const int64_t *nstep = d.nstep + (int64_t)ghost * B * (kPend + 1);
-    const int pass = ghost ? kPassFamilyG : kPassFamily;
-    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t err = 0;
-
-    // kept for k_place, whose closing block changes both
-    if (blockIdx.x == 0) {
-        for (int b = tid; b < B; b += kThreads) d.Nbase[(int64_t)ghost * B + b] = Ncur[b];
-        if (tid == 0) ctl->wpar = par;
+    uint32_t err = 0, step0, par, set;
+    int B;
+    int64_t ntiles;
+    {
+        const Dev &d = fresh(self);
+        Ctl *ctl = d.ctl;
+        step0 = ctl->step;
+        par = ctl->chunk & 1u;
+        set = ghost ? ctl->gcur : ctl->cur;
+        B = d.B;
+        ntiles = d.tileW[(int64_t)(2 * par + ghost) * (B + 1) + B];
+        // kept for k_place, whose closing block changes both
+        if (blockIdx.x == 0) {
+            const int64_t *Ncur = ghost ? d.NG : d.N;
+            for (int b = tid; b < B; b += kThreads) d.Nbase[(int64_t)ghost * B + b] = Ncur[b];
+            if (tid == 0) ctl->wpar = par;
+        }
     }
     // Tallies stay in LDS while the block works on one instance; they go to
     // the instance's counters when the block moves on to another one, and the
@@ -219,14 +226,35 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
     bool first = true;
     if (tid < 5) s_tal[tid] = 0;
     for (;;) {
-        if (tid == 0) s_t = (int32_t)next_tile_static_first(&ctl->ticket[pass], ntiles, first);
+        if (tid == 0) {
+            const Dev &d = fresh(self);
+            s_t = (int32_t)next_tile_static_first(&d.ctl->ticket[ghost ? kPassFamilyG : kPassFamily], ntiles, first);
+        }
         for (int q = tid; q < kChunk * kWL; q += kThreads) (&s_evl[0][0])[q] = 0ull;
         if (tid < kClasses) s_ccnt[tid] = 0u;
         lds_barrier();
         const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
         if (t >= ntiles) break;
-        const int b = __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
+        // tile t is tile tl of instance b: its range of nr particles from i0
+        // on, and its area of alen slots of the inactive set from a0 on
+        int b, nr, i00;
+        int64_t i0, a0;
+        uint32_t alen;
+        {
+            const Dev &d = fresh(self);
+            const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
+            b = B == 1 ? 0 : __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
+            const InstParam &P = inst_param(d, b);
+            const int64_t base = ghost ? P.gbase : P.base, n = (ghost ? d.NG : d.N)[b], tl = t - plan[b];
+            const int64_t R = d.wrange[2 * (at * B + b)], area = d.wrange[2 * (at * B + b) + 1];
+            i00 = (int)(tl * R);
+            i0 = base + tl * R;
+            nr = (int)min(R, n - tl * R);
+            a0 = base + tl * area;
+            alen = (uint32_t)min(area, (int64_t)0x7FFFFFFF);
+        }
         if (b != cb) {
+            const Dev &d = fresh(self);
             if (tid == 0 && cb >= 0) {
                 int64_t *T = d.tally + (int64_t)cb * kTalCount;
                 if (s_tal[0]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)s_tal[0]);
@@ -237,28 +265,21 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                 for (int q = 0; q < 5; ++q) s_tal[q] = 0;
             }
             cb = b;
-            if (tid < pend) s_nst[tid] = (uint32_t)nstep[(int64_t)b * (kPend + 1) + tid];
+            if (tid < pend) s_nst[tid] = (uint32_t)d.nstep[((int64_t)ghost * B + b) * (kPend + 1) + tid];
         }
-        const InstParam &P = inst_param(d, b);
-        const int64_t base = ghost ? P.gbase : P.base;
-        const int64_t cap = ghost ? P.gcap : P.cap;
-        const int64_t n = Ncur[b], tl = t - plan[b], T = plan[b + 1] - plan[b];
-        const int R = (int)walk_range(P, ghost, n);
-        const int64_t i0 = base + tl * R;                       // the range
-        const int nr = (int)min((int64_t)R, n - tl * R);
-        const int64_t area = cap / T, a0 = base + tl * area;    // the tile's area
-        const uint32_t alen = (uint32_t)min(area, (int64_t)0x7FFFFFFF);
-
         // the range's clocks, lanes on consecutive particles; the next ids
         // are loaded while the draws of the last ones run
         {
-            uint64_t id = E.id[i0 + min(tid, nr - 1)];
+            const Dev &d = fresh(self);
+            const InstParam &P = inst_param(d, b);
+            const uint64_t *ids = (ghost ? d.gens : d.ens)[set].id + i0;
+            uint64_t id = ids[min(tid, nr - 1)];
             for (int j = 0; j * kThreads < nr; ++j) {
                 const int li = j * kThreads + tid;
                 const uint64_t cur = id;
                 const Clock c = clock_of(d, cur, P.key);
                 const uint64_t in = __ballot(li < nr);
-                id = E.id[i0 + min(li + kThreads, nr - 1)];
+                id = ids[min(li + kThreads, nr - 1)];
                 for (int s = 0; s < S; ++s) {
                     const uint32_t w = clock_word(d, c, step0 + (uint32_t)s, P.key);
                     uint64_t m = __ballot(w < P.ib_lo);
@@ -274,6 +295,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
         uint32_t nl = 0;                     // offspring of the tile so far
         for (int s = 0; s < S; ++s) {
             const uint32_t step = step0 + (uint32_t)s;
+            const int FS = ghost ? fresh(self).gftile : fresh(self).ftile;   // event parents taken at a time
             const uint32_t nl0 = nl;         // those of earlier steps
             const int nw = nw0 + (int)((nl0 + 63u) / 64u);
             if (tid == 0) s_born[s] = nl0;
@@ -290,7 +312,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                     else if (wi < nw && wl < kWL) m = s_evl[s][wl];
                     else if (wi < nw)        // past the bits kept in LDS
                         for (uint32_t q = 0; q < 64u && (uint32_t)wl * 64u + q < nl0; ++q)
-                            m |= (uint64_t)((smask[a0 + wl * 64 + q] >> (kChunk + s)) & 1u) << q;
+                            m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)[a0 + wl * 64 + q] >> (kChunk + s)) & 1u) << q;
                     uint32_t tot;
                     uint32_t pos = run + block_excl((uint32_t)__popcll(m), s_wsum[it & 1], tot);
                     while (m) {
@@ -314,10 +336,13 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                 const bool live = tid < FS && q0 + (uint32_t)tid < np;
                 // the thread's event parent at the start of the step
                 auto load_root = [&]() {
+                    const Dev &d = fresh(self);
+                    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
                     const uint32_t it = s_item[tid];
                     const bool loc = (it & kLocal) != 0u;
                     const uint32_t l = it & ~kLocal;
-                    const Ens X = loc ? S_ : E;
+                    const Ens *sets = ghost ? d.gens : d.ens;
+                    const Ens E = sets[set], A = sets[set ^ 1u], X = loc ? A : E;
                     const int64_t pi = (loc ? a0 : i0) + (int64_t)l;
                     Node root;
                     root.x[0] = X.x0[pi];
@@ -333,12 +358,12 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                     root.D[2] = TAN ? X.D[2 * dstride + pi] : 0.0;
                     int m;
                     if (loc) {
-                        s_cls[tid] = (uint8_t)(smask[pi] & (kClasses - 1));
+                        s_cls[tid] = (uint8_t)((ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1));
                         m = -1;              // steps since the one it was born in
                         for (int q = 1; q <= s; ++q) m += l < s_born[q] ? 1 : 0;
                     } else {
                         s_cls[tid] = 0;
-                        m = pend + s - birth_of(s_nst, pend, (uint32_t)(tl * R) + l);
+                        m = pend + s - birth_of(s_nst, pend, (uint32_t)i00 + l);
                     }
                     root.x[0] = advanced(root.x[0], (d.vfac * root.k[0]) * d.dt, m);
                     if (DIM == 2) root.x[1] = advanced(root.x[1], (d.vfac * root.k[1]) * d.dt, m);
@@ -353,6 +378,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                     bool act = false;
                     if (live) {
                         cur = load_root();
+                        const Dev &d = fresh(self);
+                        const InstParam &P = inst_param(d, b);
                         const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
                         cur.te = cur.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
                         cur.ua0 = unit53(r.c, r.d);
@@ -360,6 +387,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                         act = cur.te <= d.dt;
                     }
                     for (int round = 0;; ++round) {
+                        const Dev &d = fresh(self);
+                        const InstParam &P = inst_param(d, b);
                         if (act) take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, F);
                         if (DIM == 2) __syncthreads(); else lds_barrier();   // 4D records may be in HBM
                         const uint32_t nq = F.nq[round & 1];
@@ -388,8 +417,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                     F.cnt[tid] = 0u;
                     if (live) {
                         const Node root = load_root();
-                        F.cnt[tid] = walk_family<DIM, SP2, TAN>(d.self, b, step, &root, false, S_, a0, 0, alen, dstride,
-                                                                &tal, &err);
+                        F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, alen, 0, &tal,
+                                                                &err);
                     }
                     __syncthreads();
                 }
@@ -401,6 +430,11 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                 // 3. records into the tile's area, each at its rank in its
                 //    family, with its class and its own jumps in the chunk's
                 //    later steps
+                const Dev &d = fresh(self);
+                const InstParam &P = inst_param(d, b);
+                const Ens &A = (ghost ? d.gens : d.ens)[set ^ 1u];
+                uint16_t *smask = ghost ? d.smaskg : d.smask;
+                const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
                 auto close_record = [&](int64_t li, uint64_t id, int slot) {
                     const uint32_t cls = (uint32_t)s_cls[slot] | (1u << s);
                     uint32_t ev = 0;
@@ -428,18 +462,18 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                         const int64_t o = a0 + li;
                         Node nd;
                         load_record<DIM, SP2, TAN>(d, F, r, nd);
-                        S_.x0[o] = nd.x[0];
-                        S_.k0[o] = nd.k[0];
+                        A.x0[o] = nd.x[0];
+                        A.k0[o] = nd.k[0];
                         if (DIM == 2) {
-                            S_.x1[o] = nd.x[1];
-                            S_.k1[o] = nd.k[1];
+                            A.x1[o] = nd.x[1];
+                            A.k1[o] = nd.k[1];
                         }
-                        if (SP2) S_.w[o] = nd.w; else S_.sg[o] = (int8_t)nd.sg;
-                        S_.id[o] = nd.id;
+                        if (SP2) A.w[o] = nd.w; else A.sg[o] = (int8_t)nd.sg;
+                        A.id[o] = nd.id;
                         if (TAN) {
-                            S_.D[o] = nd.D[0];
-                            S_.D[dstride + o] = nd.D[1];
-                            S_.D[2 * dstride + o] = nd.D[2];
+                            A.D[o] = nd.D[0];
+                            A.D[dstride + o] = nd.D[1];
+                            A.D[2 * dstride + o] = nd.D[2];
                         }
                         close_record(li, nd.id, slot);
                     }
@@ -449,9 +483,9 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
                         const Node root = load_root();
                         Tally none{0, 0, 0, 0, 0};
                         const int64_t f = (int64_t)nl + (int64_t)excl;
-                        const uint32_t c = walk_family<DIM, SP2, TAN>(d.self, b, step, &root, true, S_, a0, f, alen, dstride,
+                        const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, alen, dstride,
                                                                       &none, &err);
-                        for (uint32_t r = 0; r < c && f + r < (int64_t)alen; ++r) close_record(f + r, S_.id[a0 + f + r], tid);
+                        for (uint32_t r = 0; r < c && f + r < (int64_t)alen; ++r) close_record(f + r, A.id[a0 + f + r], tid);
                     }
                     atomicAdd((unsigned long long *)&s_tal[0], (unsigned long long)tal.events);
                     atomicAdd((unsigned long long *)&s_tal[1], (unsigned long long)tal.pairs);
@@ -472,16 +506,20 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
         }
         lds_barrier();
         // the tile's counts per class, also summed over groups of tiles
+        const Dev &d = fresh(self);
         if (tid < kClasses) {
+            uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
+            uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
             const uint32_t c = s_ccnt[tid];
             wcnt[t * kClasses + tid] = c;
             if (c) atomicAdd(&wsup[(t / kSupGroup) * kClasses + tid], c);
             if (c && B > kFewInst) atomicAdd(&d.wtot[((int64_t)ghost * B + b) * kClasses + tid], c);
         }
         if (adv) {
+            const Ens &E = (ghost ? d.gens : d.ens)[set];
             for (int li = tid; li < nr; li += kThreads) {
                 const int64_t i = i0 + li;
-                const int m = pend + S - birth_of(s_nst, pend, (uint32_t)(tl * R + li));
+                const int m = pend + S - birth_of(s_nst, pend, (uint32_t)(i00 + li));
                 const double c0 = (d.vfac * E.k0[i]) * d.dt;
                 __builtin_nontemporal_store(advanced(E.x0[i], c0, m), &E.x0[i]);
                 if (DIM == 2) {
@@ -493,11 +531,11 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(De
         lds_barrier();
     }
     if (tid == 0) {
-        int64_t *T = d.fpart + (int64_t)blockIdx.x * 8;
+        int64_t *T = fresh(self).fpart + (int64_t)blockIdx.x * 8;
         T[0] = cb;
         for (int q = 0; q < 5; ++q) T[1 + q] = s_tal[q];
     }
-    if (err) atomicOr(&ctl->err, err);
+    if (err) atomicOr(&fresh(self).ctl->err, err);
 }
 
 // Per class c (threads tid mod kClasses = c; all threads of the block call):
@@ -582,7 +620,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         const InstParam &P = d.ip[b];
         const int64_t base = ghost ? P.gbase : P.base;
         const int64_t cap = ghost ? P.gcap : P.cap;
-        const int64_t T = plan[b + 1] - plan[b], a0 = base + (t - plan[b]) * (cap / T);
+        const int64_t a0 = base + (t - plan[b]) * d.wrange[2 * ((int64_t)(2 * par + ghost) * B + b) + 1];
         if (tid < kClasses) {   // lower classes, earlier tiles, less the class's start in the tile
             uint32_t o = s_below[tid];
             for (int c = 0; c < tid; ++c) o += s_tot[c] - s_own[c];
@@ -737,7 +775,7 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
     }
     // the tile plans
     block_plan(d.tileA + (int64_t)ghost * (B + 1), Ncur, B, kTileA);
-    block_prefix(next, B, [&](int b) { return walk_tiles(d, ghost, b, Ncur[b]); });
+    plan_walk(d, par ^ 1u, ghost, Ncur);
     if (tid == 0 && advance) {
         ctl->step = step + (uint32_t)S;
         ctl->chunk += 1u;
