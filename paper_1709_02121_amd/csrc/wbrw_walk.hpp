@@ -477,7 +477,11 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                         }
                         close_record(li, nd.id, slot);
                     }
-                    atomicMax(&F.maxdepth, deep);
+                    // the wavefront's deepest level by ballots (an atomic
+                    // maximum of per-lane values takes the lanes one by one)
+                    uint32_t top = 0;
+                    while (__ballot(deep > top)) ++top;
+                    if (lane == 0) atomicMax(&F.maxdepth, top);
                 } else {
                     if (live) {
                         const Node root = load_root();
