@@ -679,10 +679,12 @@ __device__ __forceinline__ void add_jump(Families<DIM, SP2, TAN> &F, int round, 
 
 // One jump: particle cur (x, k at its birth time t0) jumps at te, its e-th
 // jump of the step, in family `slot`, with path `key` of `lev` levels.  rec:
-// its record, or kNone for a parent's first jump.
+// its record, or kNone for a parent's first jump.  The caller takes the pair
+// slots m0, m0 + mstep, ... (other wavefronts the others), and with m0 = 0
+// what the jump has once.
 template <int DIM, bool SP2, bool TAN, bool ONE>
 __device__ __forceinline__ void take_jump(const Dev &d, const InstParam &P, uint32_t step, int round, Node &cur,
-                                          uint64_t key, int lev, int slot, uint32_t rec,
+                                          uint64_t key, int lev, int slot, uint32_t rec, int m0, int mstep,
                                           Families<DIM, SP2, TAN> &F)
 {
     using FT = Families<DIM, SP2, TAN>;
@@ -696,10 +698,8 @@ __device__ __forceinline__ void take_jump(const Dev &d, const InstParam &P, uint
     const int sh = 56 - 8 * lev;
     cur.xe[0] = cur.x[0] + (d.vfac * cur.k[0]) * (te - cur.t0);
     cur.xe[1] = DIM == 2 ? cur.x[1] + (d.vfac * cur.k[1]) * (te - cur.t0) : 0.0;
-    atomicAdd(&F.events, 1u);
-    const W4 rn = draw(cur.id, step, kTagStep, cur.e + 1u, 0u, seed, pk);
     const int mend = slot_end<TAN>(d, cur, M);
-    for (int m = 0; m < mend; ++m) {
+    for (int m = m0; m < mend; m += mstep) {
         PairDraw J;
         W4 rc;
         if (!slot_draw<DIM, SP2, TAN, ONE>(d, P, cur, step, m, M, J, rc)) continue;
@@ -733,6 +733,9 @@ __device__ __forceinline__ void take_jump(const Dev &d, const InstParam &P, uint
             pend &= s0 ? 2u : 0u;
         }
     }
+    if (m0 != 0) return;
+    atomicAdd(&F.events, 1u);
+    const W4 rn = draw(cur.id, step, kTagStep, cur.e + 1u, 0u, seed, pk);
     const double un = unit53(rn.a, rn.b);
     if (!surely_no_jump(un, te, d.dt, g0)) {
         const double tn = te + (-ln_series(1.0 - un) / g0);

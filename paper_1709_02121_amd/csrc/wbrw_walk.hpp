@@ -334,11 +334,11 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                 F.head[tid] = kNone;
                 __syncthreads();
                 const bool live = tid < FS && q0 + (uint32_t)tid < np;
-                // the thread's event parent at the start of the step
-                auto load_root = [&]() {
+                // event parent ti at the start of the step
+                auto load_root = [&](int ti) {
                     const Dev &d = fresh(self);
                     const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-                    const uint32_t it = s_item[tid];
+                    const uint32_t it = s_item[ti];
                     const bool loc = (it & kLocal) != 0u;
                     const uint32_t l = it & ~kLocal;
                     const Ens *sets = ghost ? d.gens : d.ens;
@@ -358,26 +358,33 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     root.D[2] = TAN ? X.D[2 * dstride + pi] : 0.0;
                     int m;
                     if (loc) {
-                        s_cls[tid] = (uint8_t)((ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1));
+                        s_cls[ti] = (uint8_t)((ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1));
                         m = -1;              // steps since the one it was born in
                         for (int q = 1; q <= s; ++q) m += l < s_born[q] ? 1 : 0;
                     } else {
-                        s_cls[tid] = 0;
+                        s_cls[ti] = 0;
                         m = pend + s - birth_of(s_nst, pend, (uint32_t)i00 + l);
                     }
                     root.x[0] = advanced(root.x[0], (d.vfac * root.k[0]) * d.dt, m);
                     if (DIM == 2) root.x[1] = advanced(root.x[1], (d.vfac * root.k[1]) * d.dt, m);
                     return root;
                 };
-                // 1. the parents' first jumps, then round by round those found
+                // 1. the parents' first jumps, then round by round those
+                //    found.  Each wavefront takes 64 jumps; where there are
+                //    few, two or four share the same ones, each with its
+                //    share of their pair slots.
                 {
+                    const int slots = ONE && !TAN ? 1 : (TAN && fresh(self).tangent == 2 ? 2 : 1) * (ONE ? 1 : fresh(self).M);
+                    uint32_t nt = min((uint32_t)FS, np - q0);      // jumps of the round
+                    int share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
+                    int ti = wv / share * 64 + lane, m0 = wv % share;
                     Node cur;
                     uint64_t key = 0ull;
                     uint32_t rec = kNone;
-                    int slot = tid, lev = 0;
+                    int slot = ti, lev = 0;
                     bool act = false;
-                    if (live) {
-                        cur = load_root();
+                    if (ti < (int)nt && m0 < slots) {
+                        cur = load_root(ti);
                         const Dev &d = fresh(self);
                         const InstParam &P = inst_param(d, b);
                         const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
@@ -389,20 +396,24 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     for (int round = 0;; ++round) {
                         const Dev &d = fresh(self);
                         const InstParam &P = inst_param(d, b);
-                        if (act) take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, F);
+                        if (act)
+                            take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, m0, share, F);
                         if (DIM == 2) __syncthreads(); else lds_barrier();   // 4D records may be in HBM
-                        const uint32_t nq = F.nq[round & 1];
-                        if (nq == 0u || F.overflow) break;
-                        act = tid < (int)nq;
+                        nt = F.nq[round & 1];
+                        if (nt == 0u || F.overflow) break;
+                        share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
+                        ti = wv / share * 64 + lane;
+                        m0 = wv % share;
+                        act = ti < (int)nt && m0 < slots;
                         if (act) {
-                            rec = F.qrec[tid];
+                            rec = F.qrec[ti];
                             load_record<DIM, SP2, TAN>(d, F, rec, cur);
-                            cur.x[0] = F.qx0[tid];
-                            cur.x[1] = DIM == 2 ? F.qx1[tid] : 0.0;
-                            cur.t0 = F.qt0[tid];
-                            cur.te = F.qte[tid];
-                            cur.ua0 = F.qua[tid];
-                            cur.e = F.qe[tid];
+                            cur.x[0] = F.qx0[ti];
+                            cur.x[1] = DIM == 2 ? F.qx1[ti] : 0.0;
+                            cur.t0 = F.qt0[ti];
+                            cur.te = F.qte[ti];
+                            cur.ua0 = F.qua[ti];
+                            cur.e = F.qe[ti];
                             key = F.key[rec];
                             slot = F.slot[rec];
                             lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
@@ -416,7 +427,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                 if (overflow) {   // (uniform) every family by the general walk
                     F.cnt[tid] = 0u;
                     if (live) {
-                        const Node root = load_root();
+                        const Node root = load_root(tid);
                         F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, alen, 0, &tal,
                                                                 &err);
                     }
@@ -484,7 +495,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     if (lane == 0) atomicMax(&F.maxdepth, top);
                 } else {
                     if (live) {
-                        const Node root = load_root();
+                        const Node root = load_root(tid);
                         Tally none{0, 0, 0, 0, 0};
                         const int64_t f = (int64_t)nl + (int64_t)excl;
                         const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, alen, dstride,
