@@ -35,7 +35,7 @@ struct Layout {
     size_t ens[2][8] = {}, gens[2][8] = {};
     size_t ip = 0, dev = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
     size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, Nsrt = 0, srtS = 0, tileW = 0, wrange = 0,
-           tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, wcnt = 0,
+           tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, ptab = 0, ptabg = 0, wpool = 0, wcnt = 0,
            wcntg = 0, wsup = 0, wsupg = 0, wtot = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
            occ = 0, Tq = 0, ntil = 0, dacc = 0, dTq = 0, bA = 0, bcopies = 0, bcls = 0,
            bcell = 0, bP = 0, bTile = 0, bG = 0, bcls_stat = 0, tileD = 0, bscan_tiles = 0, hist = 0, xitab = 0,
@@ -62,18 +62,21 @@ int32_t guide_buckets(int32_t n)
     return k;
 }
 
-// guide[i] = the last j < n with cum[j] <= t_i, t_i = (i / kg) cum[n] rounded
-// as the sampler rounds u1 cum[n] (kg a power of two, so i / kg is exact and
-// u1 >= i / kg gives u1 cum[n] >= t_i); cum is non-decreasing
-void build_guide(const std::vector<double> &cum, int32_t n, int32_t kg, std::vector<int32_t> &guide)
+// Bucket i's first bin is the last j < n with cum[j] <= t_i, t_i = (i / kg)
+// cum[n] rounded as the sampler rounds u1 cum[n] (kg a power of two, so i / kg
+// is exact and u1 >= i / kg gives u1 cum[n] >= t_i), its last bin the first of
+// bucket i + 1; cum is non-decreasing
+void build_guide(const std::vector<double> &cum, int32_t n, int32_t kg, std::vector<GuideEntry> &guide)
 {
-    guide.assign((size_t)kg + 1, 0);
+    guide.assign((size_t)kg, GuideEntry{0, 0, 0.0});
     int32_t j = 0;
     for (int32_t i = 0; i <= kg; ++i) {
         const double t = ((double)i / (double)kg) * cum[n];
         while (j + 1 < n && cum[j + 1] <= t) ++j;
-        guide[i] = j;
+        if (i < kg) guide[i].lo = j;
+        if (i > 0) guide[i - 1].hi = j;
     }
+    for (GuideEntry &g : guide) g.next = cum[g.lo + 1];
 }
 
 int validate(const wbrw_config *c)
@@ -227,16 +230,18 @@ Layout make_layout(const wbrw_config *c)
     }
     L.smask = take(cur, C * 2);
     L.wcnt = take(cur, (size_t)L.tilesW * kClasses * 4);
+    L.ptab = take(cur, (size_t)L.tilesW * kPages * 4);
     if (tan) {
         L.smaskg = take(cur, G * 2);
         L.wcntg = take(cur, (size_t)L.tilesWg * kClasses * 4);
+        L.ptabg = take(cur, (size_t)L.tilesWg * kPages * 4);
     }
     L.ip = take(cur, BB * sizeof(InstParam));
     L.dev = take(cur, sizeof(Dev));
     for (int m = 0; m < c->n_components; ++m)
         if (c->comp[m].kind == WBRW_KERNEL_TABLE) {
             L.tab[m] = take(cur, ((size_t)c->comp[m].table_n + 1) * 8);
-            L.guide[m] = take(cur, ((size_t)guide_buckets(c->comp[m].table_n) + 1) * 4);
+            L.guide[m] = take(cur, (size_t)guide_buckets(c->comp[m].table_n) * sizeof(GuideEntry));
         }
     L.off = take(cur, BB * Nh * 8);
     if (c->init_hist) L.hist = take(cur, BB * Nh * 8);
@@ -263,6 +268,7 @@ Layout make_layout(const wbrw_config *c)
     L.Nbase = take(cur, 2 * BB * 8);
     L.nstep = take(cur, 2 * BB * (kPend + 1) * 8);
     L.wtot = take(cur, 2 * BB * kClasses * 4);
+    L.wpool = take(cur, 2 * BB * 8);
     L.tileA = take(cur, 2 * (BB + 1) * 8);
     L.Nsrt = take(cur, BB * 8);
     L.srtS = take(cur, (BB + 1) * 8);
@@ -448,29 +454,35 @@ int parents_at_a_time(const wbrw_handle *h, bool ghost, int pool, int queue)
     return std::max(kParents, (int)n / kParents * kParents);
 }
 
-// Most particles in a tile of k_walk, for an instance whose particles jump in
-// a step with probability p: so many that three quarters of the event parents
-// taken at a time are found in a step (the offspring's add to them).
-int range_limit(double p, int parents)
+// Growth of the particle number per step: a jump leaves rb records, see above.
+double growth(const wbrw_handle *h, const InstParam &P)
 {
-    const double r = std::min(p > 0.0 ? 0.75 * parents / p : (double)kRangeMax, (double)kRangeMax);
-    return (int)std::max<int64_t>(kRangeMin, (int64_t)r / kRangeMin * kRangeMin);
+    double rb = 0.0;
+    for (int m = 0; m < h->M; ++m) {
+        const double sp1 = 4.0 / 3.14159265358979 * P.c[m];
+        rb += (h->strategy == WBRW_SP2 ? 2.0 : sp1) + (h->tangent == 2 ? sp1 : 0.0);
+    }
+    return rb * P.gamma0 * h->d.dt;
 }
 
 // Steps per launch of k_walk: as many as the ensemble takes to grow by about
-// e^1.2, at most kChunk (a jump leaves rb records, see above).
+// e^1.7, at most kChunk (4D, growing by e^0.32 a step, 1e7 particles to their
+// first annihilation: 22.7 ms at one step per launch, 21.2 at two, 20.5 at five).
 int chunk_steps(const wbrw_handle *h)
 {
     double grow = 0.0;
-    for (const InstParam &P : h->ip) {
-        double rb = 0.0;
-        for (int m = 0; m < h->M; ++m) {
-            const double sp1 = 4.0 / 3.14159265358979 * P.c[m];
-            rb += (h->strategy == WBRW_SP2 ? 2.0 : sp1) + (h->tangent == 2 ? sp1 : 0.0);
-        }
-        grow = std::max(grow, rb * P.gamma0 * h->d.dt);
-    }
-    return grow > 0.0 ? std::max(1, std::min(kChunk, (int)(1.2 / grow))) : kChunk;
+    for (const InstParam &P : h->ip) grow = std::max(grow, growth(h, P));
+    return grow > 0.0 ? std::max(1, std::min(kChunk, (int)(1.7 / grow))) : kChunk;
+}
+
+// Most particles in a tile of k_walk: so many that a chunk's first step finds
+// about the event parents taken at a time (1e7 barrier: 4.61 ms at 0.8 of
+// that, 4.33 at 0.85 to 1; 256 instances 14.4 and 13.9).
+int range_limit(const wbrw_handle *h, const InstParam &P, int parents)
+{
+    const double p = -std::expm1(-P.gamma0 * h->d.dt);
+    const double r = std::min(p > 0.0 ? (double)parents / p : (double)kRangeMax, (double)kRangeMax);
+    return (int)std::max<int64_t>(kRangeMin, (int64_t)r / kRangeMin * kRangeMin);
 }
 
 template <int DIM>
@@ -583,7 +595,7 @@ int upload_counts(wbrw_t h, const std::vector<int64_t> &N, const std::vector<int
             const int64_t r = g ? walk_range(n[b], P.gwt, P.gwr) : walk_range(n[b], P.wt, P.wr), t = ceil_div(n[b], r);
             walk[b + 1] = walk[b] + t;
             range[2 * b] = r;
-            range[2 * b + 1] = (g ? P.gcap : P.cap) / std::max<int64_t>(t, 1);
+            range[2 * b + 1] = page_bits(r, t);
             ns[(size_t)b * (kPend + 1)] = n[b];
         }
         v.push_back(plan);
@@ -934,7 +946,8 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
         // xi_m = (2/(pi hbar)) sum_j |F[V](2 q_j)| dq
         xi_tab[m] = ((2.0 * cm[q.table_n]) * dq) / (0x1.921fb54442d18p+1 * cfg->hbar);
         d.tab[m].cum = at<double>(w, L.tab[m]);
-        d.tab[m].guide = at<int32_t>(w, L.guide[m]);
+        d.tab[m].guide = at<GuideEntry>(w, L.guide[m]);
+        d.tab[m].total = cm[q.table_n];
         d.tab[m].kg = guide_buckets(q.table_n);
         d.tab[m].n = q.table_n;
         d.tab[m].q_lo = q.q_lo;
@@ -964,9 +977,8 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
         int64_t total = 0;
         for (int b = 0; b < h->B; ++b) total += cfg->N0[b];
         for (InstParam &P : h->ip) {
-            const double p = -std::expm1(-P.gamma0 * cfg->dt);
-            P.wr = range_limit(p, d.ftile);
-            P.gwr = range_limit(p, d.gftile);
+            P.wr = range_limit(h, P, d.ftile);
+            P.gwr = range_limit(h, P, d.gftile);
             // small ensembles still spread over the chip: four tiles per
             // compute unit over all instances
             const double want = 4.0 * h->cus;
@@ -1013,6 +1025,9 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.Nbase = at<int64_t>(w, L.Nbase);
     d.nstep = at<int64_t>(w, L.nstep);
     d.wtot = at<uint32_t>(w, L.wtot);
+    d.wpool = at<uint64_t>(w, L.wpool);
+    d.ptab = at<uint32_t>(w, L.ptab);
+    d.ptabg = h->tangent ? at<uint32_t>(w, L.ptabg) : nullptr;
     d.tileA = at<int64_t>(w, L.tileA);
     d.Nsrt = at<int64_t>(w, L.Nsrt);
     d.srtS = at<int64_t>(w, L.srtS);
@@ -1081,12 +1096,12 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     if (L.xitab &&
         hipMemcpyAsync((void *)d.xi_tab, xitabs.data(), 8 * xitabs.size(), hipMemcpyHostToDevice, s) != hipSuccess)
         return fail(WBRW_EHIP);
-    std::vector<std::vector<int32_t>> guides(kMaxM);
+    std::vector<std::vector<GuideEntry>> guides(kMaxM);
     for (int m = 0; m < h->M; ++m) {
         if (cfg->comp[m].kind != WBRW_KERNEL_TABLE) continue;
         build_guide(cums[m], cfg->comp[m].table_n, d.tab[m].kg, guides[m]);
         if (hipMemcpyAsync((void *)d.tab[m].cum, cums[m].data(), 8 * cums[m].size(), hipMemcpyHostToDevice, s) != hipSuccess ||
-            hipMemcpyAsync((void *)d.tab[m].guide, guides[m].data(), 4 * guides[m].size(), hipMemcpyHostToDevice, s) != hipSuccess)
+            hipMemcpyAsync((void *)d.tab[m].guide, guides[m].data(), sizeof(GuideEntry) * guides[m].size(), hipMemcpyHostToDevice, s) != hipSuccess)
             return fail(WBRW_EHIP);
     }
     if (cfg->init_hist) {

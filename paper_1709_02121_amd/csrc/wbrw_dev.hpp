@@ -32,6 +32,8 @@ constexpr int kPend = 32;               // steps between materialisations of the
 constexpr int kRangeMin = 64;           // particles in a tile of k_walk, at least; a multiple of 64
 constexpr int kRangeMax = 8192;         // particles in a tile of k_walk, at most
 constexpr int kLocalBits = 4096;        // offspring of a tile whose event bits are kept in LDS
+constexpr int kPages = 32;              // pages of a tile's offspring in the inactive set, at most
+constexpr int kEvenPages = 24;          // of them of one size; each further one twice the one before
 constexpr int kFewInst = 8;             // instances whose class totals are summed from the tiles'
 constexpr int kMaxGrid = 8192;          // blocks of a persistent launch (per-block partials)
 // 4D family kernels: the payloads of a tile's records beyond the block's LDS
@@ -77,13 +79,22 @@ struct InstParam {
     uint32_t pad;
 };
 
+// A bucket of a table's guide: the bins [lo, hi] that its draws can fall in
+// and the cumulative sum at the start of bin lo + 1, which decides between
+// two of them.
+struct GuideEntry {
+    int32_t lo, hi;
+    double next;
+};
+
 struct Table {
-    const double *cum;    // n + 1 cumulative sums of |F[V](2q_j)|
-    const int32_t *guide; // kg + 1 entries: guide[i] = the last bin j < n with
-                          // cum[j] <= (i / kg) cum[n] (as the sampler rounds it)
+    const double *cum;        // n + 1 cumulative sums of |F[V](2q_j)|
+    const GuideEntry *guide;  // kg buckets: lo of bucket i is the last bin j < n with
+                              // cum[j] <= (i / kg) cum[n] (as the sampler rounds it)
     int32_t n;
-    int32_t kg;           // guide buckets, a power of two >= n
+    int32_t kg;               // guide buckets, a power of two >= n
     double q_lo, dq;
+    double total;             // cum[n]
 };
 
 struct Ens {
@@ -142,8 +153,10 @@ struct Dev {
                                 // positions were materialised (real, ghost); entry 0 always holds
     int64_t *tileA;             // [2][B+1] streaming-tile plan (real, ghost)
     int64_t *tileW;             // [2][2][B+1] walk-tile plan (parity; real, ghost)
-    int64_t *wrange;            // [2][2][B][2] its particles per tile, and the slots of a tile's
-                                // area in the inactive set
+    int64_t *wrange;            // [2][2][B][2] its particles per tile, and the binary logarithm
+                                // of the slots of a page (see page_slot)
+    uint64_t *wpool;            // [2][B] slots handed out as further pages (zero between chunks)
+    uint32_t *ptab, *ptabg;     // per walk tile: the first slots of its kPages pages
     int64_t *tileR;             // [B+1] regeneration-tile plan
     int64_t *tileG;             // [B+1] ghost-regeneration plan
     int64_t *tally;             // [B][kTalCount]
@@ -153,7 +166,7 @@ struct Dev {
     int64_t *rstart;            // first cell of every regeneration tile (written by k_scan)
     uint64_t *stS;              // scan-tile sums of |n_nu|, then their exclusive prefix
     uint64_t *stG;              // look-back status words of k_ghosts
-    uint16_t *smask, *smaskg;           // per slot of the tiles' areas: the offspring's class, and
+    uint16_t *smask, *smaskg;           // per slot of the tiles' pages: the offspring's class, and
                                         // from bit kChunk on the chunk's steps in which it jumps
     uint32_t *wcnt, *wcntg;             // per walk tile: records of each class
     uint32_t *wsup, *wsupg;             // [2] (parity) per kSupGroup walk tiles: their sums
@@ -191,6 +204,39 @@ struct Dev {
     int64_t *bscan_tiles;       // [B+1] tiles per instance for the residual scan
     int64_t tstride;            // tiles per class in bTile
 };
+
+// Pages.  A tile's offspring wait in the inactive buffer set for their places
+// in pages of 2^sh slots, the largest power of two up to half a tile's range:
+// tile tl of the instance has the page at tl 2^sh, and takes further ones
+// from the slots behind all first pages as it grows.  T first pages take at
+// most (N + R) / 2 slots and a tile that takes further ones no more in them
+// than it has offspring, so whatever the tiles' shares, they fit where the
+// offspring will fit behind the N > R particles.  (From the 25th page on
+// pages double, and up to half of such a tile's slots may stay empty; it
+// has offspring for 6 to 12 times its range by then.)  A single tile has all
+// slots.
+__host__ __device__ __forceinline__ int32_t page_bits(int64_t range, int64_t tiles)
+{
+    if (tiles <= 1) return 31;
+    int32_t sh = 5;
+    while ((int64_t)(4 << sh) <= range) ++sh;
+    return sh;
+}
+// slots in the first np pages
+__device__ __forceinline__ int64_t page_extent(int np, int sh)
+{
+    if (np <= kEvenPages) return (int64_t)np << sh;
+    return ((int64_t)kEvenPages << sh) + (((int64_t)2 << (np - kEvenPages)) - 2 << sh);
+}
+// slot (from the instance's first) of offspring l
+__device__ __forceinline__ uint32_t page_slot(const uint32_t *pages, int sh, uint32_t l)
+{
+    const uint32_t p = l >> sh;
+    if (p < (uint32_t)kEvenPages) return pages[p] + (l - (p << sh));
+    const uint32_t k = p - (uint32_t)kEvenPages + 2u;           // in units of a page, from 2 on
+    const int j = 31 - __builtin_clz(k);                        // page 24 + j - 1 starts at unit 2^j
+    return pages[kEvenPages + j - 1] + (l - (((uint32_t)kEvenPages - 2u + (1u << j)) << sh));
+}
 
 // Particles in a tile of k_walk for an ensemble of n: an equal share of a
 // whole multiple of `tiles` tiles (so that the blocks that run at once all
@@ -488,7 +534,7 @@ __device__ __forceinline__ void plan_walk(const Dev &d, uint32_t par, int ghost,
         const int64_t r = ghost ? walk_range(n[b], P.gwt, P.gwr) : walk_range(n[b], P.wt, P.wr);
         const int64_t t = (n[b] + r - 1) / r;
         d.wrange[2 * (at * d.B + b)] = r;
-        d.wrange[2 * (at * d.B + b) + 1] = (ghost ? P.gcap : P.cap) / (t > 0 ? t : 1);
+        d.wrange[2 * (at * d.B + b) + 1] = page_bits(r, t);
         return t;
     });
 }

@@ -29,9 +29,9 @@ __device__ __forceinline__ double phase_offset(const Dev &d, int m, const double
 // bin is the last j < n with cum[j] <= u1 cum[n].  A guide table (Chen and
 // Asau's method) gives the answer's range: for u1 in bucket i = floor(u1 kg)
 // the target u1 cum[n] lies between the rounded bucket ends, so the bin lies
-// in [guide[i], guide[i + 1]], nearly always one or two bins wide, where a
-// binary search over the whole table took 12 dependent loads.  The bin found
-// is the same.
+// in the bucket's [lo, hi], nearly always one or two bins wide, which one
+// 16-byte entry settles; wider ones are searched.  The bin found is that of
+// a search over the whole table (12 dependent loads).
 template <bool ONE>
 __device__ __forceinline__ double kick_sample(const Dev &d, const InstParam &P, int m, double u1,
                                               double u2)
@@ -41,13 +41,17 @@ __device__ __forceinline__ double kick_sample(const Dev &d, const InstParam &P, 
         const double z = R * cos_det(kTwoPi * u2);
         return z * P.sq[m];
     }
-    const Table T = d.tab[m];
-    const double target = u1 * T.cum[T.n];
-    const int i = (int)(u1 * (double)T.kg);
-    int lo = T.guide[i], hi = T.guide[i + 1];
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (T.cum[mid] <= target) lo = mid; else hi = mid - 1;
+    const Table &T = d.tab[m];
+    const double target = u1 * T.total;
+    const GuideEntry g = T.guide[(int)(u1 * (double)T.kg)];
+    int lo = g.lo, hi = g.hi;
+    if (hi == lo + 1) {
+        lo = g.next <= target ? hi : lo;
+    } else {
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (T.cum[mid] <= target) lo = mid; else hi = mid - 1;
+        }
     }
     return T.q_lo + ((double)lo + u2) * T.dq;
 }
@@ -364,12 +368,13 @@ __device__ __forceinline__ void slot_child(const Dev &d, const InstParam &P, con
 // General depth-first walk of one family (any number of jumps and levels),
 // by one lane: the path of the tiles whose families the pool below cannot
 // hold.  Counting (emit false) tallies and counts the records; emitting
-// writes every record from first_rec on.  Its stack makes it large, so it is
+// writes every record, the r-th as offspring first_rec + r (< cap) of the
+// tile's pages.  Its stack makes it large, so it is
 // a function of its own: the common path keeps its registers.
 template <int DIM, bool SP2, bool TAN>
 __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step, const Node *root, bool emit,
-                                             Ens out, int64_t base, int64_t first_rec, int64_t cap, int64_t dstride,
-                                             Tally *tl, uint32_t *err)
+                                             Ens out, int64_t base, int64_t first_rec, int64_t cap,
+                                             const uint32_t *pages, int sh, int64_t dstride, Tally *tl, uint32_t *err)
 {
     const Dev &d = *dp;
     const InstParam &P = d.ip[b];
@@ -446,7 +451,7 @@ __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step
             if (emit) {
                 const int64_t li = first_rec + nrec;
                 if (li < cap) {
-                    const int64_t o = base + li;
+                    const int64_t o = base + page_slot(pages, sh, (uint32_t)li);
                     out.x0[o] = cur.xe[0] + (d.vfac * ch.k[0]) * (d.dt - cur.te);
                     out.k0[o] = ch.k[0];
                     if (DIM == 2) {

@@ -10,7 +10,7 @@
 //           3.2.1), keeping one bit each in LDS.  Then, step by step, it
 //           gathers the jumping particles of the range and of its offspring,
 //           in order, and takes their jumps (wbrw_step.hpp).  Offspring go to
-//           the tile's area of the inactive buffer set, in order.
+//           pages of the inactive buffer set, in order.
 // k_place   puts the offspring of all tiles behind the particles, in the
 //           order of the whole ensemble's steps, and closes the chunk.
 //
@@ -196,6 +196,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
     __shared__ uint32_t s_ccnt[kClasses];     // records of each class
     __shared__ uint32_t s_born[kChunk + 1];   // offspring at the start of each step
     __shared__ uint32_t s_nst[kPend + 1];
+    __shared__ uint32_t s_page[kPages];
+    __shared__ int64_t s_limit;               // offspring the pages hold
     constexpr uint32_t kLocal = 0x80000000u;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -236,22 +238,23 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
         const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
         if (t >= ntiles) break;
         // tile t is tile tl of instance b: its range of nr particles from i0
-        // on, and its area of alen slots of the inactive set from a0 on
-        int b, nr, i00;
-        int64_t i0, a0;
-        uint32_t alen;
+        // on; its offspring go to pages of 2^sh slots behind a0
+        int b, nr, i00, sh, npage = 1;
+        int64_t i0, a0, limit;
         {
             const Dev &d = fresh(self);
             const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
             b = B == 1 ? 0 : __builtin_amdgcn_readfirstlane(segment_of(plan, B, t));
             const InstParam &P = inst_param(d, b);
             const int64_t base = ghost ? P.gbase : P.base, n = (ghost ? d.NG : d.N)[b], tl = t - plan[b];
-            const int64_t R = d.wrange[2 * (at * B + b)], area = d.wrange[2 * (at * B + b) + 1];
+            const int64_t R = d.wrange[2 * (at * B + b)];
+            sh = (int)d.wrange[2 * (at * B + b) + 1];
             i00 = (int)(tl * R);
             i0 = base + tl * R;
             nr = (int)min(R, n - tl * R);
-            a0 = base + tl * area;
-            alen = (uint32_t)min(area, (int64_t)0x7FFFFFFF);
+            a0 = base;
+            limit = min((int64_t)1 << sh, ghost ? P.gcap : P.cap);
+            if (tid == 0) s_page[0] = (uint32_t)(tl << (sh & 31));
         }
         if (b != cb) {
             const Dev &d = fresh(self);
@@ -312,7 +315,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     else if (wi < nw && wl < kWL) m = s_evl[s][wl];
                     else if (wi < nw)        // past the bits kept in LDS
                         for (uint32_t q = 0; q < 64u && (uint32_t)wl * 64u + q < nl0; ++q)
-                            m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)[a0 + wl * 64 + q] >> (kChunk + s)) & 1u) << q;
+                            m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)[a0 + page_slot(s_page, sh, wl * 64 + q)] >>
+                                             (kChunk + s)) & 1u) << q;
                     uint32_t tot;
                     uint32_t pos = run + block_excl((uint32_t)__popcll(m), s_wsum[it & 1], tot);
                     while (m) {
@@ -343,7 +347,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     const uint32_t l = it & ~kLocal;
                     const Ens *sets = ghost ? d.gens : d.ens;
                     const Ens E = sets[set], A = sets[set ^ 1u], X = loc ? A : E;
-                    const int64_t pi = (loc ? a0 : i0) + (int64_t)l;
+                    const int64_t pi = loc ? a0 + page_slot(s_page, sh, l) : i0 + (int64_t)l;
                     Node root;
                     root.x[0] = X.x0[pi];
                     root.x[1] = DIM == 2 ? X.x1[pi] : 0.0;
@@ -428,8 +432,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     F.cnt[tid] = 0u;
                     if (live) {
                         const Node root = load_root(tid);
-                        F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, alen, 0, &tal,
-                                                                &err);
+                        F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, 0, s_page, sh, 0,
+                                                                &tal, &err);
                     }
                     __syncthreads();
                 }
@@ -437,6 +441,29 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                 uint32_t agg;
                 const uint32_t excl = block_excl(F.cnt[tid], s_wsum[0], agg);
                 F.first[tid] = excl;
+                if ((int64_t)nl + agg > limit && npage < kPages && sh < 31) {   // (uniform) further pages
+                    int np2 = npage;
+                    while (np2 < kPages && page_extent(np2, sh) < (int64_t)nl + agg) ++np2;
+                    if (tid == 0) {
+                        const Dev &d = fresh(self);
+                        const InstParam &P = inst_param(d, b);
+                        const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
+                        const int64_t take = page_extent(np2, sh) - page_extent(npage, sh);
+                        const int64_t from = ((plan[b + 1] - plan[b]) << sh) +
+                            (int64_t)atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * B + b], (unsigned long long)take);
+                        int64_t lim = limit;
+                        for (int q = npage; q < np2; ++q) {
+                            const int64_t at2 = from + page_extent(q, sh) - page_extent(npage, sh);
+                            s_page[q] = (uint32_t)at2;
+                            if (from + page_extent(q + 1, sh) - page_extent(npage, sh) <= (ghost ? P.gcap : P.cap))
+                                lim = page_extent(q + 1, sh);
+                        }
+                        s_limit = lim;
+                    }
+                    npage = np2;
+                    lds_barrier();
+                    limit = s_limit;
+                }
                 lds_barrier();
                 // 3. records into the tile's area, each at its rank in its
                 //    family, with its class and its own jumps in the chunk's
@@ -455,7 +482,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                             ev |= 1u << q;
                             if (li < kLocalBits) atomicOr(&s_evl[q][li >> 6], 1ull << (li & 63));
                         }
-                    smask[a0 + li] = (uint16_t)(cls | (ev << kChunk));
+                    smask[a0 + page_slot(s_page, sh, (uint32_t)li)] = (uint16_t)(cls | (ev << kChunk));
                     atomicAdd(&s_ccnt[cls], 1u);
                 };
                 if (!overflow) {
@@ -469,8 +496,8 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                         for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
                         deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
                         const int64_t li = (int64_t)nl + (int64_t)(F.first[slot] + rank);
-                        if (li >= (int64_t)alen) { err |= kErrCapacity; continue; }
-                        const int64_t o = a0 + li;
+                        if (li >= limit) { err |= kErrCapacity; continue; }
+                        const int64_t o = a0 + page_slot(s_page, sh, (uint32_t)li);
                         Node nd;
                         load_record<DIM, SP2, TAN>(d, F, r, nd);
                         A.x0[o] = nd.x[0];
@@ -498,9 +525,10 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                         const Node root = load_root(tid);
                         Tally none{0, 0, 0, 0, 0};
                         const int64_t f = (int64_t)nl + (int64_t)excl;
-                        const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, alen, dstride,
-                                                                      &none, &err);
-                        for (uint32_t r = 0; r < c && f + r < (int64_t)alen; ++r) close_record(f + r, A.id[a0 + f + r], tid);
+                        const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, limit, s_page, sh,
+                                                                      dstride, &none, &err);
+                        for (uint32_t r = 0; r < c && f + r < limit; ++r)
+                            close_record(f + r, A.id[a0 + page_slot(s_page, sh, (uint32_t)(f + r))], tid);
                     }
                     atomicAdd((unsigned long long *)&s_tal[0], (unsigned long long)tal.events);
                     atomicAdd((unsigned long long *)&s_tal[1], (unsigned long long)tal.pairs);
@@ -508,7 +536,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     atomicAdd((unsigned long long *)&s_tal[3], (unsigned long long)tal.cap);
                     atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tal.maxdepth);
                 }
-                nl = min(nl + agg, alen);
+                nl = (uint32_t)min((int64_t)nl + agg, limit);
                 lds_barrier();
                 if (tid == 0 && !overflow) {
                     s_tal[0] += F.events;
@@ -522,6 +550,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
         lds_barrier();
         // the tile's counts per class, also summed over groups of tiles
         const Dev &d = fresh(self);
+        if (tid < npage) (ghost ? d.ptabg : d.ptab)[t * kPages + tid] = s_page[tid];
         if (tid < kClasses) {
             uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
             uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
@@ -599,6 +628,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
     }
     __shared__ uint32_t s_red[2 * kThreads];
     __shared__ uint32_t s_below[kClasses], s_tot[kClasses], s_own[kClasses], s_off[kClasses];
+    __shared__ uint32_t s_page[kPages];
     Ctl *ctl = d.ctl;
     const int B = d.B;
     const uint32_t par = ctl->wpar;
@@ -608,6 +638,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
     const Ens E = pick_set(d, ghost, set);
     const Ens A = pick_set(d, ghost, set ^ 1u);
     const uint16_t *smask = ghost ? d.smaskg : d.smask;
+    const uint32_t *ptab = ghost ? d.ptabg : d.ptab;
     const uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
     const uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
     const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
@@ -631,11 +662,12 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         }
         __syncthreads();
         if (tid < kClasses) s_own[tid] = wcnt[t * kClasses + tid];
+        if (tid >= kThreads - kPages) s_page[tid - (kThreads - kPages)] = ptab[t * kPages + tid - (kThreads - kPages)];
         __syncthreads();
         const InstParam &P = d.ip[b];
         const int64_t base = ghost ? P.gbase : P.base;
         const int64_t cap = ghost ? P.gcap : P.cap;
-        const int64_t a0 = base + (t - plan[b]) * d.wrange[2 * ((int64_t)(2 * par + ghost) * B + b) + 1];
+        const int sh = (int)d.wrange[2 * ((int64_t)(2 * par + ghost) * B + b) + 1];
         if (tid < kClasses) {   // lower classes, earlier tiles, less the class's start in the tile
             uint32_t o = s_below[tid];
             for (int c = 0; c < tid; ++c) o += s_tot[c] - s_own[c];
@@ -646,7 +678,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         __syncthreads();
         const int64_t n0 = d.Nbase[(int64_t)ghost * B + b];
         for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
-            const int64_t i = a0 + r;
+            const int64_t i = base + page_slot(s_page, sh, r);
             const uint32_t cls = smask[i] & (kClasses - 1);
             const int64_t dst = n0 + (int64_t)(uint32_t)(s_off[cls] + r);
             double x0 = A.x0[i], x1 = DIM == 2 ? A.x1[i] : 0.0;
@@ -758,6 +790,7 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
             if (!adv) ns[pend + s + 1] = n;
         }
         if (adv) ns[0] = n;
+        d.wpool[(int64_t)ghost * B + b] = 0ull;
         if (!ghost) T[kTalPSteps] += ps;
         Ncur[b] = n;
         if (d.ann_limit > 0 && n > d.ann_limit) over = 1;
