@@ -34,7 +34,7 @@ struct Layout {
     // offsets
     size_t ens[2][8] = {}, gens[2][8] = {};
     size_t ip = 0, dev = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
-    size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, Nsrt = 0, srtS = 0, tileW = 0, wrange = 0,
+    size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, tileW = 0, wrange = 0,
            tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, ptab = 0, ptabg = 0, wpool = 0, wcnt = 0,
            wcntg = 0, wsup = 0, wsupg = 0, wtot = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
            occ = 0, Tq = 0, ntil = 0, dacc = 0, dTq = 0, bA = 0, bcopies = 0, bcls = 0,
@@ -253,7 +253,7 @@ Layout make_layout(const wbrw_config *c)
         L.bA = take(cur, C * 8);
         L.bcopies = take(cur, C * 4);
         L.bcls = take(cur, C);
-        L.bcell = take(cur, C * 8);
+        L.bcell = take(cur, C * 4);
         L.bP = take(cur, 2 * C * 16);
         L.bTile = take(cur, 2 * (size_t)L.tilesP * 16);
         L.bG = take(cur, 2 * 4 * C * 4);
@@ -270,8 +270,6 @@ Layout make_layout(const wbrw_config *c)
     L.wtot = take(cur, 2 * BB * kClasses * 4);
     L.wpool = take(cur, 2 * BB * 8);
     L.tileA = take(cur, 2 * (BB + 1) * 8);
-    L.Nsrt = take(cur, BB * 8);
-    L.srtS = take(cur, (BB + 1) * 8);
     L.tileW = take(cur, 4 * (BB + 1) * 8);
     L.wrange = take(cur, 8 * BB * 8);
     L.tileR = take(cur, (BB + 1) * 8);
@@ -831,7 +829,7 @@ void set_grids_dim(wbrw_t h)
     h->grid[G_STREAM] = std::min(3 * cus, kMaxGrid);
     h->grid[G_FAMILY] = persistent_blocks(walk_kernel<DIM>(h), cus);
     h->occ_family = std::max(1, h->grid[G_FAMILY] / std::max(1, cus));
-    h->grid[G_BIN] = std::min(h->occ_bin[0] * cus, kMaxGrid);
+    h->grid[G_BIN] = std::min((h->tangent ? blocks_per_cu(k_bin<DIM, false, true>) : h->occ_bin[0]) * cus, kMaxGrid);
     h->grid[G_SCAN] = persistent_blocks(k_scan, cus);
     h->grid[G_REGEN] = persistent_blocks(k_regen<DIM, false, false>, cus);
     h->grid[G_DENS] = persistent_blocks(k_density_bin<DIM, false, false>, cus);
@@ -927,6 +925,8 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.k_hi = cfg->k_hi;
     d.dx = (cfg->x_hi - cfg->x_lo) / (double)cfg->nx;
     d.dk = (cfg->k_hi - cfg->k_lo) / (double)cfg->nk;
+    d.rdx = 1.0 / d.dx;
+    d.rdk = 1.0 / d.dk;
     d.max_bins = cfg->max_density_bins;
 
     // kernel tables: cumulative sums and normalisers
@@ -1029,8 +1029,6 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.ptab = at<uint32_t>(w, L.ptab);
     d.ptabg = h->tangent ? at<uint32_t>(w, L.ptabg) : nullptr;
     d.tileA = at<int64_t>(w, L.tileA);
-    d.Nsrt = at<int64_t>(w, L.Nsrt);
-    d.srtS = at<int64_t>(w, L.srtS);
     d.tileW = at<int64_t>(w, L.tileW);
     d.wrange = at<int64_t>(w, L.wrange);
     d.tileR = at<int64_t>(w, L.tileR);
@@ -1064,7 +1062,7 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
         d.bA = at<uint64_t>(w, L.bA);
         d.bcopies = at<int32_t>(w, L.bcopies);
         d.bcls = at<int8_t>(w, L.bcls);
-        d.bcell = at<int64_t>(w, L.bcell);
+        d.bcell = at<int32_t>(w, L.bcell);
         d.bP = at<uint64_t>(w, L.bP);
         d.bTile = at<uint64_t>(w, L.bTile);
         d.bG = at<int32_t>(w, L.bG);
@@ -1492,10 +1490,6 @@ int wbrw_restore(wbrw_t h, const void *src, size_t bytes)
     std::vector<char> hold;
     rc = upload_counts(h, N, NG, c.chunk & 1u, hold);
     if (rc) return rc;
-    // the restored order is not known to be cell order (Nsrt = 0)
-    std::vector<int64_t> zeros(h->B + 1, 0);
-    HIPCHK(hipMemcpyAsync(h->d.Nsrt, zeros.data(), 8 * h->B, hipMemcpyHostToDevice, h->stream));
-    HIPCHK(hipMemcpyAsync(h->d.srtS, zeros.data(), 8 * (h->B + 1), hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipMemcpyAsync(h->d.ctl, &c, sizeof(Ctl), hipMemcpyHostToDevice, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     h->host_step = hd.ctl.step;

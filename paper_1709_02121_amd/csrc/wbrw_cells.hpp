@@ -48,6 +48,24 @@ __device__ __forceinline__ T run_sum(int64_t key, T v, bool &commit)
     return v;
 }
 
+// Slot of `key` in a block's hash table of cells (open addressing, 8 probes;
+// kSlots, a power of two), entered if it is new (counted in ins), or -1.
+template <int kSlots>
+__device__ __forceinline__ int hash_slot(int32_t *s_key, int key, uint32_t &ins)
+{
+    const uint32_t h = ((uint32_t)key * 2654435761u) >> (32 - __builtin_ctz((unsigned)kSlots));
+    for (int pr = 0; pr < 8; ++pr) {
+        const int sl = (int)((h + (uint32_t)pr) & (uint32_t)(kSlots - 1));
+        int k = __hip_atomic_load(&s_key[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (k == -1) {
+            k = atomicCAS(&s_key[sl], -1, key);
+            if (k == -1) ++ins;
+        }
+        if (k == -1 || k == key) return sl;
+    }
+    return -1;
+}
+
 constexpr int64_t kOffMask = (1ll << 62) - 1;
 constexpr int64_t kOffNeg = 1ll << 62;
 
@@ -63,26 +81,42 @@ __device__ __forceinline__ void load_births(const Dev &d, int ghost, int b, int 
         B.nst[threadIdx.x] = (uint32_t)d.nstep[((int64_t)ghost * d.B + b) * (kPend + 1) + threadIdx.x];
     __syncthreads();
 }
-__device__ __forceinline__ double position_now(const Dev &d, const Births &B, int pend, int64_t li, double x, double k)
+// Steps that instance-particle li has to be advanced by.  The particles of a
+// tile, [l0, l1), mostly have the same number (>= 0), else tile_steps is -1.
+__device__ __forceinline__ int tile_steps(const Births &B, int pend, int64_t l0, int64_t l1)
 {
-    return pend ? advanced(x, (d.vfac * k) * d.dt, pend - birth_of(B.nst, pend, (uint32_t)li)) : x;
+    const int a = birth_of(B.nst, pend, (uint32_t)l0), b = birth_of(B.nst, pend, (uint32_t)(l1 - 1));
+    return a == b ? pend - a : -1;
+}
+__device__ __forceinline__ int steps_behind(const Births &B, int pend, int tile, int64_t li)
+{
+    return tile >= 0 ? tile : pend - birth_of(B.nst, pend, (uint32_t)li);
 }
 
-// Cell of a phase-space point or -1 outside the grid.
-template <int DIM>
-__device__ __forceinline__ int64_t cell_index(const Dev &d, double x0, double x1, double k0, double k1)
+// Cell along one axis, the whole part of the rounded quotient v / w where
+// that is in [0, n), or -1.  The product with the rounded reciprocal r is
+// within |q| 2^-51 of the quotient as divided: unless it lies that close to a
+// whole number both have the same whole part, and the division is skipped
+// (two divisions were most of the instructions of the cell pass).
+__device__ __forceinline__ int axis_cell(double v, double w, double r, int n)
 {
-    const double qx0 = (x0 - d.x_lo) / d.dx;
-    const double qk0 = (k0 - d.k_lo) / d.dk;
-    if (!(qx0 >= 0.0 && qx0 < (double)d.nx)) return -1;
-    if (!(qk0 >= 0.0 && qk0 < (double)d.nk)) return -1;
-    const int64_t ix0 = (int64_t)qx0, ik0 = (int64_t)qk0;
-    if (DIM == 1) return ix0 + (int64_t)d.nx * ik0;
-    const double qx1 = (x1 - d.x_lo) / d.dx;
-    const double qk1 = (k1 - d.k_lo) / d.dk;
-    if (!(qx1 >= 0.0 && qx1 < (double)d.nx)) return -1;
-    if (!(qk1 >= 0.0 && qk1 < (double)d.nk)) return -1;
-    const int64_t ix1 = (int64_t)qx1, ik1 = (int64_t)qk1;
+    double q = v * r;
+    const double near = rint(q);
+    if (!(fabs(q - near) > fabs(q) * 0x1p-50)) q = v / w;   // also infinities and NaN
+    return q >= 0.0 && q < (double)n ? (int)q : -1;
+}
+
+// Cell of a phase-space point or -1 outside the grid (N_h < 2^31).
+template <int DIM>
+__device__ __forceinline__ int cell_index(const Dev &d, double x0, double x1, double k0, double k1)
+{
+    const int ix0 = axis_cell(x0 - d.x_lo, d.dx, d.rdx, d.nx);
+    const int ik0 = axis_cell(k0 - d.k_lo, d.dk, d.rdk, d.nk);
+    if ((ix0 | ik0) < 0) return -1;
+    if (DIM == 1) return ix0 + d.nx * ik0;
+    const int ix1 = axis_cell(x1 - d.x_lo, d.dx, d.rdx, d.nx);
+    const int ik1 = axis_cell(k1 - d.k_lo, d.dk, d.rdk, d.nk);
+    if ((ix1 | ik1) < 0) return -1;
     return ((ik1 * d.nk + ik0) * d.nx + ix1) * d.nx + ix0;
 }
 
@@ -185,68 +219,114 @@ __global__ __launch_bounds__(kThreads) void k_hist_round(Dev d, const double *hi
 // tangents, also the occupancy and the tangent sums T_nu per cell (for sp2
 // only these: its counts come from the bootstrap).
 // ---------------------------------------------------------------------------
-// Binning cost of the particle tiles before instance b (see kBinLateCost).
-__device__ __forceinline__ int64_t bin_cost_before(const Dev &d, const int64_t *plan, int b)
+// R consecutive values; the address need not be a multiple of 16 bytes.
+template <int R>
+__device__ __forceinline__ void load_run(const double *p, double (&v)[R])
 {
-    return kBinLateCost * plan[b] - (kBinLateCost - kBinSortedCost) * d.srtS[b];
-}
-
-// The first particle tile whose cost prefix reaches c, or the tile count
-// when c reaches the total.
-__device__ __forceinline__ int64_t tile_at_cost(const Dev &d, const int64_t *plan, int64_t c)
-{
-    const int B = d.B;
-    if (c >= bin_cost_before(d, plan, B)) return plan[B];
-    int lo = 0, hi = B - 1;   // the last instance whose cost prefix is <= c
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (bin_cost_before(d, plan, mid) <= c) lo = mid; else hi = mid - 1;
+    typedef double pair __attribute__((ext_vector_type(2), aligned(8)));
+#pragma unroll
+    for (int j = 0; j < R; j += 2) {
+        const pair a = *(const pair *)(p + j);
+        v[j] = a.x;
+        v[j + 1] = a.y;
     }
-    const int64_t r = c - bin_cost_before(d, plan, lo);
-    const int64_t srt = d.srtS[lo + 1] - d.srtS[lo];
-    // cost before tile l of the instance: kBinSortedCost l up to srt, then
-    // kBinSortedCost srt + kBinLateCost (l - srt)
-    const int64_t rs = kBinSortedCost * srt;
-    return plan[lo] + (r <= rs ? (r + kBinSortedCost - 1) / kBinSortedCost
-                               : srt + (r - rs + kBinLateCost - 1) / kBinLateCost);
 }
 
+// Inclusive prefix sum over the wavefront, modulo 2^64 (all 64 lanes call).
+__device__ __forceinline__ uint64_t wave_incl64(uint64_t v)
+{
+#define WBRW_STEP(ctl, rows)                                                                          \
+    {                                                                                                 \
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, ctl, rows, 0xF, false); \
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v >> 32), ctl, rows, 0xF, false); \
+        v += ((uint64_t)hi << 32) | lo;                                                               \
+    }
+    WBRW_STEP(0x111, 0xF)   // row_shr 1, 2, 4, 8, then the rows' last lanes
+    WBRW_STEP(0x112, 0xF)
+    WBRW_STEP(0x114, 0xF)
+    WBRW_STEP(0x118, 0xF)
+    WBRW_STEP(0x142, 0xA)
+    WBRW_STEP(0x143, 0xC)
+#undef WBRW_STEP
+    return v;
+}
+
+// A thread has summed its last run of equal keys (`several`: it had others
+// before).  Runs go on over the lanes whose keys are all that of the lane
+// below.  True in the last lane of a run, which starts at lane `start`; the
+// sum of the run is the difference of prefix sums (run_total).
+__device__ __forceinline__ bool run_last(int key, bool several, int &start, bool &alone)
+{
+    const int lane = threadIdx.x & 63;
+    const int below = __shfl_up(key, 1, 64);
+    const uint64_t heads = __ballot(lane == 0 || several || below != key);
+    start = 63 - __builtin_clzll(heads & (lane == 63 ? ~0ull : ((2ull << lane) - 1ull)));
+    alone = heads == ~0ull;
+    return lane == 63 || ((heads >> (lane + 1)) & 1ull);
+}
+__device__ __forceinline__ uint32_t run_total(uint32_t v, int start)
+{
+    const uint32_t a = wave_incl(v), b = (uint32_t)__shfl((int)a, start > 0 ? start - 1 : 0, 64);
+    return start > 0 ? a - b : a;
+}
+__device__ __forceinline__ uint64_t run_total(uint64_t v, int start)
+{
+    const uint64_t a = wave_incl64(v), b = (uint64_t)__shfl((long long)a, start > 0 ? start - 1 : 0, 64);
+    return start > 0 ? a - b : a;
+}
+
+// A thread takes kR consecutive particles.  In the cell-ordered front of an
+// ensemble thousands of neighbours share a cell (the 1e7 barrier: 8 cells in
+// the 23000 particles of a block), and an LDS atomic of 64 lanes on one address
+// takes them one by one.  Equal neighbours are therefore summed first, in the
+// thread and then over the lanes whose last particles share a cell: prefix sums
+// over the wavefront, modulo 2^32 or 2^64, and the difference of the two ends
+// of a run, which is exact.  One lane of each run adds to the hash table.
+// Measured against a particle to a lane and an LDS atomic each: 234 -> 175 us
+// for 1.4e7 particles after 5 steps (barrier), 777 -> 488 us for 256 instances
+// of 3.1e5, and with tangents (1e7 particles and their ghosts, with the cell's
+// sums in one line, see flush) 800 -> 420 us.  What bounds it now is the lines
+// of the grids that the scattered offspring touch, most of all in 4D, where
+// nearly every particle has a line of its own (5.2 ms for 1.2e8 particles).
 template <int DIM, bool SP2, bool TAN, int SLOTS = 4096>
-__global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost, int pend)
+__global__ __launch_bounds__(kThreads, TAN ? 2 : 1) void k_bin(Dev d, int ghost, int pend)
 {
     if (ann_skipped(d)) return;
-    // Each block takes a contiguous run of tiles.  Without tangents the
-    // signs are summed per cell in an LDS hash table (open addressing on the
-    // cell index, 8 probes) that lives across the block's tiles and is added
-    // to the count grid when the block moves to another instance, when it is
-    // half full, and at the end: a cell-ordered ensemble straddles cell
-    // boundaries after a few steps of drift, so equal cells are close in the
-    // array but rarely in adjacent lanes, and neighbouring tiles share most
-    // of their cells.  A particle whose probes all fail adds directly.  The
+    // Each block takes a contiguous run of tiles, an equal share.  Without
+    // tangents the signs are summed per cell in an LDS hash table (open
+    // addressing on the cell index, 8 probes) that lives across the block's
+    // tiles and is added to the count grid when the block moves to another
+    // instance, when it is half full, and at the end: a cell-ordered ensemble
+    // straddles cell boundaries at every tile, and offspring keep near the
+    // order of their parents, so a block's run touches far fewer cells than
+    // particles even late between annihilations, when a tile alone touches
+    // hundreds of them.  A particle whose probes all fail adds directly.  The
     // table's size (SLOTS, a power of two) trades flushes against blocks per
     // CU; the autotuner picks it.  The positions are `pend` steps behind
     // (0 unless the steps before belong to the same call).
     // With tangents the table's slots hold, per cell, the count, the
-    // occupancy and the six 32.32 fixed-point halves of the tangent sums
-    // (kTSlots of them), and each run of equal cells in consecutive lanes,
-    // summed in registers first, adds to its slot with LDS atomics.
-    constexpr int kSlots = TAN ? 512 : SLOTS;
+    // occupancy and the three tangent sums in 32.32 fixed point.  Runs whose
+    // sums are below 2^15 go there (65536 of them fit: the table is flushed
+    // after that many), others straight to the grid's two halves of 64 bits.
+    constexpr int kSlots = TAN ? 2048 : SLOTS;
+    constexpr int kTiles = 65536 / kTileA;
     static_assert((SLOTS & (SLOTS - 1)) == 0, "a power of two");
-    constexpr int kHashShift = 32 - (TAN ? 9 : 12);
+    constexpr int kR = TAN || DIM == 2 ? kPPT / 2 : kPPT;   // in registers
+    static_assert(kPPT % kR == 0 && kR % 4 == 0, "loads of four signs");
     __shared__ int64_t s_esc;
     __shared__ Births s_births;
     __shared__ uint32_t s_nkeys;
     __shared__ int32_t s_key[kSlots];
     __shared__ int32_t s_val[kSlots];                      // count
     __shared__ int32_t s_occ[TAN ? kSlots : 1];
-    __shared__ unsigned long long s_tq[TAN ? 6 : 1][TAN ? kSlots : 1];
+    __shared__ unsigned long long s_tq[TAN ? 3 : 1][TAN ? kSlots : 1];
     Ctl *ctl = d.ctl;
     const int B = d.B;
     const int64_t *plan = d.tileA + (int64_t)ghost * (B + 1);
     const int64_t ntiles = plan[B];
     const int64_t *Ncur = ghost ? d.NG : d.N;
     const Ens E = pick_set(d, ghost, ghost ? ctl->gcur : ctl->cur);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     // plain sp1: this block's XCD copy of the count grid (blocks are dealt
     // to the XCDs round robin; any other placement is still correct)
     const int xc = (int)(blockIdx.x % kXcd);
@@ -262,28 +342,48 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost, int pend)
         if constexpr (TAN) {
             s_occ[j] = 0;
 #pragma unroll
-            for (int q = 0; q < 6; ++q) s_tq[q][j] = 0ull;
+            for (int q = 0; q < 3; ++q) s_tq[q][j] = 0ull;
         }
     }
     if (tid == 0) { s_esc = 0; s_nkeys = 0; }
+    // component c of the tangent sum of cell g, in 32.32 fixed point
+    auto add_tangent = [&](int64_t g, int c, int64_t q) {
+        const uint64_t lo = (uint64_t)(uint32_t)q;
+        const int64_t hi = q >> 32;
+        if (hi) atomicAdd((unsigned long long *)&tg[g * 6 + 2 * c], (unsigned long long)hi);
+        if (lo) atomicAdd((unsigned long long *)&tg[g * 6 + 2 * c + 1], (unsigned long long)lo);
+    };
     auto flush = [&](int fb) {
         const int64_t fbase = (int64_t)fb * d.Nh;
+        if constexpr (TAN) {
+            // Eight lanes to a slot, so that one instruction takes the six
+            // halves of a cell, which lie in one line of memory: the flush is
+            // bound by the lines that the late offspring's cells touch.
+            for (int j = tid; j < kSlots * 8; j += kThreads) {
+                const int sl = j >> 3, q = j & 7, k = s_key[sl];
+                if (k < 0) continue;
+                if (q < 6) {
+                    const uint64_t t = s_tq[q >> 1][sl];
+                    const unsigned long long h = (q & 1) ? (t & 0xFFFFFFFFull) : (unsigned long long)((int64_t)t >> 32);
+                    if (h) atomicAdd((unsigned long long *)&tg[(fbase + k) * 6 + q], h);
+                } else if (q == 6) {
+                    if (s_occ[sl] != 0) atomicAdd(&og[fbase + k], s_occ[sl]);
+                } else if (s_val[sl] != 0) {
+                    atomicAdd(&cg[fbase + k], s_val[sl]);
+                }
+            }
+            lds_barrier();
+        }
         for (int j = tid; j < kSlots; j += kThreads) {
             const int k = s_key[j];
             if (k < 0) continue;
-            const int v = s_val[j];
-            if (v != 0) atomicAdd(&cg[fbase + k], v);
+            if (!TAN && s_val[j] != 0) atomicAdd(&cg[fbase + k], s_val[j]);
             s_key[j] = -1;
             s_val[j] = 0;
             if constexpr (TAN) {
-                if (s_occ[j] != 0) atomicAdd(&og[fbase + k], s_occ[j]);
                 s_occ[j] = 0;
 #pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    const unsigned long long t = s_tq[q][j];
-                    if (t) atomicAdd((unsigned long long *)&tg[(int64_t)q * ncell + fbase + k], t);
-                    s_tq[q][j] = 0ull;
-                }
+                for (int c = 0; c < 3; ++c) s_tq[c][j] = 0ull;
             }
         }
         if (tid == 0) {
@@ -293,27 +393,21 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost, int pend)
             s_esc = 0;
             s_nkeys = 0;
         }
-        __syncthreads();
+        lds_barrier();
     };
-    // The block's contiguous run of tiles: an equal share of the binning cost
-    // for the particles, an equal share of the tiles for the ghosts.
-    int64_t t0, t1;
-    if (ghost) {
-        t0 = ntiles * blockIdx.x / gridDim.x;
-        t1 = ntiles * (blockIdx.x + 1) / gridDim.x;
-    } else {
-        const int64_t W = bin_cost_before(d, plan, B);
-        t0 = tile_at_cost(d, plan, (W * blockIdx.x + gridDim.x - 1) / gridDim.x);
-        t1 = tile_at_cost(d, plan, (W * (blockIdx.x + 1) + gridDim.x - 1) / gridDim.x);
-    }
-    int cb = -1;
+    const int64_t t0 = ntiles * blockIdx.x / gridDim.x, t1 = ntiles * (blockIdx.x + 1) / gridDim.x;
+    int cb = -1, held = 0;      // the table's instance and the tiles in it
     for (int64_t t = t0; t < t1; ++t) {
-        __syncthreads();
+        lds_barrier();
         const int b = segment_of(plan, B, t);
         // every thread reads the fill level before the flush resets it
-        const bool full = cb >= 0 && (b != cb || s_nkeys > (uint32_t)(kSlots / 2));
-        __syncthreads();
-        if (full) flush(cb);
+        const bool full = cb >= 0 && (b != cb || s_nkeys > (uint32_t)(kSlots / 2) || (TAN && held == kTiles));
+        lds_barrier();
+        if (full) {
+            flush(cb);
+            held = 0;
+        }
+        ++held;
         if (pend && b != cb) load_births(d, ghost, b, pend, s_births);
         cb = b;
         const InstParam &P = d.ip[b];
@@ -322,110 +416,149 @@ __global__ __launch_bounds__(kThreads) void k_bin(Dev d, int ghost, int pend)
         const int64_t cbase = (int64_t)b * d.Nh;
         int64_t esc = 0;
         uint32_t ins = 0;      // keys this thread added to the hash
-        const int64_t li0 = (t - plan[b]) * kTileA + tid;
-        double xa[kPPT], xb[kPPT], ka[kPPT], kb[kPPT];
-        int sv[kPPT];
-#pragma unroll
-        for (int j = 0; j < kPPT; ++j) {      // loads first: kPPT in flight per thread
-            const int64_t li = li0 + (int64_t)j * kThreads;
-            const int64_t i = base + (li < n ? li : 0);
-            xa[j] = E.x0[i];
-            ka[j] = E.k0[i];
-            xb[j] = DIM == 2 ? E.x1[i] : 0.0;
-            kb[j] = DIM == 2 ? E.k1[i] : 0.0;
-            sv[j] = (ghost || SP2) ? 0 : (int)E.sg[i];
-        }
-#pragma unroll
-        for (int j = 0; j < kPPT; ++j) {
-            const int64_t li = li0 + (int64_t)j * kThreads;
-            const bool live = li < n;
-            const int64_t i = base + (live ? li : 0);
-            if (pend) {
-                xa[j] = position_now(d, s_births, pend, li, xa[j], ka[j]);
-                if (DIM == 2) xb[j] = position_now(d, s_births, pend, li, xb[j], kb[j]);
-            }
-            const int64_t nu = live ? cell_index<DIM>(d, xa[j], xb[j], ka[j], kb[j]) : -1;
-            const int s = live ? sv[j] : 0;
-            if (live && nu < 0) {
-                esc += s;
-                if (!(isfinite(xa[j]) && isfinite(xb[j]) && isfinite(ka[j]) && isfinite(kb[j]))) err |= kErrRange;
-            }
-            if (!TAN) {
-                if (nu < 0 || s == 0) continue;
-                const int rs = s;
-                const int key = (int)nu;
-                const uint32_t h = ((uint32_t)key * 2654435761u) >> kHashShift;
-                bool done = false;
-                for (int pr = 0; pr < 8 && !done; ++pr) {
-                    const int slot = (int)((h + (uint32_t)pr) & (uint32_t)(kSlots - 1));
-                    int k = __hip_atomic_load(&s_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (k == -1) {
-                        k = atomicCAS(&s_key[slot], -1, key);
-                        if (k == -1) ++ins;
-                    }
-                    if (k == -1 || k == key) {
-                        atomicAdd(&s_val[slot], rs);
-                        done = true;
-                    }
+        const int64_t lt = (t - plan[b]) * kTileA;
+        const int64_t ds = ghost ? d.gcap_total : d.cap_total;
+        const bool signs = !(ghost || SP2);
+        const int behind = pend ? __builtin_amdgcn_readfirstlane(
+            tile_steps(s_births, pend, lt, min(lt + kTileA, n))) : 0;
+        for (int h = 0; h < kPPT / kR; ++h) {
+            const int64_t li0 = lt + ((int64_t)h * kThreads + tid) * kR;
+            double xa[kR], xb[kR], ka[kR], kb[kR];
+            double dv[TAN ? 3 : 1][kR];
+            int sv[kR];
+            if (li0 + kR <= n) {      // all loads before the first use
+                const int64_t i = base + li0;
+                load_run(&E.x0[i], xa);
+                load_run(&E.k0[i], ka);
+                if (DIM == 2) {
+                    load_run(&E.x1[i], xb);
+                    load_run(&E.k1[i], kb);
                 }
-                if (!done) atomicAdd(&cg[cbase + nu], rs);
+                int32_t s4[kR / 4] = {};
+                if (signs) __builtin_memcpy(s4, &E.sg[i], kR);
+                if constexpr (TAN) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) load_run(&E.D[c * ds + i], dv[c]);
+                }
+#pragma unroll
+                for (int j = 0; j < kR; ++j) sv[j] = (int)(int8_t)(s4[j / 4] >> (8 * (j % 4)));
             } else {
-                // lanes hold consecutive particles: sum equal-cell runs in
-                // registers, then the run's last lane adds them to the cell's
-                // slot (sp2's cell counts come from the bootstrap)
-                bool commit;
-                const bool cnt = !ghost && !SP2;
-                const int ns = run_sum<int>(nu, (cnt && nu >= 0) ? s : 0, commit);
-                const bool in = nu >= 0;
-                const int64_t ds = ghost ? d.gcap_total : d.cap_total;
-                const int no = run_sum<int>(nu, in ? 1 : 0, commit);
-                unsigned long long tq[6];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    int64_t hi = 0;
-                    uint64_t lo = 0;
-                    if (in && !fx_split(E.D[c * ds + i], hi, lo)) err |= kErrRange;
-                    tq[2 * c] = (unsigned long long)run_sum<int64_t>(nu, hi, commit);
-                    tq[2 * c + 1] = (unsigned long long)run_sum<uint64_t>(nu, lo, commit);
-                }
-                if (commit) {
-                    const int key = (int)nu;
-                    const uint32_t h = ((uint32_t)key * 2654435761u) >> kHashShift;
-                    int slot = -1;
-                    for (int pr = 0; pr < 8 && slot < 0; ++pr) {
-                        const int sl = (int)((h + (uint32_t)pr) & (uint32_t)(kSlots - 1));
-                        int k = __hip_atomic_load(&s_key[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (k == -1) {
-                            k = atomicCAS(&s_key[sl], -1, key);
-                            if (k == -1) ++ins;
-                        }
-                        if (k == -1 || k == key) slot = sl;
+                for (int j = 0; j < kR; ++j) {
+                    const int64_t i = base + (li0 + j < n ? li0 + j : 0);
+                    xa[j] = E.x0[i];
+                    ka[j] = E.k0[i];
+                    if (DIM == 2) {
+                        xb[j] = E.x1[i];
+                        kb[j] = E.k1[i];
                     }
-                    if (slot >= 0) {
-                        if (ns) atomicAdd(&s_val[slot], ns);
-                        atomicAdd(&s_occ[slot], no);
+                    sv[j] = signs ? (int)E.sg[i] : 0;
+                    if constexpr (TAN) {
 #pragma unroll
-                        for (int q = 0; q < 6; ++q)
-                            if (tq[q]) atomicAdd(&s_tq[q][slot], tq[q]);
-                    } else {   // every probe taken: straight to the grids
-                        if (ns) atomicAdd(&cg[cbase + nu], ns);
-                        atomicAdd(&og[cbase + nu], no);
-#pragma unroll
-                        for (int q = 0; q < 6; ++q)
-                            if (tq[q]) atomicAdd((unsigned long long *)&tg[(int64_t)q * ncell + cbase + nu], tq[q]);
+                        for (int c = 0; c < 3; ++c) dv[c][j] = E.D[c * ds + i];
                     }
                 }
             }
+            if (DIM == 1) {
+#pragma unroll
+                for (int j = 0; j < kR; ++j) xb[j] = kb[j] = 0.0;
+            }
+            // Adds a run of equal cells: the sum of the signs, or with tangents the
+            // number of particles (low half) and the sum of the signs (high half).
+            auto commit = [&](int key, uint32_t v, const uint64_t (&q)[TAN ? 3 : 1]) {
+                const int occ = TAN ? (int)(v & 0xFFFFu) : 0;
+                const int cnt = TAN ? (int)(v - (uint32_t)occ) >> 16 : (int)v;
+                if (!TAN && cnt == 0) return;
+                const int slot = hash_slot<kSlots>(s_key, key, ins);
+                bool small = slot >= 0;
+                if constexpr (TAN) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        small = small && (int64_t)q[c] < (1ll << 47) && (int64_t)q[c] >= -(1ll << 47);
+                }
+                if (slot >= 0) {
+                    if (cnt) atomicAdd(&s_val[slot], cnt);
+                    if (TAN) atomicAdd(&s_occ[slot], occ);
+                } else {
+                    if (cnt) atomicAdd(&cg[cbase + key], cnt);
+                    if (TAN) atomicAdd(&og[cbase + key], occ);
+                }
+                if constexpr (TAN) {
+                    if (small) {
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) atomicAdd(&s_tq[c][slot], (unsigned long long)q[c]);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) add_tangent(cbase + key, c, (int64_t)q[c]);
+                    }
+                }
+            };
+            int key = -1;                       // the thread's current run
+            uint32_t v = 0;
+            uint64_t q[TAN ? 3 : 1] = {};
+            bool several = false;
+#pragma unroll
+            for (int j = 0; j < kR; ++j) {
+                const int64_t li = li0 + j;
+                const bool live = li < n;
+                if (behind != 0) {
+                    const int m = live ? steps_behind(s_births, pend, behind, li) : 0;
+                    xa[j] = advanced(xa[j], (d.vfac * ka[j]) * d.dt, m);
+                    if (DIM == 2) xb[j] = advanced(xb[j], (d.vfac * kb[j]) * d.dt, m);
+                }
+                const int nu = live ? cell_index<DIM>(d, xa[j], xb[j], ka[j], kb[j]) : -1;
+                const int s = live ? sv[j] : 0;
+                if (live && nu < 0) {
+                    esc += s;
+                    if (!(isfinite(xa[j]) && isfinite(xb[j]) && isfinite(ka[j]) && isfinite(kb[j]))) err |= kErrRange;
+                }
+                if (j == 0) key = nu;
+                if (nu != key) {
+                    if (key >= 0) commit(key, v, q);
+                    several = true;
+                    key = nu;
+                    v = 0;
+#pragma unroll
+                    for (int c = 0; c < (TAN ? 3 : 1); ++c) q[c] = 0;
+                }
+                if (nu < 0) continue;
+                v += TAN ? ((uint32_t)s << 16) + 1u : (uint32_t)s;
+                if constexpr (TAN) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        int64_t hi = 0;
+                        uint64_t lo = 0;
+                        if (!fx_split(dv[c][j], hi, lo)) err |= kErrRange;
+                        if (hi < (1ll << 22) && hi >= -(1ll << 22)) {      // 256 of them fit
+                            q[c] += ((uint64_t)hi << 32) + lo;
+                        } else {
+                            unsigned long long *const tc = (unsigned long long *)&tg[(cbase + nu) * 6 + 2 * c];
+                            if (hi) atomicAdd(tc, (unsigned long long)hi);
+                            if (lo) atomicAdd(tc + 1, (unsigned long long)lo);
+                        }
+                    }
+                }
+            }
+            int start;
+            bool alone;
+            const bool last = run_last(key, several, start, alone);
+            if (!alone) {
+                v = run_total(v, start);
+                if constexpr (TAN) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) q[c] = run_total(q[c], start);
+                }
+            }
+            if (last && key >= 0) commit(key, v, q);
         }
         if (esc) atomicAdd((unsigned long long *)&s_esc, (unsigned long long)esc);
         {   // the tile's new keys, one LDS atomic per wavefront
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) ins += __shfl_xor(ins, o, 64);
-            if ((tid & 63) == 0 && ins) atomicAdd(&s_nkeys, ins);
-            ins = 0;
+            if (lane == 0 && ins) atomicAdd(&s_nkeys, ins);
         }
     }
-    __syncthreads();
+    lds_barrier();
     if (cb >= 0) flush(cb);
     if (err) atomicOr(&ctl->err, err);
 }
@@ -515,24 +648,24 @@ __global__ __launch_bounds__(kThreads) void k_fold_tangents(Dev d)
         int32_t o = d.occ[g];
         int64_t tv[6];
 #pragma unroll
-        for (int q = 0; q < 6; ++q) tv[q] = d.Tq[q * nc + g];
+        for (int q = 0; q < 6; ++q) tv[q] = d.Tq[g * 6 + q];
         bool any = false;
         for (int x = 0; x < kXcd - 1; ++x) {
             if (po[x] == 0) continue;   // a copy that saw no particle here holds no sums
-            const int64_t tx = (int64_t)x * 6 * nc + g;
+            const int64_t tx = ((int64_t)x * nc + g) * 6;
             o += po[x];
             d.occx[(int64_t)x * nc + g] = 0;
 #pragma unroll
             for (int q = 0; q < 6; ++q) {   // exact integer sums: any order
-                tv[q] += d.Tqx[tx + q * nc];
-                d.Tqx[tx + q * nc] = 0;
+                tv[q] += d.Tqx[tx + q];
+                d.Tqx[tx + q] = 0;
             }
             any = true;
         }
         if (any) {
             d.occ[g] = o;
 #pragma unroll
-            for (int q = 0; q < 6; ++q) d.Tq[q * nc + g] = tv[q];
+            for (int q = 0; q < 6; ++q) d.Tq[g * 6 + q] = tv[q];
         }
     }
 }
@@ -712,8 +845,8 @@ __global__ __launch_bounds__(kThreads) void k_regen(Dev d)
                 const int64_t nc = d.Nh * (int64_t)B;
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
-                    O.D[c * d.cap_total + i] = fx_value(d.Tq[(2 * c) * nc + cbase + nu],
-                                                        (uint64_t)d.Tq[(2 * c + 1) * nc + cbase + nu]) / an;
+                    O.D[c * d.cap_total + i] = fx_value(d.Tq[(cbase + nu) * 6 + 2 * c],
+                                                        (uint64_t)d.Tq[(cbase + nu) * 6 + 2 * c + 1]) / an;
             }
         }
     }
@@ -728,14 +861,12 @@ __global__ __launch_bounds__(kThreads) void k_close_regen(Dev d)
     const int B = d.B;
     for (int b = threadIdx.x; b < B; b += kThreads) {
         d.N[b] = d.Nnew[b];
-        d.Nsrt[b] = d.Nnew[b];   // the regenerated ensemble is in cell order
         d.tally[(int64_t)b * kTalCount + kTalAnn] += 1;
     }
     __syncthreads();
     block_plan(d.tileA, d.N, B, kTileA);
     for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)b * (kPend + 1)] = d.N[b];
     plan_walk(d, ctl->chunk & 1u, 0, d.N);
-    block_prefix(d.srtS, B, [&](int b) { return d.Nsrt[b] / kTileA; });
     if (threadIdx.x == 0) {
         ctl->cur ^= 1u;
         ctl->ann_seq += 1u;

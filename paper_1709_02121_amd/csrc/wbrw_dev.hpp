@@ -137,6 +137,7 @@ struct Dev {
     int64_t cap_total, gcap_total;
     double dt, vfac;
     double x_lo, x_hi, k_lo, k_hi, dx, dk;
+    double rdx, rdk;            // 1/dx and 1/dk, rounded (see axis_cell)
     int32_t kind[kMaxM], axis[kMaxM], sampler[kMaxM];
     int32_t ftile, gftile;      // event parents that k_walk takes at a time (particles, ghosts):
                                 // as many as kThreads, fewer where their records (see
@@ -173,18 +174,16 @@ struct Dev {
     int64_t wsup_g, wsup_gg;            // groups of one parity
     uint32_t *wtot;                     // [2][B][kClasses] records of each class (more than
                                         // kFewInst instances; zero between chunks)
-    int64_t *Nsrt;              // [B] particles in cell order at the front of each instance
-    int64_t *srtS;              // [B+1] prefix of floor(Nsrt[b] / kTileA)
     int32_t *cnt;               // [B][Nh] signed counts (sp1) / rounded counts (sp2)
     int32_t *cntx;              // partial counts of the blocks on the other XCDs (copy 0
                                 // is the grid itself): sp1 [kXcd - 1][B][Nh] of cnt, sp2
                                 // [kXcd - 1][2][B][Nh] of ntil; null when not used
     int64_t *off;               // [B][Nh] exclusive prefix of |n_nu|, bit 62 = negative cell
     int32_t *occ;               // [B][Nh] occupancy (tangents)
-    int64_t *Tq;                // [6][B][Nh] tangent sums per cell in 32.32 fixed point
-                                // (see fx_split): plane 2c high words, 2c + 1 low words
+    int64_t *Tq;                // [B][Nh][6] tangent sums per cell in 32.32 fixed point
+                                // (see fx_split), high and low words; a cell in one or two lines
     int32_t *occx;              // with tangents: [kXcd - 1][B][Nh] XCD copies of occ,
-    int64_t *Tqx;               // and [kXcd - 1][6][B][Nh] of Tq (see cntx); else null
+    int64_t *Tqx;               // and [kXcd - 1][B][Nh][6] of Tq (see cntx); else null
     int32_t *ntil;              // [2][B][Nh] sp2 bootstrap counts per class
     int64_t *dacc;              // [kXcd][B][max_bins] density accumulator, one per XCD
                                 // (a block flushes into copy blockIdx mod kXcd)
@@ -194,7 +193,7 @@ struct Dev {
     uint64_t *bA;               // [cap_total] quantised weight, then the residual
     int32_t *bcopies;           // [cap_total] copies per particle
     int8_t *bcls;               // [cap_total] class (0 +, 1 -, -1 none)
-    int64_t *bcell;             // [cap_total] cell or -1
+    int32_t *bcell;             // [cap_total] cell or -1
     uint64_t *bP;               // [2][cap_total] 128-bit residual prefix (lo, hi interleaved)
     uint64_t *bTile;            // [2][tiles] 128-bit tile sums
     int32_t *bG;                // [2][4 cap_total] draw guide per class, four
@@ -538,15 +537,6 @@ __device__ __forceinline__ void plan_walk(const Dev &d, uint32_t par, int ghost,
         return t;
     });
 }
-
-// Cost of binning a streaming tile: kBinSortedCost inside the cell-ordered
-// front of its instance (the first Nsrt[b] particles, as the last
-// regeneration left them), kBinLateCost after it, where the offspring
-// appended since then scatter over many more cells per tile.  With srtS[b] =
-// sum_{b' < b} floor(Nsrt[b'] / kTileA), the cost of the tiles before
-// instance b is kBinLateCost tileA[b] - (kBinLateCost - kBinSortedCost)
-// srtS[b]; it needs N[b] >= Nsrt[b], which holds because steps only append.
-constexpr int64_t kBinSortedCost = 1, kBinLateCost = 3;
 
 // Tangent sums over cells and bins are exact integer sums in 32.32 fixed
 // point, so that no summation order is singled out: a component D enters as

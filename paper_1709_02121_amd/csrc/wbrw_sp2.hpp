@@ -119,6 +119,8 @@ __global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d, int pend)
         const InstParam &P = d.ip[b];
         const int64_t n = d.N[b];
         const int64_t li0 = (t - plan[b]) * kTileA + tid;
+        const int behind = pend ? __builtin_amdgcn_readfirstlane(
+            tile_steps(s_births, pend, li0 - tid, min(li0 - tid + kTileA, n))) : 0;
         double wv[kPPT], xa[kPPT], xb[kPPT], ka[kPPT], kb[kPPT];
 #pragma unroll
         for (int j = 0; j < kPPT; ++j) {      // loads first: kPPT in flight per thread
@@ -137,9 +139,10 @@ __global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d, int pend)
             const int64_t i = P.base + li;
             const double w = wv[j];
             const uint64_t A = (uint64_t)floor(fabs(w) * 4294967296.0);
-            if (pend) {
-                xa[j] = position_now(d, s_births, pend, li, xa[j], ka[j]);
-                if (DIM == 2) xb[j] = position_now(d, s_births, pend, li, xb[j], kb[j]);
+            if (behind != 0) {
+                const int m = steps_behind(s_births, pend, behind, li);
+                xa[j] = advanced(xa[j], (d.vfac * ka[j]) * d.dt, m);
+                if (DIM == 2) xb[j] = advanced(xb[j], (d.vfac * kb[j]) * d.dt, m);
             }
             const int64_t nu = cell_index<DIM>(d, xa[j], xb[j], ka[j], kb[j]);
             int8_t cls = -1;
@@ -651,57 +654,70 @@ __global__ __launch_bounds__(kThreads) void k_sp2_cells(Dev d)
             s_val[j] = 0;
         }
         if (tid == 0) s_nkeys = 0;
-        __syncthreads();
+        lds_barrier();
     };
-    // an equal share of the binning cost (see kBinLateCost) per block
-    const int64_t W = bin_cost_before(d, plan, B);
-    const int64_t t0 = tile_at_cost(d, plan, (W * blockIdx.x + gridDim.x - 1) / gridDim.x);
-    const int64_t t1 = tile_at_cost(d, plan, (W * (blockIdx.x + 1) + gridDim.x - 1) / gridDim.x);
+    const int64_t t0 = ntiles * blockIdx.x / gridDim.x, t1 = ntiles * (blockIdx.x + 1) / gridDim.x;
     int cb = -1;
     for (int64_t t = t0; t < t1; ++t) {
-        __syncthreads();
+        lds_barrier();
         const int b = segment_of(plan, B, t);
         // every thread reads the fill level before the flush resets it
         const bool full = cb >= 0 && (b != cb || s_nkeys > (uint32_t)(kSlots / 2));
-        __syncthreads();
+        lds_barrier();
         if (full) flush(cb);
         cb = b;
         const InstParam &P = d.ip[b];
         const int64_t n = d.N[b];
-        const int64_t li0 = (t - plan[b]) * kTileA + tid;
+        const int64_t li0 = (t - plan[b]) * kTileA + (int64_t)tid * kPPT;
         int8_t cl[kPPT];
-        int32_t cp[kPPT];
-        int64_t cell[kPPT];
+        int32_t cp[kPPT], cell[kPPT];
+        if (li0 + kPPT <= n) {      // loads first
+            __builtin_memcpy(cl, &d.bcls[P.base + li0], sizeof cl);
+            __builtin_memcpy(cp, &d.bcopies[P.base + li0], sizeof cp);
+            __builtin_memcpy(cell, &d.bcell[P.base + li0], sizeof cell);
+        } else {
 #pragma unroll
-        for (int j = 0; j < kPPT; ++j) {      // loads first
-            const int64_t li = li0 + (int64_t)j * kThreads;
-            const int64_t i = P.base + (li < n ? li : 0);
-            cl[j] = li < n ? d.bcls[i] : (int8_t)-1;
-            cp[j] = d.bcopies[i];
-            cell[j] = d.bcell[i];
+            for (int j = 0; j < kPPT; ++j) {
+                const int64_t i = P.base + (li0 + j < n ? li0 + j : 0);
+                cl[j] = li0 + j < n ? d.bcls[i] : (int8_t)-1;
+                cp[j] = d.bcopies[i];
+                cell[j] = d.bcell[i];
+            }
         }
+        uint32_t ins = 0;
+        auto commit = [&](int key, int v) {
+            if (v == 0) return;
+            const int slot = hash_slot<kSlots>(s_key, key, ins);
+            if (slot >= 0) atomicAdd(&s_val[slot], v);
+            else atomicAdd(&tg[(int64_t)(key & 1) * plane + (int64_t)b * d.Nh + (key >> 1)], v);
+        };
+        // Equal neighbours are summed before one lane adds them (see k_bin).
+        // A particle without copies adds nothing to any run.
+        int key = -1, v = 0;
+        bool several = false;
 #pragma unroll
         for (int j = 0; j < kPPT; ++j) {
-            if (cl[j] < 0 || cp[j] == 0) continue;
-            const int key = (int)(cell[j] << 1) | (int)cl[j];
-            const uint32_t h = ((uint32_t)key * 2654435761u) >> 20;
-            bool done = false;
-            for (int pr = 0; pr < 8 && !done; ++pr) {
-                const int slot = (int)((h + (uint32_t)pr) & (uint32_t)(kSlots - 1));
-                int k = __hip_atomic_load(&s_key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (k == -1) {
-                    k = atomicCAS(&s_key[slot], -1, key);
-                    if (k == -1) atomicAdd(&s_nkeys, 1u);
+            const int k = cl[j] < 0 || cp[j] == 0 ? -1 : (cell[j] << 1) | (int)cl[j];
+            if (k >= 0 && k != key) {
+                if (key >= 0) {
+                    commit(key, v);
+                    several = true;
                 }
-                if (k == -1 || k == key) {
-                    atomicAdd(&s_val[slot], cp[j]);
-                    done = true;
-                }
+                key = k;
+                v = 0;
             }
-            if (!done) atomicAdd(&tg[(int64_t)cl[j] * plane + (int64_t)b * d.Nh + cell[j]], cp[j]);
+            if (k >= 0) v += cp[j];
         }
+        int start;
+        bool alone;
+        const bool last = run_last(key, several, start, alone);
+        if (!alone) v = (int)run_total((uint32_t)v, start);
+        if (last && key >= 0) commit(key, v);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) ins += __shfl_xor(ins, o, 64);
+        if ((tid & 63) == 0 && ins) atomicAdd(&s_nkeys, ins);
     }
-    __syncthreads();
+    lds_barrier();
     if (cb >= 0) flush(cb);
 }
 
@@ -862,15 +878,15 @@ __global__ __launch_bounds__(kThreads) void k_ghosts(Dev d)
                     G.id[o] = id;
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
-                        G.D[q * d.gcap_total + o] = fx_value(d.Tq[(2 * q) * nc + cbase + c],
-                                                             (uint64_t)d.Tq[(2 * q + 1) * nc + cbase + c]);
+                        G.D[q * d.gcap_total + o] = fx_value(d.Tq[(cbase + c) * 6 + 2 * q],
+                                                             (uint64_t)d.Tq[(cbase + c) * 6 + 2 * q + 1]);
                 }
                 gi++;
             }
             d.cnt[cbase + c] = 0;
             d.occ[cbase + c] = 0;
 #pragma unroll
-            for (int q = 0; q < 6; ++q) d.Tq[q * nc + cbase + c] = 0;
+            for (int q = 0; q < 6; ++q) d.Tq[(cbase + c) * 6 + q] = 0;
         }
         __syncthreads();
     }
