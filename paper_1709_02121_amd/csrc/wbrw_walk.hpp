@@ -177,28 +177,344 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *s_w, uint32
     return excl;
 }
 
+// What a block of k_walk keeps in LDS.
+constexpr uint32_t kLocal = 0x80000000u;
+struct WalkTile {
+    int64_t i0, a0, limit;       // first particle, pages' base, offspring the pages hold
+    uint32_t nl, q0;             // offspring so far, event parents of step s that are done
+    int s, b, nr, i00, sh, npage;
+};
+template <int DIM, bool SP2, bool TAN>
+struct WalkShared {
+    static constexpr int kW0 = kRangeMax / 64;       // words of a step's bits of the range
+    static constexpr int kWL = kLocalBits / 64;      // ... of the offspring
+    Families<DIM, SP2, TAN> F;
+    uint64_t ev[kChunk][kW0];
+    unsigned long long evl[kChunk][kWL];
+    int64_t tal[5];
+    int64_t limit;                // offspring the pages hold
+    WalkTile rest;                // what k_walk leaves to walk_rest
+    int32_t t;
+    uint32_t wsum[2][4];
+    uint32_t item[kThreads];      // event parents: index in the range, or
+                                  // kLocal | index among the offspring
+    uint32_t ccnt[kClasses];      // records of each class
+    uint32_t born[kChunk + 1];    // offspring at the start of each step
+    uint32_t nst[kPend + 1];
+    uint32_t page[kPages];
+    uint8_t cls[kThreads];        // the event parents' classes
+};
+
+// Takes the event parents of tile T through steps T.s .. S - 1, batch by batch
+// (k_walk).  False where the families of a batch outgrow the pool, with what is
+// left to do in W.rest.  With GENERAL it is taken on from there, each family by
+// the general walk of one lane.
+template <int DIM, bool SP2, bool TAN, bool ONE, bool GENERAL>
+__device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
+                                           uint32_t par, WalkTile &T, WalkShared<DIM, SP2, TAN> &W, uint32_t &err)
+{
+    using FT = Families<DIM, SP2, TAN>;
+    FT &F = W.F;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int b = T.b, nr = T.nr, i00 = T.i00, sh = T.sh, B = fresh(self).B;
+    const int64_t i0 = T.i0, a0 = T.a0;
+    int npage = T.npage;
+    int64_t limit = T.limit;
+    uint32_t nl = T.nl;                  // offspring of the tile so far
+    auto barrier = [] { if (GENERAL) __syncthreads(); else lds_barrier(); };
+    const int nw0 = (nr + 63) / 64;
+    int s = GENERAL ? T.s : 0;
+    uint32_t q0 = GENERAL ? T.q0 : 0u;
+    for (; s < S; ++s, q0 = 0u) {
+        const uint32_t step = step0 + (uint32_t)s;
+        const int FS = ghost ? fresh(self).gftile : fresh(self).ftile;   // event parents taken at a time
+        const uint32_t nl0 = q0 > 0u ? W.born[s] : nl;         // those of earlier steps
+        const int nw = nw0 + (int)((nl0 + 63u) / 64u);
+        if (tid == 0 && q0 == 0u) W.born[s] = nl0;
+        uint32_t np = 0;                 // event parents of the step
+        for (;; q0 += (uint32_t)FS) {
+            // event parents [q0, q0 + FS) of the step, in order: first
+            // the range's, then the offspring's
+            if (GENERAL || nl0 > (uint32_t)kLocalBits) __syncthreads(); else lds_barrier();
+            uint32_t run = 0;
+            for (int w0 = 0, it = 0; w0 < nw; w0 += kThreads, ++it) {
+                const int wi = w0 + tid, wl = wi - nw0;
+                uint64_t m = 0;
+                if (wi < nw0) m = W.ev[s][wi];
+                else if (wi < nw && wl < WalkShared<DIM, SP2, TAN>::kWL) m = W.evl[s][wl];
+                else if (wi < nw)        // past the bits kept in LDS
+                    for (uint32_t q = 0; q < 64u && (uint32_t)wl * 64u + q < nl0; ++q)
+                        m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)[a0 + page_slot(W.page, sh, wl * 64 + q)] >>
+                                         (kChunk + s)) & 1u) << q;
+                uint32_t tot;
+                uint32_t pos = run + block_excl((uint32_t)__popcll(m), W.wsum[it & 1], tot);
+                while (m) {
+                    const int k = __builtin_ctzll(m);
+                    m &= m - 1ull;
+                    if (pos >= q0 && pos < q0 + (uint32_t)FS)
+                        W.item[pos - q0] = wi < nw0 ? (uint32_t)(wi * 64 + k) : kLocal | (uint32_t)(wl * 64 + k);
+                    ++pos;
+                }
+                run += tot;
+            }
+            np = run;
+            if (q0 >= np) break;
+            if (tid == 0) {
+                F.n = F.nq[0] = F.nq[1] = F.overflow = F.events = F.pairs = F.maxdepth = 0u;
+                F.killed = 0;
+            }
+            F.cnt[tid] = 0u;
+            F.head[tid] = kNone;
+            __syncthreads();
+            const bool live = tid < FS && q0 + (uint32_t)tid < np;
+            // event parent ti at the start of the step
+            auto load_root = [&](int ti) {
+                const Dev &d = fresh(self);
+                const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
+                const uint32_t it = W.item[ti];
+                const bool loc = (it & kLocal) != 0u;
+                const uint32_t l = it & ~kLocal;
+                const Ens *sets = ghost ? d.gens : d.ens;
+                const Ens E = sets[set], A = sets[set ^ 1u], X = loc ? A : E;
+                const int64_t pi = loc ? a0 + page_slot(W.page, sh, l) : i0 + (int64_t)l;
+                Node root;
+                root.x[0] = X.x0[pi];
+                root.x[1] = DIM == 2 ? X.x1[pi] : 0.0;
+                root.k[0] = X.k0[pi];
+                root.k[1] = DIM == 2 ? X.k1[pi] : 0.0;
+                root.t0 = 0.0;
+                root.id = X.id[pi];
+                root.w = SP2 ? X.w[pi] : 0.0;
+                root.sg = SP2 ? 0 : (int32_t)X.sg[pi];
+                root.D[0] = TAN ? X.D[pi] : 0.0;
+                root.D[1] = TAN ? X.D[dstride + pi] : 0.0;
+                root.D[2] = TAN ? X.D[2 * dstride + pi] : 0.0;
+                int m;
+                if (loc) {
+                    W.cls[ti] = (uint8_t)((ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1));
+                    m = -1;              // steps since the one it was born in
+                    for (int q = 1; q <= s; ++q) m += l < W.born[q] ? 1 : 0;
+                } else {
+                    W.cls[ti] = 0;
+                    m = pend + s - birth_of(W.nst, pend, (uint32_t)i00 + l);
+                }
+                root.x[0] = advanced(root.x[0], (d.vfac * root.k[0]) * d.dt, m);
+                if (DIM == 2) root.x[1] = advanced(root.x[1], (d.vfac * root.k[1]) * d.dt, m);
+                return root;
+            };
+            // 1. the parents' first jumps, then round by round those
+            //    found.  Each wavefront takes 64 jumps; where there are
+            //    few, two or four share the same ones, each with its
+            //    share of their pair slots.
+            Tally tal{0, 0, 0, 0, 0};
+            if constexpr (!GENERAL) {
+                const int slots = ONE && !TAN ? 1 : (TAN && fresh(self).tangent == 2 ? 2 : 1) * (ONE ? 1 : fresh(self).M);
+                uint32_t nt = min((uint32_t)FS, np - q0);      // jumps of the round
+                int share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
+                int ti = wv / share * 64 + lane, m0 = wv % share;
+                Node cur;
+                uint64_t key = 0ull;
+                uint32_t rec = kNone;
+                int slot = ti, lev = 0;
+                bool act = false;
+                if (ti < (int)nt && m0 < slots) {
+                    cur = load_root(ti);
+                    const Dev &d = fresh(self);
+                    const InstParam &P = inst_param(d, b);
+                    const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
+                    cur.te = cur.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
+                    cur.ua0 = unit53(r.c, r.d);
+                    cur.e = 0u;
+                    act = cur.te <= d.dt;
+                }
+                for (int round = 0;; ++round) {
+                    const Dev &d = fresh(self);
+                    const InstParam &P = inst_param(d, b);
+                    if (act)
+                        take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, m0, share, F);
+                    if (DIM == 2) __syncthreads(); else lds_barrier();   // 4D records may be in HBM
+                    nt = F.nq[round & 1];
+                    if (nt == 0u || F.overflow) break;
+                    share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
+                    ti = wv / share * 64 + lane;
+                    m0 = wv % share;
+                    act = ti < (int)nt && m0 < slots;
+                    if (act) {
+                        rec = F.qrec[ti];
+                        load_record<DIM, SP2, TAN>(d, F, rec, cur);
+                        cur.x[0] = F.qx0[ti];
+                        cur.x[1] = DIM == 2 ? F.qx1[ti] : 0.0;
+                        cur.t0 = F.qt0[ti];
+                        cur.te = F.qte[ti];
+                        cur.ua0 = F.qua[ti];
+                        cur.e = F.qe[ti];
+                        key = F.key[rec];
+                        slot = F.slot[rec];
+                        lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
+                    }
+                    if (tid == 0) F.nq[(round + 1) & 1] = 0u;
+                    lds_barrier();
+                }
+            }
+            if constexpr (!GENERAL) {
+                if (F.overflow) {    // (uniform)
+                    if (tid == 0) {
+                        W.rest = T;
+                        W.rest.nl = nl;
+                        W.rest.q0 = q0;
+                        W.rest.s = s;
+                        W.rest.npage = npage;
+                        W.rest.limit = limit;
+                    }
+                    return false;
+                }
+            } else if (live) {
+                const Node root = load_root(tid);
+                F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, 0, W.page, sh, 0, &tal, &err);
+            }
+            if (GENERAL) barrier();
+            // 2. ordered exclusive scan of the families' record counts
+            uint32_t agg;
+            const uint32_t excl = block_excl(F.cnt[tid], W.wsum[0], agg);
+            F.first[tid] = excl;
+            if ((int64_t)nl + agg > limit && npage < kPages && sh < 31) {   // (uniform) further pages
+                int np2 = npage;
+                while (np2 < kPages && page_extent(np2, sh) < (int64_t)nl + agg) ++np2;
+                if (tid == 0) {
+                    const Dev &d = fresh(self);
+                    const InstParam &P = inst_param(d, b);
+                    const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
+                    const int64_t take = page_extent(np2, sh) - page_extent(npage, sh);
+                    const int64_t from = ((plan[b + 1] - plan[b]) << sh) +
+                        (int64_t)atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * B + b], (unsigned long long)take);
+                    int64_t lim = limit;
+                    for (int q = npage; q < np2; ++q) {
+                        const int64_t at2 = from + page_extent(q, sh) - page_extent(npage, sh);
+                        W.page[q] = (uint32_t)at2;
+                        if (from + page_extent(q + 1, sh) - page_extent(npage, sh) <= (ghost ? P.gcap : P.cap))
+                            lim = page_extent(q + 1, sh);
+                    }
+                    W.limit = lim;
+                }
+                npage = np2;
+                barrier();
+                limit = W.limit;
+            }
+            barrier();
+            // 3. records into the tile's area, each at its rank in its
+            //    family, with its class and its own jumps in the chunk's
+            //    later steps
+            const Dev &d = fresh(self);
+            const InstParam &P = inst_param(d, b);
+            const Ens &A = (ghost ? d.gens : d.ens)[set ^ 1u];
+            uint16_t *smask = ghost ? d.smaskg : d.smask;
+            const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
+            auto close_record = [&](int64_t li, uint64_t id, int slot) {
+                const uint32_t cls = (uint32_t)W.cls[slot] | (1u << s);
+                uint32_t ev = 0;
+                const Clock c = clock_of(d, id, P.key);
+                for (int q = s + 1; q < S; ++q)
+                    if (clock_jumps(d, P, c, id, step0 + (uint32_t)q)) {
+                        ev |= 1u << q;
+                        if (li < kLocalBits) atomicOr(&W.evl[q][li >> 6], 1ull << (li & 63));
+                    }
+                smask[a0 + page_slot(W.page, sh, (uint32_t)li)] = (uint16_t)(cls | (ev << kChunk));
+                atomicAdd(&W.ccnt[cls], 1u);
+            };
+            if constexpr (!GENERAL) {
+                const uint32_t nrec = F.n;
+                uint32_t deep = 0;
+                for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
+                    const uint64_t key = F.key[r];
+                    if (key == 0ull) continue;
+                    const int slot = F.slot[r];
+                    uint32_t rank = 0;
+                    for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
+                    deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
+                    const int64_t li = (int64_t)nl + (int64_t)(F.first[slot] + rank);
+                    if (li >= limit) { err |= kErrCapacity; continue; }
+                    const int64_t o = a0 + page_slot(W.page, sh, (uint32_t)li);
+                    Node nd;
+                    load_record<DIM, SP2, TAN>(d, F, r, nd);
+                    A.x0[o] = nd.x[0];
+                    A.k0[o] = nd.k[0];
+                    if (DIM == 2) {
+                        A.x1[o] = nd.x[1];
+                        A.k1[o] = nd.k[1];
+                    }
+                    if (SP2) A.w[o] = nd.w; else A.sg[o] = (int8_t)nd.sg;
+                    A.id[o] = nd.id;
+                    if (TAN) {
+                        A.D[o] = nd.D[0];
+                        A.D[dstride + o] = nd.D[1];
+                        A.D[2 * dstride + o] = nd.D[2];
+                    }
+                    close_record(li, nd.id, slot);
+                }
+                // the wavefront's deepest level by ballots (an atomic
+                // maximum of per-lane values takes the lanes one by one)
+                uint32_t top = 0;
+                while (__ballot(deep > top)) ++top;
+                if (lane == 0) atomicMax(&F.maxdepth, top);
+            } else {
+                if (live) {
+                    const Node root = load_root(tid);
+                    Tally none{0, 0, 0, 0, 0};
+                    const int64_t f = (int64_t)nl + (int64_t)excl;
+                    const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, limit, W.page, sh,
+                                                                  dstride, &none, &err);
+                    for (uint32_t r = 0; r < c && f + r < limit; ++r)
+                        close_record(f + r, A.id[a0 + page_slot(W.page, sh, (uint32_t)(f + r))], tid);
+                }
+                atomicAdd((unsigned long long *)&W.tal[0], (unsigned long long)tal.events);
+                atomicAdd((unsigned long long *)&W.tal[1], (unsigned long long)tal.pairs);
+                atomicAdd((unsigned long long *)&W.tal[2], (unsigned long long)tal.killed);
+                atomicAdd((unsigned long long *)&W.tal[3], (unsigned long long)tal.cap);
+                atomicMax((unsigned long long *)&W.tal[4], (unsigned long long)tal.maxdepth);
+            }
+            nl = (uint32_t)min((int64_t)nl + agg, limit);
+            barrier();
+            if (tid == 0 && !GENERAL) {
+                W.tal[0] += F.events;
+                W.tal[1] += F.pairs;
+                W.tal[2] += F.killed;
+                W.tal[4] = max(W.tal[4], (int64_t)F.maxdepth);
+            }
+            if (q0 + (uint32_t)FS >= np) break;
+        }
+    }
+    T.npage = npage;
+    return true;
+}
+
+// What is left of a tile whose families have outgrown the pool.  A function of
+// its own, called where k_walk holds nothing else: with the general walk's
+// calls inside the steps the common path spilt 100 vector registers and took
+// longer (256 instances 8.95 ms a pass and 7.63 so, barrier of 1e7 2.32 and
+// 2.12, of 1e4 1.02 and 0.88, weighted 1e7 1.78 and 1.52, 4D 12.3 and 11.2).
+template <int DIM, bool SP2, bool TAN>
+__device__ __noinline__ uint32_t walk_rest(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
+                                           uint32_t par, WalkShared<DIM, SP2, TAN> *W)
+{
+    const uint64_t p = (uint64_t)self;
+    const Dev *uniform = (const Dev *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32) |
+                                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p));
+    WalkTile T = W->rest;
+    T.b = __builtin_amdgcn_readfirstlane(T.b);
+    uint32_t err = 0;
+    walk_steps<DIM, SP2, TAN, false, true>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
+    if (threadIdx.x == 0) W->rest.npage = T.npage;
+    __syncthreads();
+    return err;
+}
+
 template <int DIM, bool SP2, bool TAN, bool ONE>
 __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(const Dev *self, int ghost, int S,
                                                                              int pend, int adv)
 {
-    using FT = Families<DIM, SP2, TAN>;
-    constexpr int kW0 = kRangeMax / 64;       // words of a step's bits of the range
-    constexpr int kWL = kLocalBits / 64;      // ... of the offspring
-    __shared__ int32_t s_t;
-    __shared__ uint32_t s_wsum[2][4];
-    __shared__ int64_t s_tal[5];
-    __shared__ FT F;
-    __shared__ uint64_t s_ev[kChunk][kW0];
-    __shared__ unsigned long long s_evl[kChunk][kWL];
-    __shared__ uint32_t s_item[kThreads];     // event parents: index in the range, or
-                                              // kLocal | index among the offspring
-    __shared__ uint8_t s_cls[kThreads];       // their classes
-    __shared__ uint32_t s_ccnt[kClasses];     // records of each class
-    __shared__ uint32_t s_born[kChunk + 1];   // offspring at the start of each step
-    __shared__ uint32_t s_nst[kPend + 1];
-    __shared__ uint32_t s_page[kPages];
-    __shared__ int64_t s_limit;               // offspring the pages hold
-    constexpr uint32_t kLocal = 0x80000000u;
+    using WS = WalkShared<DIM, SP2, TAN>;
+    constexpr int kWL = WS::kWL;
+    __shared__ WS W;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     uint32_t err = 0, step0, par, set;
@@ -226,20 +542,20 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
     // line would serialise the whole grid.
     int cb = -1;
     bool first = true;
-    if (tid < 5) s_tal[tid] = 0;
+    if (tid < 5) W.tal[tid] = 0;
     for (;;) {
         if (tid == 0) {
             const Dev &d = fresh(self);
-            s_t = (int32_t)next_tile_static_first(&d.ctl->ticket[ghost ? kPassFamilyG : kPassFamily], ntiles, first);
+            W.t = (int32_t)next_tile_static_first(&d.ctl->ticket[ghost ? kPassFamilyG : kPassFamily], ntiles, first);
         }
-        for (int q = tid; q < kChunk * kWL; q += kThreads) (&s_evl[0][0])[q] = 0ull;
-        if (tid < kClasses) s_ccnt[tid] = 0u;
+        for (int q = tid; q < kChunk * kWL; q += kThreads) (&W.evl[0][0])[q] = 0ull;
+        if (tid < kClasses) W.ccnt[tid] = 0u;
         lds_barrier();
-        const int64_t t = __builtin_amdgcn_readfirstlane(s_t);
+        const int64_t t = __builtin_amdgcn_readfirstlane(W.t);
         if (t >= ntiles) break;
         // tile t is tile tl of instance b: its range of nr particles from i0
         // on; its offspring go to pages of 2^sh slots behind a0
-        int b, nr, i00, sh, npage = 1;
+        int b, nr, i00, sh;
         int64_t i0, a0, limit;
         {
             const Dev &d = fresh(self);
@@ -254,21 +570,21 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             nr = (int)min(R, n - tl * R);
             a0 = base;
             limit = min((int64_t)1 << sh, ghost ? P.gcap : P.cap);
-            if (tid == 0) s_page[0] = (uint32_t)(tl << (sh & 31));
+            if (tid == 0) W.page[0] = (uint32_t)(tl << (sh & 31));
         }
         if (b != cb) {
             const Dev &d = fresh(self);
             if (tid == 0 && cb >= 0) {
                 int64_t *T = d.tally + (int64_t)cb * kTalCount;
-                if (s_tal[0]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)s_tal[0]);
-                if (s_tal[1]) atomicAdd((unsigned long long *)&T[kTalPairs], (unsigned long long)s_tal[1]);
-                if (s_tal[2]) atomicAdd((unsigned long long *)&T[kTalKilled], (unsigned long long)s_tal[2]);
-                if (s_tal[3]) atomicAdd((unsigned long long *)&T[kTalEventCap], (unsigned long long)s_tal[3]);
-                if (s_tal[4]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)s_tal[4]);
-                for (int q = 0; q < 5; ++q) s_tal[q] = 0;
+                if (W.tal[0]) atomicAdd((unsigned long long *)&T[kTalEvents], (unsigned long long)W.tal[0]);
+                if (W.tal[1]) atomicAdd((unsigned long long *)&T[kTalPairs], (unsigned long long)W.tal[1]);
+                if (W.tal[2]) atomicAdd((unsigned long long *)&T[kTalKilled], (unsigned long long)W.tal[2]);
+                if (W.tal[3]) atomicAdd((unsigned long long *)&T[kTalEventCap], (unsigned long long)W.tal[3]);
+                if (W.tal[4]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)W.tal[4]);
+                for (int q = 0; q < 5; ++q) W.tal[q] = 0;
             }
             cb = b;
-            if (tid < pend) s_nst[tid] = (uint32_t)d.nstep[((int64_t)ghost * B + b) * (kPend + 1) + tid];
+            if (tid < pend) W.nst[tid] = (uint32_t)d.nstep[((int64_t)ghost * B + b) * (kPend + 1) + tid];
         }
         // the range's clocks, lanes on consecutive particles; the next ids
         // are loaded while the draws of the last ones run
@@ -290,271 +606,25 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     if (band)
                         m |= band & __ballot(clock_exact(cur, step0 + (uint32_t)s, d.seed, P.key, P.thr_lo, P.thr_hi,
                                                          P.gamma0, d.dt));
-                    if (lane == 0) s_ev[s][j * (kThreads / 64) + wv] = m & in;
+                    if (lane == 0) W.ev[s][j * (kThreads / 64) + wv] = m & in;
                 }
             }
         }
-        const int nw0 = (nr + 63) / 64;
-        uint32_t nl = 0;                     // offspring of the tile so far
-        for (int s = 0; s < S; ++s) {
-            const uint32_t step = step0 + (uint32_t)s;
-            const int FS = ghost ? fresh(self).gftile : fresh(self).ftile;   // event parents taken at a time
-            const uint32_t nl0 = nl;         // those of earlier steps
-            const int nw = nw0 + (int)((nl0 + 63u) / 64u);
-            if (tid == 0) s_born[s] = nl0;
-            uint32_t np = 0;                 // event parents of the step
-            for (uint32_t q0 = 0;; q0 += (uint32_t)FS) {
-                // event parents [q0, q0 + FS) of the step, in order: first
-                // the range's, then the offspring's
-                if (nl0 > (uint32_t)kLocalBits) __syncthreads(); else lds_barrier();
-                uint32_t run = 0;
-                for (int w0 = 0, it = 0; w0 < nw; w0 += kThreads, ++it) {
-                    const int wi = w0 + tid, wl = wi - nw0;
-                    uint64_t m = 0;
-                    if (wi < nw0) m = s_ev[s][wi];
-                    else if (wi < nw && wl < kWL) m = s_evl[s][wl];
-                    else if (wi < nw)        // past the bits kept in LDS
-                        for (uint32_t q = 0; q < 64u && (uint32_t)wl * 64u + q < nl0; ++q)
-                            m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)[a0 + page_slot(s_page, sh, wl * 64 + q)] >>
-                                             (kChunk + s)) & 1u) << q;
-                    uint32_t tot;
-                    uint32_t pos = run + block_excl((uint32_t)__popcll(m), s_wsum[it & 1], tot);
-                    while (m) {
-                        const int k = __builtin_ctzll(m);
-                        m &= m - 1ull;
-                        if (pos >= q0 && pos < q0 + (uint32_t)FS)
-                            s_item[pos - q0] = wi < nw0 ? (uint32_t)(wi * 64 + k) : kLocal | (uint32_t)(wl * 64 + k);
-                        ++pos;
-                    }
-                    run += tot;
-                }
-                np = run;
-                if (q0 >= np) break;
-                if (tid == 0) {
-                    F.n = F.nq[0] = F.nq[1] = F.overflow = F.events = F.pairs = F.maxdepth = 0u;
-                    F.killed = 0;
-                }
-                F.cnt[tid] = 0u;
-                F.head[tid] = kNone;
-                __syncthreads();
-                const bool live = tid < FS && q0 + (uint32_t)tid < np;
-                // event parent ti at the start of the step
-                auto load_root = [&](int ti) {
-                    const Dev &d = fresh(self);
-                    const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-                    const uint32_t it = s_item[ti];
-                    const bool loc = (it & kLocal) != 0u;
-                    const uint32_t l = it & ~kLocal;
-                    const Ens *sets = ghost ? d.gens : d.ens;
-                    const Ens E = sets[set], A = sets[set ^ 1u], X = loc ? A : E;
-                    const int64_t pi = loc ? a0 + page_slot(s_page, sh, l) : i0 + (int64_t)l;
-                    Node root;
-                    root.x[0] = X.x0[pi];
-                    root.x[1] = DIM == 2 ? X.x1[pi] : 0.0;
-                    root.k[0] = X.k0[pi];
-                    root.k[1] = DIM == 2 ? X.k1[pi] : 0.0;
-                    root.t0 = 0.0;
-                    root.id = X.id[pi];
-                    root.w = SP2 ? X.w[pi] : 0.0;
-                    root.sg = SP2 ? 0 : (int32_t)X.sg[pi];
-                    root.D[0] = TAN ? X.D[pi] : 0.0;
-                    root.D[1] = TAN ? X.D[dstride + pi] : 0.0;
-                    root.D[2] = TAN ? X.D[2 * dstride + pi] : 0.0;
-                    int m;
-                    if (loc) {
-                        s_cls[ti] = (uint8_t)((ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1));
-                        m = -1;              // steps since the one it was born in
-                        for (int q = 1; q <= s; ++q) m += l < s_born[q] ? 1 : 0;
-                    } else {
-                        s_cls[ti] = 0;
-                        m = pend + s - birth_of(s_nst, pend, (uint32_t)i00 + l);
-                    }
-                    root.x[0] = advanced(root.x[0], (d.vfac * root.k[0]) * d.dt, m);
-                    if (DIM == 2) root.x[1] = advanced(root.x[1], (d.vfac * root.k[1]) * d.dt, m);
-                    return root;
-                };
-                // 1. the parents' first jumps, then round by round those
-                //    found.  Each wavefront takes 64 jumps; where there are
-                //    few, two or four share the same ones, each with its
-                //    share of their pair slots.
-                {
-                    const int slots = ONE && !TAN ? 1 : (TAN && fresh(self).tangent == 2 ? 2 : 1) * (ONE ? 1 : fresh(self).M);
-                    uint32_t nt = min((uint32_t)FS, np - q0);      // jumps of the round
-                    int share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
-                    int ti = wv / share * 64 + lane, m0 = wv % share;
-                    Node cur;
-                    uint64_t key = 0ull;
-                    uint32_t rec = kNone;
-                    int slot = ti, lev = 0;
-                    bool act = false;
-                    if (ti < (int)nt && m0 < slots) {
-                        cur = load_root(ti);
-                        const Dev &d = fresh(self);
-                        const InstParam &P = inst_param(d, b);
-                        const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
-                        cur.te = cur.t0 + (-ln_series(1.0 - unit53(r.a, r.b)) / P.gamma0);
-                        cur.ua0 = unit53(r.c, r.d);
-                        cur.e = 0u;
-                        act = cur.te <= d.dt;
-                    }
-                    for (int round = 0;; ++round) {
-                        const Dev &d = fresh(self);
-                        const InstParam &P = inst_param(d, b);
-                        if (act)
-                            take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, m0, share, F);
-                        if (DIM == 2) __syncthreads(); else lds_barrier();   // 4D records may be in HBM
-                        nt = F.nq[round & 1];
-                        if (nt == 0u || F.overflow) break;
-                        share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
-                        ti = wv / share * 64 + lane;
-                        m0 = wv % share;
-                        act = ti < (int)nt && m0 < slots;
-                        if (act) {
-                            rec = F.qrec[ti];
-                            load_record<DIM, SP2, TAN>(d, F, rec, cur);
-                            cur.x[0] = F.qx0[ti];
-                            cur.x[1] = DIM == 2 ? F.qx1[ti] : 0.0;
-                            cur.t0 = F.qt0[ti];
-                            cur.te = F.qte[ti];
-                            cur.ua0 = F.qua[ti];
-                            cur.e = F.qe[ti];
-                            key = F.key[rec];
-                            slot = F.slot[rec];
-                            lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
-                        }
-                        if (tid == 0) F.nq[(round + 1) & 1] = 0u;
-                        lds_barrier();
-                    }
-                }
-                const bool overflow = F.overflow != 0u;
-                Tally tal{0, 0, 0, 0, 0};
-                if (overflow) {   // (uniform) every family by the general walk
-                    F.cnt[tid] = 0u;
-                    if (live) {
-                        const Node root = load_root(tid);
-                        F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, 0, s_page, sh, 0,
-                                                                &tal, &err);
-                    }
-                    __syncthreads();
-                }
-                // 2. ordered exclusive scan of the families' record counts
-                uint32_t agg;
-                const uint32_t excl = block_excl(F.cnt[tid], s_wsum[0], agg);
-                F.first[tid] = excl;
-                if ((int64_t)nl + agg > limit && npage < kPages && sh < 31) {   // (uniform) further pages
-                    int np2 = npage;
-                    while (np2 < kPages && page_extent(np2, sh) < (int64_t)nl + agg) ++np2;
-                    if (tid == 0) {
-                        const Dev &d = fresh(self);
-                        const InstParam &P = inst_param(d, b);
-                        const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
-                        const int64_t take = page_extent(np2, sh) - page_extent(npage, sh);
-                        const int64_t from = ((plan[b + 1] - plan[b]) << sh) +
-                            (int64_t)atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * B + b], (unsigned long long)take);
-                        int64_t lim = limit;
-                        for (int q = npage; q < np2; ++q) {
-                            const int64_t at2 = from + page_extent(q, sh) - page_extent(npage, sh);
-                            s_page[q] = (uint32_t)at2;
-                            if (from + page_extent(q + 1, sh) - page_extent(npage, sh) <= (ghost ? P.gcap : P.cap))
-                                lim = page_extent(q + 1, sh);
-                        }
-                        s_limit = lim;
-                    }
-                    npage = np2;
-                    lds_barrier();
-                    limit = s_limit;
-                }
-                lds_barrier();
-                // 3. records into the tile's area, each at its rank in its
-                //    family, with its class and its own jumps in the chunk's
-                //    later steps
-                const Dev &d = fresh(self);
-                const InstParam &P = inst_param(d, b);
-                const Ens &A = (ghost ? d.gens : d.ens)[set ^ 1u];
-                uint16_t *smask = ghost ? d.smaskg : d.smask;
-                const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-                auto close_record = [&](int64_t li, uint64_t id, int slot) {
-                    const uint32_t cls = (uint32_t)s_cls[slot] | (1u << s);
-                    uint32_t ev = 0;
-                    const Clock c = clock_of(d, id, P.key);
-                    for (int q = s + 1; q < S; ++q)
-                        if (clock_jumps(d, P, c, id, step0 + (uint32_t)q)) {
-                            ev |= 1u << q;
-                            if (li < kLocalBits) atomicOr(&s_evl[q][li >> 6], 1ull << (li & 63));
-                        }
-                    smask[a0 + page_slot(s_page, sh, (uint32_t)li)] = (uint16_t)(cls | (ev << kChunk));
-                    atomicAdd(&s_ccnt[cls], 1u);
-                };
-                if (!overflow) {
-                    const uint32_t nrec = F.n;
-                    uint32_t deep = 0;
-                    for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
-                        const uint64_t key = F.key[r];
-                        if (key == 0ull) continue;
-                        const int slot = F.slot[r];
-                        uint32_t rank = 0;
-                        for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
-                        deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
-                        const int64_t li = (int64_t)nl + (int64_t)(F.first[slot] + rank);
-                        if (li >= limit) { err |= kErrCapacity; continue; }
-                        const int64_t o = a0 + page_slot(s_page, sh, (uint32_t)li);
-                        Node nd;
-                        load_record<DIM, SP2, TAN>(d, F, r, nd);
-                        A.x0[o] = nd.x[0];
-                        A.k0[o] = nd.k[0];
-                        if (DIM == 2) {
-                            A.x1[o] = nd.x[1];
-                            A.k1[o] = nd.k[1];
-                        }
-                        if (SP2) A.w[o] = nd.w; else A.sg[o] = (int8_t)nd.sg;
-                        A.id[o] = nd.id;
-                        if (TAN) {
-                            A.D[o] = nd.D[0];
-                            A.D[dstride + o] = nd.D[1];
-                            A.D[2 * dstride + o] = nd.D[2];
-                        }
-                        close_record(li, nd.id, slot);
-                    }
-                    // the wavefront's deepest level by ballots (an atomic
-                    // maximum of per-lane values takes the lanes one by one)
-                    uint32_t top = 0;
-                    while (__ballot(deep > top)) ++top;
-                    if (lane == 0) atomicMax(&F.maxdepth, top);
-                } else {
-                    if (live) {
-                        const Node root = load_root(tid);
-                        Tally none{0, 0, 0, 0, 0};
-                        const int64_t f = (int64_t)nl + (int64_t)excl;
-                        const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, limit, s_page, sh,
-                                                                      dstride, &none, &err);
-                        for (uint32_t r = 0; r < c && f + r < limit; ++r)
-                            close_record(f + r, A.id[a0 + page_slot(s_page, sh, (uint32_t)(f + r))], tid);
-                    }
-                    atomicAdd((unsigned long long *)&s_tal[0], (unsigned long long)tal.events);
-                    atomicAdd((unsigned long long *)&s_tal[1], (unsigned long long)tal.pairs);
-                    atomicAdd((unsigned long long *)&s_tal[2], (unsigned long long)tal.killed);
-                    atomicAdd((unsigned long long *)&s_tal[3], (unsigned long long)tal.cap);
-                    atomicMax((unsigned long long *)&s_tal[4], (unsigned long long)tal.maxdepth);
-                }
-                nl = (uint32_t)min((int64_t)nl + agg, limit);
-                lds_barrier();
-                if (tid == 0 && !overflow) {
-                    s_tal[0] += F.events;
-                    s_tal[1] += F.pairs;
-                    s_tal[2] += F.killed;
-                    s_tal[4] = max(s_tal[4], (int64_t)F.maxdepth);
-                }
-                if (q0 + (uint32_t)FS >= np) break;
-            }
+        WalkTile T{i0, a0, limit, 0u, 0u, 0, b, nr, i00, sh, 1};
+        if (!walk_steps<DIM, SP2, TAN, ONE, false>(self, ghost, S, pend, set, step0, par, T, W, err)) {
+            __syncthreads();
+            err |= walk_rest<DIM, SP2, TAN>(self, ghost, S, pend, set, step0, par, &W);
+            T.npage = W.rest.npage;
         }
+        const int npage = T.npage;
         lds_barrier();
         // the tile's counts per class, also summed over groups of tiles
         const Dev &d = fresh(self);
-        if (tid < npage) (ghost ? d.ptabg : d.ptab)[t * kPages + tid] = s_page[tid];
+        if (tid < npage) (ghost ? d.ptabg : d.ptab)[t * kPages + tid] = W.page[tid];
         if (tid < kClasses) {
             uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
             uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
-            const uint32_t c = s_ccnt[tid];
+            const uint32_t c = W.ccnt[tid];
             wcnt[t * kClasses + tid] = c;
             if (c) atomicAdd(&wsup[(t / kSupGroup) * kClasses + tid], c);
             if (c && B > kFewInst) atomicAdd(&d.wtot[((int64_t)ghost * B + b) * kClasses + tid], c);
@@ -563,7 +633,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             const Ens &E = (ghost ? d.gens : d.ens)[set];
             for (int li = tid; li < nr; li += kThreads) {
                 const int64_t i = i0 + li;
-                const int m = pend + S - birth_of(s_nst, pend, (uint32_t)(i00 + li));
+                const int m = pend + S - birth_of(W.nst, pend, (uint32_t)(i00 + li));
                 const double c0 = (d.vfac * E.k0[i]) * d.dt;
                 __builtin_nontemporal_store(advanced(E.x0[i], c0, m), &E.x0[i]);
                 if (DIM == 2) {
@@ -577,7 +647,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
     if (tid == 0) {
         int64_t *T = fresh(self).fpart + (int64_t)blockIdx.x * 8;
         T[0] = cb;
-        for (int q = 0; q < 5; ++q) T[1 + q] = s_tal[q];
+        for (int q = 0; q < 5; ++q) T[1 + q] = W.tal[q];
     }
     if (err) atomicOr(&fresh(self).ctl->err, err);
 }
