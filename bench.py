@@ -11,11 +11,12 @@ annihilation and the density readout, which are inside the timed region.
 value = sum over timed steps of the particles held at the start of the step,
 divided by the wall time.  Inputs are resident on the GPU before timing starts.
 
-Roofline: the whole step (its four launches) against HBM, with the survey's
-model of 34 algorithmic bytes per particle-step (read x, k, id; write x; the
-offspring records and the parents' signs), timed by HIP events around every
-step on the launch stream inside the timed region.  The same steps are then
-run again with events around every kernel, for the per-kernel split
+Roofline: the whole step against HBM, with a model of 34 algorithmic bytes per
+particle-step (read x, k, id; write x; the offspring records and the parents'
+signs), timed by HIP events around every launch group of up to five steps on
+the launch stream inside the timed region.  (A launch group reads x, k and id
+once for its steps, so it may move fewer bytes than the model.)  The same steps
+are then run again with events around every kernel, for the per-kernel split
 (`kernels`, with the dominant kernel named).
 
 Printed: one JSON line on stdout (everything else goes to stderr).
@@ -37,20 +38,13 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0   # MI355X HBM3E
 ANN_EVERY = 10
 STEP_MODEL_BYTES = 34   # algorithmic bytes per particle-step of the 1D sp1 step
-# the placement launch's first block closes the step (tallies, counts, the next plan)
-STEP_KERNELS = (("stream", "k_stream"), ("events", "k_events"), ("family", "k_family"),
-                ("place", "k_place_records"))
-TRAFFIC_SOURCES = ("wbrw_stream.hpp", "wbrw_step.hpp", "wbrw_math.hpp", "wbrw_dev.hpp")
+# the placement launch's first block closes the steps (tallies, counts, the next plan)
+STEP_KERNELS = (("family", "k_walk"), ("place", "k_place"))
+TRAFFIC_SOURCES = ("wbrw_walk.hpp", "wbrw_step.hpp", "wbrw_math.hpp", "wbrw_dev.hpp")
 
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
-
-
-def stream_bytes_per_particle_step(dim):
-    """Algorithmic HBM bytes of the streaming pass per particle-step: read
-    x, k (f64 per axis) and the lineage id (u64), write x."""
-    return dim * 8 * 2 + 8 + dim * 8
 
 
 def run_form(P, torch, cfg, steps, warmup, every=ANN_EVERY, use_graph=False, density=True,
@@ -70,14 +64,18 @@ def run_form(P, torch, cfg, steps, warmup, every=ANN_EVERY, use_graph=False, den
     held = {}
 
     def advance(n):
+        # stretches up to the next annihilation or checkpoint, one call each
         nonlocal done
-        for _ in range(n):
-            sim.step(1)
-            done += 1
-            if every and done % every == 0:
-                sim.annihilate()
-                if density and not adjoint:
-                    sim.density()
+        end = done + n
+        while done < end:
+            m = end - done
+            for q in (every, snap_every):
+                if q:
+                    m = min(m, q - done % q)
+            sim.run(m, every)
+            done += m
+            if every and done % every == 0 and density and not adjoint:
+                sim.density()
             if snap_every and done % snap_every == 0:
                 held["snap"] = sim.snapshot()      # the latest checkpoint is kept
 
@@ -117,7 +115,7 @@ def run_form(P, torch, cfg, steps, warmup, every=ANN_EVERY, use_graph=False, den
             sim.profile(False)
         return wall, sum(sim.stats(b)["particle_steps"] for b in range(sim.B)) - ps0, prof
 
-    # the timed region: exactly `steps` steps, with two HIP events per step
+    # the timed region: exactly `steps` steps, with two HIP events per launch group
     # (none inside a graph replay)
     wall, ps, step_prof = timed(steps, None if use_graph else "steps")
     # the same number of steps again with HIP events around every kernel
@@ -171,8 +169,8 @@ def measured_traffic():
 
 def step_roofline(res):
     """Roofline of the whole step: STEP_MODEL_BYTES per particle-step over the
-    mean step time of the timed region (HIP events around each step), with
-    the per-kernel split of the profiled pass."""
+    mean step time of the timed region (HIP events around each launch group),
+    with the per-kernel split of the profiled pass."""
     sp = res["step_profile"]
     if not sp or sp["step"][1] == 0:
         return None
@@ -188,22 +186,18 @@ def step_roofline(res):
         ms, n = prof[st]
         if n == 0:
             continue
-        kern[name] = {"avg_launch_us": round(ms * 1e3 / n, 2), "share": round(ms / total, 4)}
-    ms_s, n_s = prof["stream"]
-    if n_s:
-        b = stream_bytes_per_particle_step(1) * res["prof_particle_steps"] / n_s
-        a = b / (ms_s * 1e-3 / n_s) / 1e9
-        kern["k_stream"].update({"bytes_per_launch": int(b), "bytes_per_particle_step":
-                                 stream_bytes_per_particle_step(1), "achieved": round(a, 1),
-                                 "frac": round(a / HBM_PEAK_GBS, 4)})
+        kern[name] = {"avg_launch_us": round(ms * 1e3 / n, 2), "us_per_step": round(ms * 1e3 / prof["step"][1], 2)
+                      if prof["step"][1] else None, "share": round(ms / total, 4)}
     dominant = max(kern, key=lambda k: kern[k]["avg_launch_us"])
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
-           "scope": "whole step: k_stream, k_events, k_family, k_place_records (with the closing block)",
+           "scope": "whole step: k_walk and k_place (with the closing block), up to five steps a launch",
            "kernel": dominant, "dominant_kernel": dominant,
            "avg_step_us": round(avg_step_s * 1e6, 2), "steps_timed": nsteps,
            "particle_steps_per_step": int(ps_step), "bytes_per_particle_step": STEP_MODEL_BYTES,
-           "bytes_per_step": int(bytes_step), "kernels": kern}
+           "bytes_per_step": int(bytes_step),
+           "note": "the model counts every step's reads and writes; a launch of several steps makes them once",
+           "kernels": kern}
     per = measured_traffic()
     if per:
         out["traffic"] = int(sum(per.values()) * ps_step)
@@ -293,11 +287,6 @@ def run_forms(P, torch, W, args):
                                         "50 steps), then the density and its backward pass")
             if r["tuned"]:
                 forms[name]["autotuned"] = r["tuned"]
-            if name == "helium_4d":
-                ms, n = r["profile"]["stream"]
-                if n:
-                    a = stream_bytes_per_particle_step(2) * r["prof_particle_steps"] / (ms * 1e-3) / 1e9
-                    forms[name]["stream_frac_hbm"] = round(a / HBM_PEAK_GBS, 4)
             log(f"{name}: {r['rate']:.4g} particle-steps/s")
         except Exception as e:   # report, never hide, a form that failed
             forms[name] = {"error": str(e)[:300]}
@@ -383,12 +372,9 @@ def long_runs(P, torch, W):
     held = {}
 
     def fwd_adj():
-        for s in range(cfg["steps"]):
-            sim.step(1)
-            if (s + 1) % ANN_EVERY == 0:
-                sim.annihilate()
-            if (s + 1) % cfg["snapshot_every"] == 0:
-                held["snap"] = sim.snapshot()
+        for _ in range(0, cfg["steps"], cfg["snapshot_every"]):
+            sim.run(cfg["snapshot_every"], ANN_EVERY)
+            held["snap"] = sim.snapshot()
         sim.density()
         held["grad"] = sim.density_vjp(g)
 

@@ -156,18 +156,19 @@ typedef struct wbrw_stats {
 
 /* Stages timed by the per-stage profiler. */
 enum wbrw_stage {
-    WBRW_STAGE_STREAM = 0,    /* clock test, free flight, event compaction */
-    WBRW_STAGE_FAMILY = 1,    /* family trees of jumping particles */
+    WBRW_STAGE_STREAM = 0,    /* unused: WBRW_STAGE_FAMILY holds the clocks and flights */
+    WBRW_STAGE_FAMILY = 1,    /* steps: clocks, jumps and family trees (up to five steps a launch) */
     WBRW_STAGE_BIN = 2,       /* annihilation: cell sums */
     WBRW_STAGE_SCAN = 3,      /* annihilation: ordered scan */
     WBRW_STAGE_REGEN = 4,     /* annihilation: regeneration */
     WBRW_STAGE_BOOTSTRAP = 5, /* sp2 bootstrap filter */
     WBRW_STAGE_DENSITY = 6,   /* density readout */
     WBRW_STAGE_GHOST = 7,     /* tangent ghosts and ghost steps */
-    WBRW_STAGE_EVENTS = 8,    /* step: ordered event list */
-    WBRW_STAGE_PLACE = 9,     /* step: record placement */
-    WBRW_STAGE_CLOSE = 10,    /* unused: the placement launch's first block closes the step */
-    WBRW_STAGE_STEP = 11,     /* a whole step, all of its launches (brackets the others) */
+    WBRW_STAGE_EVENTS = 8,    /* unused: the order of the offspring is found as they are placed */
+    WBRW_STAGE_PLACE = 9,     /* steps: offspring into their places */
+    WBRW_STAGE_CLOSE = 10,    /* unused: the placement launch's first block closes the steps */
+    WBRW_STAGE_STEP = 11,     /* whole steps, all launches of a group of up to five (brackets
+                                 the others); counted in steps */
     WBRW_STAGE_COUNT = 12
 };
 
@@ -189,9 +190,12 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes,
               void *hip_stream, wbrw_t *out);
 
 /* Advances every instance by nsteps time steps (Alg. 1 between t_l and
- * t_{l+1} = t_l + dt; Sec. 2).  Enqueues 4 kernels per step (streaming, event
- * list, families, record placement whose first block does the bookkeeping;
- * 8 with tangents, whose ghosts take a second such pass); no host
+ * t_{l+1} = t_l + dt; Sec. 2).  Enqueues two kernels per group of up to five
+ * steps (fewer where the ensemble grows fast): one takes every particle and
+ * its offspring through the steps, the other puts the offspring in order, and
+ * its first block does the bookkeeping; four with tangents, whose ghosts take
+ * a second such pass.  More steps in one call need fewer launches; the results
+ * do not depend on how steps are divided into calls.  No host
  * synchronisation. */
 int wbrw_step(wbrw_t h, int32_t nsteps);
 
@@ -294,9 +298,11 @@ int wbrw_export(wbrw_t h, int32_t b, int32_t ghost, int64_t n, double *x, double
 
 /* Launch configuration of the plain step and annihilation: six int32,
  * {streaming blocks, family blocks, streaming threads per block, streaming
- * particles per thread, binning blocks, binning hash slots}.  The streaming
- * tile is always 2048 particles; the shapes offered are 256 x 8, 128 x 16
- * (1D only) and 512 x 4, the hash sizes 4096, 2048 and 8192 slots.  Results
+ * particles per thread, binning blocks, binning hash slots}.  The family
+ * blocks are those of the kernel that takes the steps; there is no streaming
+ * kernel any more, and its shapes (256 x 8, 128 x 16 in 1D only, 512 x 4) are
+ * kept and reported but change nothing.  Hash sizes are 4096, 2048 and 8192
+ * slots (with tangents always 2048).  Results
  * do not depend on the configuration: every kernel's arithmetic and output
  * order are the same under all of them (the parallel scheme of Sec. 4 with
  * per-particle random streams). */
@@ -306,11 +312,10 @@ int wbrw_get_launch(wbrw_t h, int32_t *cfg);
  * drops captured graphs. */
 int wbrw_set_launch(wbrw_t h, const int32_t *cfg);
 
-/* Autotuner.  Runs 2 * max(#streaming candidates, #family candidates) *
- * steps_per_candidate time steps of the handle's own ensemble (they are real
- * steps: results do not depend on launch shapes) while timing the streaming
- * kernel over its block shapes and grid sizes (blocks per compute unit) and
- * the family kernel over its grid sizes; for a plain sp1 ensemble it also
+/* Autotuner.  Runs 2 * #family candidates * steps_per_candidate time steps of
+ * the handle's own ensemble (they are real steps: results do not depend on
+ * launch shapes) while timing the family kernel over its grid sizes (blocks
+ * per compute unit); for a plain sp1 ensemble it also
  * times the binning pass alone over its hash sizes and grids (its counts are
  * cleared and its escape tallies restored, so the ensemble and its stats are
  * unchanged).  Keeps the fastest of each.  chosen (host, may be NULL)
@@ -319,14 +324,15 @@ int wbrw_set_launch(wbrw_t h, const int32_t *cfg);
 int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen);
 
 /* Per-stage timing with hip events recorded on the handle's stream around
- * every kernel of a stage and around every whole step (enable == 1 starts a
- * fresh measurement; enable == 2 the same with whole steps marked only, two
- * events per step; enable == 0 stops recording).  Not used inside graph
+ * every kernel of a stage and around every group of steps (enable == 1 starts
+ * a fresh measurement; enable == 2 the same with groups of steps marked only,
+ * two events each; enable == 0 stops recording).  Not used inside graph
  * capture. */
 int wbrw_profile(wbrw_t h, int32_t enable);
 
 /* Synchronises, then writes for each stage s < WBRW_STAGE_COUNT the summed
- * kernel time in ms (ms[s]) and the number of timed launches (launches[s]). */
+ * kernel time in ms (ms[s]) and the number of timed launches (launches[s]; of
+ * steps for WBRW_STAGE_STEP). */
 int wbrw_profile_read(wbrw_t h, double *ms, int64_t *launches);
 
 /* Releases host-side state.  The workspace stays the caller's. */

@@ -329,10 +329,10 @@ class Simulation:
     LAUNCH_KEYS = ("stream_blocks", "family_blocks", "stream_threads", "stream_ppt", "bin_blocks", "bin_slots")
 
     def autotune(self, steps_per_candidate=1):
-        """Times the streaming kernel over its block shapes and grid sizes and the
-        family kernel over its grid sizes on real steps, and (plain sp1) the
-        binning pass over its hash sizes and grids without changing the
-        ensemble; keeps the fastest (results are unchanged by the choice).
+        """Times the kernel that takes the steps ("family") over its grid sizes on
+        real steps, and (plain sp1) the binning pass over its hash sizes and
+        grids without changing the ensemble; keeps the fastest (results are
+        unchanged by the choice).
         Returns the launch configuration (see launch())."""
         out = np.zeros(6, dtype=np.int32)
         _check(lib().wbrw_autotune(self.h, int(steps_per_candidate), out.ctypes.data_as(C.c_void_p)),
@@ -340,8 +340,9 @@ class Simulation:
         return dict(zip(self.LAUNCH_KEYS, (int(v) for v in out)))
 
     def launch(self):
-        """The launch configuration: grid sizes of the streaming, family and
-        binning kernels, the streaming block shape and the binning hash size."""
+        """The launch configuration: grid sizes of the family (steps) and binning
+        kernels and the binning hash size.  The streaming grid and block shape
+        are kept for callers that set them and change nothing."""
         out = np.zeros(6, dtype=np.int32)
         _check(lib().wbrw_get_launch(self.h, out.ctypes.data_as(C.c_void_p)), "wbrw_get_launch")
         return dict(zip(self.LAUNCH_KEYS, (int(v) for v in out)))
@@ -410,12 +411,14 @@ class Simulation:
 
     def profile(self, enable=True, steps_only=False):
         """Start (enable) or stop HIP-event timing on the handle's stream: every
-        stage and whole step, or whole steps only (two events per step)."""
+        stage and group of up to five steps, or groups of steps only (two events
+        each)."""
         mode = 0 if not enable else (2 if steps_only else 1)
         _check(lib().wbrw_profile(self.h, mode), "wbrw_profile")
 
     def profile_read(self):
-        """{stage: (total ms, launches)} of the kernels timed since profile(True)."""
+        """{stage: (total ms, launches)} of the kernels timed since profile(True);
+        "step" counts steps."""
         ms = np.zeros(len(self.STAGES))
         n = np.zeros(len(self.STAGES), dtype=np.int64)
         _check(lib().wbrw_profile_read(self.h, ms.ctypes.data_as(C.c_void_p),
