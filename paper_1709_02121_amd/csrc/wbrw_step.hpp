@@ -541,7 +541,7 @@ __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step
 // ---------------------------------------------------------------------------
 template <int DIM, bool SP2, bool TAN>
 struct Families {
-    static constexpr int kLds = DIM == 2 ? (SP2 ? 336 : 384) : 512;           // records whose payload is in LDS
+    static constexpr int kLds = DIM == 2 ? (SP2 ? 332 : 384) : 512;           // records whose payload is in LDS
     static constexpr int kRec = kLds + (DIM == 2 ? kGPool : 0); // records in all
     static constexpr int kQueue = DIM == 2 ? 192 : 128;         // further jumps of a round
     static constexpr int kLevels = 8;

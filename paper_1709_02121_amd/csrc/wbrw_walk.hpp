@@ -9,8 +9,10 @@
 //           step whether it jumps (exact clocks for a constant gamma0, Sec.
 //           3.2.1), keeping one bit each in LDS.  Then, step by step, it
 //           gathers the jumping particles of the range and of its offspring,
-//           in order, and takes their jumps (wbrw_step.hpp).  Offspring go to
-//           pages of the inactive buffer set, in order.
+//           in order, and takes their jumps (wbrw_step.hpp); where there are
+//           few, generation by generation: the range's jumps in all steps,
+//           then those of their offspring, and so on, by step and in order.
+//           Offspring go to pages of the inactive buffer set, in order.
 // k_place   puts the offspring of all tiles behind the particles, in the
 //           order of the whole ensemble's steps, and closes the chunk.
 //
@@ -23,7 +25,12 @@
 // first ancestor; within a class and tile by the tile's own order.  So the
 // place of a record is the sum of the lower classes, its class's records in
 // earlier tiles, and its index within its class and tile, and no step waits
-// for another tile.
+// for another tile.  Nor does a step wait for the one before: a particle goes
+// on with its wave vector whatever it leaves behind, so all steps' jumps of
+// the range can be one list, and the offspring of a generation, listed by step
+// and parent, are class by class in the order of the steps one by one.  (Step
+// by step a small ensemble's tile has a chain of five, each with a jump or
+// two.)
 //
 // Positions.  A particle's x in the array is its position at the last
 // materialisation (or at the end of the step of its birth, if later); its
@@ -181,8 +188,11 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *s_w, uint32
 constexpr uint32_t kLocal = 0x80000000u;
 struct WalkTile {
     int64_t i0, a0, limit;       // first particle, pages' base, offspring the pages hold
-    uint32_t nl, q0;             // offspring so far, event parents of step s that are done
-    int s, b, nr, i00, sh, npage;
+    uint32_t nl, q0;             // offspring so far, event parents of the list that are done
+    uint32_t g0, g1;             // the list's offspring
+    int s;                       // its step, or (merged) the generation
+    bool merged;                 // lists by generation
+    int b, nr, i00, sh, npage;
 };
 template <int DIM, bool SP2, bool TAN>
 struct WalkShared {
@@ -193,23 +203,27 @@ struct WalkShared {
     unsigned long long evl[kChunk][kWL];
     int64_t tal[5];
     int64_t limit;                // offspring the pages hold
-    WalkTile rest;                // what k_walk leaves to walk_rest
+    WalkTile rest;                // what k_walk leaves to walk_general, and gets back
     int32_t t;
     uint32_t wsum[2][4];
+    uint32_t total;               // event parents of the range, all steps
     uint32_t item[kThreads];      // event parents: index in the range, or
                                   // kLocal | index among the offspring
     uint32_t ccnt[kClasses];      // records of each class
-    uint32_t born[kChunk + 1];    // offspring at the start of each step
     uint32_t nst[kPend + 1];
     uint32_t page[kPages];
-    uint8_t cls[kThreads];        // the event parents' classes
+    uint8_t cls[kThreads];        // the step of the chunk the event parents jump in and,
+                                  // above its kStepBits, their classes
+    static constexpr int kStepBits = 3;
+    __device__ __forceinline__ int step(int slot) const { return cls[slot] & ((1 << kStepBits) - 1); }
+    static_assert(kChunk <= (1 << kStepBits) && (kClasses << kStepBits) <= 256, "a byte");
 };
 
-// Takes the event parents of tile T through steps T.s .. S - 1, batch by batch
-// (k_walk).  False where the families of a batch outgrow the pool, with what is
-// left to do in W.rest.  With GENERAL it is taken on from there, each family by
-// the general walk of one lane.
-template <int DIM, bool SP2, bool TAN, bool ONE, bool GENERAL>
+// Takes the event parents of tile T from generation T.g0 .. T.g1 on, batch by
+// batch (k_walk).  False where the families of a batch outgrow the pool, with
+// what is left to do in W.rest.  With GENERAL that batch alone is taken, each
+// family by the general walk of one lane.
+template <int DIM, bool SP2, bool TAN, bool ONE, bool GENERAL, bool MERGED>
 __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
                                            uint32_t par, WalkTile &T, WalkShared<DIM, SP2, TAN> &W, uint32_t &err)
 {
@@ -223,41 +237,55 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
     uint32_t nl = T.nl;                  // offspring of the tile so far
     auto barrier = [] { if (GENERAL) __syncthreads(); else lds_barrier(); };
     const int nw0 = (nr + 63) / 64;
-    int s = GENERAL ? T.s : 0;
-    uint32_t q0 = GENERAL ? T.q0 : 0u;
-    for (; s < S; ++s, q0 = 0u) {
-        const uint32_t step = step0 + (uint32_t)s;
+    int s0 = T.s;
+    uint32_t g0 = T.g0, g1 = T.g1, q0 = T.q0;
+    for (;; q0 = 0u) {
         const int FS = ghost ? fresh(self).gftile : fresh(self).ftile;   // event parents taken at a time
-        const uint32_t nl0 = q0 > 0u ? W.born[s] : nl;         // those of earlier steps
-        const int nw = nw0 + (int)((nl0 + 63u) / 64u);
-        if (tid == 0 && q0 == 0u) W.born[s] = nl0;
-        uint32_t np = 0;                 // event parents of the step
+        // the list: steps sa .. sz - 1, of each the range's bits (step by
+        // step, or the first generation) and those of offspring g0 .. g1 - 1
+        const uint32_t sa = MERGED ? 0u : (uint32_t)s0, sz = MERGED ? (uint32_t)S : sa + 1u;
+        const uint32_t nr0 = MERGED && s0 > 0 ? 0u : (uint32_t)nw0;
+        const uint32_t wa = g0 / 64u, nw = nr0 + (g1 + 63u) / 64u - wa;
+        uint32_t np = 0;                 // event parents of the list
         for (;; q0 += (uint32_t)FS) {
-            // event parents [q0, q0 + FS) of the step, in order: first
-            // the range's, then the offspring's
-            if (GENERAL || nl0 > (uint32_t)kLocalBits) __syncthreads(); else lds_barrier();
-            uint32_t run = 0;
-            for (int w0 = 0, it = 0; w0 < nw; w0 += kThreads, ++it) {
-                const int wi = w0 + tid, wl = wi - nw0;
+            // event parents [q0, q0 + FS) of the list, by step and in order
+            if (GENERAL || g1 > (uint32_t)kLocalBits) __syncthreads(); else lds_barrier();
+            uint32_t run = 0, s = sa, w = (uint32_t)tid;      // word w of step s
+            for (uint32_t w0 = 0, it = 0; w0 < nw * (sz - sa); w0 += kThreads, w += kThreads, ++it) {
+                if (MERGED)
+                    for (; w >= nw && s < sz; w -= nw) ++s;
+                const uint32_t wl = wa + w - nr0;
+                const bool loc = w >= nr0;
                 uint64_t m = 0;
-                if (wi < nw0) m = W.ev[s][wi];
-                else if (wi < nw && wl < WalkShared<DIM, SP2, TAN>::kWL) m = W.evl[s][wl];
-                else if (wi < nw)        // past the bits kept in LDS
-                    for (uint32_t q = 0; q < 64u && (uint32_t)wl * 64u + q < nl0; ++q)
-                        m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)[a0 + page_slot(W.page, sh, wl * 64 + q)] >>
-                                         (kChunk + s)) & 1u) << q;
+                if (MERGED ? s < sz : w < nw) {
+                    if (!loc) {
+                        m = W.ev[s][w];
+                    } else {
+                        if (wl < (uint32_t)WalkShared<DIM, SP2, TAN>::kWL) m = W.evl[s][wl];
+                        else             // past the bits kept in LDS
+                            for (uint32_t q = 0; q < 64u && wl * 64u + q < g1; ++q)
+                                m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)
+                                                 [a0 + page_slot(W.page, sh, wl * 64u + q)] >> (kChunk + s)) & 1u) << q;
+                        if (MERGED && wl == wa) m &= ~0ull << (g0 & 63u);
+                        if (MERGED && wl == g1 / 64u) m &= (1ull << (g1 & 63u)) - 1ull;
+                    }
+                }
                 uint32_t tot;
                 uint32_t pos = run + block_excl((uint32_t)__popcll(m), W.wsum[it & 1], tot);
+                if (pos >= q0 + (uint32_t)FS || pos + (uint32_t)__popcll(m) <= q0) m = 0;
                 while (m) {
                     const int k = __builtin_ctzll(m);
                     m &= m - 1ull;
-                    if (pos >= q0 && pos < q0 + (uint32_t)FS)
-                        W.item[pos - q0] = wi < nw0 ? (uint32_t)(wi * 64 + k) : kLocal | (uint32_t)(wl * 64 + k);
+                    if (pos >= q0 && pos < q0 + (uint32_t)FS) {
+                        W.item[pos - q0] = loc ? kLocal | (wl * 64u + (uint32_t)k) : w * 64u + (uint32_t)k;
+                        if (MERGED) W.cls[pos - q0] = (uint8_t)s;
+                    }
                     ++pos;
                 }
                 run += tot;
+                if (run >= q0 + (uint32_t)FS && np > 0u) break;     // (np is known)
             }
-            np = run;
+            if (np == 0u) np = run;
             if (q0 >= np) break;
             if (tid == 0) {
                 F.n = F.nq[0] = F.nq[1] = F.overflow = F.events = F.pairs = F.maxdepth = 0u;
@@ -272,6 +300,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 const Dev &d = fresh(self);
                 const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
                 const uint32_t it = W.item[ti];
+                const int s = MERGED ? W.step(ti) : s0;
                 const bool loc = (it & kLocal) != 0u;
                 const uint32_t l = it & ~kLocal;
                 const Ens *sets = ghost ? d.gens : d.ens;
@@ -290,13 +319,13 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 root.D[1] = TAN ? X.D[dstride + pi] : 0.0;
                 root.D[2] = TAN ? X.D[2 * dstride + pi] : 0.0;
                 int m;
-                if (loc) {
-                    W.cls[ti] = (uint8_t)((ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1));
-                    m = -1;              // steps since the one it was born in
-                    for (int q = 1; q <= s; ++q) m += l < W.born[q] ? 1 : 0;
-                } else {
-                    W.cls[ti] = 0;
+                if (!loc) {
+                    if (!MERGED) W.cls[ti] = 0;
                     m = pend + s - birth_of(W.nst, pend, (uint32_t)i00 + l);
+                } else {                 // steps since that of its birth, the class's highest
+                    const uint32_t cls = (ghost ? d.smaskg : d.smask)[pi] & (kClasses - 1);
+                    W.cls[ti] = (uint8_t)((MERGED ? s : 0) | (cls << W.kStepBits));
+                    m = s - 1 - (31 - __builtin_clz(cls));
                 }
                 root.x[0] = advanced(root.x[0], (d.vfac * root.k[0]) * d.dt, m);
                 if (DIM == 2) root.x[1] = advanced(root.x[1], (d.vfac * root.k[1]) * d.dt, m);
@@ -314,11 +343,12 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 int ti = wv / share * 64 + lane, m0 = wv % share;
                 Node cur;
                 uint64_t key = 0ull;
-                uint32_t rec = kNone;
+                uint32_t rec = kNone, step = step0 + (uint32_t)s0;
                 int slot = ti, lev = 0;
                 bool act = false;
                 if (ti < (int)nt && m0 < slots) {
                     cur = load_root(ti);
+                    if (MERGED) step = step0 + W.step(ti);
                     const Dev &d = fresh(self);
                     const InstParam &P = inst_param(d, b);
                     const W4 r = draw(cur.id, step, kTagStep, 0u, 0u, d.seed, P.key);
@@ -350,6 +380,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                         cur.e = F.qe[ti];
                         key = F.key[rec];
                         slot = F.slot[rec];
+                        if (MERGED) step = step0 + W.step(slot);
                         lev = key ? FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8 : 0;
                     }
                     if (tid == 0) F.nq[(round + 1) & 1] = 0u;
@@ -362,7 +393,9 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                         W.rest = T;
                         W.rest.nl = nl;
                         W.rest.q0 = q0;
-                        W.rest.s = s;
+                        W.rest.g0 = g0;
+                        W.rest.g1 = g1;
+                        W.rest.s = s0;
                         W.rest.npage = npage;
                         W.rest.limit = limit;
                     }
@@ -370,7 +403,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 }
             } else if (live) {
                 const Node root = load_root(tid);
-                F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step, &root, false, Ens{}, a0, 0, 0, W.page, sh, 0, &tal, &err);
+                F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step0 + (uint32_t)(MERGED ? W.step(tid) : s0), &root, false, Ens{}, a0, 0, 0, W.page, sh, 0, &tal, &err);
             }
             if (GENERAL) barrier();
             // 2. ordered exclusive scan of the families' record counts
@@ -410,11 +443,12 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             uint16_t *smask = ghost ? d.smaskg : d.smask;
             const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
             auto close_record = [&](int64_t li, uint64_t id, int slot) {
-                const uint32_t cls = (uint32_t)W.cls[slot] | (1u << s);
+                const int s = MERGED ? W.step(slot) : s0;
+                const uint32_t cls = (uint32_t)(W.cls[slot] >> W.kStepBits) | (1u << s);
                 uint32_t ev = 0;
                 const Clock c = clock_of(d, id, P.key);
-                for (int q = s + 1; q < S; ++q)
-                    if (clock_jumps(d, P, c, id, step0 + (uint32_t)q)) {
+                for (int q = MERGED ? 1 : s + 1; q < S; ++q)
+                    if ((!MERGED || q > s) && clock_jumps(d, P, c, id, step0 + (uint32_t)q)) {
                         ev |= 1u << q;
                         if (li < kLocalBits) atomicOr(&W.evl[q][li >> 6], 1ull << (li & 63));
                     }
@@ -461,7 +495,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     const Node root = load_root(tid);
                     Tally none{0, 0, 0, 0, 0};
                     const int64_t f = (int64_t)nl + (int64_t)excl;
-                    const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step, &root, true, A, a0, f, limit, W.page, sh,
+                    const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step0 + (uint32_t)(MERGED ? W.step(tid) : s0), &root, true, A, a0, f, limit, W.page, sh,
                                                                   dstride, &none, &err);
                     for (uint32_t r = 0; r < c && f + r < limit; ++r)
                         close_record(f + r, A.id[a0 + page_slot(W.page, sh, (uint32_t)(f + r))], tid);
@@ -480,30 +514,47 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 W.tal[2] += F.killed;
                 W.tal[4] = max(W.tal[4], (int64_t)F.maxdepth);
             }
+            if constexpr (GENERAL) {
+                T.nl = nl;
+                T.q0 = q0 + (uint32_t)FS;
+                T.npage = npage;
+                T.limit = limit;
+                return true;
+            }
             if (q0 + (uint32_t)FS >= np) break;
         }
+        ++s0;
+        if (MERGED) g0 = g1;             // the next generation
+        g1 = nl;
+        if (s0 == S || (MERGED && g0 == g1)) break;
     }
     T.npage = npage;
     return true;
 }
 
-// What is left of a tile whose families have outgrown the pool.  A function of
-// its own, called where k_walk holds nothing else: with the general walk's
-// calls inside the steps the common path spilt 100 vector registers and took
-// longer (256 instances 8.95 ms a pass and 7.63 so, barrier of 1e7 2.32 and
-// 2.12, of 1e4 1.02 and 0.88, weighted 1e7 1.78 and 1.52, 4D 12.3 and 11.2).
+// A value that is the same in all lanes, for scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
+}
+
+// A batch whose families have outgrown the pool.  A function of its own, called
+// where k_walk holds nothing else: with the general walk's calls inside the
+// steps the common path spilt 100 vector registers and took longer (256
+// instances 8.95 ms a pass and 7.63 so, barrier of 1e7 2.32 and 2.12, of 1e4
+// 1.02 and 0.88, weighted 1e7 1.78 and 1.52, 4D 12.3 and 11.2).
 template <int DIM, bool SP2, bool TAN>
-__device__ __noinline__ uint32_t walk_rest(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
+__device__ __noinline__ uint32_t walk_general(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
                                            uint32_t par, WalkShared<DIM, SP2, TAN> *W)
 {
-    const uint64_t p = (uint64_t)self;
-    const Dev *uniform = (const Dev *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(p >> 32)) << 32) |
-                                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p));
+    const Dev *uniform = (const Dev *)uniform64((int64_t)self);
     WalkTile T = W->rest;
     T.b = __builtin_amdgcn_readfirstlane(T.b);
     uint32_t err = 0;
-    walk_steps<DIM, SP2, TAN, false, true>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
-    if (threadIdx.x == 0) W->rest.npage = T.npage;
+    if (DIM == 1 && T.merged) walk_steps<DIM, SP2, TAN, false, true, DIM == 1>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
+    else walk_steps<DIM, SP2, TAN, false, true, false>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
+    if (threadIdx.x == 0) W->rest = T;
     __syncthreads();
     return err;
 }
@@ -550,6 +601,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
         }
         for (int q = tid; q < kChunk * kWL; q += kThreads) (&W.evl[0][0])[q] = 0ull;
         if (tid < kClasses) W.ccnt[tid] = 0u;
+        if (tid == 0) W.total = 0u;
         lds_barrier();
         const int64_t t = __builtin_amdgcn_readfirstlane(W.t);
         if (t >= ntiles) break;
@@ -557,6 +609,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
         // on; its offspring go to pages of 2^sh slots behind a0
         int b, nr, i00, sh;
         int64_t i0, a0, limit;
+        bool merged;
         {
             const Dev &d = fresh(self);
             const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
@@ -593,6 +646,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             const InstParam &P = inst_param(d, b);
             const uint64_t *ids = (ghost ? d.gens : d.ens)[set].id + i0;
             uint64_t id = ids[min(tid, nr - 1)];
+            uint32_t nev = 0;
             for (int j = 0; j * kThreads < nr; ++j) {
                 const int li = j * kThreads + tid;
                 const uint64_t cur = id;
@@ -606,15 +660,36 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                     if (band)
                         m |= band & __ballot(clock_exact(cur, step0 + (uint32_t)s, d.seed, P.key, P.thr_lo, P.thr_hi,
                                                          P.gamma0, d.dt));
-                    if (lane == 0) W.ev[s][j * (kThreads / 64) + wv] = m & in;
+                    m &= in;
+                    nev += (uint32_t)__popcll(m);
+                    if (lane == 0) W.ev[s][j * (kThreads / 64) + wv] = m;
                 }
             }
+            // Do all steps' jumps of the range fit one list?  (1e4 barrier: the
+            // kernel takes 44.5 us step by step and 31.5 so, 2e5 cat state 61
+            // and 45; at 1e7, whose tiles find 440 jumps for 256 threads,
+            // lists of all steps took 284 us and single steps 264.  4D step by
+            // step: its ensembles are large, and the second path alone cost
+            // them 1 %.)
+            merged = DIM == 1 && S > 1;
+            if (merged) {
+                if (lane == 0 && nev) atomicAdd(&W.total, nev);
+                lds_barrier();
+                merged = __builtin_amdgcn_readfirstlane((int)W.total) <= (ghost ? d.gftile : d.ftile);
+            }
         }
-        WalkTile T{i0, a0, limit, 0u, 0u, 0, b, nr, i00, sh, 1};
-        if (!walk_steps<DIM, SP2, TAN, ONE, false>(self, ghost, S, pend, set, step0, par, T, W, err)) {
+        WalkTile T{i0, a0, limit, 0u, 0u, 0u, 0u, 0, merged, b, nr, i00, sh, 1};
+        while (!(DIM == 1 && merged ? walk_steps<DIM, SP2, TAN, ONE, false, DIM == 1>(self, ghost, S, pend, set, step0, par, T, W, err)
+                        : walk_steps<DIM, SP2, TAN, ONE, false, false>(self, ghost, S, pend, set, step0, par, T, W, err))) {
             __syncthreads();
-            err |= walk_rest<DIM, SP2, TAN>(self, ghost, S, pend, set, step0, par, &W);
-            T.npage = W.rest.npage;
+            err |= walk_general<DIM, SP2, TAN>(self, ghost, S, pend, set, step0, par, &W);
+            T.nl = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.nl);
+            T.q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.q0);
+            T.g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.g0);
+            T.g1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.g1);
+            T.s = __builtin_amdgcn_readfirstlane(W.rest.s);
+            T.npage = __builtin_amdgcn_readfirstlane(W.rest.npage);
+            T.limit = uniform64(W.rest.limit);
         }
         const int npage = T.npage;
         lds_barrier();
@@ -625,7 +700,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
             uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
             const uint32_t c = W.ccnt[tid];
-            wcnt[t * kClasses + tid] = c;
+            wcnt[t * kClasses + tid] = tid ? c : (uint32_t)merged;      // (no class 0)
             if (c) atomicAdd(&wsup[(t / kSupGroup) * kClasses + tid], c);
             if (c && B > kFewInst) atomicAdd(&d.wtot[((int64_t)ghost * B + b) * kClasses + tid], c);
         }
@@ -738,13 +813,19 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         const int64_t base = ghost ? P.gbase : P.base;
         const int64_t cap = ghost ? P.gcap : P.cap;
         const int sh = (int)d.wrange[2 * ((int64_t)(2 * par + ghost) * B + b) + 1];
-        if (tid < kClasses) {   // lower classes, earlier tiles, less the class's start in the tile
+        if (tid < kClasses) {
+            // lower classes, earlier tiles, less the class's start in the tile:
+            // a tile holds its offspring by class, or (where k_walk merged the
+            // steps, s_own[0]) by generation, then by class
             uint32_t o = s_below[tid];
-            for (int c = 0; c < tid; ++c) o += s_tot[c] - s_own[c];
+            for (int c = 1; c < kClasses; ++c) {
+                const int order = s_own[0] ? __popc(c) - __popc(tid) : 0;
+                o += (c < tid ? s_tot[c] : 0u) - (order < 0 || (order == 0 && c < tid) ? s_own[c] : 0u);
+            }
             s_off[tid] = o;
         }
         uint32_t nrec = 0;
-        for (int c = 0; c < kClasses; ++c) nrec += s_own[c];
+        for (int c = 1; c < kClasses; ++c) nrec += s_own[c];
         __syncthreads();
         const int64_t n0 = d.Nbase[(int64_t)ghost * B + b];
         for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {

@@ -86,11 +86,13 @@ def _crowded(gdt, kind, n0):
     return cfg
 
 
-@pytest.mark.parametrize("kind,gdt,n0,steps", [("sp1", 0.2, 1_250_000, 3), ("sp1", 0.3, 700_000, 2), ("sp1", 1.2, 3000, 2),
+@pytest.mark.parametrize("kind,gdt,n0,steps", [("sp1", 0.2, 1_250_000, 3), ("sp1", 0.2, 250_000, 5), ("sp1", 0.3, 700_000, 2),
+                                               ("sp1", 1.2, 3000, 2),
                                                ("sp2", 1.2, 3000, 2), ("tangent", 2.0, 3000, 2), ("pairs", 1.2, 3000, 1)])
 def test_families_beyond_the_pool(P, O, kind, gdt, n0, steps):  # noqa: F811
     """Tiles of which some batch outgrows the pool, in the first step of a
-    launch and in later ones."""
+    launch and in later ones, and (250 000: some 230 jumps of five steps in a
+    tile, 224 to a batch) in one list of all steps or step by step."""
     cfg = _crowded(gdt, kind, n0)
     g, r = P.Simulation(cfg), O.OracleSim(cfg)
     for n in (steps, 1):
