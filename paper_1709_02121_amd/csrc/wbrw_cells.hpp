@@ -79,7 +79,7 @@ __device__ __forceinline__ void load_births(const Dev &d, int ghost, int b, int 
 {
     if ((int)threadIdx.x < pend)
         B.nst[threadIdx.x] = (uint32_t)d.nstep[((int64_t)ghost * d.B + b) * (kPend + 1) + threadIdx.x];
-    __syncthreads();
+    block_sync();
 }
 // Steps that instance-particle li has to be advanced by.  The particles of a
 // tile, [l0, l1), mostly have the same number (>= 0), else tile_steps is -1.
@@ -626,13 +626,13 @@ __global__ __launch_bounds__(kThreads) void k_scan_sums(Dev d)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
         if (lane == 0) s_w[wv] = sum;
-        __syncthreads();
+        block_sync();
         if (tid == 0) {
             uint64_t tot = 0;
             for (int q = 0; q < kThreads / 64; ++q) tot += s_w[q];
             d.stS[t] = tot;
         }
-        __syncthreads();
+        block_sync();
     }
 }
 
@@ -689,7 +689,7 @@ __global__ __launch_bounds__(kThreads) void k_close_scan(Dev d)
         }
         d.Nnew[b] = n;
     }
-    __syncthreads();
+    block_sync();
     block_plan(d.tileR, d.Nnew, B, kTileR);
 }
 
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kThreads) void k_scan(Dev d, int zero_counts)
             if (lane == 63) s_tot[j * kW + wv] = incl;
             ex[j] = incl - a;
         }
-        __syncthreads();
+        block_sync();
         if (wv == 0) {   // exclusive scan of the kPPT * kW totals, in place
             const uint32_t a = lane < kPPT * kW ? s_tot[lane] : 0u;
             uint32_t incl = a;
@@ -740,7 +740,7 @@ __global__ __launch_bounds__(kThreads) void k_scan(Dev d, int zero_counts)
             }
             if (lane < kPPT * kW) s_tot[lane] = incl - a;
         }
-        __syncthreads();
+        block_sync();
         const int64_t tbase = (int64_t)(d.stS[t] - d.stS[(int64_t)b * tiles_per]);
         const InstParam &P = d.ip[b];
         int64_t *rst = d.rstart + P.rbase;
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(kThreads) void k_scan(Dev d, int zero_counts)
                 rst[q] = c;
             if (zero_counts && v[j] != 0) d.cnt[cbase + c] = 0;
         }
-        __syncthreads();
+        block_sync();
     }
 }
 
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(kThreads) void k_regen(Dev d)
     constexpr int kCells = 2048;
     __shared__ int64_t s_off[kCells];
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        __syncthreads();
+        block_sync();
         const int b = segment_of(d.tileR, B, t);
         const InstParam &P = d.ip[b];
         const int64_t nout = d.Nnew[b];
@@ -805,7 +805,7 @@ __global__ __launch_bounds__(kThreads) void k_regen(Dev d)
         const bool staged = span <= kCells;
         if (staged)
             for (int c = tid; c < (int)span; c += kThreads) s_off[c] = off[nu_lo + c];
-        __syncthreads();
+        block_sync();
 #pragma unroll
         for (int j = 0; j < kTileR / kThreads; ++j) {
             const int64_t o = q * kTileR + (int64_t)j * kThreads + tid;
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(kThreads) void k_close_regen(Dev d)
         d.N[b] = d.Nnew[b];
         d.tally[(int64_t)b * kTalCount + kTalAnn] += 1;
     }
-    __syncthreads();
+    block_sync();
     block_plan(d.tileA, d.N, B, kTileA);
     for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)b * (kPend + 1)] = d.N[b];
     plan_walk(d, ctl->chunk & 1u, 0, d.N);
@@ -909,7 +909,7 @@ __global__ __launch_bounds__(kThreads) void k_density_bin(Dev d, int ghost, int 
         for (int j = tid; j < width; j += kThreads) s_raw[j] = 0ull;
     int cb = -1;
     auto flush = [&](int fb) {
-        __syncthreads();
+        block_sync();
         for (int j = tid; j < width; j += kThreads) {
             const uint64_t v = s_raw[j];
             if (v == 0ull) continue;
@@ -922,10 +922,10 @@ __global__ __launch_bounds__(kThreads) void k_density_bin(Dev d, int ghost, int 
                 atomicAdd((unsigned long long *)&dx[(int64_t)fb * d.max_bins + j], (unsigned long long)v);
             }
         }
-        __syncthreads();
+        block_sync();
     };
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        __syncthreads();
+        block_sync();
         const int b = segment_of(plan, B, t);
         if (priv && b != cb) {
             if (cb >= 0) flush(cb);

@@ -247,6 +247,28 @@ __host__ __device__ __forceinline__ int64_t walk_range(int64_t n, int32_t tiles,
     const int64_t r = ((n + t - 1) / t + kRangeMin - 1) / kRangeMin * kRangeMin;
     return r < kRangeMin ? kRangeMin : (r > most ? most : r);
 }
+// Synchronises the block.  The wait is spelt out: a barrier at the top of a
+// loop can lose the one that its fence asks for, where nothing is under way
+// before the loop but LDS operations of the loop's end are (the pass that
+// places waits drops it on its first visit and does not put it back when it
+// comes round).  Wavefronts then read what others had yet to write: the cell
+// pass lost a few hundred of 2e7 particles in one annihilation of fifty.
+__device__ __forceinline__ void block_sync()
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+// The same where only LDS is shared: stores to global memory may still be
+// under way.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // An annihilation kernel enqueued after a step of wbrw_run_adaptive does
 // nothing unless that step's closing kernel asked for the annihilation.
 __device__ __forceinline__ bool ann_skipped(const Dev &d)
@@ -418,7 +440,7 @@ __device__ __forceinline__ uint64_t scan_chunks(const uint64_t *cnt, uint64_t *p
     uint64_t carry = 0;
     for (int64_t c0 = 0; c0 < T; c0 += C) {
         const int n = (int)min((int64_t)C, T - c0);
-        __syncthreads();
+        block_sync();
         uint64_t v[P], acc = 0;
 #pragma unroll
         for (int r = 0; r < P; ++r)   // clamped, unconditional: no branch between the loads
@@ -428,7 +450,7 @@ __device__ __forceinline__ uint64_t scan_chunks(const uint64_t *cnt, uint64_t *p
             const int i = r * kThreads + tid;
             s_v[i + i / P] = v[r];
         }
-        __syncthreads();
+        block_sync();
 #pragma unroll
         for (int r = 0; r < P; ++r) {
             v[r] = tid * P + r < n ? s_v[run0 + r] : 0ull;
@@ -441,7 +463,7 @@ __device__ __forceinline__ uint64_t scan_chunks(const uint64_t *cnt, uint64_t *p
             if (lane >= o) incl += y;
         }
         if (lane == 63) s_w[wv] = incl;
-        __syncthreads();
+        block_sync();
         uint64_t below = 0, chunk = 0;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -455,7 +477,7 @@ __device__ __forceinline__ uint64_t scan_chunks(const uint64_t *cnt, uint64_t *p
             s_v[run0 + r] = run;
             run += v[r];
         }
-        __syncthreads();
+        block_sync();
 #pragma unroll
         for (int r = 0; r < P; ++r) {
             const int i = r * kThreads + tid;
@@ -463,7 +485,7 @@ __device__ __forceinline__ uint64_t scan_chunks(const uint64_t *cnt, uint64_t *p
         }
         carry += chunk;
     }
-    __syncthreads();
+    block_sync();
     return carry;
 }
 
@@ -487,7 +509,7 @@ __device__ __forceinline__ void block_prefix(int64_t *plan, int B, F value)
             plan[1] = value(0);
             plan[0] = 0;
         }
-        __syncthreads();
+        block_sync();
         return;
     }
     __shared__ int64_t s_w[kThreads / 64];
@@ -501,9 +523,9 @@ __device__ __forceinline__ void block_prefix(int64_t *plan, int B, F value)
             const int64_t y = __shfl_up(incl, o, 64);
             if (lane >= o) incl += y;
         }
-        __syncthreads();
+        block_sync();
         if (lane == 63) s_w[wv] = incl;
-        __syncthreads();
+        block_sync();
         int64_t below = 0, chunk = 0;
 #pragma unroll
         for (int w = 0; w < kThreads / 64; ++w) {
@@ -515,7 +537,7 @@ __device__ __forceinline__ void block_prefix(int64_t *plan, int B, F value)
         carry += chunk;
     }
     if (tid == 0) plan[B] = carry;
-    __syncthreads();
+    block_sync();
 }
 
 // plan[b] = sum_{b' < b} ceil(cnt[b'] / tile), plan[B] = total; one block.

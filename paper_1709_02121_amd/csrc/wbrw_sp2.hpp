@@ -60,9 +60,9 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long v, un
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    __syncthreads();
+    block_sync();
     if (lane == 0) s_w[wv] = v;
-    __syncthreads();
+    block_sync();
     unsigned long long t = 0;
     if (threadIdx.x == 0)
         for (int q = 0; q < kThreads / 64; ++q) t += s_w[q];
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_classify(Dev d, int pend)
         if (b != cb) {
             if (cb >= 0) publish(cb, false);
             cb = b;
-            __syncthreads();
+            block_sync();
             load_births(d, 0, b, pend, s_births);
         }
         const InstParam &P = d.ip[b];
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_close_classify(Dev d, int grid
     if (lds)
         for (int b = tid; b < B; b += kThreads)
             for (int q = 0; q < 5; ++q) s_acc[q][b] = 0;
-    __syncthreads();
+    block_sync();
     for (int g = tid; g < grid; g += kThreads) {
         const int64_t *F = d.fpart + (int64_t)g * 8;
         if (F[0] < 0) continue;
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_close_classify(Dev d, int grid
             }
         }
     }
-    __syncthreads();
+    block_sync();
     if (lds)
         for (int b = tid; b < B; b += kThreads) {
             int64_t *st = d.bcls_stat + (int64_t)b * 8;
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_resid(Dev d)
             if (cb >= 0) publish(cb, false);
             cb = b;
         }
-        __syncthreads();
+        block_sync();
         const InstParam &P = d.ip[b];
         const int64_t n = d.N[b];
         const int64_t *st = d.bcls_stat + (int64_t)b * 8;
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_resid(Dev d)
             }
             if ((tid & 63) == 0) { s_wlo[c][tid >> 6] = lo; s_whi[c][tid >> 6] = hi; }
         }
-        __syncthreads();
+        block_sync();
         if (tid == 0) {
             for (int c = 0; c < 2; ++c) {
                 u128 sum = 0;
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_resid(Dev d)
                 st128(d.bTile + 2 * ((int64_t)c * d.tstride + t), sum);
             }
         }
-        __syncthreads();
+        block_sync();
     }
     publish(cb, true);
 }
@@ -334,7 +334,7 @@ __device__ __forceinline__ void scan_u128_exclusive(uint64_t *v, int64_t t0, int
     u128 carry = 0;
     for (int64_t c0 = t0; c0 < t1; c0 += C) {
         const int n = (int)min((int64_t)C, t1 - c0);
-        __syncthreads();
+        block_sync();
         u128 x[P];
 #pragma unroll
         for (int r = 0; r < P; ++r)   // clamped, unconditional: no branch between the loads
@@ -345,7 +345,7 @@ __device__ __forceinline__ void scan_u128_exclusive(uint64_t *v, int64_t t0, int
             s_lo[i + i / P] = (uint64_t)x[r];
             s_hi[i + i / P] = (uint64_t)(x[r] >> 64);
         }
-        __syncthreads();
+        block_sync();
         u128 acc = 0;
 #pragma unroll
         for (int r = 0; r < P; ++r) {
@@ -363,7 +363,7 @@ __device__ __forceinline__ void scan_u128_exclusive(uint64_t *v, int64_t t0, int
             }
         }
         if (lane == 63) { s_wlo[wv] = lo; s_whi[wv] = hi; }
-        __syncthreads();
+        block_sync();
         u128 below = 0, chunk = 0;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
@@ -378,7 +378,7 @@ __device__ __forceinline__ void scan_u128_exclusive(uint64_t *v, int64_t t0, int
             s_hi[run0 + r] = (uint64_t)(run >> 64);
             run += x[r];
         }
-        __syncthreads();
+        block_sync();
 #pragma unroll
         for (int r = 0; r < P; ++r) {
             const int i = r * kThreads + tid;
@@ -386,7 +386,7 @@ __device__ __forceinline__ void scan_u128_exclusive(uint64_t *v, int64_t t0, int
         }
         carry += chunk;
     }
-    __syncthreads();
+    block_sync();
 }
 
 __global__ __launch_bounds__(kThreads) void k_sp2_tilescan(Dev d, int rgrid)
@@ -423,7 +423,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_tilescan(Dev d, int rgrid)
             d.Nnew[b] = st[kBNr0];            // staging for the draw plan (class 0)
             d.NGnew[b] = st[kBNr1];           // (class 1)
         }
-        __syncthreads();
+        block_sync();
     }
 }
 
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_prefix(Dev d)
         }
         for (int c = 0; c < 2; ++c) {
             const int64_t Nr = st[kBNr0 + c];
-            __syncthreads();                  // s_lo, s_hi free again
+            block_sync();                  // s_lo, s_hi free again
             if (Nr <= 0) continue;
             const u128 tb = ld128(d.bTile + 2 * ((int64_t)c * d.tstride + t));
             uint64_t elo[kPPT], ehi[kPPT];    // exclusive within (row, wavefront)
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_prefix(Dev d)
                 elo[j] = lo - v;
                 ehi[j] = hi - (lo < v ? 1ull : 0ull);
             }
-            __syncthreads();
+            block_sync();
             if (wv == 0) {   // exclusive scan of the kPPT * kW totals, in place
                 const uint64_t v0 = lane < kPPT * kW ? s_lo[lane] : 0ull;
                 const uint64_t v1 = lane < kPPT * kW ? s_hi[lane] : 0ull;
@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kThreads) void k_sp2_prefix(Dev d)
                 const uint64_t xlo = lo - v0, xhi = hi - v1 - (lo < v0 ? 1ull : 0ull);
                 if (lane < kPPT * kW) { s_lo[lane] = xlo; s_hi[lane] = xhi; }
             }
-            __syncthreads();
+            block_sync();
             const int gb = sp2_guide_bits(Nr);
             const u128 R = (u128)(uint64_t)st[kBS0 + c] * (u128)(uint64_t)Nr;
             int32_t *G = d.bG + 4 * ((int64_t)c * C + P.base);
@@ -832,7 +832,7 @@ __global__ __launch_bounds__(kThreads) void k_ghosts(Dev d)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     for (;;) {
         if (tid == 0) s_t = next_tile(&ctl->ticket[kPassGhost], ntiles);
-        __syncthreads();
+        block_sync();
         const int64_t t = s_t;
         if (t >= ntiles) break;
         const int b = (int)(t / tiles_per);
@@ -851,7 +851,7 @@ __global__ __launch_bounds__(kThreads) void k_ghosts(Dev d)
             if (lane >= o) incl += y;
         }
         if (lane == 63) s_wsum[wv] = incl;
-        __syncthreads();
+        block_sync();
         uint32_t woff = 0, agg = 0;
         for (int q = 0; q < 4; ++q) { if (q < wv) woff += s_wsum[q]; agg += s_wsum[q]; }
         if (wv == 0) {
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(kThreads) void k_ghosts(Dev d)
                 s_excl = excl;
             }
         }
-        __syncthreads();
+        block_sync();
         int64_t gi = (int64_t)s_excl + (int64_t)(woff + incl - sum);
         for (int j = 0; j < kPPT; ++j) {
             const int64_t c = c0 + j;
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(kThreads) void k_ghosts(Dev d)
 #pragma unroll
             for (int q = 0; q < 6; ++q) d.Tq[(cbase + c) * 6 + q] = 0;
         }
-        __syncthreads();
+        block_sync();
     }
 }
 
@@ -903,7 +903,7 @@ __global__ __launch_bounds__(kThreads) void k_close_ghosts(Dev d)
         if (n > d.ip[b].gcap) { atomicOr(&ctl->err, kErrCapacity); n = d.ip[b].gcap; }
         d.NG[b] = n;
     }
-    __syncthreads();
+    block_sync();
     block_plan(d.tileA + (B + 1), d.NG, B, kTileA);
     for (int b = threadIdx.x; b < B; b += kThreads) d.nstep[(int64_t)(B + b) * (kPend + 1)] = d.NG[b];
     plan_walk(d, ctl->chunk & 1u, 1, d.NG);

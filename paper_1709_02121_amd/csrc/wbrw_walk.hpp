@@ -143,15 +143,6 @@ __device__ __forceinline__ bool clock_jumps(const Dev &d, const InstParam &P, co
     return j;
 }
 
-// Synchronises the block where only LDS is shared: stores to global memory
-// may still be under way.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Inclusive scan of v over the wavefront, by data-parallel moves within rows
 // of 16 lanes and broadcasts of the rows' last lanes (all 64 lanes call).
 __device__ __forceinline__ uint32_t wave_incl(uint32_t v)
@@ -235,7 +226,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
     int npage = T.npage;
     int64_t limit = T.limit;
     uint32_t nl = T.nl;                  // offspring of the tile so far
-    auto barrier = [] { if (GENERAL) __syncthreads(); else lds_barrier(); };
+    auto barrier = [] { if (GENERAL) block_sync(); else lds_barrier(); };
     const int nw0 = (nr + 63) / 64;
     int s0 = T.s;
     uint32_t g0 = T.g0, g1 = T.g1, q0 = T.q0;
@@ -249,7 +240,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
         uint32_t np = 0;                 // event parents of the list
         for (;; q0 += (uint32_t)FS) {
             // event parents [q0, q0 + FS) of the list, by step and in order
-            if (GENERAL || g1 > (uint32_t)kLocalBits) __syncthreads(); else lds_barrier();
+            if (GENERAL || g1 > (uint32_t)kLocalBits) block_sync(); else lds_barrier();
             uint32_t run = 0, s = sa, w = (uint32_t)tid;      // word w of step s
             for (uint32_t w0 = 0, it = 0; w0 < nw * (sz - sa); w0 += kThreads, w += kThreads, ++it) {
                 if (MERGED)
@@ -293,7 +284,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             }
             F.cnt[tid] = 0u;
             F.head[tid] = kNone;
-            __syncthreads();
+            block_sync();
             const bool live = tid < FS && q0 + (uint32_t)tid < np;
             // event parent ti at the start of the step
             auto load_root = [&](int ti) {
@@ -362,7 +353,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     const InstParam &P = inst_param(d, b);
                     if (act)
                         take_jump<DIM, SP2, TAN, ONE>(d, P, step, round, cur, key, lev, slot, rec, m0, share, F);
-                    if (DIM == 2) __syncthreads(); else lds_barrier();   // 4D records may be in HBM
+                    if (DIM == 2) block_sync(); else lds_barrier();   // 4D records may be in HBM
                     nt = F.nq[round & 1];
                     if (nt == 0u || F.overflow) break;
                     share = slots == 1 || nt > 128u ? 1 : (nt > 64u ? 2 : 4);
@@ -555,7 +546,7 @@ __device__ __noinline__ uint32_t walk_general(const Dev *self, int ghost, int S,
     if (DIM == 1 && T.merged) walk_steps<DIM, SP2, TAN, false, true, DIM == 1>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
     else walk_steps<DIM, SP2, TAN, false, true, false>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
     if (threadIdx.x == 0) W->rest = T;
-    __syncthreads();
+    block_sync();
     return err;
 }
 
@@ -681,7 +672,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
         WalkTile T{i0, a0, limit, 0u, 0u, 0u, 0u, 0, merged, b, nr, i00, sh, 1};
         while (!(DIM == 1 && merged ? walk_steps<DIM, SP2, TAN, ONE, false, DIM == 1>(self, ghost, S, pend, set, step0, par, T, W, err)
                         : walk_steps<DIM, SP2, TAN, ONE, false, false>(self, ghost, S, pend, set, step0, par, T, W, err))) {
-            __syncthreads();
+            block_sync();
             err |= walk_general<DIM, SP2, TAN>(self, ghost, S, pend, set, step0, par, &W);
             T.nl = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.nl);
             T.q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.q0);
@@ -746,10 +737,10 @@ __device__ __forceinline__ void class_sums(const uint32_t *wcnt, const uint32_t 
         return v;
     };
     const uint32_t v0 = sum(a, m), v1 = sum(m, z);
-    __syncthreads();
+    block_sync();
     s_red[tid] = v0;
     s_red[kThreads + tid] = v1;
-    __syncthreads();
+    block_sync();
     below = total = 0;
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
@@ -805,10 +796,10 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         } else if (tid < kClasses) {
             s_below[tid] += s_own[tid];
         }
-        __syncthreads();
+        block_sync();
         if (tid < kClasses) s_own[tid] = wcnt[t * kClasses + tid];
         if (tid >= kThreads - kPages) s_page[tid - (kThreads - kPages)] = ptab[t * kPages + tid - (kThreads - kPages)];
-        __syncthreads();
+        block_sync();
         const InstParam &P = d.ip[b];
         const int64_t base = ghost ? P.gbase : P.base;
         const int64_t cap = ghost ? P.gcap : P.cap;
@@ -826,7 +817,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         }
         uint32_t nrec = 0;
         for (int c = 1; c < kClasses; ++c) nrec += s_own[c];
-        __syncthreads();
+        block_sync();
         const int64_t n0 = d.Nbase[(int64_t)ghost * B + b];
         for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
             const int64_t i = base + page_slot(s_page, sh, r);
@@ -857,7 +848,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
             if (TAN)
                 for (int c = 0; c < 3; ++c) E.D[c * dstride + o] = D[c];
         }
-        __syncthreads();
+        block_sync();
     }
     if (err) atomicOr(&ctl->err, err);
 }
@@ -895,7 +886,7 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
     if (lds)
         for (int b = tid; b < B; b += kThreads)
             for (int q = 0; q < 5; ++q) s_acc[q][b] = 0;
-    __syncthreads();
+    block_sync();
     for (int g = tid; g < fgrid; g += kThreads) {
         const int64_t *F = d.fpart + (int64_t)g * 8;
         if (F[0] < 0) continue;
@@ -913,7 +904,7 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
             if (F[5]) atomicMax((unsigned long long *)&T[kTalMaxDepth], (unsigned long long)F[5]);
         }
     }
-    __syncthreads();
+    block_sync();
     int over = 0;         // an instance of this thread holds more than ann_limit
     // counts from the class totals: by all threads from the tiles' counts
     // where there are few instances, else kept per instance by k_walk (whose
@@ -951,9 +942,9 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
             uint32_t below, tot;
             class_sums(wcnt, wsup, plan[b], plan[b], plan[b + 1], s_red, below, tot);
             if (tid < kClasses) s_tot[tid] = tot;
-            __syncthreads();
+            block_sync();
             if (tid == 0) finish(b, [&](int c) { return s_tot[c]; });
-            __syncthreads();
+            block_sync();
         }
     } else {
         for (int b = tid; b < B; b += kThreads) {
@@ -965,7 +956,12 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
     // conditional annihilation after this step (chunks of one step):
     // scheduled, or an instance about to outgrow the threshold (the real
     // ensemble's closing block)
-    const int any_over = __syncthreads_or(over);
+    __shared__ int s_over;
+    if (tid == 0) s_over = 0;
+    block_sync();
+    if (over) s_over = 1;
+    block_sync();
+    const int any_over = s_over;
     if (d.cond_ann && !ghost && tid == 0) {
         const bool sched = d.ann_every > 0 && (step + (uint32_t)S) % (uint32_t)d.ann_every == 0u;
         ctl->ann_now = (sched || any_over) ? 1u : 0u;

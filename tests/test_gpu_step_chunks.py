@@ -140,3 +140,36 @@ def test_runs_of_equal_cells(P, O, n0, kind):  # noqa: F811
         g.step(6)
         r.step(6)
         _compare_all(g, r, cfg, f"runs {n0}")
+
+
+def test_cell_sums_over_many_annihilations(P):  # noqa: F811
+    """1e7 particles, 100 annihilations whose cell passes empty their tables
+    many times: every cell's net sign is that of the particles before, counted
+    by torch."""
+    import ctypes as C
+
+    import torch
+    cfg = W.gaussian_barrier_large("sp1")
+    g = cfg["grid"]
+    dx, dk = (g["x_hi"] - g["x_lo"]) / g["nx"], (g["k_hi"] - g["k_lo"]) / g["nk"]
+    s = P.Simulation(cfg)
+
+    def net():
+        n = s.count()
+        x, k = (torch.empty(n, dtype=torch.float64, device="cuda") for _ in range(2))
+        sign = torch.empty(n, dtype=torch.int8, device="cuda")
+        torch.cuda.synchronize()
+        assert P.lib().wbrw_export(s.h, 0, 0, n, *(C.c_void_p(t.data_ptr()) for t in (x, k, sign)),
+                                   None, None, None) == P.OK
+        qx, qk = (x - g["x_lo"]) / dx, (k - g["k_lo"]) / dk
+        inside = (qx >= 0) & (qx < g["nx"]) & (qk >= 0) & (qk < g["nk"])
+        cell = qx.floor().long() + g["nx"] * qk.floor().long()
+        return torch.zeros(g["nx"] * g["nk"], dtype=torch.int64, device="cuda").index_add_(
+            0, cell[inside], sign[inside].long())
+
+    for ep in range(100):
+        s.step(10)
+        before = net()
+        s.annihilate()
+        assert torch.equal(net(), before), f"annihilation {ep}"
+    say(f"many annihilations: n={s.count()}")
