@@ -404,10 +404,9 @@ int persistent_blocks(K kernel, int cus, int nt = kThreads)
     return std::min(blocks_per_cu(kernel, nt) * cus, kMaxGrid);
 }
 
-// Streaming block shapes (threads, particles per thread; a tile is always
-// kTileA particles) and binning hash sizes the autotuner chooses among.
-// The 4D streaming kernel holds five values per particle, too many for 16
-// particles per thread, so shape 1 is 1D only.
+// Streaming block shapes that a launch configuration may name (they have no
+// effect, see wbrw_get_launch; shape 1 in 1D only) and the binning hash sizes
+// the autotuner chooses among.
 constexpr int kStreamShapes[3][2] = {{kThreads, kPPT}, {128, 16}, {512, 4}};
 constexpr int kBinSlots[3] = {4096, 2048, 8192};
 
@@ -1635,9 +1634,9 @@ int wbrw_set_launch(wbrw_t h, const int32_t *cfg)
     return WBRW_OK;
 }
 
-// Candidates: every streaming shape at 1..(its occupancy) blocks per CU
-// (from the list below), the family kernel likewise, and for plain sp1 every
-// binning hash size at its full occupancy and half of it.
+// Candidates: k_walk at 1..(its occupancy) blocks per CU (from the list below),
+// and for plain sp1 every binning hash size at its full occupancy and half of
+// it.
 static const int kPerCu[] = {1, 2, 3, 4, 6, 8, 12, 16};
 
 int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
@@ -1715,8 +1714,7 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
         }
     }
     if (rc) { h->prof = prof; h->marks = saved; return rc; }
-    // step candidates: step i runs streaming candidate i mod |cs| and family
-    // candidate i mod |cf|; the first pass warms caches and code
+    // each candidate in turn; the first pass warms caches and code
     for (int pass = 0; pass < 2 && !rc; ++pass) {
         for (size_t i = 0; i < ncand && !rc; ++i) {
             h->grid[G_FAMILY] = cf[i];

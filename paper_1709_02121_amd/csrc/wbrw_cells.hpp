@@ -282,8 +282,8 @@ __device__ __forceinline__ uint64_t run_total(uint64_t v, int start)
 // thread and then over the lanes whose last particles share a cell: prefix sums
 // over the wavefront, modulo 2^32 or 2^64, and the difference of the two ends
 // of a run, which is exact.  One lane of each run adds to the hash table.
-// Measured against a particle to a lane and an LDS atomic each: 234 -> 175 us
-// for 1.4e7 particles after 5 steps (barrier), 777 -> 488 us for 256 instances
+// Measured against a particle to a lane and an LDS atomic each: 234 -> 179 us
+// for 1.4e7 particles (barrier, 1e7 to start with), 777 -> 491 us for 256 instances
 // of 3.1e5, and with tangents (1e7 particles and their ghosts, with the cell's
 // sums in one line, see flush) 800 -> 420 us.  What bounds it now is the lines
 // of the grids that the scattered offspring touch, most of all in 4D, where

@@ -14,8 +14,8 @@ namespace wbrw {
 
 constexpr int kMaxM = 4;
 constexpr int kThreads = 256;           // threads per block in every kernel
-constexpr int kPPT = 8;                 // particles (or cells) per thread in streaming passes
-constexpr int kTileA = kThreads * kPPT; // particles per streaming tile
+constexpr int kPPT = 8;                 // particles (or cells) per thread in the passes over all of them
+constexpr int kTileA = kThreads * kPPT; // particles per tile of those passes
 constexpr int kParents = 32;            // fewest event parents taken at a time (see Dev::ftile)
 constexpr int kTileS = kThreads * kPPT; // cells per scan tile
 constexpr int kSupGroup = 64;           // walk tiles per group sum of their counts
@@ -152,7 +152,7 @@ struct Dev {
     int64_t *Nbase;             // [2][B] counts at the start of the chunk (real, ghost): its records go after them
     int64_t *nstep;             // [2][B][kPend + 1] counts at the start of every step since the
                                 // positions were materialised (real, ghost); entry 0 always holds
-    int64_t *tileA;             // [2][B+1] streaming-tile plan (real, ghost)
+    int64_t *tileA;             // [2][B+1] plan of those tiles (real, ghost)
     int64_t *tileW;             // [2][2][B+1] walk-tile plan (parity; real, ghost)
     int64_t *wrange;            // [2][2][B][2] its particles per tile, and the binary logarithm
                                 // of the slots of a page (see page_slot)
