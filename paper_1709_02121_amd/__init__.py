@@ -228,8 +228,12 @@ class Simulation:
         _check(lib().wbrw_workspace_size(C.byref(c), C.byref(nbytes)), "wbrw_workspace_size")
         self.workspace_bytes = int(nbytes.value)
         with torch.cuda.device(self.device):
-            self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
             self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+            # On the handle's stream: the allocator then gives the memory of a
+            # dropped Simulation, whose work may still be under way, only to
+            # what comes after that work.
+            with torch.cuda.stream(self.stream):
+                self.workspace = torch.empty(self.workspace_bytes, dtype=torch.uint8, device=self.device)
         h = C.c_void_p()
         _check(lib().wbrw_init(C.byref(c), C.c_void_p(self.workspace.data_ptr()),
                                self.workspace_bytes, C.c_void_p(self.stream.cuda_stream),

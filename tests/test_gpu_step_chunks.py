@@ -173,3 +173,29 @@ def test_cell_sums_over_many_annihilations(P):  # noqa: F811
         s.annihilate()
         assert torch.equal(net(), before), f"annihilation {ep}"
     say(f"many annihilations: n={s.count()}")
+
+
+@pytest.mark.parametrize("graph", [False, True])
+def test_dropped_while_its_work_is_under_way(P, O, graph):  # noqa: F811
+    """Handles on two streams, each dropped while its work may be under way:
+    the next one, on the other stream, must not get its memory."""
+    import torch
+    cfgs = [W.batched_barriers(B=14, seed=3, capacity=60_000, N0=np.full(14, n, dtype=np.int64)) for n in (4000, 3500)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    want = []
+    for c in cfgs:
+        r = O.OracleSim(c)
+        r.run(16, 10)
+        want.append(r.density())
+    got, last = [], None
+    for k in (0, 1, 0, 1):
+        s = P.Simulation(cfgs[k], stream=streams[k])
+        assert s.workspace.data_ptr() != last
+        last = s.workspace.data_ptr()
+        s.run(16, 10, use_graph=graph)
+        got.append((k, s.density()))
+        del s
+    torch.cuda.synchronize()
+    say(f"dropped while its work is under way: graph {graph}")
+    for k, d in got:
+        assert np.array_equal(d.cpu().numpy(), want[k])
