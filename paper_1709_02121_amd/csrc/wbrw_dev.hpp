@@ -32,8 +32,9 @@ constexpr int kPend = 32;               // steps between materialisations of the
 constexpr int kRangeMin = 64;           // particles in a tile of k_walk, at least; a multiple of 64
 constexpr int kRangeMax = 8192;         // particles in a tile of k_walk, at most
 constexpr int kLocalBits = 4096;        // offspring of a tile whose event bits are kept in LDS
-constexpr int kPages = 32;              // pages of a tile's offspring in the inactive set, at most
-constexpr int kEvenPages = 24;          // of them of one size; each further one twice the one before
+constexpr int kDirect = 24;             // pages of a tile's offspring that the tile itself lists
+constexpr int kPages = kDirect + 1;     // their entries, and where the table of further pages starts
+constexpr int kTableMin = 64;           // pages that such a table holds, at least
 constexpr int kFewInst = 8;             // instances whose class totals are summed from the tiles'
 constexpr int kMaxGrid = 8192;          // blocks of a persistent launch (per-block partials)
 // 4D family kernels: the payloads of a tile's records beyond the block's LDS
@@ -156,8 +157,10 @@ struct Dev {
     int64_t *tileW;             // [2][2][B+1] walk-tile plan (parity; real, ghost)
     int64_t *wrange;            // [2][2][B][2] its particles per tile, and the binary logarithm
                                 // of the slots of a page (see page_slot)
-    uint64_t *wpool;            // [2][B] slots handed out as further pages (zero between chunks)
-    uint32_t *ptab, *ptabg;     // per walk tile: the first slots of its kPages pages
+    uint64_t *wpool;            // [2][B] slots handed out as further pages, then [2] entries of
+                                // ptx and ptxg handed out (zero between chunks)
+    uint32_t *ptab, *ptabg;     // per walk tile: its kPages entries (see page_slot)
+    uint32_t *ptx, *ptxg;       // tables of the tiles with more than kDirect pages
     int64_t *tileR;             // [B+1] regeneration-tile plan
     int64_t *tileG;             // [B+1] ghost-regeneration plan
     int64_t *tally;             // [B][kTalCount]
@@ -208,12 +211,16 @@ struct Dev {
 // in pages of 2^sh slots, the largest power of two up to half a tile's range:
 // tile tl of the instance has the page at tl 2^sh, and takes further ones
 // from the slots behind all first pages as it grows.  T first pages take at
-// most (N + R) / 2 slots and a tile that takes further ones no more in them
-// than it has offspring, so whatever the tiles' shares, they fit where the
-// offspring will fit behind the N > R particles.  (From the 25th page on
-// pages double, and up to half of such a tile's slots may stay empty; it
-// has offspring for 6 to 12 times its range by then.)  A single tile has all
-// slots.
+// most (N + R) / 2 slots, and a tile that takes further ones has fewer slots in
+// them than offspring, so whatever the tiles' shares and however far they
+// grow, the pages fit where the offspring will fit behind the N > R particles.
+// A single tile has all slots.
+//
+// The first kDirect pages are listed with the tile, all others in a table of
+// its own in ptx, which is replaced by one of twice the size when it is full.
+// The tables that a tile has had are less than four entries for each of its
+// pages, and pages have 32 slots or more: an eighth of the slots is room for
+// all of them.
 __host__ __device__ __forceinline__ int32_t page_bits(int64_t range, int64_t tiles)
 {
     if (tiles <= 1) return 31;
@@ -221,20 +228,22 @@ __host__ __device__ __forceinline__ int32_t page_bits(int64_t range, int64_t til
     while ((int64_t)(4 << sh) <= range) ++sh;
     return sh;
 }
-// slots in the first np pages
-__device__ __forceinline__ int64_t page_extent(int np, int sh)
+// entries of the table of a tile with np pages
+__host__ __device__ __forceinline__ uint32_t page_table(int np)
 {
-    if (np <= kEvenPages) return (int64_t)np << sh;
-    return ((int64_t)kEvenPages << sh) + (((int64_t)2 << (np - kEvenPages)) - 2 << sh);
+    if (np <= kDirect) return 0u;
+    uint32_t n = kTableMin;
+    while (n < (uint32_t)(np - kDirect)) n <<= 1;
+    return n;
 }
-// slot (from the instance's first) of offspring l
-__device__ __forceinline__ uint32_t page_slot(const uint32_t *pages, int sh, uint32_t l)
+// slot (from the instance's first) of offspring l; more(): ptx or ptxg
+template <class F>
+__host__ __device__ __forceinline__ int64_t page_slot(const uint32_t *pages, int sh, uint32_t l, F more)
 {
     const uint32_t p = l >> sh;
-    if (p < (uint32_t)kEvenPages) return pages[p] + (l - (p << sh));
-    const uint32_t k = p - (uint32_t)kEvenPages + 2u;           // in units of a page, from 2 on
-    const int j = 31 - __builtin_clz(k);                        // page 24 + j - 1 starts at unit 2^j
-    return pages[kEvenPages + j - 1] + (l - (((uint32_t)kEvenPages - 2u + (1u << j)) << sh));
+    uint32_t first = pages[p < (uint32_t)kDirect ? p : (uint32_t)kDirect];
+    if (p >= (uint32_t)kDirect) first = more()[first + (p - (uint32_t)kDirect)];
+    return first + (l - (p << sh));
 }
 
 // Particles in a tile of k_walk for an ensemble of n: an equal share of a

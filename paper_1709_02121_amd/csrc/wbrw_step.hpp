@@ -369,12 +369,13 @@ __device__ __forceinline__ void slot_child(const Dev &d, const InstParam &P, con
 // by one lane: the path of the tiles whose families the pool below cannot
 // hold.  Counting (emit false) tallies and counts the records; emitting
 // writes every record, the r-th as offspring first_rec + r (< cap) of the
-// tile's pages.  Its stack makes it large, so it is
+// tile's pages (more: the further ones, see page_slot).  Its stack makes it large, so it is
 // a function of its own: the common path keeps its registers.
 template <int DIM, bool SP2, bool TAN>
 __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step, const Node *root, bool emit,
                                              Ens out, int64_t base, int64_t first_rec, int64_t cap,
-                                             const uint32_t *pages, int sh, int64_t dstride, Tally *tl, uint32_t *err)
+                                             const uint32_t *pages, const uint32_t *more, int sh, int64_t dstride, Tally *tl,
+                                             uint32_t *err)
 {
     const Dev &d = *dp;
     const InstParam &P = d.ip[b];
@@ -451,7 +452,7 @@ __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step
             if (emit) {
                 const int64_t li = first_rec + nrec;
                 if (li < cap) {
-                    const int64_t o = base + page_slot(pages, sh, (uint32_t)li);
+                    const int64_t o = base + page_slot(pages, sh, (uint32_t)li, [&] { return more; });
                     out.x0[o] = cur.xe[0] + (d.vfac * ch.k[0]) * (d.dt - cur.te);
                     out.k0[o] = ch.k[0];
                     if (DIM == 2) {

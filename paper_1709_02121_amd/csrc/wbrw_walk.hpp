@@ -175,15 +175,22 @@ __device__ __forceinline__ uint32_t block_excl(uint32_t v, uint32_t *s_w, uint32
     return excl;
 }
 
+// A value that is the same in all lanes, for scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
+}
+
 // What a block of k_walk keeps in LDS.
 constexpr uint32_t kLocal = 0x80000000u;
 struct WalkTile {
-    int64_t i0, a0, limit;       // first particle, pages' base, offspring the pages hold
+    int64_t i0, a0;              // first particle, pages' base
     uint32_t nl, q0;             // offspring so far, event parents of the list that are done
     uint32_t g0, g1;             // the list's offspring
     int s;                       // its step, or (merged) the generation
     bool merged;                 // lists by generation
-    int b, nr, i00, sh, npage;
+    int b, nr, i00, sh;
 };
 template <int DIM, bool SP2, bool TAN>
 struct WalkShared {
@@ -193,7 +200,7 @@ struct WalkShared {
     uint64_t ev[kChunk][kW0];
     unsigned long long evl[kChunk][kWL];
     int64_t tal[5];
-    int64_t limit;                // offspring the pages hold
+    int64_t limit;                // offspring that the pages hold
     WalkTile rest;                // what k_walk leaves to walk_general, and gets back
     int32_t t;
     uint32_t wsum[2][4];
@@ -203,6 +210,7 @@ struct WalkShared {
     uint32_t ccnt[kClasses];      // records of each class
     uint32_t nst[kPend + 1];
     uint32_t page[kPages];
+    int npage;                    // the tile's pages (thread 0 adds to them)
     uint8_t cls[kThreads];        // the step of the chunk the event parents jump in and,
                                   // above its kStepBits, their classes
     static constexpr int kStepBits = 3;
@@ -223,10 +231,9 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int b = T.b, nr = T.nr, i00 = T.i00, sh = T.sh, B = fresh(self).B;
     const int64_t i0 = T.i0, a0 = T.a0;
-    int npage = T.npage;
-    int64_t limit = T.limit;
     uint32_t nl = T.nl;                  // offspring of the tile so far
     auto barrier = [] { if (GENERAL) block_sync(); else lds_barrier(); };
+    auto more = [&]() -> const uint32_t * { return ghost ? fresh(self).ptxg : fresh(self).ptx; };
     const int nw0 = (nr + 63) / 64;
     int s0 = T.s;
     uint32_t g0 = T.g0, g1 = T.g1, q0 = T.q0;
@@ -256,7 +263,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                         else             // past the bits kept in LDS
                             for (uint32_t q = 0; q < 64u && wl * 64u + q < g1; ++q)
                                 m |= (uint64_t)(((ghost ? fresh(self).smaskg : fresh(self).smask)
-                                                 [a0 + page_slot(W.page, sh, wl * 64u + q)] >> (kChunk + s)) & 1u) << q;
+                                                 [a0 + page_slot(W.page, sh, wl * 64u + q, more)] >> (kChunk + s)) & 1u) << q;
                         if (MERGED && wl == wa) m &= ~0ull << (g0 & 63u);
                         if (MERGED && wl == g1 / 64u) m &= (1ull << (g1 & 63u)) - 1ull;
                     }
@@ -296,7 +303,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 const uint32_t l = it & ~kLocal;
                 const Ens *sets = ghost ? d.gens : d.ens;
                 const Ens E = sets[set], A = sets[set ^ 1u], X = loc ? A : E;
-                const int64_t pi = loc ? a0 + page_slot(W.page, sh, l) : i0 + (int64_t)l;
+                const int64_t pi = loc ? a0 + page_slot(W.page, sh, l, more) : i0 + (int64_t)l;
                 Node root;
                 root.x[0] = X.x0[pi];
                 root.x[1] = DIM == 2 ? X.x1[pi] : 0.0;
@@ -387,42 +394,44 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                         W.rest.g0 = g0;
                         W.rest.g1 = g1;
                         W.rest.s = s0;
-                        W.rest.npage = npage;
-                        W.rest.limit = limit;
                     }
                     return false;
                 }
             } else if (live) {
                 const Node root = load_root(tid);
-                F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step0 + (uint32_t)(MERGED ? W.step(tid) : s0), &root, false, Ens{}, a0, 0, 0, W.page, sh, 0, &tal, &err);
+                F.cnt[tid] = walk_family<DIM, SP2, TAN>(self, b, step0 + (uint32_t)(MERGED ? W.step(tid) : s0), &root, false, Ens{}, a0, 0, 0, W.page, more(), sh, 0, &tal, &err);
             }
             if (GENERAL) barrier();
             // 2. ordered exclusive scan of the families' record counts
             uint32_t agg;
+            const int64_t room = uniform64(W.limit);   // (read before the barrier that thread 0 may grow it after)
             const uint32_t excl = block_excl(F.cnt[tid], W.wsum[0], agg);
             F.first[tid] = excl;
-            if ((int64_t)nl + agg > limit && npage < kPages && sh < 31) {   // (uniform) further pages
-                int np2 = npage;
-                while (np2 < kPages && page_extent(np2, sh) < (int64_t)nl + agg) ++np2;
+            if ((int64_t)nl + agg > room && sh < 31) {      // (uniform) further pages, as many as fit
                 if (tid == 0) {
                     const Dev &d = fresh(self);
                     const InstParam &P = inst_param(d, b);
                     const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
-                    const int64_t take = page_extent(np2, sh) - page_extent(npage, sh);
+                    int q = W.npage;
+                    const int64_t want = (((int64_t)nl + agg + (((int64_t)1 << sh) - 1)) >> sh) - q;
                     const int64_t from = ((plan[b + 1] - plan[b]) << sh) +
-                        (int64_t)atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * B + b], (unsigned long long)take);
-                    int64_t lim = limit;
-                    for (int q = npage; q < np2; ++q) {
-                        const int64_t at2 = from + page_extent(q, sh) - page_extent(npage, sh);
-                        W.page[q] = (uint32_t)at2;
-                        if (from + page_extent(q + 1, sh) - page_extent(npage, sh) <= (ghost ? P.gcap : P.cap))
-                            lim = page_extent(q + 1, sh);
+                        (int64_t)atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * B + b], (unsigned long long)(want << sh));
+                    const int64_t left = (ghost ? P.gcap : P.cap) - from;
+                    const int np = q + (int)(left > 0 ? min(want, left >> sh) : 0);
+                    const uint32_t old = W.page[kDirect], size = page_table(np);
+                    uint32_t table = old, *tab = ghost ? d.ptxg : d.ptx;
+                    if (size != page_table(q)) {
+                        table = (uint32_t)atomicAdd((unsigned long long *)&d.wpool[2 * (int64_t)B + ghost], (unsigned long long)size);
+                        for (int j = 0; j < q - kDirect; ++j) tab[table + j] = tab[old + j];
+                        W.page[kDirect] = table;
                     }
-                    W.limit = lim;
+                    uint32_t first = (uint32_t)from;
+                    for (; q < min(np, kDirect); ++q, first += 1u << sh) W.page[q] = first;
+                    for (; q < np; ++q, first += 1u << sh) tab[table + (q - kDirect)] = first;
+                    W.npage = np;
+                    W.limit = (int64_t)np << sh;
                 }
-                npage = np2;
-                barrier();
-                limit = W.limit;
+                block_sync();
             }
             barrier();
             // 3. records into the tile's area, each at its rank in its
@@ -431,9 +440,10 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             const Dev &d = fresh(self);
             const InstParam &P = inst_param(d, b);
             const Ens &A = (ghost ? d.gens : d.ens)[set ^ 1u];
+            const int64_t limit = uniform64(W.limit);
             uint16_t *smask = ghost ? d.smaskg : d.smask;
             const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-            auto close_record = [&](int64_t li, uint64_t id, int slot) {
+            auto close_record = [&](int64_t li, int64_t o, uint64_t id, int slot) {
                 const int s = MERGED ? W.step(slot) : s0;
                 const uint32_t cls = (uint32_t)(W.cls[slot] >> W.kStepBits) | (1u << s);
                 uint32_t ev = 0;
@@ -443,7 +453,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                         ev |= 1u << q;
                         if (li < kLocalBits) atomicOr(&W.evl[q][li >> 6], 1ull << (li & 63));
                     }
-                smask[a0 + page_slot(W.page, sh, (uint32_t)li)] = (uint16_t)(cls | (ev << kChunk));
+                smask[o] = (uint16_t)(cls | (ev << kChunk));
                 atomicAdd(&W.ccnt[cls], 1u);
             };
             if constexpr (!GENERAL) {
@@ -458,7 +468,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
                     const int64_t li = (int64_t)nl + (int64_t)(F.first[slot] + rank);
                     if (li >= limit) { err |= kErrCapacity; continue; }
-                    const int64_t o = a0 + page_slot(W.page, sh, (uint32_t)li);
+                    const int64_t o = a0 + page_slot(W.page, sh, (uint32_t)li, more);
                     Node nd;
                     load_record<DIM, SP2, TAN>(d, F, r, nd);
                     A.x0[o] = nd.x[0];
@@ -474,7 +484,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                         A.D[dstride + o] = nd.D[1];
                         A.D[2 * dstride + o] = nd.D[2];
                     }
-                    close_record(li, nd.id, slot);
+                    close_record(li, o, nd.id, slot);
                 }
                 // the wavefront's deepest level by ballots (an atomic
                 // maximum of per-lane values takes the lanes one by one)
@@ -486,10 +496,12 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     const Node root = load_root(tid);
                     Tally none{0, 0, 0, 0, 0};
                     const int64_t f = (int64_t)nl + (int64_t)excl;
-                    const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step0 + (uint32_t)(MERGED ? W.step(tid) : s0), &root, true, A, a0, f, limit, W.page, sh,
+                    const uint32_t c = walk_family<DIM, SP2, TAN>(self, b, step0 + (uint32_t)(MERGED ? W.step(tid) : s0), &root, true, A, a0, f, limit, W.page, more(), sh,
                                                                   dstride, &none, &err);
-                    for (uint32_t r = 0; r < c && f + r < limit; ++r)
-                        close_record(f + r, A.id[a0 + page_slot(W.page, sh, (uint32_t)(f + r))], tid);
+                    for (uint32_t r = 0; r < c && f + r < limit; ++r) {
+                        const int64_t o = a0 + page_slot(W.page, sh, (uint32_t)(f + r), more);
+                        close_record(f + r, o, A.id[o], tid);
+                    }
                 }
                 atomicAdd((unsigned long long *)&W.tal[0], (unsigned long long)tal.events);
                 atomicAdd((unsigned long long *)&W.tal[1], (unsigned long long)tal.pairs);
@@ -508,8 +520,6 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             if constexpr (GENERAL) {
                 T.nl = nl;
                 T.q0 = q0 + (uint32_t)FS;
-                T.npage = npage;
-                T.limit = limit;
                 return true;
             }
             if (q0 + (uint32_t)FS >= np) break;
@@ -519,15 +529,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
         g1 = nl;
         if (s0 == S || (MERGED && g0 == g1)) break;
     }
-    T.npage = npage;
     return true;
-}
-
-// A value that is the same in all lanes, for scalar registers.
-__device__ __forceinline__ int64_t uniform64(int64_t v)
-{
-    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
-                     (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v));
 }
 
 // A batch whose families have outgrown the pool.  A function of its own, called
@@ -599,7 +601,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
         // tile t is tile tl of instance b: its range of nr particles from i0
         // on; its offspring go to pages of 2^sh slots behind a0
         int b, nr, i00, sh;
-        int64_t i0, a0, limit;
+        int64_t i0, a0;
         bool merged;
         {
             const Dev &d = fresh(self);
@@ -613,8 +615,11 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             i0 = base + tl * R;
             nr = (int)min(R, n - tl * R);
             a0 = base;
-            limit = min((int64_t)1 << sh, ghost ? P.gcap : P.cap);
-            if (tid == 0) W.page[0] = (uint32_t)(tl << (sh & 31));
+            if (tid == 0) {
+                W.page[0] = (uint32_t)(tl << (sh & 31));
+                W.npage = 1;
+                W.limit = min((int64_t)1 << sh, ghost ? P.gcap : P.cap);
+            }
         }
         if (b != cb) {
             const Dev &d = fresh(self);
@@ -669,7 +674,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                 merged = __builtin_amdgcn_readfirstlane((int)W.total) <= (ghost ? d.gftile : d.ftile);
             }
         }
-        WalkTile T{i0, a0, limit, 0u, 0u, 0u, 0u, 0, merged, b, nr, i00, sh, 1};
+        WalkTile T{i0, a0, 0u, 0u, 0u, 0u, 0, merged, b, nr, i00, sh};
         while (!(DIM == 1 && merged ? walk_steps<DIM, SP2, TAN, ONE, false, DIM == 1>(self, ghost, S, pend, set, step0, par, T, W, err)
                         : walk_steps<DIM, SP2, TAN, ONE, false, false>(self, ghost, S, pend, set, step0, par, T, W, err))) {
             block_sync();
@@ -679,14 +684,11 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             T.g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.g0);
             T.g1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.g1);
             T.s = __builtin_amdgcn_readfirstlane(W.rest.s);
-            T.npage = __builtin_amdgcn_readfirstlane(W.rest.npage);
-            T.limit = uniform64(W.rest.limit);
         }
-        const int npage = T.npage;
         lds_barrier();
         // the tile's counts per class, also summed over groups of tiles
         const Dev &d = fresh(self);
-        if (tid < npage) (ghost ? d.ptabg : d.ptab)[t * kPages + tid] = W.page[tid];
+        if (tid < min(W.npage, kPages)) (ghost ? d.ptabg : d.ptab)[t * kPages + tid] = W.page[tid];
         if (tid < kClasses) {
             uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
             uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
@@ -774,7 +776,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
     const Ens E = pick_set(d, ghost, set);
     const Ens A = pick_set(d, ghost, set ^ 1u);
     const uint16_t *smask = ghost ? d.smaskg : d.smask;
-    const uint32_t *ptab = ghost ? d.ptabg : d.ptab;
+    const uint32_t *ptab = ghost ? d.ptabg : d.ptab, *more = ghost ? d.ptxg : d.ptx;
     const uint32_t *wcnt = ghost ? d.wcntg : d.wcnt;
     const uint32_t *wsup = (ghost ? d.wsupg : d.wsup) + (int64_t)par * (ghost ? d.wsup_gg : d.wsup_g) * kClasses;
     const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
@@ -820,7 +822,7 @@ __global__ __launch_bounds__(kThreads) void k_place(Dev d, int ghost, int S, int
         block_sync();
         const int64_t n0 = d.Nbase[(int64_t)ghost * B + b];
         for (uint32_t r = (uint32_t)tid; r < nrec; r += kThreads) {
-            const int64_t i = base + page_slot(s_page, sh, r);
+            const int64_t i = base + page_slot(s_page, sh, r, [&] { return more; });
             const uint32_t cls = smask[i] & (kClasses - 1);
             const int64_t dst = n0 + (int64_t)(uint32_t)(s_off[cls] + r);
             double x0 = A.x0[i], x1 = DIM == 2 ? A.x1[i] : 0.0;
@@ -971,6 +973,7 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
     // the tile plans
     block_plan(d.tileA + (int64_t)ghost * (B + 1), Ncur, B, kTileA);
     plan_walk(d, par ^ 1u, ghost, Ncur);
+    if (tid == 0) d.wpool[2 * (int64_t)B + ghost] = 0ull;
     if (tid == 0 && advance) {
         ctl->step = step + (uint32_t)S;
         ctl->chunk += 1u;
