@@ -536,9 +536,10 @@ __device__ __noinline__ uint32_t walk_family(const Dev *dp, int b, uint32_t step
 // record (a parent by a pool entry with path 0, which is no output).
 //
 // Payloads past kLds go to the block's overflow area in HBM (4D), the paths
-// and links stay in LDS.  A tile whose records, queue, levels (8) or jump
-// indexes (15) do not fit is done again by walk_family; Dev::ftile, the
-// parents per tile, is chosen so that this is rare.
+// and links stay in LDS.  Parents whose records, queue, levels (8) or jump
+// indexes (15) do not fit are taken again: half as many at a time, or, where a
+// path does not fit or they are few already, by walk_family.
+// Dev::ftile, the parents taken at first, is chosen so that this is rare.
 // ---------------------------------------------------------------------------
 template <int DIM, bool SP2, bool TAN>
 struct Families {
@@ -560,7 +561,8 @@ struct Families {
     // per family
     uint32_t cnt[kThreads], first[kThreads];
     uint32_t head[kThreads];
-    uint32_t n, nq[2], overflow;
+    uint32_t n, nq[2];
+    uint32_t overflow;            // bits: 1 records or jumps, 2 paths that do not fit
     uint32_t events, pairs, maxdepth;
     long long killed;
 };
@@ -577,7 +579,7 @@ __device__ __forceinline__ uint32_t add_record(const Dev &d, Families<DIM, SP2, 
     using FT = Families<DIM, SP2, TAN>;
     const uint32_t r = atomicAdd(&F.n, 1u);
     if (r >= (uint32_t)FT::kRec || (DIM == 2 && r >= (uint32_t)FT::kLds && r - (uint32_t)FT::kLds >= gpool_cap(d))) {
-        F.overflow = 1u;
+        atomicOr(&F.overflow, 1u);
         return kNone;
     }
     const double x0 = xe[0] + (d.vfac * ch.k[0]) * (d.dt - te);
@@ -671,7 +673,7 @@ __device__ __forceinline__ void add_jump(Families<DIM, SP2, TAN> &F, int round, 
     using FT = Families<DIM, SP2, TAN>;
     const uint32_t q = atomicAdd(&F.nq[round & 1], 1u);
     if (q >= (uint32_t)FT::kQueue || rec == kNone) {
-        F.overflow = 1u;
+        atomicOr(&F.overflow, 1u);
         return;
     }
     F.qx0[q] = x[0];
@@ -698,7 +700,7 @@ __device__ __forceinline__ void take_jump(const Dev &d, const InstParam &P, uint
     const int M = ONE ? 1 : d.M;
     const double te = cur.te, g0 = P.gamma0;
     if (lev >= FT::kLevels || cur.e >= 15u) {
-        F.overflow = 1u;
+        atomicOr(&F.overflow, 2u);
         return;
     }
     const int sh = 56 - 8 * lev;

@@ -210,6 +210,7 @@ struct WalkShared {
     uint32_t ccnt[kClasses];      // records of each class
     uint32_t nst[kPend + 1];
     uint32_t page[kPages];
+    int parents;                  // event parents taken at a time in this tile
     int npage;                    // the tile's pages (thread 0 adds to them)
     uint8_t cls[kThreads];        // the step of the chunk the event parents jump in and,
                                   // above its kStepBits, their classes
@@ -219,9 +220,12 @@ struct WalkShared {
 };
 
 // Takes the event parents of tile T from generation T.g0 .. T.g1 on, batch by
-// batch (k_walk).  False where the families of a batch outgrow the pool, with
-// what is left to do in W.rest.  With GENERAL that batch alone is taken, each
-// family by the general walk of one lane.
+// batch (k_walk).  False where a path of a batch does not fit, or its records
+// even with kParents of them, with what is left to do in W.rest.  With GENERAL
+// the next kThreads event parents are taken, each family by the general walk of
+// one lane.  (Such ensembles mostly have batches of kParents, which would leave
+// seven of eight lanes idle: 1e5 particles, gamma0 dt = 1.2, 2200 us by batches
+// of 32 and 1900 by 256.)
 template <int DIM, bool SP2, bool TAN, bool ONE, bool GENERAL, bool MERGED>
 __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
                                            uint32_t par, WalkTile &T, WalkShared<DIM, SP2, TAN> &W, uint32_t &err)
@@ -237,17 +241,19 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
     const int nw0 = (nr + 63) / 64;
     int s0 = T.s;
     uint32_t g0 = T.g0, g1 = T.g1, q0 = T.q0;
+    // event parents taken at a time (a batch)
+    auto parents = [&] { return GENERAL ? kThreads : __builtin_amdgcn_readfirstlane(W.parents); };
     for (;; q0 = 0u) {
-        const int FS = ghost ? fresh(self).gftile : fresh(self).ftile;   // event parents taken at a time
         // the list: steps sa .. sz - 1, of each the range's bits (step by
         // step, or the first generation) and those of offspring g0 .. g1 - 1
         const uint32_t sa = MERGED ? 0u : (uint32_t)s0, sz = MERGED ? (uint32_t)S : sa + 1u;
         const uint32_t nr0 = MERGED && s0 > 0 ? 0u : (uint32_t)nw0;
         const uint32_t wa = g0 / 64u, nw = nr0 + (g1 + 63u) / 64u - wa;
         uint32_t np = 0;                 // event parents of the list
-        for (;; q0 += (uint32_t)FS) {
+        for (;;) {
             // event parents [q0, q0 + FS) of the list, by step and in order
             if (GENERAL || g1 > (uint32_t)kLocalBits) block_sync(); else lds_barrier();
+            const int FS = parents();
             uint32_t run = 0, s = sa, w = (uint32_t)tid;      // word w of step s
             for (uint32_t w0 = 0, it = 0; w0 < nw * (sz - sa); w0 += kThreads, w += kThreads, ++it) {
                 if (MERGED)
@@ -387,6 +393,18 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             }
             if constexpr (!GENERAL) {
                 if (F.overflow) {    // (uniform)
+                    // Records or jumps than there is room for: half as
+                    // many parents, for the rest of the tile.  (Ensembles
+                    // crowded where |sin| is near 1 leave 1.57 times the
+                    // records that Dev::ftile counts with.  7e5 particles,
+                    // gamma0 dt = 0.3, two steps: 270 us so, 1550 with every
+                    // such batch by the general walk.)
+                    const int fs = parents();
+                    if (F.overflow == 1u && fs > kParents) {
+                        lds_barrier();
+                        if (tid == 0) W.parents = max(kParents, fs / 2 / kParents * kParents);
+                        continue;
+                    }
                     if (tid == 0) {
                         W.rest = T;
                         W.rest.nl = nl;
@@ -519,10 +537,11 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             }
             if constexpr (GENERAL) {
                 T.nl = nl;
-                T.q0 = q0 + (uint32_t)FS;
+                T.q0 = q0 + (uint32_t)kThreads;
                 return true;
             }
-            if (q0 + (uint32_t)FS >= np) break;
+            q0 += (uint32_t)parents();
+            if (q0 >= np) break;
         }
         ++s0;
         if (MERGED) g0 = g1;             // the next generation
@@ -532,7 +551,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
     return true;
 }
 
-// A batch whose families have outgrown the pool.  A function of its own, called
+// Event parents whose families do not fit the pool.  A function of its own, called
 // where k_walk holds nothing else: with the general walk's calls inside the
 // steps the common path spilt 100 vector registers and took longer (256
 // instances 8.95 ms a pass and 7.63 so, barrier of 1e7 2.32 and 2.12, of 1e4
@@ -618,6 +637,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             if (tid == 0) {
                 W.page[0] = (uint32_t)(tl << (sh & 31));
                 W.npage = 1;
+                W.parents = ghost ? d.gftile : d.ftile;
                 W.limit = min((int64_t)1 << sh, ghost ? P.gcap : P.cap);
             }
         }
