@@ -278,6 +278,8 @@ class Simulation:
         if out is None:
             with self.torch.cuda.stream(self.stream):
                 out = self.torch.empty((self.B, nbins), dtype=self.torch.float64, device=self.device)
+        else:
+            self._order_after_caller()
         _check(lib().wbrw_density(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density")
         self._order_for_caller()
@@ -291,6 +293,7 @@ class Simulation:
         lo = d["lo"] if lo is None else lo
         hi = d["hi"] if hi is None else hi
         assert out.dtype == self.torch.float64 and out.numel() == self.B * nbins and out.is_contiguous()
+        self._order_after_caller()
         _check(lib().wbrw_density_noalloc(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density_noalloc")
         self._order_for_caller()
@@ -304,6 +307,8 @@ class Simulation:
         if out is None:
             with self.torch.cuda.stream(self.stream):
                 out = self.torch.empty((self.B, 3, nbins), dtype=self.torch.float64, device=self.device)
+        else:
+            self._order_after_caller()
         _check(lib().wbrw_density_tangent(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density_tangent")
         self._order_for_caller()
@@ -315,6 +320,14 @@ class Simulation:
         if cur.cuda_stream != self.stream.cuda_stream:
             cur.wait_stream(self.stream)
 
+    def _order_after_caller(self):
+        """Make the handle's stream wait for what is enqueued on torch's current
+        stream: the work that fills a tensor handed over by the caller, and
+        what is still to read a buffer or memory that is about to be written."""
+        cur = self.torch.cuda.current_stream(self.device)
+        if cur.cuda_stream != self.stream.cuda_stream:
+            self.stream.wait_stream(cur)
+
     def density_vjp(self, g, axis=0, nbins=None, lo=None, hi=None):
         """sum_j g[b, j] d rho[b, j] / d theta for every instance, shape (B, 3)."""
         t = self.torch
@@ -322,6 +335,7 @@ class Simulation:
         nbins = d["nbins"] if nbins is None else nbins
         lo = d["lo"] if lo is None else lo
         hi = d["hi"] if hi is None else hi
+        self._order_after_caller()
         with t.cuda.stream(self.stream):
             g = g.to(device=self.device, dtype=t.float64).reshape(self.B, nbins).contiguous()
             out = t.empty((self.B, 3), dtype=t.float64, device=self.device)
@@ -361,10 +375,12 @@ class Simulation:
         n = C.c_size_t()
         _check(lib().wbrw_snapshot_size(self.h, C.byref(n)), "wbrw_snapshot_size")
         buf = self.torch.empty(int(n.value), dtype=self.torch.uint8, device=self.device)
+        self._order_after_caller()
         _check(lib().wbrw_snapshot(self.h, C.c_void_p(buf.data_ptr()), int(n.value)), "wbrw_snapshot")
         return buf
 
     def restore(self, buf):
+        self._order_after_caller()
         _check(lib().wbrw_restore(self.h, C.c_void_p(buf.data_ptr()), buf.numel()), "wbrw_restore")
 
     def stats(self, b=0):
@@ -396,6 +412,7 @@ class Simulation:
         tan = bool(self.cfg.get("track_tangent", 0))
         D = t.empty((n, 3), dtype=t.float64, device=dev) if tan else None
         p = lambda a: C.c_void_p(a.data_ptr()) if (a is not None and n > 0) else None
+        self._order_after_caller()
         _check(lib().wbrw_export(self.h, b, int(ghost), n, p(x), p(k), p(s), p(w), p(ids), p(D)),
                "wbrw_export")
         out = {"x": x.cpu().numpy(), "k": k.cpu().numpy(), "id": ids.cpu().numpy().view(np.uint64)}
