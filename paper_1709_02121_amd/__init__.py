@@ -282,7 +282,7 @@ class Simulation:
             self._order_after_caller()
         _check(lib().wbrw_density(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density")
-        self._order_for_caller()
+        self._order_for_caller(out)
         return out
 
     def density_noalloc(self, out, axis=0, nbins=None, lo=None, hi=None):
@@ -296,7 +296,7 @@ class Simulation:
         self._order_after_caller()
         _check(lib().wbrw_density_noalloc(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density_noalloc")
-        self._order_for_caller()
+        self._order_for_caller(out)
         return out
 
     def density_tangent(self, axis=0, nbins=None, lo=None, hi=None, out=None):
@@ -311,14 +311,19 @@ class Simulation:
             self._order_after_caller()
         _check(lib().wbrw_density_tangent(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density_tangent")
-        self._order_for_caller()
+        self._order_for_caller(out)
         return out
 
-    def _order_for_caller(self):
-        """Make results visible to work the caller enqueues on torch's current stream."""
+    def _order_for_caller(self, out):
+        """Make the results in `out` visible to work the caller enqueues on torch's
+        current stream.  Memory that was allocated on the handle's stream is
+        marked as used there: dropped, it is not handed to the handle's next
+        results before that work is done."""
         cur = self.torch.cuda.current_stream(self.device)
         if cur.cuda_stream != self.stream.cuda_stream:
             cur.wait_stream(self.stream)
+            if out.is_cuda:     # (a caller's buffer may be pinned host memory)
+                out.record_stream(cur)
 
     def _order_after_caller(self):
         """Make the handle's stream wait for what is enqueued on torch's current
@@ -341,7 +346,7 @@ class Simulation:
             out = t.empty((self.B, 3), dtype=t.float64, device=self.device)
         _check(lib().wbrw_density_vjp(self.h, axis, nbins, lo, hi, C.c_void_p(g.data_ptr()),
                                       C.c_void_p(out.data_ptr())), "wbrw_density_vjp")
-        self._order_for_caller()
+        self._order_for_caller(out)
         return out
 
     LAUNCH_KEYS = ("stream_blocks", "family_blocks", "stream_threads", "stream_ppt", "bin_blocks", "bin_slots")

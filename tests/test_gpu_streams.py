@@ -96,3 +96,30 @@ def _snapshots(s):
         h.fill_(7)
     del held, h
     same(s.particles())
+
+
+def test_results_in_use_on_another_stream(P):  # noqa: F811
+    """A density that the current stream is still to read, dropped: the next one
+    is not written over it."""
+    import torch
+    s = _barrier(P, gamma0=0.45, track_tangent=1)
+    g = torch.ones(240, dtype=torch.float64, device="cuda")
+    say("streams: results")
+    for call in (s.density, s.density_tangent, lambda: s.density_vjp(g)):
+        first = call()
+        want = first.cpu()
+        torch.cuda.synchronize()
+        _busy(torch)
+        read = first.clone()
+        del first
+        s.step(4)
+        # (not density_vjp, which waits for the current stream by itself)
+        nxt = [s.density(nbins=n) for n in (240, 240, 3)] + [s.density_tangent()]
+        torch.cuda.synchronize()
+        assert torch.equal(read.cpu(), want)
+        del nxt
+    pinned = torch.zeros((1, 240), dtype=torch.float64, pin_memory=True)
+    want = s.density().cpu()
+    s.density(out=pinned)
+    torch.cuda.synchronize()
+    assert torch.equal(pinned, want)
