@@ -50,12 +50,21 @@ class WBRWDensity(torch.autograd.Function):
         sim = Simulation(theta_config(cfg, theta.detach().cpu().numpy()), device=device)
         # whole stretches of steps and annihilations per call, up to the next checkpoint
         steps, done = int(steps), 0
-        snap = int(snapshot_every) if checkpoints is not None and snapshot_every else 0
+        every = abs(annihilate_every or 0)
+        whole = every < 2 ** 31 and every == int(every)      # a period that sim.run takes
+        snap = checkpoints is not None and bool(snapshot_every)
         while done < steps:
-            n = min(steps - done, snap - done % snap) if snap else steps - done
-            sim.run(n, int(annihilate_every or 0))
+            n = 1 if snap or not whole else steps
+            while done + n < steps and whole and (done + n) % snapshot_every != 0:
+                n += 1
+            if whole:
+                sim.run(n, int(every))
+            else:
+                sim.step(1)
+                if (done + 1) % every == 0:
+                    sim.annihilate()
             done += n
-            if snap and done % snap == 0:
+            if snap and done % snapshot_every == 0:
                 checkpoints.append((done, sim.snapshot()))
         rho = sim.density()[0]
         ctx.sim = sim
