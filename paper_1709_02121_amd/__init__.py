@@ -325,12 +325,14 @@ class Simulation:
             if out.is_cuda:     # (a caller's buffer may be pinned host memory)
                 out.record_stream(cur)
 
-    def _order_after_caller(self):
+    def _order_after_caller(self, copies=False):
         """Make the handle's stream wait for what is enqueued on torch's current
         stream: the work that fills a tensor handed over by the caller, and
-        what is still to read a buffer or memory that is about to be written."""
+        what is still to read a buffer or memory that is about to be written.
+        copies: the call begins with a synchronous copy to the host, which
+        waits for the default stream by itself."""
         cur = self.torch.cuda.current_stream(self.device)
-        if cur.cuda_stream != self.stream.cuda_stream:
+        if cur.cuda_stream != self.stream.cuda_stream and not (copies and cur.cuda_stream == 0):
             self.stream.wait_stream(cur)
 
     def density_vjp(self, g, axis=0, nbins=None, lo=None, hi=None):
@@ -380,12 +382,12 @@ class Simulation:
         n = C.c_size_t()
         _check(lib().wbrw_snapshot_size(self.h, C.byref(n)), "wbrw_snapshot_size")
         buf = self.torch.empty(int(n.value), dtype=self.torch.uint8, device=self.device)
-        self._order_after_caller()
+        self._order_after_caller(copies=True)
         _check(lib().wbrw_snapshot(self.h, C.c_void_p(buf.data_ptr()), int(n.value)), "wbrw_snapshot")
         return buf
 
     def restore(self, buf):
-        self._order_after_caller()
+        self._order_after_caller(copies=True)
         _check(lib().wbrw_restore(self.h, C.c_void_p(buf.data_ptr()), buf.numel()), "wbrw_restore")
 
     def stats(self, b=0):
@@ -417,7 +419,7 @@ class Simulation:
         tan = bool(self.cfg.get("track_tangent", 0))
         D = t.empty((n, 3), dtype=t.float64, device=dev) if tan else None
         p = lambda a: C.c_void_p(a.data_ptr()) if (a is not None and n > 0) else None
-        self._order_after_caller()
+        self._order_after_caller(copies=True)
         _check(lib().wbrw_export(self.h, b, int(ghost), n, p(x), p(k), p(s), p(w), p(ids), p(D)),
                "wbrw_export")
         out = {"x": x.cpu().numpy(), "k": k.cpu().numpy(), "id": ids.cpu().numpy().view(np.uint64)}
