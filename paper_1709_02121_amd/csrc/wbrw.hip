@@ -978,6 +978,19 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
                           : parents_at_a_time(h, false, Families<2, false, false>::kRec, Families<2, false, false>::kQueue);
     h->chunk = chunk_steps(h);
     d.gftile = parents_at_a_time(h, true, Families<1, false, true>::kRec, Families<1, false, true>::kQueue);
+    {
+        int64_t total = 0;
+        for (int b = 0; b < h->B; ++b) total += cfg->N0[b];
+        for (InstParam &P : h->ip) {
+            P.wr = range_limit(h, P, d.ftile);
+            P.gwr = range_limit(h, P, d.gftile);
+            // small ensembles still spread over the chip: four tiles per
+            // compute unit over all instances
+            const double want = 4.0 * h->cus;
+            P.wt = std::max(1, total > 0 ? (int)(want * (double)P.N0 / (double)total) : 1);
+            P.gwt = std::max(1, (int)want / h->B);
+        }
+    }
     for (int s = 0; s < 2; ++s) {
         Ens &E = d.ens[s];
         E.x0 = at<double>(w, L.ens[s][0]);
@@ -1067,19 +1080,6 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     }
 
     if (h->dim == 1) set_grids_dim<1>(h); else set_grids_dim<2>(h);
-    {
-        int64_t total = 0;
-        for (int b = 0; b < h->B; ++b) total += cfg->N0[b];
-        for (InstParam &P : h->ip) {
-            P.wr = range_limit(h, P, d.ftile);
-            P.gwr = range_limit(h, P, d.gftile);
-            // small ensembles still spread over the chip: a tile for each
-            // resident block, over all instances
-            const double want = h->grid[G_FAMILY];
-            P.wt = std::max(1, total > 0 ? (int)(want * (double)P.N0 / (double)total) : 1);
-            P.gwt = std::max(1, h->grid[G_FAMILY] / h->B);
-        }
-    }
     d.self = at<Dev>(w, L.dev);
 
     hipStream_t s = h->stream;
