@@ -200,7 +200,8 @@ struct WalkShared {
     uint64_t ev[kChunk][kW0];
     unsigned long long evl[kChunk][kWL];
     int64_t tal[5];
-    int64_t limit;                // offspring that the pages hold
+    uint32_t limit, cap;          // offspring that the pages hold; the instance's slots
+    uint32_t pool;                // ... and those of all first pages
     WalkTile rest;                // what k_walk leaves to walk_general, and gets back
     int32_t t;
     uint32_t wsum[2][4];
@@ -228,12 +229,12 @@ struct WalkShared {
 // of 32 and 1900 by 256.)
 template <int DIM, bool SP2, bool TAN, bool ONE, bool GENERAL, bool MERGED>
 __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
-                                           uint32_t par, WalkTile &T, WalkShared<DIM, SP2, TAN> &W, uint32_t &err)
+                                           WalkTile &T, WalkShared<DIM, SP2, TAN> &W, uint32_t &err)
 {
     using FT = Families<DIM, SP2, TAN>;
     FT &F = W.F;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int b = T.b, nr = T.nr, i00 = T.i00, sh = T.sh, B = fresh(self).B;
+    const int b = T.b, nr = T.nr, i00 = T.i00, sh = T.sh;
     const int64_t i0 = T.i0, a0 = T.a0;
     uint32_t nl = T.nl;                  // offspring of the tile so far
     auto barrier = [] { if (GENERAL) block_sync(); else lds_barrier(); };
@@ -422,24 +423,22 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             if (GENERAL) barrier();
             // 2. ordered exclusive scan of the families' record counts
             uint32_t agg;
-            const int64_t room = uniform64(W.limit);   // (read before the barrier that thread 0 may grow it after)
+            // (read before the barrier that thread 0 may change it after)
+            const uint32_t room = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.limit);
             const uint32_t excl = block_excl(F.cnt[tid], W.wsum[0], agg);
             F.first[tid] = excl;
-            if ((int64_t)nl + agg > room && sh < 31) {      // (uniform) further pages, as many as fit
+            if (nl + agg > room && sh < 31) {      // (uniform) further pages, as many as fit
                 if (tid == 0) {
                     const Dev &d = fresh(self);
-                    const InstParam &P = inst_param(d, b);
-                    const int64_t at = 2 * par + (uint32_t)ghost, *plan = d.tileW + at * (B + 1);
                     int q = W.npage;
-                    const int64_t want = (((int64_t)nl + agg + (((int64_t)1 << sh) - 1)) >> sh) - q;
-                    const int64_t from = ((plan[b + 1] - plan[b]) << sh) +
-                        (int64_t)atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * B + b], (unsigned long long)(want << sh));
-                    const int64_t left = (ghost ? P.gcap : P.cap) - from;
-                    const int np = q + (int)(left > 0 ? min(want, left >> sh) : 0);
+                    const uint32_t want = ((nl + agg + ((1u << sh) - 1u)) >> sh) - (uint32_t)q;
+                    const uint64_t from = W.pool +
+                        atomicAdd((unsigned long long *)&d.wpool[(int64_t)ghost * d.B + b], (unsigned long long)want << sh);
+                    const int np = q + (int)(from < W.cap ? min(want, (W.cap - (uint32_t)from) >> sh) : 0u);
                     const uint32_t old = W.page[kDirect], size = page_table(np);
                     uint32_t table = old, *tab = ghost ? d.ptxg : d.ptx;
                     if (size != page_table(q)) {
-                        table = (uint32_t)atomicAdd((unsigned long long *)&d.wpool[2 * (int64_t)B + ghost], (unsigned long long)size);
+                        table = (uint32_t)atomicAdd((unsigned long long *)&d.wpool[2 * (int64_t)d.B + ghost], (unsigned long long)size);
                         for (int j = 0; j < q - kDirect; ++j) tab[table + j] = tab[old + j];
                         W.page[kDirect] = table;
                     }
@@ -447,7 +446,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     for (; q < min(np, kDirect); ++q, first += 1u << sh) W.page[q] = first;
                     for (; q < np; ++q, first += 1u << sh) tab[table + (q - kDirect)] = first;
                     W.npage = np;
-                    W.limit = (int64_t)np << sh;
+                    W.limit = (uint32_t)np << sh;
                 }
                 block_sync();
             }
@@ -458,10 +457,10 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             const Dev &d = fresh(self);
             const InstParam &P = inst_param(d, b);
             const Ens &A = (ghost ? d.gens : d.ens)[set ^ 1u];
-            const int64_t limit = uniform64(W.limit);
+            const uint32_t limit = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.limit);
             uint16_t *smask = ghost ? d.smaskg : d.smask;
             const int64_t dstride = ghost ? d.gcap_total : d.cap_total;
-            auto close_record = [&](int64_t li, int64_t o, uint64_t id, int slot) {
+            auto close_record = [&](uint32_t li, int64_t o, uint64_t id, int slot) {
                 const int s = MERGED ? W.step(slot) : s0;
                 const uint32_t cls = (uint32_t)(W.cls[slot] >> W.kStepBits) | (1u << s);
                 uint32_t ev = 0;
@@ -484,9 +483,9 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     uint32_t rank = 0;
                     for (uint32_t q = F.head[slot]; q != kNone; q = F.next[q]) rank += F.key[q] < key ? 1u : 0u;
                     deep = max(deep, (uint32_t)(FT::kLevels - (__ffsll((unsigned long long)key) - 1) / 8));
-                    const int64_t li = (int64_t)nl + (int64_t)(F.first[slot] + rank);
+                    const uint32_t li = nl + F.first[slot] + rank;
                     if (li >= limit) { err |= kErrCapacity; continue; }
-                    const int64_t o = a0 + page_slot(W.page, sh, (uint32_t)li, more);
+                    const int64_t o = a0 + page_slot(W.page, sh, li, more);
                     Node nd;
                     load_record<DIM, SP2, TAN>(d, F, r, nd);
                     A.x0[o] = nd.x[0];
@@ -518,7 +517,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                                                                   dstride, &none, &err);
                     for (uint32_t r = 0; r < c && f + r < limit; ++r) {
                         const int64_t o = a0 + page_slot(W.page, sh, (uint32_t)(f + r), more);
-                        close_record(f + r, o, A.id[o], tid);
+                        close_record((uint32_t)(f + r), o, A.id[o], tid);
                     }
                 }
                 atomicAdd((unsigned long long *)&W.tal[0], (unsigned long long)tal.events);
@@ -527,7 +526,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 atomicAdd((unsigned long long *)&W.tal[3], (unsigned long long)tal.cap);
                 atomicMax((unsigned long long *)&W.tal[4], (unsigned long long)tal.maxdepth);
             }
-            nl = (uint32_t)min((int64_t)nl + agg, limit);
+            nl = min(nl + agg, limit);
             barrier();
             if (tid == 0 && !GENERAL) {
                 W.tal[0] += F.events;
@@ -558,14 +557,14 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
 // 1.02 and 0.88, weighted 1e7 1.78 and 1.52, 4D 12.3 and 11.2).
 template <int DIM, bool SP2, bool TAN>
 __device__ __noinline__ uint32_t walk_general(const Dev *self, int ghost, int S, int pend, uint32_t set, uint32_t step0,
-                                           uint32_t par, WalkShared<DIM, SP2, TAN> *W)
+                                           WalkShared<DIM, SP2, TAN> *W)
 {
     const Dev *uniform = (const Dev *)uniform64((int64_t)self);
     WalkTile T = W->rest;
     T.b = __builtin_amdgcn_readfirstlane(T.b);
     uint32_t err = 0;
-    if (DIM == 1 && T.merged) walk_steps<DIM, SP2, TAN, false, true, DIM == 1>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
-    else walk_steps<DIM, SP2, TAN, false, true, false>(uniform, ghost, S, pend, set, step0, par, T, *W, err);
+    if (DIM == 1 && T.merged) walk_steps<DIM, SP2, TAN, false, true, DIM == 1>(uniform, ghost, S, pend, set, step0, T, *W, err);
+    else walk_steps<DIM, SP2, TAN, false, true, false>(uniform, ghost, S, pend, set, step0, T, *W, err);
     if (threadIdx.x == 0) W->rest = T;
     block_sync();
     return err;
@@ -638,7 +637,9 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
                 W.page[0] = (uint32_t)(tl << (sh & 31));
                 W.npage = 1;
                 W.parents = ghost ? d.gftile : d.ftile;
-                W.limit = min((int64_t)1 << sh, ghost ? P.gcap : P.cap);
+                W.cap = (uint32_t)(ghost ? P.gcap : P.cap);
+                W.limit = min(1u << sh, W.cap);
+                W.pool = (uint32_t)(plan[b + 1] - plan[b]) << (sh & 31);
             }
         }
         if (b != cb) {
@@ -695,10 +696,10 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             }
         }
         WalkTile T{i0, a0, 0u, 0u, 0u, 0u, 0, merged, b, nr, i00, sh};
-        while (!(DIM == 1 && merged ? walk_steps<DIM, SP2, TAN, ONE, false, DIM == 1>(self, ghost, S, pend, set, step0, par, T, W, err)
-                        : walk_steps<DIM, SP2, TAN, ONE, false, false>(self, ghost, S, pend, set, step0, par, T, W, err))) {
+        while (!(DIM == 1 && merged ? walk_steps<DIM, SP2, TAN, ONE, false, DIM == 1>(self, ghost, S, pend, set, step0, T, W, err)
+                        : walk_steps<DIM, SP2, TAN, ONE, false, false>(self, ghost, S, pend, set, step0, T, W, err))) {
             block_sync();
-            err |= walk_general<DIM, SP2, TAN>(self, ghost, S, pend, set, step0, par, &W);
+            err |= walk_general<DIM, SP2, TAN>(self, ghost, S, pend, set, step0, &W);
             T.nl = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.nl);
             T.q0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.q0);
             T.g0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.rest.g0);
