@@ -488,6 +488,24 @@ int range_limit(const wbrw_handle *h, const InstParam &P, int parents)
     return (int)std::max<int64_t>(kRangeMin, (int64_t)r / kRangeMin * kRangeMin);
 }
 
+// Tiles that k_walk cuts the instances into where that leaves them small
+// enough: one for each block of its grid, over all instances, so that a round
+// of tiles takes all blocks.  (1e6 particles with ghost pairs, whose blocks are
+// three to a compute unit: 2.21 ms a pass with four tiles to a unit, two rounds of
+// them, and 1.96 so; 4D 2e5 1.46 and 1.36.)
+void set_tiles(wbrw_handle *h)
+{
+    int64_t total = 0;
+    for (const InstParam &P : h->ip) total += P.N0;
+    const double want = h->grid[G_FAMILY];
+    for (InstParam &P : h->ip) {
+        P.wr = range_limit(h, P, h->d.ftile);
+        P.gwr = range_limit(h, P, h->d.gftile);
+        P.wt = std::max(1, total > 0 ? (int)(want * (double)P.N0 / (double)total) : 1);
+        P.gwt = std::max(1, (int)want / h->B);
+    }
+}
+
 template <int DIM>
 void launch_bin_plain(const wbrw_handle *h, hipStream_t s, int pend)
 {
@@ -978,19 +996,6 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
                           : parents_at_a_time(h, false, Families<2, false, false>::kRec, Families<2, false, false>::kQueue);
     h->chunk = chunk_steps(h);
     d.gftile = parents_at_a_time(h, true, Families<1, false, true>::kRec, Families<1, false, true>::kQueue);
-    {
-        int64_t total = 0;
-        for (int b = 0; b < h->B; ++b) total += cfg->N0[b];
-        for (InstParam &P : h->ip) {
-            P.wr = range_limit(h, P, d.ftile);
-            P.gwr = range_limit(h, P, d.gftile);
-            // small ensembles still spread over the chip: four tiles per
-            // compute unit over all instances
-            const double want = 4.0 * h->cus;
-            P.wt = std::max(1, total > 0 ? (int)(want * (double)P.N0 / (double)total) : 1);
-            P.gwt = std::max(1, (int)want / h->B);
-        }
-    }
     for (int s = 0; s < 2; ++s) {
         Ens &E = d.ens[s];
         E.x0 = at<double>(w, L.ens[s][0]);
@@ -1080,6 +1085,7 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     }
 
     if (h->dim == 1) set_grids_dim<1>(h); else set_grids_dim<2>(h);
+    set_tiles(h);
     d.self = at<Dev>(w, L.dev);
 
     hipStream_t s = h->stream;
@@ -1601,6 +1607,15 @@ static void read_launch(const wbrw_handle *h, int32_t *c)
     c[5] = h->bin_slots;
 }
 
+// The walk's grid has been chosen: the next plans are made for it.
+static int plan_for_grid(wbrw_t h)
+{
+    set_tiles(h);
+    HIPCHK(hipMemcpyAsync((void *)h->d.ip, h->ip.data(), sizeof(InstParam) * h->B, hipMemcpyHostToDevice, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    return WBRW_OK;
+}
+
 static void drop_graphs(wbrw_t h)
 {
     if (h->gexec) {   // a captured epoch holds the old launch shapes
@@ -1639,7 +1654,7 @@ int wbrw_set_launch(wbrw_t h, const int32_t *cfg)
     h->grid[G_FAMILY] = cfg[1];
     h->grid[G_BIN] = cfg[4];
     drop_graphs(h);
-    return WBRW_OK;
+    return plan_for_grid(h);
 }
 
 // Candidates: k_walk at 1..(its occupancy) blocks per CU (from the list below),
@@ -1756,6 +1771,7 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
     h->marks = saved;
     h->prof = prof;
     drop_graphs(h);
+    rc = plan_for_grid(h);
     if (rc) return rc;
     if (chosen) read_launch(h, chosen);
     return WBRW_OK;

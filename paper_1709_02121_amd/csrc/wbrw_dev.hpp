@@ -247,8 +247,9 @@ __host__ __device__ __forceinline__ int64_t page_slot(const uint32_t *pages, int
 }
 
 // Particles in a tile of k_walk for an ensemble of n: an equal share of a
-// whole multiple of `tiles` tiles (so that the blocks that run at once all
-// take the same number of tiles), rounded up to kRangeMin, at most `most`.
+// whole multiple of `tiles` tiles, those of one round (see set_tiles), so that
+// the blocks that run at once all take the same number of tiles; rounded up
+// to kRangeMin, at most `most`.
 __host__ __device__ __forceinline__ int64_t walk_range(int64_t n, int32_t tiles, int32_t most)
 {
     const int64_t waves = (n + (int64_t)tiles * most - 1) / ((int64_t)tiles * most);
