@@ -315,10 +315,12 @@ int wbrw_set_launch(wbrw_t h, const int32_t *cfg);
 /* Autotuner.  Runs 2 * #family candidates * steps_per_candidate time steps of
  * the handle's own ensemble (they are real steps: results do not depend on
  * launch shapes) while timing the family kernel over its grid sizes (blocks
- * per compute unit); for a plain sp1 ensemble it also
- * times the binning pass alone over its hash sizes and grids (its counts are
- * cleared and its escape tallies restored, so the ensemble and its stats are
- * unchanged).  Keeps the fastest of each.  chosen (host, may be NULL)
+ * per compute unit).  A candidate's steps are one call, in groups as
+ * wbrw_step's: with steps_per_candidate the length of the stretches to be run,
+ * the launches timed are those of the run.  For a plain sp1 ensemble it also
+ * times the binning pass alone, on positions that are up to date, over its
+ * hash sizes and grids (its counts are cleared and its escape tallies restored,
+ * so the ensemble and its stats are unchanged).  Keeps the fastest of each.  chosen (host, may be NULL)
  * receives the launch configuration (wbrw_get_launch's six values).
  * Synchronises; drops captured graphs. */
 int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen);

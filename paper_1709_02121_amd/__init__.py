@@ -355,9 +355,9 @@ class Simulation:
 
     def autotune(self, steps_per_candidate=1):
         """Times the kernel that takes the steps ("family") over its grid sizes on
-        real steps, and (plain sp1) the binning pass over its hash sizes and
-        grids without changing the ensemble; keeps the fastest (results are
-        unchanged by the choice).
+        real steps, steps_per_candidate in one call, and (plain sp1) the binning
+        pass over its hash sizes and grids without changing the ensemble; keeps
+        the fastest (results are unchanged by the choice).
         Returns the launch configuration (see launch())."""
         out = np.zeros(6, dtype=np.int32)
         _check(lib().wbrw_autotune(self.h, int(steps_per_candidate), out.ctypes.data_as(C.c_void_p)),

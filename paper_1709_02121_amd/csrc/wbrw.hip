@@ -1744,7 +1744,7 @@ int wbrw_autotune(wbrw_t h, int32_t steps_per_candidate, int32_t *chosen)
             int64_t before = 0, after = 0;
             if (hipStreamSynchronize(h->stream) != hipSuccess || (rc = psteps(before))) { rc = rc ? rc : WBRW_EHIP; break; }
             h->prof = 1;
-            for (int k = 0; k < steps_per_candidate && !rc; ++k) rc = enqueue_steps(h, 1, false);
+            rc = enqueue_steps(h, steps_per_candidate, false);     // in launches as wbrw_step's
             h->prof = 0;
             if (rc) break;
             if (hipStreamSynchronize(h->stream) != hipSuccess || (rc = psteps(after))) { rc = rc ? rc : WBRW_EHIP; break; }
