@@ -842,7 +842,6 @@ __global__ __launch_bounds__(kThreads) void k_regen(Dev d)
             if (TAN) {
                 const int64_t nxt = (nu + 1 < d.Nh) ? (off[nu + 1] & kOffMask) : nout;
                 const double an = (double)(nxt - (onu & kOffMask));
-                const int64_t nc = d.Nh * (int64_t)B;
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     O.D[c * d.cap_total + i] = fx_value(d.Tq[(cbase + nu) * 6 + 2 * c],

@@ -328,26 +328,6 @@ __device__ __forceinline__ void lb_publish(uint64_t *st, uint32_t epoch, uint32_
     __hip_atomic_store(st, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// exclusive prefix of tile t over the tiles [first, t) of its segment
-__device__ __forceinline__ uint32_t lb_lookback(uint64_t *st, int64_t t, int64_t first, uint32_t epoch)
-{
-    uint32_t excl = 0;
-    int64_t p = t - 1;
-    while (p >= first) {
-        uint64_t w;
-        for (;;) {
-            w = __hip_atomic_load(st + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t hi = (uint32_t)(w >> 32);
-            if ((hi >> 2) == epoch && (hi & 3u) != 0u) break;
-            __builtin_amdgcn_s_sleep(1);
-        }
-        excl += (uint32_t)w;
-        if (((uint32_t)(w >> 32) & 3u) == 2u) break;
-        --p;
-    }
-    return excl;
-}
-
 // Wave-parallel look-back: the 64 lanes of one wavefront examine 64
 // predecessors per round, wait until each has published, and sum back to the
 // nearest inclusive prefix.  Returns the exclusive prefix to every lane.
@@ -596,11 +576,6 @@ __device__ __forceinline__ double fx_value(int64_t hs, uint64_t ls)
 {
     const int64_t h = hs + (int64_t)(ls >> 32);
     return (double)h + (double)(ls & 0xFFFFFFFFull) * 0x1p-32;
-}
-
-__device__ __forceinline__ uint32_t lane_rank(uint64_t mask)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 }  // namespace wbrw

@@ -224,12 +224,10 @@ __global__ __launch_bounds__(kThreads) void k_sp2_resid(Dev d)
     if (ann_skipped(d)) return;
     __shared__ uint64_t s_wlo[2][kThreads / 64], s_whi[2][kThreads / 64];   // wavefront residual sums
     __shared__ unsigned long long s_w[kThreads / 64];
-    Ctl *ctl = d.ctl;
     const int B = d.B;
     const int64_t *plan = d.tileA;
     const int64_t ntiles = plan[B];
     const int tid = threadIdx.x;
-    const int64_t C = d.cap_total;
     unsigned long long ks[2] = {0, 0};       // this thread's kept copies per class
     auto publish = [&](int fb, bool last) {
         const unsigned long long k0 = block_sum(ks[0], s_w), k1 = block_sum(ks[1], s_w);
@@ -393,7 +391,6 @@ __global__ __launch_bounds__(kThreads) void k_sp2_tilescan(Dev d, int rgrid)
 {
     if (ann_skipped(d)) return;
     __shared__ unsigned long long s_w[kThreads / 64];
-    Ctl *ctl = d.ctl;
     const int B = d.B;
     const int tid = threadIdx.x;
     for (int b = blockIdx.x; b < B; b += gridDim.x) {
@@ -828,7 +825,6 @@ __global__ __launch_bounds__(kThreads) void k_ghosts(Dev d)
     const int64_t tiles_per = (d.Nh + kTileS - 1) / kTileS;
     const int64_t ntiles = tiles_per * B;
     const Ens G = pick_set(d, 1, ctl->gcur ^ 1u);
-    const int64_t nc = d.Nh * (int64_t)B;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     for (;;) {
         if (tid == 0) s_t = next_tile(&ctl->ticket[kPassGhost], ntiles);

@@ -89,7 +89,7 @@ __device__ __forceinline__ double advanced(double x, double c, int m)
 struct Clock {
     uint32_t id_hi, h1, l1, h2, l2;
 };
-__device__ __forceinline__ Clock clock_of(const Dev &d, uint64_t id, uint32_t key)
+__device__ __forceinline__ Clock clock_of(uint64_t id, uint32_t key)
 {
     const uint64_t p0 = (uint64_t)(uint32_t)id * 0xD2511F53ull;
     const uint32_t c2 = (uint32_t)(p0 >> 32) ^ key;
@@ -464,7 +464,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 const int s = MERGED ? W.step(slot) : s0;
                 const uint32_t cls = (uint32_t)(W.cls[slot] >> W.kStepBits) | (1u << s);
                 uint32_t ev = 0;
-                const Clock c = clock_of(d, id, P.key);
+                const Clock c = clock_of(id, P.key);
                 for (int q = MERGED ? 1 : s + 1; q < S; ++q)
                     if ((!MERGED || q > s) && clock_jumps(d, P, c, id, step0 + (uint32_t)q)) {
                         ev |= 1u << q;
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(kThreads, (DIM == 2 || TAN) ? 3 : 4) void k_walk(co
             for (int j = 0; j * kThreads < nr; ++j) {
                 const int li = j * kThreads + tid;
                 const uint64_t cur = id;
-                const Clock c = clock_of(d, cur, P.key);
+                const Clock c = clock_of(cur, P.key);
                 const uint64_t in = __ballot(li < nr);
                 id = ids[min(li + kThreads, nr - 1)];
                 for (int s = 0; s < S; ++s) {
