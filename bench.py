@@ -14,9 +14,12 @@ divided by the wall time.  Inputs are resident on the GPU before timing starts.
 Roofline: the whole step against HBM, with a model of 34 algorithmic bytes per
 particle-step (read x, k, id; write x; the offspring records and the parents'
 signs), timed by HIP events around every launch group of up to five steps on
-the launch stream inside the timed region.  (A launch group reads x, k and id
-once for its steps, so it may move fewer bytes than the model.)  The same steps
-are then run again with events around every kernel, for the per-kernel split
+the launch stream inside the timed region.  That is a rate of work, not of
+memory: a launch group reads x, k and id once for its steps and moves fewer
+bytes.  `measured` is the HBM rate itself, from the bytes that the counters of
+the committed profile give for these kernel sources (left out if the sources
+have changed since); what bounds the step is issue (the integer products of the
+clock words, the jumps' dependent FP64 chains).  The same steps are then run again with events around every kernel, for the per-kernel split
 (`kernels`, with the dominant kernel named).
 
 Printed: one JSON line on stdout (everything else goes to stderr).
@@ -189,18 +192,21 @@ def step_roofline(res):
         kern[name] = {"avg_launch_us": round(ms * 1e3 / n, 2), "us_per_step": round(ms * 1e3 / prof["step"][1], 2)
                       if prof["step"][1] else None, "share": round(ms / total, 4)}
     dominant = max(kern, key=lambda k: kern[k]["avg_launch_us"])
-    out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    out = {"bound": "issue", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
            "scope": "whole step: k_walk and k_place (with the closing block), up to five steps a launch",
            "kernel": dominant, "dominant_kernel": dominant,
            "avg_step_us": round(avg_step_s * 1e6, 2), "steps_timed": nsteps,
            "particle_steps_per_step": int(ps_step), "bytes_per_particle_step": STEP_MODEL_BYTES,
            "bytes_per_step": int(bytes_step),
-           "note": "the model counts every step's reads and writes; a launch of several steps makes them once",
+           "note": "achieved and frac are by the model, which counts every step's reads and writes; a launch of "
+                   "several steps makes them once (measured: the HBM rate by the counters)",
            "kernels": kern}
     per = measured_traffic()
     if per:
         out["traffic"] = int(sum(per.values()) * ps_step)
+        gbs = out["traffic"] / avg_step_s / 1e9
+        out["measured"] = {"GBps": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4)}
         out["traffic_per_kernel"] = {k: int(v * ps_step) for k, v in per.items()}
     return out
 
@@ -454,12 +460,14 @@ def main():
     roof = step_roofline(main_res)
     if roof is not None:
         cr = copy_rate(torch)
-        roof["attainable"] = {"what": "plain 1 GiB device copy, read + write, same GPU",
-                              "GBps": round(cr, 1), "frac": round(roof["achieved"] / cr, 4)}
+        roof["attainable"] = {"what": "plain 1 GiB device copy, read + write, same GPU", "GBps": round(cr, 1)}
+        if "measured" in roof:
+            roof["attainable"]["frac"] = round(roof["measured"]["GBps"] / cr, 4)
     log(f"sp1 1e7: {main_res['rate']:.4g} particle-steps/s, n_end={main_res['n_end']}, "
         f"profile={ {k: (round(v[0], 3), v[1]) for k, v in main_res['profile'].items()} }")
     if roof:
-        log(f"step: {roof['avg_step_us']} us, {roof['achieved']} GB/s ({roof['frac']} of peak), "
+        log(f"step: {roof['avg_step_us']} us, {roof['achieved']} GB/s by the model ({roof['frac']} of peak), "
+            f"measured {roof.get('measured')}, "
             f"dominant {roof['dominant_kernel']}")
     main_res.pop("sim")
 
