@@ -239,6 +239,7 @@ class Simulation:
                                self.workspace_bytes, C.c_void_p(self.stream.cuda_stream),
                                C.byref(h)), "wbrw_init")
         self.h = h
+        self._ready = torch.cuda.Event()
         self.B = int(cfg["B"])
         self.dim = int(cfg["dim"])
 
@@ -276,8 +277,7 @@ class Simulation:
         lo = d["lo"] if lo is None else lo
         hi = d["hi"] if hi is None else hi
         if out is None:
-            with self.torch.cuda.stream(self.stream):
-                out = self.torch.empty((self.B, nbins), dtype=self.torch.float64, device=self.device)
+            out = self._result((self.B, nbins))
         else:
             self._order_after_caller()
         _check(lib().wbrw_density(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
@@ -305,14 +305,26 @@ class Simulation:
         lo = d["lo"] if lo is None else lo
         hi = d["hi"] if hi is None else hi
         if out is None:
-            with self.torch.cuda.stream(self.stream):
-                out = self.torch.empty((self.B, 3, nbins), dtype=self.torch.float64, device=self.device)
+            out = self._result((self.B, 3, nbins))
         else:
             self._order_after_caller()
         _check(lib().wbrw_density_tangent(self.h, axis, nbins, lo, hi, C.c_void_p(out.data_ptr())),
                "wbrw_density_tangent")
         self._order_for_caller(out)
         return out
+
+    def _result(self, shape):
+        """Memory for a result, allocated on the handle's stream."""
+        t = self.torch.cuda
+        cur = t.current_stream(self.device)
+        if t.current_device() != cur.device_index:
+            with t.stream(self.stream):
+                return self.torch.empty(shape, dtype=self.torch.float64, device=self.device)
+        t.set_stream(self.stream)       # (t.stream takes three times as long)
+        try:
+            return self.torch.empty(shape, dtype=self.torch.float64, device=self.device)
+        finally:
+            t.set_stream(cur)
 
     def _order_for_caller(self, out):
         """Make the results in `out` visible to work the caller enqueues on torch's
@@ -321,7 +333,9 @@ class Simulation:
         results before that work is done."""
         cur = self.torch.cuda.current_stream(self.device)
         if cur.cuda_stream != self.stream.cuda_stream:
-            cur.wait_stream(self.stream)
+            # (one event for all calls: a wait is for the record before it)
+            self._ready.record(self.stream)
+            cur.wait_event(self._ready)
             if out.is_cuda:     # (a caller's buffer may be pinned host memory)
                 out.record_stream(cur)
 

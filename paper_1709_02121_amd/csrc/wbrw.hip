@@ -35,7 +35,7 @@ struct Layout {
     size_t ens[2][8] = {}, gens[2][8] = {};
     size_t ip = 0, dev = 0, tab[kMaxM] = {}, guide[kMaxM] = {}, ctl = 0;
     size_t N = 0, NG = 0, Nnew = 0, NGnew = 0, Nbase = 0, nstep = 0, tileA = 0, tileW = 0, wrange = 0,
-           tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, ptab = 0, ptabg = 0, ptx = 0, ptxg = 0, wpool = 0, wcnt = 0,
+           tileR = 0, tileG = 0, tally = 0, fpart = 0, rstart = 0, rtiles = 0, smask = 0, smaskg = 0, ptab = 0, ptabg = 0, wpool = 0, wcnt = 0,
            wcntg = 0, wsup = 0, wsupg = 0, wtot = 0, stS = 0, stG = 0, cnt = 0, cntx = 0, occx = 0, Tqx = 0, off = 0,
            occ = 0, Tq = 0, ntil = 0, dacc = 0, dTq = 0, bA = 0, bcopies = 0, bcls = 0,
            bcell = 0, bP = 0, bTile = 0, bG = 0, bcls_stat = 0, tileD = 0, bscan_tiles = 0, hist = 0, xitab = 0,
@@ -230,13 +230,11 @@ Layout make_layout(const wbrw_config *c)
     }
     L.smask = take(cur, C * 2);
     L.wcnt = take(cur, (size_t)L.tilesW * kClasses * 4);
-    L.ptab = take(cur, (size_t)L.tilesW * kPages * 4);
-    L.ptx = take(cur, (C / 8 + kTableMin) * 4);
+    L.ptab = take(cur, (size_t)L.tilesW * (kPages + kTableShare) * 4);
     if (tan) {
         L.smaskg = take(cur, G * 2);
         L.wcntg = take(cur, (size_t)L.tilesWg * kClasses * 4);
-        L.ptabg = take(cur, (size_t)L.tilesWg * kPages * 4);
-        L.ptxg = take(cur, (G / 8 + kTableMin) * 4);
+        L.ptabg = take(cur, (size_t)L.tilesWg * (kPages + kTableShare) * 4);
     }
     L.ip = take(cur, BB * sizeof(InstParam));
     L.dev = take(cur, sizeof(Dev));
@@ -270,7 +268,7 @@ Layout make_layout(const wbrw_config *c)
     L.Nbase = take(cur, 2 * BB * 8);
     L.nstep = take(cur, 2 * BB * (kPend + 1) * 8);
     L.wtot = take(cur, 2 * BB * kClasses * 4);
-    L.wpool = take(cur, (2 * BB + 2) * 8);
+    L.wpool = take(cur, 2 * BB * 8);
     L.tileA = take(cur, 2 * (BB + 1) * 8);
     L.tileW = take(cur, 4 * (BB + 1) * 8);
     L.wrange = take(cur, 8 * BB * 8);
@@ -1038,8 +1036,8 @@ int wbrw_init(const wbrw_config *cfg, void *workspace, size_t workspace_bytes, v
     d.wpool = at<uint64_t>(w, L.wpool);
     d.ptab = at<uint32_t>(w, L.ptab);
     d.ptabg = h->tangent ? at<uint32_t>(w, L.ptabg) : nullptr;
-    d.ptx = at<uint32_t>(w, L.ptx);
-    d.ptxg = h->tangent ? at<uint32_t>(w, L.ptxg) : nullptr;
+    d.ptx = d.ptab + L.tilesW * kPages;
+    d.ptxg = h->tangent ? d.ptabg + L.tilesWg * kPages : nullptr;
     d.tileA = at<int64_t>(w, L.tileA);
     d.tileW = at<int64_t>(w, L.tileW);
     d.wrange = at<int64_t>(w, L.wrange);

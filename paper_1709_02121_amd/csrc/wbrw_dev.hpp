@@ -32,9 +32,10 @@ constexpr int kPend = 32;               // steps between materialisations of the
 constexpr int kRangeMin = 64;           // particles in a tile of k_walk, at least; a multiple of 64
 constexpr int kRangeMax = 8192;         // particles in a tile of k_walk, at most
 constexpr int kLocalBits = 4096;        // offspring of a tile whose event bits are kept in LDS
-constexpr int kDirect = 24;             // pages of a tile's offspring that the tile itself lists
+constexpr int kDirect = 23;             // pages of a tile's offspring that the tile itself lists
 constexpr int kPages = kDirect + 1;     // their entries, and where the table of further pages starts
 constexpr int kTableMin = 64;           // pages that such a table holds, at least
+constexpr int kTableShare = kRangeMin / 8;  // entries of such tables for each possible tile
 constexpr int kFewInst = 8;             // instances whose class totals are summed from the tiles'
 constexpr int kMaxGrid = 8192;          // blocks of a persistent launch (per-block partials)
 // 4D family kernels: the payloads of a tile's records beyond the block's LDS
@@ -115,7 +116,8 @@ struct Ctl {
     uint32_t ann_now;          // conditional annihilation: the one after this step runs
     uint32_t chunk;            // chunks of steps so far: its parity picks the tile plan and group sums
     uint32_t wpar;             // parity of the chunk that k_place closes
-    uint32_t fill[24];         // the counters below start a line of their own: their
+    uint32_t table[2];         // entries of ptx and ptxg handed out (zero between chunks)
+    uint32_t fill[22];         // the counters below start a line of their own: their
                                // atomics do not hold up the reads of the words above
     uint32_t ticket[kPassCount];   // zero between launches (see next_tile)
 };
@@ -157,10 +159,9 @@ struct Dev {
     int64_t *tileW;             // [2][2][B+1] walk-tile plan (parity; real, ghost)
     int64_t *wrange;            // [2][2][B][2] its particles per tile, and the binary logarithm
                                 // of the slots of a page (see page_slot)
-    uint64_t *wpool;            // [2][B] slots handed out as further pages, then [2] entries of
-                                // ptx and ptxg handed out (zero between chunks)
+    uint64_t *wpool;            // [2][B] slots handed out as further pages (zero between chunks)
     uint32_t *ptab, *ptabg;     // per walk tile: its kPages entries (see page_slot)
-    uint32_t *ptx, *ptxg;       // tables of the tiles with more than kDirect pages
+    uint32_t *ptx, *ptxg;       // behind them: tables of the tiles with more than kDirect pages
     int64_t *tileR;             // [B+1] regeneration-tile plan
     int64_t *tileG;             // [B+1] ghost-regeneration plan
     int64_t *tally;             // [B][kTalCount]

@@ -393,7 +393,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                 }
             }
             if constexpr (!GENERAL) {
-                if (F.overflow) {    // (uniform)
+                if (__builtin_expect(F.overflow != 0u, 0)) {    // (uniform)
                     // Records or jumps than there is room for: half as
                     // many parents, for the rest of the tile.  (Ensembles
                     // crowded where |sin| is near 1 leave 1.57 times the
@@ -427,7 +427,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
             const uint32_t room = (uint32_t)__builtin_amdgcn_readfirstlane((int)W.limit);
             const uint32_t excl = block_excl(F.cnt[tid], W.wsum[0], agg);
             F.first[tid] = excl;
-            if (nl + agg > room && sh < 31) {      // (uniform) further pages, as many as fit
+            if (__builtin_expect(nl + agg > room && sh < 31, 0)) {     // (uniform) further pages, as many as fit
                 if (tid == 0) {
                     const Dev &d = fresh(self);
                     int q = W.npage;
@@ -438,7 +438,7 @@ __device__ __forceinline__ bool walk_steps(const Dev *self, int ghost, int S, in
                     const uint32_t old = W.page[kDirect], size = page_table(np);
                     uint32_t table = old, *tab = ghost ? d.ptxg : d.ptx;
                     if (size != page_table(q)) {
-                        table = (uint32_t)atomicAdd((unsigned long long *)&d.wpool[2 * (int64_t)d.B + ghost], (unsigned long long)size);
+                        table = atomicAdd(&d.ctl->table[ghost], size);
                         for (int j = 0; j < q - kDirect; ++j) tab[table + j] = tab[old + j];
                         W.page[kDirect] = table;
                     }
@@ -994,7 +994,7 @@ __device__ void close_chunk(const Dev &d, int ghost, int S, int pend, int adv, i
     // the tile plans
     block_plan(d.tileA + (int64_t)ghost * (B + 1), Ncur, B, kTileA);
     plan_walk(d, par ^ 1u, ghost, Ncur);
-    if (tid == 0) d.wpool[2 * (int64_t)B + ghost] = 0ull;
+    if (tid == 0) ctl->table[ghost] = 0u;
     if (tid == 0 && advance) {
         ctl->step = step + (uint32_t)S;
         ctl->chunk += 1u;

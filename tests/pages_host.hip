@@ -19,7 +19,7 @@ static int one(std::mt19937_64 &g, int64_t N, double scale, int &tables)
     for (auto &x : m) M += x = g() % 3 ? (int64_t)(scale * 64.0 * ((double)(g() % 1000) / 500.0)) : 0;
     const int64_t cap = N + M;
     if (cap >= (1ll << 25)) return 0;
-    std::vector<uint32_t> ptx(cap / 8 + kTableMin, ~0u);
+    std::vector<uint32_t> ptx((cap + kRangeMin - 1) / kRangeMin * kTableShare, ~0u);
     std::vector<std::vector<uint32_t>> page(T, std::vector<uint32_t>(kPages, ~0u));
     std::vector<int> np(T, 1);
     std::vector<uint8_t> taken(cap, 0);
