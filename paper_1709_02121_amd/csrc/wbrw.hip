@@ -489,8 +489,8 @@ int range_limit(const wbrw_handle *h, const InstParam &P, int parents)
 // Tiles that k_walk cuts the instances into where that leaves them small
 // enough: one for each block of its grid, over all instances, so that a round
 // of tiles takes all blocks.  (1e6 particles with ghost pairs, whose blocks are
-// three to a compute unit: 2.21 ms a pass with four tiles to a unit, two rounds of
-// them, and 1.96 so; 4D 2e5 1.46 and 1.36.)
+// three to a compute unit: 2.24 ms a pass with four tiles to a unit, two rounds of
+// them, and 1.97 so; 4D 2e5 1.47 and 1.33.)
 void set_tiles(wbrw_handle *h)
 {
     int64_t total = 0;
