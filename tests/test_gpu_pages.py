@@ -93,3 +93,28 @@ def test_offspring_beyond_the_event_bits(P, O):  # noqa: F811
     g.step(5)
     say(f"offspring beyond the event bits: {r.count(1)}")
     _compare_all(g, r, cfg, "5 steps")
+
+
+def test_offspring_beyond_the_event_bits_4d(P, O):  # noqa: F811
+    """The same in 4D, where a tile of 2500 grows fourfold in a launch and a
+    jump has three components."""
+    cfg = W.helium_soft_coulomb()
+    grid = dict(cfg["grid"], x_lo=5.0, x_hi=20.0, nx=3, k_lo=-16.0, k_hi=16.0, nk=4)
+    hist = np.zeros((2, 4, 4, 3, 3))
+    hist[1, 1:3, 1:3] = 138.0 / (100 * 5.0 ** 2 * 8.0 ** 2)          # 36 cells of 138 particles
+    cfg.update(B=2, N0=np.array([1_000_000, 100]), capacity=np.array([1_000_000, 100_000]), grid=grid,
+               init_histogram=hist.reshape(2, -1))
+    r = O.OracleSim(cfg)
+    g = P.Simulation(cfg)
+    n0 = r.count(1)
+    r.step(4)
+    assert r.count(1) - n0 > 2 * 4500          # two tiles
+    r.step(1)
+    g.step(5)
+    say(f"offspring beyond the event bits, 4d: {n0} -> {r.count(1)}")
+    _compare_all(g, r, cfg, "4d 5 steps")
+    g.annihilate()
+    r.annihilate()
+    g.step(2)
+    r.step(2)
+    _compare_all(g, r, cfg, "4d 2 steps more")
