@@ -299,7 +299,8 @@ int wbrw_export(wbrw_t h, int32_t b, int32_t ghost, int64_t n, double *x, double
 /* Launch configuration of the plain step and annihilation: six int32,
  * {streaming blocks, family blocks, streaming threads per block, streaming
  * particles per thread, binning blocks, binning hash slots}.  The family
- * blocks are those of the kernel that takes the steps; there is no streaming
+ * blocks are those of the kernel that takes the steps (the ensembles are cut
+ * into tiles for that many); there is no streaming
  * kernel any more, and its shapes (256 x 8, 128 x 16 in 1D only, 512 x 4) are
  * kept and reported but change nothing.  Hash sizes are 4096, 2048 and 8192
  * slots (with tangents always 2048).  Results
